@@ -66,6 +66,8 @@ enum { SD_BNORM = 0, SD_RHO, SD_BETA, SD_TRUE, SD_EST, SD_NSUM, SD_NSUM2, SD_PRH
 
 enum { MODE_START = 0, MODE_ARNOLDI = 1 };
 
+struct SweepTile;
+
 struct PlanDev {
   const ProbDesc* desc;
   const int* blk2prob;
@@ -95,6 +97,15 @@ struct PlanDev {
   int reorth_mode;   // 0 one Gram-Schmidt pass, 1 always two, 2 two where needed
   const double* ctl;  // device [tol, maxit] of the current solve (kernel arguments
                       // stay constant, so captured graphs remain valid)
-  int fused;          // 1: one-sweep Arnoldi steps (k_fused_sweep / k_post_fused)
+  int fused;          // one-sweep Arnoldi steps: 1 k_fused_sweep, 2 k_sweep; k_post_fused
   const FusedTile* tiles;
+  // complex64 one-sweep steps (fused = 2, k_sweep): update coefficients in
+  // sw_slot order and the factor of z, in FP32; the cycle's split of the work
+  // (k_sweep_plan)
+  float2* coefS;      // [nb][128]
+  float* zs;          // [nb]
+  SweepTile* sw_tiles;
+  int* sw_count;      // [1] tiles
+  int* sw_tile0;      // [nb]
+  int* sw_ntile;      // [nb]
 };

@@ -133,7 +133,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   }
   A.carve(&dd, nb);
   A.carve(&db2p, s->nchunks);
-  if (s->fused) A.carve(&s->dtiles, s->htiles.size());
+  if (s->fused == 1) A.carve(&s->dtiles, s->htiles.size());
   A.carve(&s->dU, nb);
   A.carve(&P.stI, (size_t)nb * ST_NI);
   A.carve(&P.stD, (size_t)nb * SD_ND);
@@ -155,11 +155,21 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   A.carve(&P.keep, (size_t)nb);
   A.carve(&P.bad, (size_t)nb);
   double* part = nullptr;
-  A.carve(&part, (size_t)std::max<size_t>(s->nchunks, s->htiles.size()) * P.NV);
+  const size_t rows = std::max<size_t>({(size_t)s->nchunks, s->htiles.size(),
+                                        s->fused == 2 ? (size_t)s->sw_most : 0});
+  A.carve(&part, rows * P.NV);
   P.partial = part;
   A.carve(&P.gpart, (size_t)nb * P.GB * std::max(1, gram_tiles(std::max(K, 1))) * 32);
   A.carve(&P.hist, (size_t)nb * std::max(1, o.hist_cap));
   A.carve(&s->dctl, 2);
+  if (s->fused == 2) {
+    A.carve(&P.coefS, (size_t)nb * DD_SW_MAXN);
+    A.carve(&P.zs, (size_t)nb);
+    A.carve(&P.sw_tiles, (size_t)s->sw_most);
+    A.carve(&P.sw_count, 1);
+    A.carve(&P.sw_tile0, (size_t)nb);
+    A.carve(&P.sw_ntile, (size_t)nb);
+  }
 }
 
 // Validates the options and builds the host-side plan of a solver (problem
@@ -285,16 +295,29 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     int GB = (int)std::min<size_t>(32, std::max<size_t>(1, (64ull << 20) / per));
     P.GB = GB;
   }
+  // One sweep per Arnoldi step: in complex64 always where it applies (a basis
+  // of at most 128 vectors whose offsets fit a buffer descriptor), in
+  // complex128 on request.
+  const bool one_pass = o.cgs_passes == 1 && NC <= DD_SW_MAXN;
+  if (one_pass && o.inner == DD_C64) {
+    s->fused = 2;
+    for (int p = 0; p < nb; ++p)
+      if ((size_t)s->hdesc[p].Dp * 8 * DD_SW_MAXN >= (size_t)DD_SW_OUT) s->fused = 0;
+    s->sw_grid = s->ncu;
+    int strips = 0;                        // one tile each at the least
+    for (int p = 0; p < nb; ++p) strips += sw_strips(ops[p]->nx);
+    s->sw_most = std::max(strips, 4 * s->sw_grid);
+  } else if (one_pass && o.fused) {
+    s->fused = 1;
+  }
   // Fused sweep tiles: strips of DD_FUSED_SW columns walked down bands of rows
-  s->fused = o.fused && o.cgs_passes == 1 && (K + m + 1) <= DD_FUSED_MAXN;
-  if (s->fused) {
+  if (s->fused == 1) {
     // two rounds of tiles over the resident workgroups (w per compute unit),
     // bands of 8 to 64 rows (each band recomputes one halo row at either end)
     int w = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &w, (o.inner == DD_C64) ? (const void*)k_fused_sweep<float, false>
-                                    : (const void*)k_fused_sweep<double, false>,
-            DD_FUSED_THREADS, 0) != hipSuccess || w < 1)
+            &w, (const void*)k_fused_sweep<double, false>, DD_FUSED_THREADS, 0) != hipSuccess ||
+        w < 1)
       w = 1;
     long long strip_rows = 0;
     for (int p = 0; p < nb; ++p)
@@ -366,7 +389,7 @@ extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const d
     for (int c = 0; c < s->hdesc[p].nblk; ++c) b2p[s->hdesc[p].blk0 + c] = p;
   auto chk = [&](hipError_t x) { if (x != hipSuccess && e == hipSuccess) e = x; };
   if (e == hipSuccess) {
-    if (s->fused)
+    if (s->fused == 1)
       chk(hipMemcpy(s->dtiles, s->htiles.data(), sizeof(FusedTile) * s->htiles.size(),
                     hipMemcpyHostToDevice));
     chk(hipMemcpy(dd, s->hdesc.data(), sizeof(ProbDesc) * nb, hipMemcpyHostToDevice));
@@ -388,7 +411,7 @@ extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const d
   P.desc = dd;
   P.blk2prob = db2p;
   P.ctl = s->dctl;
-  P.fused = s->fused ? 1 : 0;
+  P.fused = s->fused;
   P.tiles = s->dtiles;
   e = precond_init(s);
   if (e != hipSuccess) {
@@ -565,6 +588,20 @@ static void launch_step(dd_solver* s, int j, hipStream_t st) {
   k_post_norm<T><<<nb, DD_BLOCK, 0, st>>>(s->P, j, MODE_ARNOLDI, 0);
 }
 
+template <bool PC>
+static void launch_sweep(dd_solver* s, int j, hipStream_t st) {
+  const int n = s->o.kmax + j + 1;     // basis vectors, at most
+  const int g = s->sw_grid;
+  if (n <= 16) k_sweep<4, 4, PC><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 32) k_sweep<4, 8, PC><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 48) k_sweep<4, 12, PC><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 64) k_sweep<4, 16, PC><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 80) k_sweep<8, 10, PC><<<g, 512, 0, st>>>(s->P, j);
+  else if (n <= 96) k_sweep<8, 12, PC><<<g, 512, 0, st>>>(s->P, j);
+  else if (n <= 112) k_sweep<8, 14, PC><<<g, 512, 0, st>>>(s->P, j);
+  else k_sweep<8, 16, PC><<<g, 512, 0, st>>>(s->P, j);
+}
+
 // One fused Arnoldi step: the sweep (update of step j, matvec and dots of
 // step j + 1) and its FP64 bookkeeping.
 template <typename T>
@@ -572,8 +609,13 @@ static void launch_fused_step(dd_solver* s, int j, hipStream_t st) {
   const int nt = (int)s->htiles.size();
   const bool pc = s->o.precond != DD_PRECOND_NONE;
   prof_mark(s, 3, st);
-  if (pc) k_fused_sweep<T, true><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
-  else k_fused_sweep<T, false><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
+  if constexpr (sizeof(T) == 4) {
+    if (pc) launch_sweep<true>(s, j, st);
+    else launch_sweep<false>(s, j, st);
+  } else {
+    if (pc) k_fused_sweep<T, true><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
+    else k_fused_sweep<T, false><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
+  }
   prof_end(s, st);
   k_post_fused<T><<<dim3(s->nb, post_slices(s, false)), DD_BLOCK, 0, st>>>(s->P, j, 0);
 }
@@ -640,6 +682,7 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     int active = 0;
     for (int p = 0; p < nb; ++p) active += snap[0][p * ST_NI + ST_ACTIVE];
     if (active == 0) break;
+    if (s->fused == 2) k_sweep_plan<<<1, DD_BLOCK, 0, st>>>(s->P, s->sw_grid, s->sw_most);
     launch_start<T, R>(s, st);
     if (s->fused) {
       // z_0 = A q~_0 (unscaled) and its dots; then the coefficients of step 0
@@ -905,6 +948,15 @@ extern "C" dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, v
       DD_HIP_CHECK(hipMemcpy(dst + (size_t)v * d.D * ib,
                              (const char*)d.basis + (size_t)(slot0 + v) * d.Dp * ib, d.D * ib,
                              hipMemcpyDeviceToHost));
+    if (what == 1 && s->fused == 2) {   // stored unnormalised
+      std::vector<double> hs(m + 1);
+      DD_HIP_CHECK(hipMemcpy(hs.data(), s->P.hscale + (size_t)p * (m + 1), sizeof(double) * (m + 1),
+                             hipMemcpyDeviceToHost));
+      for (int v = 0; v < nvec; ++v) {
+        float* q = (float*)(dst + (size_t)v * d.D * ib);
+        for (int e = 0; e < 2 * d.D; ++e) q[e] = (float)(q[e] * hs[v]);
+      }
+    }
     return DD_OK;
   }
   if (what == 2) {

@@ -13,6 +13,7 @@
 #pragma once
 
 #include "solver.h"
+#include "sweep.h"
 
 template <typename T> struct OpP;
 template <> struct OpP<float> {
@@ -1093,7 +1094,9 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     // order for the norm, so every slice has the same s_{j+1})
     const int nv = (c0 < c1) ? 2 * (c1 - c0) : 0;
     const int gfix = max(1, min(64, DD_BLOCK / (2 * per + 1)));
-    reduce_rows<PT>(P, d.t0, d.nt, nv + 1, red, (c0 < c1) ? 2 * c0 : 2 * nn, 2 * nn, gfix);
+    // the sweeps write FP64 rows
+    reduce_rows<double>(P, P.fused == 2 ? P.sw_tile0[p] : d.t0, P.fused == 2 ? P.sw_ntile[p] : d.nt,
+                        nv + 1, red, (c0 < c1) ? 2 * c0 : 2 * nn, 2 * nn, gfix);
     if (t == 0) nrm2[0] = red[nv];
     __syncthreads();
     const double nrm = sqrt(nrm2[0]);
@@ -1118,7 +1121,19 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     const double sv = (v < k) ? 1.0 : (v - k == (init ? 0 : j + 1) ? snew : hs[v - k]);
     const double gs = snew * sv * sv;
     cNew[v] = dv;
-    cB[v] = make_double2(gs * dv.x, gs * dv.y);
+    if (P.fused == 2)
+      P.coefS[(size_t)p * DD_SW_MAXN + v] =
+          make_float2((float)(gs * dv.x), (float)(gs * dv.y));
+    else
+      cB[v] = make_double2(gs * dv.x, gs * dv.y);
+  }
+  if (P.fused == 2 && lead) {
+    // slots of vectors that this cycle has not reached yet meet values read as
+    // zero: they hold finite numbers
+    if (init)
+      for (int v = nn + t; v < DD_SW_MAXN; v += DD_BLOCK)
+        P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2(0.f, 0.f);
+    if (t == 0) P.zs[p] = (float)snew;
   }
   if (lead && !init) {
     __syncthreads();

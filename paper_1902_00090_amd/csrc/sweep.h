@@ -1,0 +1,346 @@
+// One-sweep Arnoldi step in complex64: the update of step j, the stencil and
+// the dot products of step j + 1 in one pass over the basis.
+//
+// The Krylov vectors are normalised one step late, q_i = s_i q~_i with FP64
+// scales s_i (C columns: s = 1), and z_j = A q~_j is kept unscaled beside the
+// basis.  With the update coefficients g the sweep forms
+//     q~_{j+1} = zs z_j - sum_v g_v b_v,      b = [C, q~_0 .. q~_j],
+// then z_{j+1} = A q~_{j+1} and its raw dots against [C, q~_0 .. q~_{j+1}].
+//
+// The stencil needs q~_{j+1} on the cells around, so a workgroup walks a strip
+// of up to 62 columns (64 lanes with one halo column on either side) down the
+// rows and recomputes the halos.  Its eight waves share the basis vectors, not
+// the columns: wave w holds the vectors w, w + 8, ... of the whole strip row,
+// PER of them, in registers.  Each row the waves exchange their parts of the
+// sum through LDS (one barrier; the buffer alternates) and every wave adds the
+// eight parts, so that all of them know the new row and apply the stencil to
+// the row behind without a second barrier; the wave's dots then use the basis
+// values of that row, which are still in its registers.  Every basis value is
+// fetched once.  Four register sets rotate: the row behind, the row being
+// updated and two rows in flight (about 120 KB per compute unit at 121
+// vectors, against the 50 KB that cover the latency of HBM at its rate).
+//
+// The dots accumulate in FP32 over at most DD_SW_FOLD rows, are then summed
+// over the 64 columns and added in FP64: one FP64 partial row per tile, reduced
+// in a fixed order by k_post_fused.
+//
+// Loads go through buffer descriptors whose range check stands for the bounds:
+// vectors past the basis and lanes outside the strip read as zero and move
+// nothing.
+#pragma once
+
+#include "solver.h"
+
+#define DD_SW_COLS 62                 // owned columns of a strip, at most
+#define DD_SW_MAXN 128                // basis vectors
+#define DD_SW_FOLD 32                 // rows between the FP64 additions
+#define DD_SW_OUT 0x80000000u         // an offset past every descriptor's range
+
+typedef unsigned int sw_u2 __attribute__((ext_vector_type(2)));
+
+// A value that no kernel writes while this one runs, at a uniform address:
+// a scalar load, which does not queue behind the vector loads in flight.
+template <typename X> __device__ __forceinline__ X ld_uni(const X* p) {
+  return *(const __attribute__((address_space(4))) X*)p;
+}
+__device__ __forceinline__ float2 ld_uni(const float2* p) {
+  const auto q = (const __attribute__((address_space(4))) float*)p;
+  return make_float2(q[0], q[1]);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t sw_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ float2 sw_ld2(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  const sw_u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+  return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+}
+__device__ __forceinline__ float sw_ld1(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+}
+
+// Strips of a grid of nx columns, and their common width.
+__host__ __device__ inline int sw_strips(int nx) { return (nx + DD_SW_COLS - 1) / DD_SW_COLS; }
+__host__ __device__ inline int sw_width(int nx) {
+  const int s = sw_strips(nx);
+  return (nx + s - 1) / s;
+}
+
+// One tile: rows [y0, y0 + rows) of a strip of problem p.
+struct SweepTile {
+  int p, strip, y0, rows;
+};
+
+// Cuts the active problems into the tiles of one cycle's sweeps: strips times
+// bands of h rows, the same h for all, chosen so that the tiles fill the fewest
+// row steps of gmax workgroups (a tile takes h + 2 of them: the halo rows are
+// recomputed), with at most `most` tiles.  Within a problem the strips of a
+// band follow each other, so that the workgroups that walk neighbouring strips
+// run at the same time on the same XCD and its L2 serves the cache lines that
+// the strips share at their edges: 62 columns are 496 bytes, which touch five
+// lines of 128.  A problem's tiles, and with them its partial rows, are
+// consecutive from tile0[p].
+__global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int gmax, int most) {
+  __shared__ int cnt[DD_BLOCK];
+  __shared__ long long best_l[DD_BLOCK];
+  const int t = threadIdx.x;
+  // thread t judges the heights t + 1, t + 257, ...
+  long long best = 1ll << 62;
+  int nymax = 1;
+  for (int p = 0; p < P.nb; ++p)
+    if (P.stI[p * ST_NI + ST_ACTIVE] != 0) nymax = max(nymax, P.desc[p].ny);
+  for (int h = t + 1; h <= nymax; h += DD_BLOCK) {
+    long long n = 0;
+    for (int p = 0; p < P.nb; ++p)
+      if (P.stI[p * ST_NI + ST_ACTIVE] != 0)
+        n += (long long)sw_strips(P.desc[p].nx) * ((P.desc[p].ny + h - 1) / h);
+    if (n <= most || h == nymax) {
+      const long long steps = (n + gmax - 1) / gmax * (h + 2);
+      best = min(best, (steps << 31) | (unsigned)h);
+    }
+  }
+  best_l[t] = best;
+  __syncthreads();
+  for (int o = DD_BLOCK / 2; o >= 1; o >>= 1) {
+    if (t < o) best_l[t] = min(best_l[t], best_l[t + o]);
+    __syncthreads();
+  }
+  const int h = (int)(best_l[0] & 0x7fffffff);
+  int done = 0;
+  for (int b = 0; b < P.nb; b += DD_BLOCK) {
+    const int p = b + t;
+    int r = 0, strips = 1;
+    if (p < P.nb && P.stI[p * ST_NI + ST_ACTIVE] != 0) {
+      strips = sw_strips(P.desc[p].nx);
+      r = strips * ((P.desc[p].ny + h - 1) / h);
+    }
+    cnt[t] = r;
+    __syncthreads();
+    for (int o = 1; o < DD_BLOCK; o <<= 1) {
+      const int x = (t >= o) ? cnt[t - o] : 0;
+      __syncthreads();
+      cnt[t] += x;
+      __syncthreads();
+    }
+    if (p < P.nb) {
+      const int t0 = done + cnt[t] - r, ny = P.desc[p].ny;
+      P.sw_tile0[p] = t0;
+      P.sw_ntile[p] = r;
+      for (int i = 0; i < r; ++i) {
+        const int y0 = i / strips * h;
+        P.sw_tiles[t0 + i] = {p, i % strips, y0, min(h, ny - y0)};
+      }
+    }
+    done += cnt[DD_BLOCK - 1];
+    __syncthreads();
+  }
+  if (t == 0) P.sw_count[0] = done;
+}
+
+template <int PER> struct SweepRow {
+  float2 b[PER];          // the wave's basis values at its lane's column
+  float2 z;               // z_j (last wave; zero in the others)
+  float eps;
+  float2 pr, pl;          // diagonal preconditioner
+};
+
+// The lane's neighbours in the wave (0 past its ends).
+__device__ __forceinline__ float2 from_west(float2 v) {
+  return make_float2(__uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.x), 0x138, 0xf, 0xf, false)),
+                     __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.y), 0x138, 0xf, 0xf, false)));
+}
+__device__ __forceinline__ float2 from_east(float2 v) {
+  return make_float2(__uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.x), 0x130, 0xf, 0xf, false)),
+                     __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.y), 0x130, 0xf, 0xf, false)));
+}
+
+// NW waves of PER vectors each.  PC: the problems carry a diagonal
+// preconditioner, z = P_L A P_R q~.
+template <int NW, int PER, bool PC>
+__global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
+  const int count = ld_uni(P.sw_count), G = gridDim.x;
+  // workgroup b runs on XCD b % 8: give each XCD neighbouring tiles
+  const int g = (G % 8 == 0) ? (int)(blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ float2 part[2][NW][64];
+  const float2 zero = make_float2(0.f, 0.f);
+
+  for (int tile = g; tile < count; tile += G) {
+    const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw_tiles + tile);
+    const int p = tl->p, strip = tl->strip, ya = tl->y0, nrows = tl->rows;
+    if (ld_uni(P.stI + p * ST_NI + ST_ACTIVE) == 0) continue;   // ended within this cycle
+    const auto* d = (const __attribute__((address_space(4))) ProbDesc*)(P.desc + p);
+    const int nx = d->nx, ny = d->ny, k = d->k;
+    const size_t Dp = d->Dp;
+    const int n = k + j + 1;
+    const float2* B = (const float2*)d->basis + (size_t)(P.kmax - k) * Dp;
+    float2* qn = (float2*)d->basis + (size_t)(P.kmax + j + 1) * Dp;
+    const float2* zin = (const float2*)d->Z + (size_t)(j & 1) * Dp;
+    float2* zout = (float2*)d->Z + (size_t)((j + 1) & 1) * Dp;
+    const float2* cf = d->cf32;
+    const float om2 = (float)d->omega2;
+    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * 8);
+    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(zin, (size_t)Dp * 8);
+    const __amdgpu_buffer_rsrc_t rE = sw_rsrc(d->eps32, (size_t)nx * ny * 4);
+    const bool has_pl = PC && d->pl != nullptr, has_pr = PC && d->pr != nullptr;
+    const __amdgpu_buffer_rsrc_t rL = sw_rsrc(has_pl ? d->pl : B, has_pl ? (size_t)Dp * 8 : 0);
+    const __amdgpu_buffer_rsrc_t rR = sw_rsrc(has_pr ? d->pr : B, has_pr ? (size_t)Dp * 8 : 0);
+    const unsigned vec = (unsigned)Dp * 8u;         // bytes of one vector
+    const float2* cS = P.coefS + (size_t)p * DD_SW_MAXN + wave;
+    float2 gc[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) gc[i] = ld_uni(cS + NW * i);
+    const float zs = ld_uni(P.zs + p);
+    float2 acc[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) acc[i] = zero;
+    float2 accn = zero;                              // conj(q~_{j+1}) z_{j+1}
+    float un2 = 0.f;                                 // ||q~_{j+1}||^2
+    double dsum = 0.0, dn0 = 0.0, dn1 = 0.0, dn2 = 0.0;
+    auto fold = [&]() {
+      float v[32];
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        v[2 * i] = (i < PER) ? acc[i < PER ? i : 0].x : 0.f;
+        v[2 * i + 1] = (i < PER) ? acc[i < PER ? i : 0].y : 0.f;
+      }
+      butterfly_step<float, 32>(v, lane);
+      dsum += (double)(v[0] + __shfl_xor(v[0], 1, 64));
+#pragma unroll
+      for (int i = 0; i < PER; ++i) acc[i] = zero;
+      if (wave == 0) {
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+          accn.x += __shfl_xor(accn.x, o, 64);
+          accn.y += __shfl_xor(accn.y, o, 64);
+          un2 += __shfl_xor(un2, o, 64);
+        }
+        dn0 += (double)accn.x;
+        dn1 += (double)accn.y;
+        dn2 += (double)un2;
+        accn = zero;
+        un2 = 0.f;
+      }
+    };
+
+    const int sw = sw_width(nx), x0 = strip * sw;
+    const int w = min(sw, nx - x0);                          // owned columns (may be 0)
+    const bool lane_ok = lane <= w + 1;
+    const bool owned = lane >= 1 && lane <= w;
+    int c = x0 - 1 + lane;
+    c = (c < 0) ? c + nx : ((c >= nx) ? c - nx : c);
+    c = lane_ok ? c : 0;
+    float2 cxm = zero, cxp = zero;
+    if (owned) {
+      cxm = cf[c];
+      cxp = cf[nx + c];
+    }
+    const int N = nrows + 2;
+    SweepRow<PER> S0, S1, S2, S3;
+    // byte offsets of the lane's cell in row 0 of the wave's first vector, of z
+    // and of eps; a row adds the same to every lane
+    const unsigned ob = lane_ok ? (unsigned)c * 8u + (unsigned)wave * vec : DD_SW_OUT;
+    const unsigned oz = (lane_ok && wave == NW - 1) ? (unsigned)c * 8u : DD_SW_OUT;
+    const unsigned oe = lane_ok ? (unsigned)c * 4u : DD_SW_OUT;
+    auto load = [&](SweepRow<PER>& s, int t) {
+      int y = ya - 1 + t;
+      y = (y < 0) ? y + ny : ((y >= ny) ? y - ny : y);
+      // rows past the tile are not fetched (a lane outside the strip may wrap
+      // into the range there: it is read and not used)
+      const unsigned row = (t < N) ? (unsigned)(y * nx) * 4u : DD_SW_OUT / 2;
+      unsigned o = ob + 2 * row;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        s.b[i] = sw_ld2(rB, o);
+        o += NW * vec;
+        asm("" : "+v"(o));      // one running offset: the multiples would fill the scalar registers
+      }
+      s.z = sw_ld2(rZ, oz + 2 * row);
+      s.eps = sw_ld1(rE, oe + row);
+      if (PC) {
+        s.pr = sw_ld2(rR, (lane_ok ? (unsigned)c * 8u : DD_SW_OUT) + 2 * row);
+        s.pl = sw_ld2(rL, (lane_ok ? (unsigned)c * 8u : DD_SW_OUT) + 2 * row);
+      }
+    };
+    // the new row's values one and two rows back: q~, P_R q~ and its
+    // neighbours to the west and east
+    float2 u1 = zero, r1 = zero, r2 = zero, rw = zero, re = zero;
+    auto step = [&](SweepRow<PER>& cur, SweepRow<PER>& prev, SweepRow<PER>& ahead, int t) {
+      load(ahead, t + 2);
+      __builtin_amdgcn_sched_barrier(0);   // rows are fetched, and so waited for, in order
+      const int ys = max(ya, ya + t - 2);
+      const float2 cym = ld_uni(cf + 2 * nx + ys), cyp = ld_uni(cf + 2 * nx + ny + ys);
+      float2 pu = cmk<float2>(-zs * cur.z.x, -zs * cur.z.y);
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        pu.x = fmaf(-gc[i].y, cur.b[i].y, fmaf(gc[i].x, cur.b[i].x, pu.x));
+        pu.y = fmaf(gc[i].y, cur.b[i].x, fmaf(gc[i].x, cur.b[i].y, pu.y));
+      }
+      part[t & 1][wave][lane] = pu;
+      __syncthreads();
+      float2 u = zero;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) u = csub(u, part[t & 1][q][lane]);
+      int y = ya - 1 + t;
+      y = (y < 0) ? y + ny : ((y >= ny) ? y - ny : y);
+      const bool mine = t >= 1 && t <= nrows;
+      float2 r = u;
+      if (has_pr) r = cmul(u, cur.pr);
+      if (t >= 2) {
+        float2 z = cmul(cxm, csub(r1, rw));
+        z = csub(z, cmul(cxp, csub(re, r1)));
+        z = cadd(z, cmul(cym, csub(r1, r2)));
+        z = csub(z, cmul(cyp, csub(r, r1)));
+        const float de = om2 * prev.eps;
+        z.x -= de * r1.x;
+        z.y -= de * r1.y;
+        if (!owned) z = zero;
+        if (has_pl) z = cmul(prev.pl, z);
+        if (wave == 1 && owned) zout[ys * nx + c] = z;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+          acc[i].x = fmaf(prev.b[i].y, z.y, fmaf(prev.b[i].x, z.x, acc[i].x));
+          acc[i].y = fmaf(-prev.b[i].y, z.x, fmaf(prev.b[i].x, z.y, acc[i].y));
+        }
+        if (wave == 0) {
+          accn.x += u1.x * z.x + u1.y * z.y;
+          accn.y += u1.x * z.y - u1.y * z.x;
+        }
+      }
+      if (wave == 0 && mine && owned) {
+        qn[y * nx + c] = u;
+        un2 += u.x * u.x + u.y * u.y;
+      }
+      rw = from_west(r);
+      re = from_east(r);
+      r2 = r1;
+      r1 = r;
+      u1 = u;
+    };
+    __syncthreads();          // the parts of the tile before have been read
+    load(S0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(S1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    int t = 0;
+    for (; t + 4 <= N; t += 4) {
+      step(S0, S3, S2, t);
+      step(S1, S0, S3, t + 1);
+      step(S2, S1, S0, t + 2);
+      step(S3, S2, S1, t + 3);
+      if ((t + 4) % DD_SW_FOLD == 0) fold();
+    }
+    if (t < N) step(S0, S3, S2, t);
+    if (t + 1 < N) step(S1, S0, S3, t + 1);
+    if (t + 2 < N) step(S2, S1, S0, t + 2);
+    fold();
+    double* prow = (double*)P.partial + (size_t)tile * P.NV;
+    const int idx = lane >> 1, v = wave + NW * (idx >> 1);
+    if ((lane & 1) == 0 && idx < 2 * PER && v < n) prow[2 * v + (idx & 1)] = dsum;
+    if (wave == 0 && lane == 0) {
+      prow[2 * n] = dn0;
+      prow[2 * n + 1] = dn1;
+      prow[2 * n + 2] = dn2;
+    }
+  }
+}

@@ -1,0 +1,110 @@
+"""The complex64 one-sweep Arnoldi step (k_sweep) at the edges of its tiles.
+
+After one cycle the stored arrays have to satisfy the relations that the step
+computes, recomputed here in complex128 from the stored vectors themselves:
+
+  * every entry of the new column is the dot product of a basis vector with
+    A q_j (the classical Gram-Schmidt coefficient);
+  * A q_j = C B_j + Q h_j.
+
+Both hold to FP32 rounding.  The bounds count the roundings: u = 2^-24; the
+stencil makes at most 12 per term; a dot product is summed over at most 32 rows
+and 8 folds before it is added in FP64; an update sums n products and the nine
+parts of the waves; stored vectors and coefficients are rounded once more.
+"""
+import numpy as np
+import pytest
+
+import torch
+
+import workloads as W
+from oracle import fdfd, precond
+
+pytestmark = pytest.mark.gpu
+
+U32 = 2.0 ** -24
+
+
+def _inst(seed, nx, ny):
+    rng = np.random.default_rng(seed)
+    eps = (2.085 + 10.165 * rng.random((ny, nx))).astype(np.float32)
+    return W.Instance(eps, W.random_complex(rng, nx * ny), nx, ny, 0.04, 1.55, 3)
+
+
+def _check(s, p, A, steps):
+    H, B = s.debug(p, "H").T, s.debug(p, "B").T
+    Q = s.debug(p, "Q").T.astype(np.complex128)
+    C = s.debug(p, "C").T.astype(np.complex128)
+    k = C.shape[1]
+    absA = abs(A)
+    basis = np.concatenate([C, Q], axis=1)
+    for j in range(steps):
+        n = k + j + 1
+        z = A @ Q[:, j]
+        size = np.linalg.norm(absA @ abs(Q[:, j]))
+        h = np.concatenate([B[:, j], H[:j + 1, j]])
+        d = basis[:, :n].conj().T @ z
+        assert np.abs(h - d).max() <= (12 + 40 + 4) * U32 * size, j
+        r = z - basis[:, :n] @ h - H[j + 1, j] * Q[:, j + 1]
+        assert np.linalg.norm(r) <= (12 + n / 8 + 9 + 4) * U32 * (size + np.abs(h).sum()), j
+        assert abs(np.linalg.norm(Q[:, j + 1]) - 1) <= 60 * U32, j
+
+
+# nx: one strip, the widest strip, the narrowest second strip, an even split,
+# three strips; restarts: every register width of the kernel and its last step
+@pytest.mark.parametrize("nx,ny,k,restart", [
+    (20, 15, 0, 31), (62, 7, 0, 33), (63, 9, 3, 61), (124, 8, 0, 64), (125, 11, 0, 97),
+    (61, 40, 20, 107), (130, 64, 0, 127)])
+def test_one_cycle_relations(nx, ny, k, restart):
+    from paper_1902_00090_amd import FdfdOp, Solver
+    inst = _inst(nx + ny, nx, ny)
+    s = Solver([FdfdOp.from_instance(inst)], restart=restart, kmax=k, cgs_passes=1)
+    if k:
+        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(np.complex64)
+        s.set_subspace([torch.tensor(V, device="cuda")])
+    b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
+    _, (info,), _ = s.solve([b], tol=0.0, maxit=restart)
+    assert info["iters"] == restart
+    _check(s, 0, fdfd.assemble_instance(inst), restart)
+    s.close()
+
+
+def test_uneven_batch_with_ended_problems():
+    """Problems that end within a cycle leave their workgroups' shares; the
+    split over the workgroups covers strips of several problems."""
+    from paper_1902_00090_amd import FdfdOp, Solver
+    insts = [_inst(i, nx, ny) for i, (nx, ny) in
+             enumerate([(24, 9), (63, 8), (20, 70), (90, 33), (17, 16)])]
+    ops = [FdfdOp.from_instance(i) for i in insts]
+    bs = [torch.tensor(i.b, dtype=torch.complex128, device="cuda") for i in insts]
+    bs[1] = bs[1] * 0                                  # ends before the first step
+    s = Solver(ops, restart=40, cgs_passes=1, kmax=2)
+    s.set_subspace([None, None, torch.tensor(
+        W.random_complex(np.random.default_rng(5), (2, insts[2].D)).astype(np.complex64),
+        device="cuda"), None, None])
+    _, infos, _ = s.solve(bs, tol=0.0, maxit=40)
+    assert [i["iters"] for i in infos] == [40, 0, 40, 40, 40]
+    for p in (0, 2, 3, 4):
+        _check(s, p, fdfd.assemble_instance(insts[p]), 40)
+    # converged fields of the whole batch, problems ending in different cycles
+    xs, infos, _ = s.solve(bs, tol=1e-6, maxit=20000)
+    for p in (0, 2, 3, 4):
+        x = xs[p].cpu().numpy()
+        A = fdfd.assemble_instance(insts[p])
+        assert np.linalg.norm(insts[p].b - A @ x) <= 1.001e-6 * np.linalg.norm(insts[p].b)
+    s.close()
+
+
+@pytest.mark.parametrize("kind", ["jacobi", "pml"])
+def test_preconditioned_cycle_relations(kind):
+    from paper_1902_00090_amd import FdfdOp, Solver
+    inst = _inst(3, 70, 21)
+    s = Solver([FdfdOp.from_instance(inst)], restart=50, cgs_passes=1, precond=kind)
+    b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
+    s.solve([b], tol=0.0, maxit=50)
+    A = fdfd.assemble_instance(inst)
+    pl, pr = (precond.jacobi(A) if kind == "jacobi" else
+              precond.pml_scaling(inst.nx, inst.ny, inst.omega, inst.dx, inst.npml))
+    _check(s, 0, precond.preconditioned(A, pl, pr), 50)
+    s.close()
+

@@ -105,7 +105,7 @@ struct PlanDev {
   float2* coefS;      // [nb][128]
   float* zs;          // [nb]
   SweepTile* sw_tiles;
-  int* sw_count;      // [1] tiles
+  int* sw_count;      // [2] tiles, workgroups that share them
   int* sw_tile0;      // [nb]
   int* sw_ntile;      // [nb]
 };

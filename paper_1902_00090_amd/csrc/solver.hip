@@ -166,7 +166,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
     A.carve(&P.coefS, (size_t)nb * DD_SW_MAXN);
     A.carve(&P.zs, (size_t)nb);
     A.carve(&P.sw_tiles, (size_t)s->sw_most);
-    A.carve(&P.sw_count, 1);
+    A.carve(&P.sw_count, 2);
     A.carve(&P.sw_tile0, (size_t)nb);
     A.carve(&P.sw_ntile, (size_t)nb);
   }
@@ -303,7 +303,7 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     s->fused = 2;
     for (int p = 0; p < nb; ++p)
       if ((size_t)s->hdesc[p].Dp * 8 * DD_SW_MAXN >= (size_t)DD_SW_OUT) s->fused = 0;
-    s->sw_grid = s->ncu;
+    s->sw_grid = 2 * s->ncu;               // at most two workgroups per compute unit
     int strips = 0;                        // one tile each at the least
     for (int p = 0; p < nb; ++p) strips += sw_strips(ops[p]->nx);
     s->sw_most = std::max(strips, 4 * s->sw_grid);
@@ -682,7 +682,7 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     int active = 0;
     for (int p = 0; p < nb; ++p) active += snap[0][p * ST_NI + ST_ACTIVE];
     if (active == 0) break;
-    if (s->fused == 2) k_sweep_plan<<<1, DD_BLOCK, 0, st>>>(s->P, s->sw_grid, s->sw_most);
+    if (s->fused == 2) k_sweep_plan<<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
     launch_start<T, R>(s, st);
     if (s->fused) {
       // z_0 = A q~_0 (unscaled) and its dots; then the coefficients of step 0

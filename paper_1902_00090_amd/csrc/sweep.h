@@ -33,6 +33,7 @@
 
 #define DD_SW_COLS 62                 // owned columns of a strip, at most
 #define DD_SW_MAXN 128                // basis vectors
+#define DD_SW_TWO 24                  // rows a workgroup from which on there are two per CU
 #define DD_SW_FOLD 32                 // rows between the FP64 additions
 #define DD_SW_OUT 0x80000000u         // an offset past every descriptor's range
 
@@ -72,29 +73,37 @@ struct SweepTile {
 
 // Cuts the active problems into the tiles of one cycle's sweeps: strips times
 // bands of h rows, the same h for all, chosen so that the tiles fill the fewest
-// row steps of gmax workgroups (a tile takes h + 2 of them: the halo rows are
-// recomputed), with at most `most` tiles.  Within a problem the strips of a
+// row steps of G workgroups (a tile takes h + 2 of them: the halo rows are
+// recomputed), with at most `most` tiles.  G is one workgroup per compute unit
+// (ncu), or two where that leaves each of them DD_SW_TWO rows or more: up to 64
+// vectors two are resident, and one computes while the other waits.  Measured
+// per step: 64 problems of 480 x 240 729 us with one and 708 with two, one such
+// problem alone 28 and 33 us.  Within a problem the strips of a
 // band follow each other, so that the workgroups that walk neighbouring strips
 // run at the same time on the same XCD and its L2 serves the cache lines that
 // the strips share at their edges: 62 columns are 496 bytes, which touch five
 // lines of 128.  A problem's tiles, and with them its partial rows, are
 // consecutive from tile0[p].
-__global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int gmax, int most) {
+__global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int most) {
   __shared__ int cnt[DD_BLOCK];
   __shared__ long long best_l[DD_BLOCK];
   const int t = threadIdx.x;
   // thread t judges the heights t + 1, t + 257, ...
-  long long best = 1ll << 62;
+  long long best = 1ll << 62, rows = 0;
   int nymax = 1;
   for (int p = 0; p < P.nb; ++p)
-    if (P.stI[p * ST_NI + ST_ACTIVE] != 0) nymax = max(nymax, P.desc[p].ny);
+    if (P.stI[p * ST_NI + ST_ACTIVE] != 0) {
+      nymax = max(nymax, P.desc[p].ny);
+      rows += (long long)sw_strips(P.desc[p].nx) * P.desc[p].ny;
+    }
+  const int G = (rows >= 2ll * ncu * DD_SW_TWO) ? 2 * ncu : ncu;
   for (int h = t + 1; h <= nymax; h += DD_BLOCK) {
     long long n = 0;
     for (int p = 0; p < P.nb; ++p)
       if (P.stI[p * ST_NI + ST_ACTIVE] != 0)
         n += (long long)sw_strips(P.desc[p].nx) * ((P.desc[p].ny + h - 1) / h);
     if (n <= most || h == nymax) {
-      const long long steps = (n + gmax - 1) / gmax * (h + 2);
+      const long long steps = (n + G - 1) / G * (h + 2);
       best = min(best, (steps << 31) | (unsigned)h);
     }
   }
@@ -133,7 +142,10 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int gmax, in
     done += cnt[DD_BLOCK - 1];
     __syncthreads();
   }
-  if (t == 0) P.sw_count[0] = done;
+  if (t == 0) {
+    P.sw_count[0] = done;
+    P.sw_count[1] = G;
+  }
 }
 
 template <int PER> struct SweepRow {
@@ -157,7 +169,8 @@ __device__ __forceinline__ float2 from_east(float2 v) {
 // preconditioner, z = P_L A P_R q~.
 template <int NW, int PER, bool PC>
 __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
-  const int count = ld_uni(P.sw_count), G = gridDim.x;
+  const int count = ld_uni(P.sw_count), G = ld_uni(P.sw_count + 1);
+  if ((int)blockIdx.x >= G) return;
   // workgroup b runs on XCD b % 8: give each XCD neighbouring tiles
   const int g = (G % 8 == 0) ? (int)(blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : blockIdx.x;
   const int lane = threadIdx.x & 63;

@@ -67,6 +67,13 @@ enum { SD_BNORM = 0, SD_RHO, SD_BETA, SD_TRUE, SD_EST, SD_NSUM, SD_NSUM2, SD_PRH
 enum { MODE_START = 0, MODE_ARNOLDI = 1 };
 
 struct SweepTile;
+// The tiles of one cycle's sweeps (k_sweep_plan)
+struct SweepPlan {
+  SweepTile* tiles;
+  int* count;         // [2] tiles, workgroups that share them
+  int* tile0;         // [nb]
+  int* ntile;         // [nb]
+};
 
 struct PlanDev {
   const ProbDesc* desc;
@@ -104,8 +111,6 @@ struct PlanDev {
   // (k_sweep_plan)
   float2* coefS;      // [nb][128]
   float* zs;          // [nb]
-  SweepTile* sw_tiles;
-  int* sw_count;      // [2] tiles, workgroups that share them
-  int* sw_tile0;      // [nb]
-  int* sw_ntile;      // [nb]
+  double* ccpart;     // [nb][33] ||w||^2 and the parts of the first pass's ||c||^2
+  SweepPlan sw, sw2;  // k_sweep, k_pass2
 };

@@ -165,10 +165,14 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   if (s->fused == 2) {
     A.carve(&P.coefS, (size_t)nb * DD_SW_MAXN);
     A.carve(&P.zs, (size_t)nb);
-    A.carve(&P.sw_tiles, (size_t)s->sw_most);
-    A.carve(&P.sw_count, 2);
-    A.carve(&P.sw_tile0, (size_t)nb);
-    A.carve(&P.sw_ntile, (size_t)nb);
+    A.carve(&P.ccpart, (size_t)nb * 33);
+    for (SweepPlan* w : {&P.sw, &P.sw2}) {
+      if (w == &P.sw2 && P.reorth_mode == 0) break;
+      A.carve(&w->tiles, (size_t)s->sw_most);
+      A.carve(&w->count, 2);
+      A.carve(&w->tile0, (size_t)nb);
+      A.carve(&w->ntile, (size_t)nb);
+    }
   }
 }
 
@@ -298,8 +302,7 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
   // One sweep per Arnoldi step: in complex64 always where it applies (a basis
   // of at most 128 vectors whose offsets fit a buffer descriptor), in
   // complex128 on request.
-  const bool one_pass = o.cgs_passes == 1 && NC <= DD_SW_MAXN;
-  if (one_pass && o.inner == DD_C64) {
+  if (o.inner == DD_C64 && NC <= DD_SW_MAXN) {
     s->fused = 2;
     for (int p = 0; p < nb; ++p)
       if ((size_t)s->hdesc[p].Dp * 8 * DD_SW_MAXN >= (size_t)DD_SW_OUT) s->fused = 0;
@@ -307,7 +310,7 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     int strips = 0;                        // one tile each at the least
     for (int p = 0; p < nb; ++p) strips += sw_strips(ops[p]->nx);
     s->sw_most = std::max(strips, 4 * s->sw_grid);
-  } else if (one_pass && o.fused) {
+  } else if (o.fused && o.cgs_passes == 1 && NC <= DD_FUSED_MAXN) {
     s->fused = 1;
   }
   // Fused sweep tiles: strips of DD_FUSED_SW columns walked down bands of rows
@@ -602,12 +605,31 @@ static void launch_sweep(dd_solver* s, int j, hipStream_t st) {
   else k_sweep<8, 16, PC><<<g, 512, 0, st>>>(s->P, j);
 }
 
-// One fused Arnoldi step: the sweep (update of step j, matvec and dots of
-// step j + 1) and its FP64 bookkeeping.
+static void launch_pass2(dd_solver* s, int j, hipStream_t st) {
+  const int n = s->o.kmax + j + 1, g = s->sw_grid;
+  if (n <= 16) k_pass2<4, 4><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 32) k_pass2<4, 8><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 48) k_pass2<4, 12><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 64) k_pass2<4, 16><<<g, 256, 0, st>>>(s->P, j);
+  else if (n <= 80) k_pass2<8, 10><<<g, 512, 0, st>>>(s->P, j);
+  else if (n <= 96) k_pass2<8, 12><<<g, 512, 0, st>>>(s->P, j);
+  else if (n <= 112) k_pass2<8, 14><<<g, 512, 0, st>>>(s->P, j);
+  else k_pass2<8, 16><<<g, 512, 0, st>>>(s->P, j);
+}
+
+// One fused Arnoldi step: the second Gram-Schmidt pass of step j where two are
+// asked for, then the sweep (update of step j, matvec and dots of step j + 1)
+// and its FP64 bookkeeping.
 template <typename T>
 static void launch_fused_step(dd_solver* s, int j, hipStream_t st) {
   const int nt = (int)s->htiles.size();
   const bool pc = s->o.precond != DD_PRECOND_NONE;
+  if (s->P.reorth_mode != 0) {
+    prof_mark(s, 1, st);
+    launch_pass2(s, j, st);
+    prof_end(s, st);
+    k_post_pass2<<<dim3(s->nb, post_slices(s, false)), DD_BLOCK, 0, st>>>(s->P, j);
+  }
   prof_mark(s, 3, st);
   if constexpr (sizeof(T) == 4) {
     if (pc) launch_sweep<true>(s, j, st);
@@ -682,7 +704,11 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     int active = 0;
     for (int p = 0; p < nb; ++p) active += snap[0][p * ST_NI + ST_ACTIVE];
     if (active == 0) break;
-    if (s->fused == 2) k_sweep_plan<<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
+    if (s->fused == 2) {
+      k_sweep_plan<false><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
+      if (s->P.reorth_mode != 0)
+        k_sweep_plan<true><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
+    }
     launch_start<T, R>(s, st);
     if (s->fused) {
       // z_0 = A q~_0 (unscaled) and its dots; then the coefficients of step 0
@@ -793,6 +819,7 @@ extern "C" dd_status dd_solver_solve(dd_solver* s, const void* const* b, const v
         // sweep of a step with n basis vectors: ib D (n + 3) + eb D
         const double cyc = st[ST_CYCLES], kk = s->hdesc[p].k;
         s->ks.bytes[0] += ((2 * ib + eb) + ib * (kk + 1)) * D * cyc;
+        s->ks.bytes[1] += ib * D * (sd[SD_NSUM2] + 2 * st2);   // a second pass reads n and z
         s->ks.bytes[3] += ib * D * (sd[SD_NSUM] + 3 * steps) + eb * D * steps;
       } else {
         s->ks.bytes[0] += (2 * ib + eb) * D * steps + ib * D * sd[SD_NSUM];

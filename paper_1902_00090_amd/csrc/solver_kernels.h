@@ -1044,12 +1044,17 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
   double2* cNew = ((init || (j & 1)) ? P.coefA : P.coefA2) + (size_t)p * P.NC;
   double2* cB = P.coefB + (size_t)p * P.NC;
   double2 gj = make_double2(0.0, 0.0);
-  int it0 = 0;
-  double nsum0 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
+  int it0 = 0, nre0 = 0;
+  double nsum0 = 0.0, nsum20 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
+  // the step took a second pass: its coefficients are in coefB (k_post_pass2)
+  const bool two = P.fused == 2 && P.reorth_mode != 0;
+  const int cgs2 = (two && !init) ? st[ST_REORTH] : 0;
   if (lead && t == 0 && !init) {
     gj = P.g[(size_t)p * (m + 1) + j];
     it0 = st[ST_ITERS];
+    nre0 = st[ST_NREORTH];
     nsum0 = sd[SD_NSUM];
+    nsum20 = sd[SD_NSUM2];
     bn = sd[SD_PBNORM];
     ctl_tol = P.ctl[0];
     ctl_maxit = P.ctl[1];
@@ -1073,6 +1078,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
         const double2 dv = cOld[v];
         const double sv = (v < k) ? 1.0 : hs[v - k];
         cv[q] = make_double2(sv * sj * dv.x, sv * sj * dv.y);
+        if (cgs2) cv[q] = dadd(cv[q], cB[v]);
       }
     }
     if (t < j) {
@@ -1095,7 +1101,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     const int nv = (c0 < c1) ? 2 * (c1 - c0) : 0;
     const int gfix = max(1, min(64, DD_BLOCK / (2 * per + 1)));
     // the sweeps write FP64 rows
-    reduce_rows<double>(P, P.fused == 2 ? P.sw_tile0[p] : d.t0, P.fused == 2 ? P.sw_ntile[p] : d.nt,
+    reduce_rows<double>(P, P.fused == 2 ? P.sw.tile0[p] : d.t0, P.fused == 2 ? P.sw.ntile[p] : d.nt,
                         nv + 1, red, (c0 < c1) ? 2 * c0 : 2 * nn, 2 * nn, gfix);
     if (t == 0) nrm2[0] = red[nv];
     __syncthreads();
@@ -1109,18 +1115,20 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
         if (v < k + j + 1) col[v] = cv[q];
       }
       __syncthreads();
-      arnoldi_column(P, p, j, k, col, nrm, snew, 0, gj, it0, 0, nsum0, 0.0, bn, ctl_tol,
-                     ctl_maxit, cs_t, sn_t, fin, nfin);
+      arnoldi_column(P, p, j, k, col, nrm, snew, cgs2, gj, it0, nre0, nsum0, nsum20, bn,
+                     ctl_tol, ctl_maxit, cs_t, sn_t, fin, nfin);
       __syncthreads();
     }
   }
   // the new raw dots and update coefficients (s_v for v <= k + j are those
   // of earlier steps; s_{j+1} = snew)
+  double cc = 0.0;      // the slice's part of the first pass's ||c||^2
   for (int v = c0 + t; v < c1; v += DD_BLOCK) {
     const double2 dv = make_double2(red[2 * (v - c0)], red[2 * (v - c0) + 1]);
     const double sv = (v < k) ? 1.0 : (v - k == (init ? 0 : j + 1) ? snew : hs[v - k]);
     const double gs = snew * sv * sv;
     cNew[v] = dv;
+    cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
     if (P.fused == 2)
       P.coefS[(size_t)p * DD_SW_MAXN + v] =
           make_float2((float)(gs * dv.x), (float)(gs * dv.y));
@@ -1135,9 +1143,60 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
         P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2(0.f, 0.f);
     if (t == 0) P.zs[p] = (float)snew;
   }
+  if (two && P.reorth_mode == 2) {
+    // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
+    __shared__ double cc_l[8];
+    cc = block_sum1<double>(cc, cc_l);
+    double* out = P.ccpart + (size_t)p * 33;
+    if (t == 0) out[1 + blockIdx.y] = cc;
+    if (lead && t < 64) {
+      // ||z||^2: the last of the first matvec's values, or the sweep's
+      double zz = 0.0;
+      if (init) {
+        const PT* row = (const PT*)P.partial + (size_t)d.blk0 * P.NV + 2 * ((nn + 15) / 16) * 16;
+        for (int c = t; c < d.nblk; c += 64) zz += (double)row[(size_t)c * P.NV];
+      } else {
+        const double* row = (const double*)P.partial + (size_t)P.sw.tile0[p] * P.NV + 2 * nn + 1;
+        for (int c = t; c < P.sw.ntile[p]; c += 64) zz += row[(size_t)c * P.NV];
+      }
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) zz += __shfl_xor(zz, o, DD_WAVE);
+      if (t == 0) out[0] = snew * snew * zz;
+    }
+  }
   if (lead && !init) {
     __syncthreads();
     if (fin) finish_cycle(P, p, k, nfin);
+  }
+}
+
+// After the second pass of a complex64 one-sweep step: the coefficients
+// h2_v = s_v e_v of the raw dots e_v (coefB, added to the column by
+// k_post_fused) and the update coefficients s_v h2_v for the sweep, whose z is
+// now the once orthogonalised vector.  Without a second pass the sweep takes
+// the first pass's coefficients, which are already in place.
+__global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
+  const int p = blockIdx.x;
+  int* st = P.stI + p * ST_NI;
+  if (st[ST_ACTIVE] == 0) return;
+  const bool re = sw_second_pass(P, p);
+  const int t = threadIdx.x;
+  if (blockIdx.y == 0 && t == 0) {
+    st[ST_REORTH] = re ? 1 : 0;
+    if (re) P.zs[p] = 1.f;
+  }
+  if (!re) return;
+  const int k = P.desc[p].k, n = k + j + 1;
+  __shared__ double red[DD_NV_MAX];
+  const int per = (n + gridDim.y - 1) / gridDim.y;
+  const int c0 = blockIdx.y * per, c1 = min(n, c0 + per);
+  if (c0 >= c1) return;
+  reduce_rows<double>(P, P.sw2.tile0[p], P.sw2.ntile[p], 2 * (c1 - c0), red, 2 * c0);
+  for (int v = c0 + t; v < c1; v += DD_BLOCK) {
+    const double sv = (v < k) ? 1.0 : P.hscale[(size_t)p * (P.m + 1) + v - k];
+    const double2 h = make_double2(sv * red[2 * (v - c0)], sv * red[2 * (v - c0) + 1]);
+    P.coefB[(size_t)p * P.NC + v] = h;
+    P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2((float)(sv * h.x), (float)(sv * h.y));
   }
 }
 

@@ -24,7 +24,7 @@ struct dd_solver {
   size_t bytes = 0;       // device workspace of the solver (owned or the caller's)
   bool owns_workspace = true;
   // one-sweep Arnoldi steps: 0 off, 1 k_fused_sweep (complex128), 2 k_sweep
-  // (complex64), both with cgs_passes = 1 and kmax + m + 1 <= 128
+  // (complex64; with two passes also k_pass2), both for kmax + m + 1 <= 128
   int fused = 0;
   int sw_grid = 0;        // workgroups of k_sweep
   int sw_most = 0;        // tiles of a cycle, at most

@@ -66,10 +66,18 @@ __host__ __device__ inline int sw_width(int nx) {
   return (nx + s - 1) / s;
 }
 
-// One tile: rows [y0, y0 + rows) of a strip of problem p.
+// One tile: rows [y0, y0 + rows) of a strip of problem p.  The second
+// Gram-Schmidt pass has no stencil: its one strip's rows are runs of 64 cells.
 struct SweepTile {
   int p, strip, y0, rows;
 };
+
+template <bool PASS2> __device__ __forceinline__ int sw_plan_strips(const ProbDesc& d) {
+  return PASS2 ? 1 : sw_strips(d.nx);
+}
+template <bool PASS2> __device__ __forceinline__ int sw_plan_rows(const ProbDesc& d) {
+  return PASS2 ? (d.D + 63) / 64 : d.ny;
+}
 
 // Cuts the active problems into the tiles of one cycle's sweeps: strips times
 // bands of h rows, the same h for all, chosen so that the tiles fill the fewest
@@ -84,7 +92,9 @@ struct SweepTile {
 // the strips share at their edges: 62 columns are 496 bytes, which touch five
 // lines of 128.  A problem's tiles, and with them its partial rows, are
 // consecutive from tile0[p].
+template <bool PASS2>
 __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int most) {
+  const SweepPlan& W = PASS2 ? P.sw2 : P.sw;
   __shared__ int cnt[DD_BLOCK];
   __shared__ long long best_l[DD_BLOCK];
   const int t = threadIdx.x;
@@ -93,15 +103,16 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int
   int nymax = 1;
   for (int p = 0; p < P.nb; ++p)
     if (P.stI[p * ST_NI + ST_ACTIVE] != 0) {
-      nymax = max(nymax, P.desc[p].ny);
-      rows += (long long)sw_strips(P.desc[p].nx) * P.desc[p].ny;
+      nymax = max(nymax, sw_plan_rows<PASS2>(P.desc[p]));
+      rows += (long long)sw_plan_strips<PASS2>(P.desc[p]) * sw_plan_rows<PASS2>(P.desc[p]);
     }
   const int G = (rows >= 2ll * ncu * DD_SW_TWO) ? 2 * ncu : ncu;
   for (int h = t + 1; h <= nymax; h += DD_BLOCK) {
     long long n = 0;
     for (int p = 0; p < P.nb; ++p)
       if (P.stI[p * ST_NI + ST_ACTIVE] != 0)
-        n += (long long)sw_strips(P.desc[p].nx) * ((P.desc[p].ny + h - 1) / h);
+        n += (long long)sw_plan_strips<PASS2>(P.desc[p]) *
+             ((sw_plan_rows<PASS2>(P.desc[p]) + h - 1) / h);
     if (n <= most || h == nymax) {
       const long long steps = (n + G - 1) / G * (h + 2);
       best = min(best, (steps << 31) | (unsigned)h);
@@ -119,8 +130,8 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int
     const int p = b + t;
     int r = 0, strips = 1;
     if (p < P.nb && P.stI[p * ST_NI + ST_ACTIVE] != 0) {
-      strips = sw_strips(P.desc[p].nx);
-      r = strips * ((P.desc[p].ny + h - 1) / h);
+      strips = sw_plan_strips<PASS2>(P.desc[p]);
+      r = strips * ((sw_plan_rows<PASS2>(P.desc[p]) + h - 1) / h);
     }
     cnt[t] = r;
     __syncthreads();
@@ -131,21 +142,37 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int
       __syncthreads();
     }
     if (p < P.nb) {
-      const int t0 = done + cnt[t] - r, ny = P.desc[p].ny;
-      P.sw_tile0[p] = t0;
-      P.sw_ntile[p] = r;
+      const int t0 = done + cnt[t] - r, ny = sw_plan_rows<PASS2>(P.desc[p]);
+      W.tile0[p] = t0;
+      W.ntile[p] = r;
       for (int i = 0; i < r; ++i) {
         const int y0 = i / strips * h;
-        P.sw_tiles[t0 + i] = {p, i % strips, y0, min(h, ny - y0)};
+        W.tiles[t0 + i] = {p, i % strips, y0, min(h, ny - y0)};
       }
     }
     done += cnt[DD_BLOCK - 1];
     __syncthreads();
   }
   if (t == 0) {
-    P.sw_count[0] = done;
-    P.sw_count[1] = G;
+    W.count[0] = done;
+    W.count[1] = G;
   }
+}
+
+// Adds the lanes' dots to the wave's sums: lanes 2 i and 2 i + 1 hold value i
+// (real and imaginary parts alternate).
+template <int PER>
+__device__ __forceinline__ void sw_fold(float2 (&acc)[PER], double& dsum, int lane) {
+  float v[32];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    v[2 * i] = (i < PER) ? acc[i < PER ? i : 0].x : 0.f;
+    v[2 * i + 1] = (i < PER) ? acc[i < PER ? i : 0].y : 0.f;
+  }
+  butterfly_step<float, 32>(v, lane);
+  dsum += (double)(v[0] + __shfl_xor(v[0], 1, 64));
+#pragma unroll
+  for (int i = 0; i < PER; ++i) acc[i] = make_float2(0.f, 0.f);
 }
 
 template <int PER> struct SweepRow {
@@ -169,7 +196,7 @@ __device__ __forceinline__ float2 from_east(float2 v) {
 // preconditioner, z = P_L A P_R q~.
 template <int NW, int PER, bool PC>
 __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
-  const int count = ld_uni(P.sw_count), G = ld_uni(P.sw_count + 1);
+  const int count = ld_uni(P.sw.count), G = ld_uni(P.sw.count + 1);
   if ((int)blockIdx.x >= G) return;
   // workgroup b runs on XCD b % 8: give each XCD neighbouring tiles
   const int g = (G % 8 == 0) ? (int)(blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : blockIdx.x;
@@ -179,7 +206,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
   const float2 zero = make_float2(0.f, 0.f);
 
   for (int tile = g; tile < count; tile += G) {
-    const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw_tiles + tile);
+    const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw.tiles + tile);
     const int p = tl->p, strip = tl->strip, ya = tl->y0, nrows = tl->rows;
     if (ld_uni(P.stI + p * ST_NI + ST_ACTIVE) == 0) continue;   // ended within this cycle
     const auto* d = (const __attribute__((address_space(4))) ProbDesc*)(P.desc + p);
@@ -208,31 +235,24 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) acc[i] = zero;
     float2 accn = zero;                              // conj(q~_{j+1}) z_{j+1}
-    float un2 = 0.f;                                 // ||q~_{j+1}||^2
-    double dsum = 0.0, dn0 = 0.0, dn1 = 0.0, dn2 = 0.0;
+    float un2 = 0.f, zz2 = 0.f;                      // ||q~_{j+1}||^2, ||z_{j+1}||^2
+    double dsum = 0.0, dn0 = 0.0, dn1 = 0.0, dn2 = 0.0, dn3 = 0.0;
     auto fold = [&]() {
-      float v[32];
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        v[2 * i] = (i < PER) ? acc[i < PER ? i : 0].x : 0.f;
-        v[2 * i + 1] = (i < PER) ? acc[i < PER ? i : 0].y : 0.f;
-      }
-      butterfly_step<float, 32>(v, lane);
-      dsum += (double)(v[0] + __shfl_xor(v[0], 1, 64));
-#pragma unroll
-      for (int i = 0; i < PER; ++i) acc[i] = zero;
+      sw_fold<PER>(acc, dsum, lane);
       if (wave == 0) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
           accn.x += __shfl_xor(accn.x, o, 64);
           accn.y += __shfl_xor(accn.y, o, 64);
           un2 += __shfl_xor(un2, o, 64);
+          zz2 += __shfl_xor(zz2, o, 64);
         }
         dn0 += (double)accn.x;
         dn1 += (double)accn.y;
         dn2 += (double)un2;
+        dn3 += (double)zz2;
         accn = zero;
-        un2 = 0.f;
+        un2 = zz2 = 0.f;
       }
     };
 
@@ -318,6 +338,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
         if (wave == 0) {
           accn.x += u1.x * z.x + u1.y * z.y;
           accn.y += u1.x * z.y - u1.y * z.x;
+          zz2 += z.x * z.x + z.y * z.y;
         }
       }
       if (wave == 0 && mine && owned) {
@@ -354,6 +375,113 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
       prow[2 * n] = dn0;
       prow[2 * n + 1] = dn1;
       prow[2 * n + 2] = dn2;
+      prow[2 * n + 3] = dn3;
     }
+  }
+}
+
+// Whether the step takes the second Gram-Schmidt pass: never, always, or when
+// the first pass removes more than half of ||w||^2 (the test of Kahan and
+// Parlett, from the sums that k_post_fused left).
+__device__ __forceinline__ bool sw_second_pass(const PlanDev& P, int p) {
+  if (P.reorth_mode != 2) return P.reorth_mode == 1;
+  const double* cc = P.ccpart + (size_t)p * 33;     // [0] ||w||^2, then the slices' parts
+  const double ww = ld_uni(cc);
+  double c = 0.0;
+#pragma unroll
+  for (int i = 1; i <= 32; ++i) c += ld_uni(cc + i);
+  return ww - c < 0.5 * ww;
+}
+
+// Second Gram-Schmidt pass of step j: z_j <- zs z_j - sum_v g_v b_v in place and
+// the raw dots of the result with the basis, one read of the basis.  The tiles
+// are runs of 64 cells; otherwise as k_sweep, without halos and stencil: a run
+// is updated and dotted at once, so three register sets rotate.
+template <int NW, int PER>
+__global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
+  const int count = ld_uni(P.sw2.count), G = ld_uni(P.sw2.count + 1);
+  if ((int)blockIdx.x >= G) return;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  __shared__ float2 part[2][NW][64];
+  const float2 zero = make_float2(0.f, 0.f);
+
+  for (int tile = blockIdx.x; tile < count; tile += G) {
+    const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw2.tiles + tile);
+    const int p = tl->p, ya = tl->y0, N = tl->rows;
+    if (ld_uni(P.stI + p * ST_NI + ST_ACTIVE) == 0 || !sw_second_pass(P, p)) continue;
+    const auto* d = (const __attribute__((address_space(4))) ProbDesc*)(P.desc + p);
+    const int k = d->k, n = k + j + 1;
+    const size_t Dp = d->Dp;
+    const float2* B = (const float2*)d->basis + (size_t)(P.kmax - k) * Dp;
+    float2* z = (float2*)d->Z + (size_t)(j & 1) * Dp;
+    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * 8);
+    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(z, (size_t)Dp * 8);
+    const unsigned vec = (unsigned)Dp * 8u;
+    const float2* cS = P.coefS + (size_t)p * DD_SW_MAXN + wave;
+    float2 gc[PER], acc[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      gc[i] = ld_uni(cS + NW * i);
+      acc[i] = zero;
+    }
+    const float zs = ld_uni(P.zs + p);
+    double dsum = 0.0;
+    struct Run {
+      float2 b[PER], z;
+    } S0, S1, S2;
+    const unsigned ob = (unsigned)lane * 8u + (unsigned)wave * vec;
+    const unsigned oz = (wave == NW - 1) ? (unsigned)lane * 8u : DD_SW_OUT;
+    auto load = [&](Run& s, int t) {
+      // a run past the tile is not fetched
+      const unsigned row = (t < N) ? (unsigned)(ya + t) * 512u : DD_SW_OUT;
+      unsigned o = ob + row;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        s.b[i] = sw_ld2(rB, o);
+        o += NW * vec;
+        asm("" : "+v"(o));
+      }
+      s.z = sw_ld2(rZ, (t < N) ? oz + row : DD_SW_OUT);
+    };
+    auto step = [&](Run& cur, Run& ahead, int t) {
+      load(ahead, t + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      float2 pu = cmk<float2>(-zs * cur.z.x, -zs * cur.z.y);
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        pu.x = fmaf(-gc[i].y, cur.b[i].y, fmaf(gc[i].x, cur.b[i].x, pu.x));
+        pu.y = fmaf(gc[i].y, cur.b[i].x, fmaf(gc[i].x, cur.b[i].y, pu.y));
+      }
+      part[t & 1][wave][lane] = pu;
+      __syncthreads();
+      float2 u = zero;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) u = csub(u, part[t & 1][q][lane]);
+      if (wave == 1) z[(ya + t) * 64 + lane] = u;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) {
+        acc[i].x = fmaf(cur.b[i].y, u.y, fmaf(cur.b[i].x, u.x, acc[i].x));
+        acc[i].y = fmaf(-cur.b[i].y, u.x, fmaf(cur.b[i].x, u.y, acc[i].y));
+      }
+      if (t % DD_SW_FOLD == DD_SW_FOLD - 1) sw_fold<PER>(acc, dsum, lane);
+    };
+    __syncthreads();          // the parts of the tile before have been read
+    load(S0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load(S1, 1);
+    __builtin_amdgcn_sched_barrier(0);
+    int t = 0;
+    for (; t + 3 <= N; t += 3) {
+      step(S0, S2, t);
+      step(S1, S0, t + 1);
+      step(S2, S1, t + 2);
+    }
+    if (t < N) step(S0, S2, t);
+    if (t + 1 < N) step(S1, S0, t + 1);
+    sw_fold<PER>(acc, dsum, lane);
+    double* prow = (double*)P.partial + (size_t)tile * P.NV;
+    const int idx = lane >> 1, v = wave + NW * (idx >> 1);
+    if ((lane & 1) == 0 && idx < 2 * PER && v < n) prow[2 * v + (idx & 1)] = dsum;
   }
 }

@@ -31,7 +31,7 @@ def _inst(seed, nx, ny):
     return W.Instance(eps, W.random_complex(rng, nx * ny), nx, ny, 0.04, 1.55, 3)
 
 
-def _check(s, p, A, steps):
+def _check(s, p, A, steps, passes=1):
     H, B = s.debug(p, "H").T, s.debug(p, "B").T
     Q = s.debug(p, "Q").T.astype(np.complex128)
     C = s.debug(p, "C").T.astype(np.complex128)
@@ -46,8 +46,12 @@ def _check(s, p, A, steps):
         d = basis[:, :n].conj().T @ z
         assert np.abs(h - d).max() <= (12 + 40 + 4) * U32 * size, j
         r = z - basis[:, :n] @ h - H[j + 1, j] * Q[:, j + 1]
-        assert np.linalg.norm(r) <= (12 + n / 8 + 9 + 4) * U32 * (size + np.abs(h).sum()), j
+        assert np.linalg.norm(r) <= (12 + passes * (n / 8 + 9) + 4) * U32 * (size + np.abs(h).sum()), j
         assert abs(np.linalg.norm(Q[:, j + 1]) - 1) <= 60 * U32, j
+    if passes == 2:     # orthogonal to the rounding of one dot product and one update
+        E = basis[:, :k + steps + 1]
+        E = E.conj().T @ E - np.eye(k + steps + 1)
+        assert np.abs(E).max() <= 2 * (44 + (k + steps) / 8 + 13) * U32
 
 
 # nx: one strip, the widest strip, the narrowest second strip, an even split,
@@ -66,6 +70,36 @@ def test_one_cycle_relations(nx, ny, k, restart):
     _, (info,), _ = s.solve([b], tol=0.0, maxit=restart)
     assert info["iters"] == restart
     _check(s, 0, fdfd.assemble_instance(inst), restart)
+    s.close()
+
+
+# runs of 64 cells: a part of one, one, several and a remainder; the same widths
+@pytest.mark.parametrize("nx,ny,k,restart,adaptive", [
+    (9, 7, 0, 20, False), (20, 16, 0, 33, True), (63, 9, 3, 61, False), (125, 11, 0, 97, True),
+    (61, 40, 20, 107, False)])
+def test_two_passes(nx, ny, k, restart, adaptive):
+    from paper_1902_00090_amd import FdfdOp, Solver
+    inst = _inst(nx + ny, nx, ny)
+    s = Solver([FdfdOp.from_instance(inst)], restart=restart, kmax=k, cgs_passes=2,
+               select_reorth=adaptive)
+    if k:
+        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(np.complex64)
+        s.set_subspace([torch.tensor(V, device="cuda")])
+    b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
+    _, (info,), _ = s.solve([b], tol=0.0, maxit=restart)
+    assert info["iters"] == restart
+    if not adaptive:
+        assert info["reorth_steps"] == restart
+        _check(s, 0, fdfd.assemble_instance(inst), restart, 2)
+    else:
+        # the test as stated, on the stored column: ||w||^2 = ||c||^2 + h_{j+1,j}^2
+        H, B = s.debug(0, "H").T, s.debug(0, "B").T
+        c = [np.sum(np.abs(H[:j + 1, j]) ** 2) + np.sum(np.abs(B[:, j]) ** 2)
+             for j in range(restart)]
+        share = [H[j + 1, j].real ** 2 / (c[j] + H[j + 1, j].real ** 2) for j in range(restart)]
+        sure = sum(x < 0.49 for x in share), sum(x < 0.51 for x in share)
+        assert sure[0] <= info["reorth_steps"] <= sure[1]
+        _check(s, 0, fdfd.assemble_instance(inst), restart, 1.999)
     s.close()
 
 

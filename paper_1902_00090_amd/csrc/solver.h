@@ -113,4 +113,7 @@ struct PlanDev {
   float* zs;          // [nb]
   double* ccpart;     // [nb][33] ||w||^2 and the parts of the first pass's ||c||^2
   SweepPlan sw, sw2;  // k_sweep, k_pass2
+  size_t sw_ld;       // tiles of a cycle at most: stride of a value's partial sums
+  int* live;          // [2][nb] the cycle goes on after the step before (by its parity)
+  int* hostact;       // [nb] host memory: progress of the solve (k_post_sweep)
 };

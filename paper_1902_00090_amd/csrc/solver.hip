@@ -90,6 +90,7 @@ extern "C" void dd_solver_destroy(dd_solver* s) {
     if (g) (void)hipGraphDestroy(g);
   if (s->cap) (void)hipStreamDestroy(s->cap);
   if (s->hctl) (void)hipHostFree(s->hctl);
+  if (s->hostact) (void)hipHostFree(s->hostact);
   delete s;
 }
 
@@ -158,6 +159,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   const size_t rows = std::max<size_t>({(size_t)s->nchunks, s->htiles.size(),
                                         s->fused == 2 ? (size_t)s->sw_most : 0});
   A.carve(&part, rows * P.NV);
+  P.sw_ld = (size_t)s->sw_most;
   P.partial = part;
   A.carve(&P.gpart, (size_t)nb * P.GB * std::max(1, gram_tiles(std::max(K, 1))) * 32);
   A.carve(&P.hist, (size_t)nb * std::max(1, o.hist_cap));
@@ -165,6 +167,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   if (s->fused == 2) {
     A.carve(&P.coefS, (size_t)nb * DD_SW_MAXN);
     A.carve(&P.zs, (size_t)nb);
+    A.carve(&P.live, (size_t)2 * nb);
     A.carve(&P.ccpart, (size_t)nb * 33);
     for (SweepPlan* w : {&P.sw, &P.sw2}) {
       if (w == &P.sw2 && P.reorth_mode == 0) break;
@@ -400,6 +403,7 @@ extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const d
     chk(hipHostMalloc((void**)&s->pinned, sizeof(int) * 3 * nb * ST_NI, hipHostMallocDefault));
     chk(hipHostMalloc((void**)&s->pinnedD, sizeof(double) * nb * SD_ND, hipHostMallocDefault));
     chk(hipHostMalloc((void**)&s->pinnedK, sizeof(unsigned long long) * nb, hipHostMallocDefault));
+    chk(hipHostMalloc((void**)&s->hostact, sizeof(int) * nb, hipHostMallocMapped | hipHostMallocCoherent));
     chk(hipHostMalloc((void**)&s->hctl, sizeof(double) * 2, hipHostMallocDefault));
     chk(hipEventCreateWithFlags(&s->ev[0], hipEventDisableTiming));
     chk(hipEventCreateWithFlags(&s->ev[1], hipEventDisableTiming));
@@ -416,6 +420,7 @@ extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const d
   P.ctl = s->dctl;
   P.fused = s->fused;
   P.tiles = s->dtiles;
+  P.hostact = s->hostact;
   e = precond_init(s);
   if (e != hipSuccess) {
     dd_set_error("dd_solver_create: %s", hipGetErrorString(e));
@@ -560,6 +565,8 @@ static void prof_collect(dd_solver* s) {
 // 32 value slices (about 256 workgroups in all), one where the adaptive
 // second-pass test needs every coefficient of the first pass at once.
 static int post_slices(const dd_solver* s, bool first_pass) {
+  // complex64 one-sweep steps: a wave a dot product, about a thousand workgroups
+  if (s->fused == 2) return std::max(4, std::min(32, 1024 / s->nb));
   if (first_pass && s->P.reorth_mode == 2) return 1;
   return std::max(1, std::min(32, 256 / std::max(1, s->nb)));
 }
@@ -639,7 +646,13 @@ static void launch_fused_step(dd_solver* s, int j, hipStream_t st) {
     else k_fused_sweep<T, false><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
   }
   prof_end(s, st);
-  k_post_fused<T><<<dim3(s->nb, post_slices(s, false)), DD_BLOCK, 0, st>>>(s->P, j, 0);
+  const int slices = post_slices(s, false);
+  if constexpr (sizeof(T) == 4) {
+    const int poll = (j + 1) % s->o.check_every == 0;
+    k_post_sweep<<<dim3(s->nb, slices + 1), DD_BLOCK, 0, st>>>(s->P, j, poll);
+  } else {
+    k_post_fused<T><<<dim3(s->nb, slices), DD_BLOCK, 0, st>>>(s->P, j, 0);
+  }
 }
 
 template <typename T, int R>
@@ -687,6 +700,35 @@ static dd_status launch_group_graph(dd_solver* s, int grp, int jend, hipStream_t
   return DD_OK;
 }
 
+// Waits until every problem has done `steps` steps of the cycle or has ended;
+// *active = those still running then.  The flags are in host memory, so neither
+// a copy nor an event enters the stream (together 10 us of an idle device every
+// check_every steps); a failed stream ends the wait.
+static dd_status wait_progress(dd_solver* s, int steps, hipStream_t st, int* active) {
+  for (int spin = 1;; ++spin) {
+    const bool drained = spin % 4096 == 0;
+    if (drained) {
+      const hipError_t e = hipStreamQuery(st);
+      if (e == hipErrorNotReady) continue;
+      DD_HIP_CHECK(e);
+    }
+    int act = 0, late = 0;
+    for (int p = 0; p < s->nb; ++p) {
+      const int v = __atomic_load_n(s->hostact + p, __ATOMIC_RELAXED);
+      late += v < 2 * steps;
+      act += v & 1;
+    }
+    if (late == 0) {
+      *active = act;
+      return DD_OK;
+    }
+    if (drained) {
+      dd_set_error("dd_solver_solve: the device made no progress");
+      return DD_EHIP;
+    }
+  }
+}
+
 template <typename T, int R>
 static dd_status run_cycles(dd_solver* s, hipStream_t st) {
   const int nb = s->nb, m = s->o.restart, g = s->nchunks;
@@ -720,6 +762,9 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
       prof_end(s, st);
       k_post_fused<T><<<dim3(nb, post_slices(s, false)), DD_BLOCK, 0, st>>>(s->P, 0, 1);
     }
+    // complex64 one-sweep steps leave their progress in host memory; no kernel
+    // of an earlier cycle runs any more
+    if (s->fused == 2) std::memset(s->hostact, 0, sizeof(int) * nb);
     int pending = -1, grp = 0;
     const int ce = s->o.check_every;
     const bool graph = s->o.use_graph && !s->prof;
@@ -733,6 +778,18 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
         if ((j + 1) % ce != 0 && j + 1 < m) continue;
       } else {
         launch_any_step<T, R>(s, j, st);
+      }
+      if (s->fused == 2) {
+        if ((j + 1) % ce == 0 && j + 1 < m) {
+          // run at most one group ahead of the device
+          if (j + 1 > ce) {
+            int act = 0;
+            dd_status rc = wait_progress(s, j + 1 - ce, st, &act);
+            if (rc != DD_OK) return rc;
+            if (act == 0) break;
+          }
+        }
+        continue;
       }
       if ((j + 1) % ce == 0 && j + 1 < m) {
         const int slot = (grp++) & 1;

@@ -1044,17 +1044,12 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
   double2* cNew = ((init || (j & 1)) ? P.coefA : P.coefA2) + (size_t)p * P.NC;
   double2* cB = P.coefB + (size_t)p * P.NC;
   double2 gj = make_double2(0.0, 0.0);
-  int it0 = 0, nre0 = 0;
-  double nsum0 = 0.0, nsum20 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
-  // the step took a second pass: its coefficients are in coefB (k_post_pass2)
-  const bool two = P.fused == 2 && P.reorth_mode != 0;
-  const int cgs2 = (two && !init) ? st[ST_REORTH] : 0;
+  int it0 = 0;
+  double nsum0 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
   if (lead && t == 0 && !init) {
     gj = P.g[(size_t)p * (m + 1) + j];
     it0 = st[ST_ITERS];
-    nre0 = st[ST_NREORTH];
     nsum0 = sd[SD_NSUM];
-    nsum20 = sd[SD_NSUM2];
     bn = sd[SD_PBNORM];
     ctl_tol = P.ctl[0];
     ctl_maxit = P.ctl[1];
@@ -1078,7 +1073,6 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
         const double2 dv = cOld[v];
         const double sv = (v < k) ? 1.0 : hs[v - k];
         cv[q] = make_double2(sv * sj * dv.x, sv * sj * dv.y);
-        if (cgs2) cv[q] = dadd(cv[q], cB[v]);
       }
     }
     if (t < j) {
@@ -1100,9 +1094,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     // order for the norm, so every slice has the same s_{j+1})
     const int nv = (c0 < c1) ? 2 * (c1 - c0) : 0;
     const int gfix = max(1, min(64, DD_BLOCK / (2 * per + 1)));
-    // the sweeps write FP64 rows
-    reduce_rows<double>(P, P.fused == 2 ? P.sw.tile0[p] : d.t0, P.fused == 2 ? P.sw.ntile[p] : d.nt,
-                        nv + 1, red, (c0 < c1) ? 2 * c0 : 2 * nn, 2 * nn, gfix);
+    reduce_rows<PT>(P, d.t0, d.nt, nv + 1, red, (c0 < c1) ? 2 * c0 : 2 * nn, 2 * nn, gfix);
     if (t == 0) nrm2[0] = red[nv];
     __syncthreads();
     const double nrm = sqrt(nrm2[0]);
@@ -1115,8 +1107,8 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
         if (v < k + j + 1) col[v] = cv[q];
       }
       __syncthreads();
-      arnoldi_column(P, p, j, k, col, nrm, snew, cgs2, gj, it0, nre0, nsum0, nsum20, bn,
-                     ctl_tol, ctl_maxit, cs_t, sn_t, fin, nfin);
+      arnoldi_column(P, p, j, k, col, nrm, snew, 0, gj, it0, 0, nsum0, 0.0, bn, ctl_tol,
+                     ctl_maxit, cs_t, sn_t, fin, nfin);
       __syncthreads();
     }
   }
@@ -1135,30 +1127,24 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     else
       cB[v] = make_double2(gs * dv.x, gs * dv.y);
   }
+  // complex64 (k_sweep): only the cycle's start comes here
   if (P.fused == 2 && lead) {
     // slots of vectors that this cycle has not reached yet meet values read as
     // zero: they hold finite numbers
-    if (init)
-      for (int v = nn + t; v < DD_SW_MAXN; v += DD_BLOCK)
-        P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2(0.f, 0.f);
+    for (int v = nn + t; v < DD_SW_MAXN; v += DD_BLOCK)
+      P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2(0.f, 0.f);
     if (t == 0) P.zs[p] = (float)snew;
   }
-  if (two && P.reorth_mode == 2) {
+  if (P.fused == 2 && P.reorth_mode == 2) {
     // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
     __shared__ double cc_l[8];
     cc = block_sum1<double>(cc, cc_l);
     double* out = P.ccpart + (size_t)p * 33;
     if (t == 0) out[1 + blockIdx.y] = cc;
     if (lead && t < 64) {
-      // ||z||^2: the last of the first matvec's values, or the sweep's
+      const PT* row = (const PT*)P.partial + (size_t)d.blk0 * P.NV + 2 * ((nn + 15) / 16) * 16;
       double zz = 0.0;
-      if (init) {
-        const PT* row = (const PT*)P.partial + (size_t)d.blk0 * P.NV + 2 * ((nn + 15) / 16) * 16;
-        for (int c = t; c < d.nblk; c += 64) zz += (double)row[(size_t)c * P.NV];
-      } else {
-        const double* row = (const double*)P.partial + (size_t)P.sw.tile0[p] * P.NV + 2 * nn + 1;
-        for (int c = t; c < P.sw.ntile[p]; c += 64) zz += row[(size_t)c * P.NV];
-      }
+      for (int c = t; c < d.nblk; c += 64) zz += (double)row[(size_t)c * P.NV];
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) zz += __shfl_xor(zz, o, DD_WAVE);
       if (t == 0) out[0] = snew * snew * zz;
@@ -1170,33 +1156,155 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
   }
 }
 
-// After the second pass of a complex64 one-sweep step: the coefficients
-// h2_v = s_v e_v of the raw dots e_v (coefB, added to the column by
-// k_post_fused) and the update coefficients s_v h2_v for the sweep, whose z is
-// now the once orthogonalised vector.  Without a second pass the sweep takes
-// the first pass's coefficients, which are already in place.
+// Sum of the tiles [t0, t0 + nt) of two neighbouring values of the sweeps'
+// partial sums (value-major, so that a wave reads them in whole lines): lanes
+// 0-31 add value v, lanes 32-63 value v + 1, in an order that depends on the
+// number of tiles alone; every lane of a half returns its sum.
+__device__ __forceinline__ double sum_tiles2(const PlanDev& P, int v, int t0, int nt) {
+  const int lane = threadIdx.x & 63;
+  const double* row = (const double*)P.partial + (size_t)(v + (lane >> 5)) * P.sw_ld + t0;
+  double s = 0.0;
+  for (int c = lane & 31; c < nt; c += 256) {
+    double a[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) a[q] = (c + 32 * q < nt) ? row[c + 32 * q] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += a[q];
+  }
+#pragma unroll
+  for (int o = 16; o >= 1; o >>= 1) s += __shfl_xor(s, o, DD_WAVE);
+  return s;
+}
+
+// After k_sweep of step j.  Workgroups y < slices of a problem: each wave takes
+// every (4 slices)-th dot product of the new z, and the norm of the new vector
+// with it, so that the coefficients of the next update need no exchange.  The
+// last workgroup forms the Arnoldi column from the dots before and updates the
+// Givens factorisation meanwhile.  The kernel is a chain of latencies (two
+// dependent loads, five shuffles, the square root, or the scan of the Givens
+// update); it moves no more than the partial sums.
+// poll: leave 2 (j + 1) + (still active) in the host's array.
+__global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int poll) {
+  const int p = blockIdx.x, slices = gridDim.y - 1, t = threadIdx.x;
+  int* st = P.stI + p * ST_NI;
+  const bool lead = (int)blockIdx.y == slices;
+  const int t0 = P.sw.tile0[p], nt = P.sw.ntile[p], k = P.desc[p].k, m = P.m;
+  const double* hs = P.hscale + (size_t)p * (m + 1);
+  // the last workgroup may end the cycle while the others still run: all go by
+  // the flag of the step before
+  if (P.live[(j & 1) * P.nb + p] == 0) {
+    if (lead && t == 0) P.live[(~j & 1) * P.nb + p] = 0;
+    if (poll && lead && t == 0)
+      __hip_atomic_store(P.hostact + p, 2 * (j + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return;
+  }
+  const int nn = k + j + 2;                     // vectors of the new dots
+  const double2* cOld = ((j & 1) ? P.coefA2 : P.coefA) + (size_t)p * P.NC;
+  double2* cNew = ((j & 1) ? P.coefA : P.coefA2) + (size_t)p * P.NC;
+  const int lane = t & 63, wave = t >> 6;
+  if (!lead) {
+    const int step = 4 * slices;
+    int v = blockIdx.y * 4 + wave;
+    const double nz = sum_tiles2(P, 2 * nn, t0, nt);       // ||q~||^2 | ||z||^2
+    const double nrm = sqrt(__shfl(nz, 0, DD_WAVE));
+    const double snew = (nrm > 0.0) ? 1.0 / nrm : 0.0;
+    double cc = 0.0;
+    for (; v < nn; v += step) {
+      const double part = sum_tiles2(P, 2 * v, t0, nt);
+      const double2 dv = make_double2(__shfl(part, 0, DD_WAVE), __shfl(part, 32, DD_WAVE));
+      const double sv = (v < k) ? 1.0 : (v - k == j + 1 ? snew : hs[v - k]);
+      const double gs = snew * sv * sv;
+      cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
+      if (lane == 0) {
+        cNew[v] = dv;
+        P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2((float)(gs * dv.x), (float)(gs * dv.y));
+      }
+    }
+    if (blockIdx.y == 0 && t == 0) P.zs[p] = (float)snew;
+    if (P.reorth_mode == 2) {
+      // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
+      __shared__ double cw[4];
+      if (lane == 0) cw[wave] = cc;
+      const double zz = __shfl(nz, 32, DD_WAVE);
+      __syncthreads();
+      double* out = P.ccpart + (size_t)p * 33;
+      if (t == 0) out[1 + blockIdx.y] = (cw[0] + cw[1]) + (cw[2] + cw[3]);
+      if (t == 0 && blockIdx.y == 0) out[0] = snew * snew * zz;
+    }
+    return;
+  }
+  // the column of step j: its dots, with a second pass's coefficients (coefB)
+  double* sd = P.stD + p * SD_ND;
+  __shared__ double2 col[DD_MAX_K + DD_MAX_M + 2];
+  __shared__ int fin, nfin;
+  const int cgs2 = P.reorth_mode != 0 ? st[ST_REORTH] : 0;
+  double2 gj = make_double2(0.0, 0.0);
+  int it0 = 0, nre0 = 0;
+  double nsum0 = 0.0, nsum20 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
+  if (t == 0) {
+    gj = P.g[(size_t)p * (m + 1) + j];
+    it0 = st[ST_ITERS];
+    nre0 = st[ST_NREORTH];
+    nsum0 = sd[SD_NSUM];
+    nsum20 = sd[SD_NSUM2];
+    bn = sd[SD_PBNORM];
+    ctl_tol = P.ctl[0];
+    ctl_maxit = P.ctl[1];
+    fin = 0;
+  }
+  double cs_t = 0.0;
+  double2 sn_t = make_double2(0.0, 0.0);
+  if (t < j) {
+    cs_t = P.cs[(size_t)p * m + t];
+    sn_t = P.sn[(size_t)p * m + t];
+  }
+  if (t < k + j + 1) {                          // k + j + 1 <= 127
+    const double2 dv = cOld[t];
+    const double sv = ((t < k) ? 1.0 : hs[t - k]) * hs[j];
+    double2 c = make_double2(sv * dv.x, sv * dv.y);
+    if (cgs2) c = dadd(c, P.coefB[(size_t)p * P.NC + t]);
+    col[t] = c;
+  }
+  const double nz = sum_tiles2(P, 2 * nn, t0, nt);
+  const double nrm = sqrt(__shfl(nz, 0, DD_WAVE));
+  const double snew = (nrm > 0.0) ? 1.0 / nrm : 0.0;
+  __syncthreads();
+  arnoldi_column(P, p, j, k, col, nrm, snew, cgs2, gj, it0, nre0, nsum0, nsum20, bn, ctl_tol,
+                 ctl_maxit, cs_t, sn_t, fin, nfin);
+  __syncthreads();
+  if (fin) finish_cycle(P, p, k, nfin);
+  if (t == 0) P.live[(~j & 1) * P.nb + p] = fin ? 0 : 1;
+  if (poll && t == 0)
+    __hip_atomic_store(P.hostact + p, 2 * (j + 1) + (fin ? 0 : 1), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// After k_pass2 of step j: the coefficients h2_v = s_v e_v of the raw dots e_v
+// (coefB, added to the column by k_post_sweep) and the update coefficients
+// s_v h2_v for the sweep, whose z is now the once orthogonalised vector.
+// Without a second pass the sweep takes the first pass's coefficients, which
+// are already in place.
 __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
   const int p = blockIdx.x;
   int* st = P.stI + p * ST_NI;
   if (st[ST_ACTIVE] == 0) return;
   const bool re = sw_second_pass(P, p);
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if (blockIdx.y == 0 && t == 0) {
     st[ST_REORTH] = re ? 1 : 0;
     if (re) P.zs[p] = 1.f;
   }
   if (!re) return;
   const int k = P.desc[p].k, n = k + j + 1;
-  __shared__ double red[DD_NV_MAX];
-  const int per = (n + gridDim.y - 1) / gridDim.y;
-  const int c0 = blockIdx.y * per, c1 = min(n, c0 + per);
-  if (c0 >= c1) return;
-  reduce_rows<double>(P, P.sw2.tile0[p], P.sw2.ntile[p], 2 * (c1 - c0), red, 2 * c0);
-  for (int v = c0 + t; v < c1; v += DD_BLOCK) {
+  for (int v = blockIdx.y * 4 + wave; v < n; v += 4 * gridDim.y) {
+    const double part = sum_tiles2(P, 2 * v, P.sw2.tile0[p], P.sw2.ntile[p]);
+    const double2 e = make_double2(__shfl(part, 0, DD_WAVE), __shfl(part, 32, DD_WAVE));
     const double sv = (v < k) ? 1.0 : P.hscale[(size_t)p * (P.m + 1) + v - k];
-    const double2 h = make_double2(sv * red[2 * (v - c0)], sv * red[2 * (v - c0) + 1]);
-    P.coefB[(size_t)p * P.NC + v] = h;
-    P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2((float)(sv * h.x), (float)(sv * h.y));
+    if (lane == 0) {
+      P.coefB[(size_t)p * P.NC + v] = make_double2(sv * e.x, sv * e.y);
+      P.coefS[(size_t)p * DD_SW_MAXN + v] =
+          make_float2((float)(sv * sv * e.x), (float)(sv * sv * e.y));
+    }
   }
 }
 

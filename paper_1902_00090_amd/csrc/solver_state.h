@@ -33,6 +33,7 @@ struct dd_solver {
   int* pinned = nullptr;     // 2 status snapshots + 1 final
   double* pinnedD = nullptr;
   unsigned long long* pinnedK = nullptr;
+  int* hostact = nullptr;    // progress of complex64 one-sweep steps, written by the device
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool has_subspace = false;
   // the basis slots and small matrices hold the last cycle of a solve (for

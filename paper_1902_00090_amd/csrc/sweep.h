@@ -21,8 +21,8 @@
 // vectors, against the 50 KB that cover the latency of HBM at its rate).
 //
 // The dots accumulate in FP32 over at most DD_SW_FOLD rows, are then summed
-// over the 64 columns and added in FP64: one FP64 partial row per tile, reduced
-// in a fixed order by k_post_fused.
+// over the 64 columns and added in FP64: one FP64 partial sum per tile and value,
+// added over the tiles in a fixed order by k_post_sweep.
 //
 // Loads go through buffer descriptors whose range check stands for the bounds:
 // vectors past the basis and lanes outside the strip read as zero and move
@@ -90,7 +90,7 @@ template <bool PASS2> __device__ __forceinline__ int sw_plan_rows(const ProbDesc
 // band follow each other, so that the workgroups that walk neighbouring strips
 // run at the same time on the same XCD and its L2 serves the cache lines that
 // the strips share at their edges: 62 columns are 496 bytes, which touch five
-// lines of 128.  A problem's tiles, and with them its partial rows, are
+// lines of 128.  A problem's tiles, and with them its partial sums, are
 // consecutive from tile0[p].
 template <bool PASS2>
 __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int most) {
@@ -145,6 +145,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int
       const int t0 = done + cnt[t] - r, ny = sw_plan_rows<PASS2>(P.desc[p]);
       W.tile0[p] = t0;
       W.ntile[p] = r;
+      if (!PASS2) P.live[p] = r > 0;
       for (int i = 0; i < r; ++i) {
         const int y0 = i / strips * h;
         W.tiles[t0 + i] = {p, i % strips, y0, min(h, ny - y0)};
@@ -368,21 +369,22 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
     if (t + 1 < N) step(S1, S0, S3, t + 1);
     if (t + 2 < N) step(S2, S1, S0, t + 2);
     fold();
-    double* prow = (double*)P.partial + (size_t)tile * P.NV;
+    double* out = (double*)P.partial + tile;
+    const size_t ld = P.sw_ld;
     const int idx = lane >> 1, v = wave + NW * (idx >> 1);
-    if ((lane & 1) == 0 && idx < 2 * PER && v < n) prow[2 * v + (idx & 1)] = dsum;
+    if ((lane & 1) == 0 && idx < 2 * PER && v < n) out[(2 * v + (idx & 1)) * ld] = dsum;
     if (wave == 0 && lane == 0) {
-      prow[2 * n] = dn0;
-      prow[2 * n + 1] = dn1;
-      prow[2 * n + 2] = dn2;
-      prow[2 * n + 3] = dn3;
+      out[(2 * n) * ld] = dn0;
+      out[(2 * n + 1) * ld] = dn1;
+      out[(2 * n + 2) * ld] = dn2;
+      out[(2 * n + 3) * ld] = dn3;
     }
   }
 }
 
 // Whether the step takes the second Gram-Schmidt pass: never, always, or when
 // the first pass removes more than half of ||w||^2 (the test of Kahan and
-// Parlett, from the sums that k_post_fused left).
+// Parlett, from the sums that the kernel before left).
 __device__ __forceinline__ bool sw_second_pass(const PlanDev& P, int p) {
   if (P.reorth_mode != 2) return P.reorth_mode == 1;
   const double* cc = P.ccpart + (size_t)p * 33;     // [0] ||w||^2, then the slices' parts
@@ -480,8 +482,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
     if (t < N) step(S0, S2, t);
     if (t + 1 < N) step(S1, S0, t + 1);
     sw_fold<PER>(acc, dsum, lane);
-    double* prow = (double*)P.partial + (size_t)tile * P.NV;
     const int idx = lane >> 1, v = wave + NW * (idx >> 1);
-    if ((lane & 1) == 0 && idx < 2 * PER && v < n) prow[2 * v + (idx & 1)] = dsum;
+    if ((lane & 1) == 0 && idx < 2 * PER && v < n)
+      ((double*)P.partial)[(size_t)(2 * v + (idx & 1)) * P.sw_ld + tile] = dsum;
   }
 }

@@ -106,11 +106,10 @@ struct PlanDev {
                       // stay constant, so captured graphs remain valid)
   int fused;          // one-sweep Arnoldi steps: 1 k_fused_sweep, 2 k_sweep; k_post_fused
   const FusedTile* tiles;
-  // complex64 one-sweep steps (fused = 2, k_sweep): update coefficients in
-  // sw_slot order and the factor of z, in FP32; the cycle's split of the work
-  // (k_sweep_plan)
-  float2* coefS;      // [nb][128]
-  float* zs;          // [nb]
+  // one-sweep steps of k_sweep (fused = 2): update coefficients in the inner
+  // precision and the factor of z; the cycle's split of the work (k_sweep_plan)
+  void* coefS;        // [nb][128]
+  double* zs;         // [nb]
   double* ccpart;     // [nb][33] ||w||^2 and the parts of the first pass's ||c||^2
   SweepPlan sw, sw2;  // k_sweep, k_pass2
   size_t sw_ld;       // tiles of a cycle at most: stride of a value's partial sums

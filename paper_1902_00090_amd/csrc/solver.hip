@@ -165,7 +165,9 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   A.carve(&P.hist, (size_t)nb * std::max(1, o.hist_cap));
   A.carve(&s->dctl, 2);
   if (s->fused == 2) {
-    A.carve(&P.coefS, (size_t)nb * DD_SW_MAXN);
+    double2* cs = nullptr;
+    A.carve(&cs, (size_t)nb * DD_SW_MAXN);
+    P.coefS = cs;
     A.carve(&P.zs, (size_t)nb);
     A.carve(&P.live, (size_t)2 * nb);
     A.carve(&P.ccpart, (size_t)nb * 33);
@@ -302,13 +304,15 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     int GB = (int)std::min<size_t>(32, std::max<size_t>(1, (64ull << 20) / per));
     P.GB = GB;
   }
-  // One sweep per Arnoldi step: in complex64 always where it applies (a basis
-  // of at most 128 vectors whose offsets fit a buffer descriptor), in
-  // complex128 on request.
-  if (o.inner == DD_C64 && NC <= DD_SW_MAXN) {
+  // One sweep per Arnoldi step where it applies: a basis of at most 128 vectors
+  // (64 in complex128) whose offsets fit a buffer descriptor; in complex128 up
+  // to 128 on request, by an older kernel.
+  const bool fits = NC <= (o.inner == DD_C64 ? DD_SW_MAXN : DD_SW_MAXN / 2);
+  bool small = true;
+  for (int p = 0; p < nb; ++p)
+    small = small && (size_t)s->hdesc[p].Dp * 8 * DD_SW_MAXN < (size_t)DD_SW_OUT;
+  if (fits && small) {
     s->fused = 2;
-    for (int p = 0; p < nb; ++p)
-      if ((size_t)s->hdesc[p].Dp * 8 * DD_SW_MAXN >= (size_t)DD_SW_OUT) s->fused = 0;
     s->sw_grid = 2 * s->ncu;               // at most two workgroups per compute unit
     int strips = 0;                        // one tile each at the least
     for (int p = 0; p < nb; ++p) strips += sw_strips(ops[p]->nx);
@@ -565,7 +569,7 @@ static void prof_collect(dd_solver* s) {
 // 32 value slices (about 256 workgroups in all), one where the adaptive
 // second-pass test needs every coefficient of the first pass at once.
 static int post_slices(const dd_solver* s, bool first_pass) {
-  // complex64 one-sweep steps: a wave a dot product, about a thousand workgroups
+  // k_sweep's steps: a wave a dot product, about a thousand workgroups
   if (s->fused == 2) return std::max(4, std::min(32, 1024 / s->nb));
   if (first_pass && s->P.reorth_mode == 2) return 1;
   return std::max(1, std::min(32, 256 / std::max(1, s->nb)));
@@ -598,30 +602,41 @@ static void launch_step(dd_solver* s, int j, hipStream_t st) {
   k_post_norm<T><<<nb, DD_BLOCK, 0, st>>>(s->P, j, MODE_ARNOLDI, 0);
 }
 
-template <bool PC>
+// Waves and vectors a wave of the one-sweep kernels for n basis vectors: four
+// waves while their registers hold the rows (two workgroups per compute unit),
+// else eight.  complex128 holds half as many: up to 64 vectors.
+#define DD_SW_LAUNCH(KERNEL, ...)                                          \
+  if constexpr (sizeof(T) == 4) {                                          \
+    if (n <= 16) DD_SW_GO(KERNEL, 4, 4, __VA_ARGS__);                      \
+    else if (n <= 32) DD_SW_GO(KERNEL, 4, 8, __VA_ARGS__);                 \
+    else if (n <= 48) DD_SW_GO(KERNEL, 4, 12, __VA_ARGS__);                \
+    else if (n <= 64) DD_SW_GO(KERNEL, 4, 16, __VA_ARGS__);                \
+    else if (n <= 80) DD_SW_GO(KERNEL, 8, 10, __VA_ARGS__);                \
+    else if (n <= 96) DD_SW_GO(KERNEL, 8, 12, __VA_ARGS__);                \
+    else if (n <= 112) DD_SW_GO(KERNEL, 8, 14, __VA_ARGS__);               \
+    else DD_SW_GO(KERNEL, 8, 16, __VA_ARGS__);                             \
+  } else {                                                                 \
+    if (n <= 16) DD_SW_GO(KERNEL, 4, 4, __VA_ARGS__);                      \
+    else if (n <= 32) DD_SW_GO(KERNEL, 4, 8, __VA_ARGS__);                 \
+    else DD_SW_GO(KERNEL, 8, 8, __VA_ARGS__);                              \
+  }
+
+template <typename T, bool PC>
 static void launch_sweep(dd_solver* s, int j, hipStream_t st) {
   const int n = s->o.kmax + j + 1;     // basis vectors, at most
-  const int g = s->sw_grid;
-  if (n <= 16) k_sweep<4, 4, PC><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 32) k_sweep<4, 8, PC><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 48) k_sweep<4, 12, PC><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 64) k_sweep<4, 16, PC><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 80) k_sweep<8, 10, PC><<<g, 512, 0, st>>>(s->P, j);
-  else if (n <= 96) k_sweep<8, 12, PC><<<g, 512, 0, st>>>(s->P, j);
-  else if (n <= 112) k_sweep<8, 14, PC><<<g, 512, 0, st>>>(s->P, j);
-  else k_sweep<8, 16, PC><<<g, 512, 0, st>>>(s->P, j);
+#define DD_SW_GO(KERNEL, NW, PER, ...) \
+  k_sweep<T, NW, PER, PC><<<s->sw_grid, 64 * NW, 0, st>>>(s->P, j)
+  DD_SW_LAUNCH(k_sweep)
+#undef DD_SW_GO
 }
 
+template <typename T>
 static void launch_pass2(dd_solver* s, int j, hipStream_t st) {
-  const int n = s->o.kmax + j + 1, g = s->sw_grid;
-  if (n <= 16) k_pass2<4, 4><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 32) k_pass2<4, 8><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 48) k_pass2<4, 12><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 64) k_pass2<4, 16><<<g, 256, 0, st>>>(s->P, j);
-  else if (n <= 80) k_pass2<8, 10><<<g, 512, 0, st>>>(s->P, j);
-  else if (n <= 96) k_pass2<8, 12><<<g, 512, 0, st>>>(s->P, j);
-  else if (n <= 112) k_pass2<8, 14><<<g, 512, 0, st>>>(s->P, j);
-  else k_pass2<8, 16><<<g, 512, 0, st>>>(s->P, j);
+  const int n = s->o.kmax + j + 1;
+#define DD_SW_GO(KERNEL, NW, PER, ...) \
+  k_pass2<T, NW, PER><<<s->sw_grid, 64 * NW, 0, st>>>(s->P, j)
+  DD_SW_LAUNCH(k_pass2)
+#undef DD_SW_GO
 }
 
 // One fused Arnoldi step: the second Gram-Schmidt pass of step j where two are
@@ -629,28 +644,27 @@ static void launch_pass2(dd_solver* s, int j, hipStream_t st) {
 // and its FP64 bookkeeping.
 template <typename T>
 static void launch_fused_step(dd_solver* s, int j, hipStream_t st) {
-  const int nt = (int)s->htiles.size();
   const bool pc = s->o.precond != DD_PRECOND_NONE;
-  if (s->P.reorth_mode != 0) {
-    prof_mark(s, 1, st);
-    launch_pass2(s, j, st);
+  const int slices = post_slices(s, false);
+  if (s->fused == 2) {
+    if (s->P.reorth_mode != 0) {
+      prof_mark(s, 1, st);
+      launch_pass2<T>(s, j, st);
+      prof_end(s, st);
+      k_post_pass2<T><<<dim3(s->nb, slices), DD_BLOCK, 0, st>>>(s->P, j);
+    }
+    prof_mark(s, 3, st);
+    if (pc) launch_sweep<T, true>(s, j, st);
+    else launch_sweep<T, false>(s, j, st);
     prof_end(s, st);
-    k_post_pass2<<<dim3(s->nb, post_slices(s, false)), DD_BLOCK, 0, st>>>(s->P, j);
-  }
-  prof_mark(s, 3, st);
-  if constexpr (sizeof(T) == 4) {
-    if (pc) launch_sweep<true>(s, j, st);
-    else launch_sweep<false>(s, j, st);
-  } else {
+    const int poll = (j + 1) % s->o.check_every == 0;
+    k_post_sweep<T><<<dim3(s->nb, slices + 1), DD_BLOCK, 0, st>>>(s->P, j, poll);
+  } else if constexpr (sizeof(T) == 8) {
+    const int nt = (int)s->htiles.size();
+    prof_mark(s, 3, st);
     if (pc) k_fused_sweep<T, true><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
     else k_fused_sweep<T, false><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
-  }
-  prof_end(s, st);
-  const int slices = post_slices(s, false);
-  if constexpr (sizeof(T) == 4) {
-    const int poll = (j + 1) % s->o.check_every == 0;
-    k_post_sweep<<<dim3(s->nb, slices + 1), DD_BLOCK, 0, st>>>(s->P, j, poll);
-  } else {
+    prof_end(s, st);
     k_post_fused<T><<<dim3(s->nb, slices), DD_BLOCK, 0, st>>>(s->P, j, 0);
   }
 }
@@ -762,7 +776,7 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
       prof_end(s, st);
       k_post_fused<T><<<dim3(nb, post_slices(s, false)), DD_BLOCK, 0, st>>>(s->P, 0, 1);
     }
-    // complex64 one-sweep steps leave their progress in host memory; no kernel
+    // k_sweep's steps leave their progress in host memory; no kernel
     // of an earlier cycle runs any more
     if (s->fused == 2) std::memset(s->hostact, 0, sizeof(int) * nb);
     int pending = -1, grp = 0;
@@ -1032,13 +1046,19 @@ extern "C" dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, v
       DD_HIP_CHECK(hipMemcpy(dst + (size_t)v * d.D * ib,
                              (const char*)d.basis + (size_t)(slot0 + v) * d.Dp * ib, d.D * ib,
                              hipMemcpyDeviceToHost));
-    if (what == 1 && s->fused == 2) {   // stored unnormalised
+    if (what == 1 && s->fused == 2) {
+      // stored unnormalised; the last vector of the cycle is given as it is
       std::vector<double> hs(m + 1);
+      int last = 0;
+      DD_HIP_CHECK(hipMemcpy(&last, s->P.stI + p * ST_NI + ST_J, sizeof(int), hipMemcpyDeviceToHost));
       DD_HIP_CHECK(hipMemcpy(hs.data(), s->P.hscale + (size_t)p * (m + 1), sizeof(double) * (m + 1),
                              hipMemcpyDeviceToHost));
-      for (int v = 0; v < nvec; ++v) {
-        float* q = (float*)(dst + (size_t)v * d.D * ib);
-        for (int e = 0; e < 2 * d.D; ++e) q[e] = (float)(q[e] * hs[v]);
+      for (int v = 0; v < last; ++v) {
+        char* q = dst + (size_t)v * d.D * ib;
+        if (s->o.inner == DD_C64)
+          for (int e = 0; e < 2 * d.D; ++e) ((float*)q)[e] = (float)(((float*)q)[e] * hs[v]);
+        else
+          for (int e = 0; e < 2 * d.D; ++e) ((double*)q)[e] *= hs[v];
       }
     }
     return DD_OK;

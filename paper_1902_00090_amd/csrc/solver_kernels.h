@@ -15,16 +15,6 @@
 #include "solver.h"
 #include "sweep.h"
 
-template <typename T> struct OpP;
-template <> struct OpP<float> {
-  static __device__ __forceinline__ const float2* cf(const ProbDesc& d) { return d.cf32; }
-  static __device__ __forceinline__ const float* eps(const ProbDesc& d) { return d.eps32; }
-};
-template <> struct OpP<double> {
-  static __device__ __forceinline__ const double2* cf(const ProbDesc& d) { return d.cf64; }
-  static __device__ __forceinline__ const double* eps(const ProbDesc& d) { return d.eps64; }
-};
-
 template <typename T> __device__ __forceinline__ c2<T> to_c(double2 a) {
   return cmk<c2<T>>((T)a.x, (T)a.y);
 }
@@ -142,6 +132,56 @@ __device__ void reduce_rows(const PlanDev& P, int blk0, int nblk, int nvals, dou
 }
 
 // ---------------------------------------------------------------------------
+// Back substitution at the end of a cycle, a chain of n steps.  The first wave does it alone:
+// lane l holds entries l, l + 64, .. of the right-hand side in registers, a
+// step's solution is broadcast by a lane read, and the columns of H are in
+// flight eight steps ahead; a workgroup with a barrier and a load in each step
+// took 70 us for 100 steps.
+__device__ __forceinline__ double2 lane_value(double2 v, int lane) {   // lane uniform
+  const auto get = [&](double x) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), lane),
+                            __builtin_amdgcn_readlane(__double2loint(x), lane));
+  };
+  return make_double2(get(v.x), get(v.y));
+}
+
+template <int Q>   // entries per lane: n <= 64 Q
+__device__ __forceinline__ void back_substitute(const double2* H, int ld, const double2* g, int n,
+                                                double2* yv, int lane) {
+  constexpr int AHEAD = Q <= 2 ? 8 : 4;
+  double2 gl[Q], inv[Q], h[AHEAD][Q];
+  const double2 zero = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int l = lane + 64 * q;
+    gl[q] = l < n ? g[l] : zero;
+    inv[q] = l < n ? H[(size_t)l * ld + l] : make_double2(1.0, 0.0);
+  }
+  auto column = [&](double2 (&c)[Q], int i) {       // entries above the diagonal of column i
+#pragma unroll
+    for (int q = 0; q < Q; ++q) c[q] = (lane + 64 * q < i) ? H[(size_t)i * ld + lane + 64 * q] : zero;
+  };
+#pragma unroll
+  for (int a = 0; a < AHEAD; ++a) column(h[a], n - 1 - a);
+#pragma unroll
+  for (int q = 0; q < Q; ++q) inv[q] = ddiv(make_double2(1.0, 0.0), inv[q]);
+  for (int i0 = n - 1; i0 >= 0; i0 -= AHEAD) {
+#pragma unroll
+    for (int a = 0; a < AHEAD; ++a) {
+      const int i = i0 - a;
+      if (i < 0) break;
+      double2 y = zero;
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if ((i >> 6) == q) y = lane_value(dmul(gl[q], inv[q]), i & 63);
+      if (lane == 0) yv[i] = y;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) gl[q] = dsub(gl[q], dmul(h[a][q], y));
+      column(h[a], i - AHEAD);
+    }
+  }
+}
+
 // Cycle end (supplement, eq:final_lsq and the decoupling it admits): with
 // q_1 = r~/||r~|| and Q orthogonal to C, the block least-squares problem
 // splits into the ordinary GMRES problem min ||beta e1 - H y|| (solved by the
@@ -149,24 +189,28 @@ __device__ void reduce_rows(const PlanDev& P, int blk0, int nblk, int nvals, dou
 // delta = V R^{-1} x_aug + Q y.  Writes the combine coefficients [z; y].
 __device__ void finish_cycle(const PlanDev& P, int p, int k, int n) {
   __shared__ double2 yv[DD_MAX_M];
-  __shared__ double2 gl[DD_MAX_M + 1];
   __shared__ double2 xa[DD_MAX_K];
   const int t = threadIdx.x;
   const int m = P.m;
   const double2* H = P.H + (size_t)p * m * (m + 1);
-  for (int i = t; i < n; i += DD_BLOCK) gl[i] = P.g[(size_t)p * (m + 1) + i];
-  __syncthreads();
-  for (int i = n - 1; i >= 0; --i) {
-    if (t == 0) yv[i] = ddiv(gl[i], H[(size_t)i * (m + 1) + i]);
-    __syncthreads();
-    const double2 yi = yv[i];
-    for (int l = t; l < i; l += DD_BLOCK) gl[l] = dsub(gl[l], dmul(H[(size_t)i * (m + 1) + l], yi));
-    __syncthreads();
+  const double2* g = P.g + (size_t)p * (m + 1);
+  if (t < 64) {
+    if (n <= 128) back_substitute<2>(H, m + 1, g, n, yv, t);
+    else back_substitute<4>(H, m + 1, g, n, yv, t);
   }
+  __syncthreads();
   if (t < k) {
     double2 s = P.c0[(size_t)p * P.kmax + t];
     const double2* Bc = P.Bc + (size_t)p * m * P.kmax;
-    for (int i = 0; i < n; ++i) s = dsub(s, dmul(Bc[(size_t)i * P.kmax + t], yv[i]));
+    int i = 0;
+    for (; i + 8 <= n; i += 8) {
+      double2 c[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) c[q] = Bc[(size_t)(i + q) * P.kmax + t];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) s = dsub(s, dmul(c[q], yv[i + q]));
+    }
+    for (; i < n; ++i) s = dsub(s, dmul(Bc[(size_t)i * P.kmax + t], yv[i]));
     xa[t] = s;
   }
   __syncthreads();
@@ -1122,18 +1166,18 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     cNew[v] = dv;
     cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
     if (P.fused == 2)
-      P.coefS[(size_t)p * DD_SW_MAXN + v] =
-          make_float2((float)(gs * dv.x), (float)(gs * dv.y));
+      ((c2<PT>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] =
+          to_c<PT>(make_double2(gs * dv.x, gs * dv.y));
     else
       cB[v] = make_double2(gs * dv.x, gs * dv.y);
   }
-  // complex64 (k_sweep): only the cycle's start comes here
+  // k_sweep: only the cycle's start comes here
   if (P.fused == 2 && lead) {
     // slots of vectors that this cycle has not reached yet meet values read as
     // zero: they hold finite numbers
     for (int v = nn + t; v < DD_SW_MAXN; v += DD_BLOCK)
-      P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2(0.f, 0.f);
-    if (t == 0) P.zs[p] = (float)snew;
+      ((c2<PT>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] = to_c<PT>(make_double2(0.0, 0.0));
+    if (t == 0) P.zs[p] = snew;
   }
   if (P.fused == 2 && P.reorth_mode == 2) {
     // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
@@ -1184,6 +1228,7 @@ __device__ __forceinline__ double sum_tiles2(const PlanDev& P, int v, int t0, in
 // dependent loads, five shuffles, the square root, or the scan of the Givens
 // update); it moves no more than the partial sums.
 // poll: leave 2 (j + 1) + (still active) in the host's array.
+template <typename T>
 __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int poll) {
   const int p = blockIdx.x, slices = gridDim.y - 1, t = threadIdx.x;
   int* st = P.stI + p * ST_NI;
@@ -1217,10 +1262,11 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
       cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
       if (lane == 0) {
         cNew[v] = dv;
-        P.coefS[(size_t)p * DD_SW_MAXN + v] = make_float2((float)(gs * dv.x), (float)(gs * dv.y));
+        ((c2<T>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] =
+            to_c<T>(make_double2(gs * dv.x, gs * dv.y));
       }
     }
-    if (blockIdx.y == 0 && t == 0) P.zs[p] = (float)snew;
+    if (blockIdx.y == 0 && t == 0) P.zs[p] = snew;
     if (P.reorth_mode == 2) {
       // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
       __shared__ double cw[4];
@@ -1284,6 +1330,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
 // s_v h2_v for the sweep, whose z is now the once orthogonalised vector.
 // Without a second pass the sweep takes the first pass's coefficients, which
 // are already in place.
+template <typename T>
 __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
   const int p = blockIdx.x;
   int* st = P.stI + p * ST_NI;
@@ -1292,7 +1339,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if (blockIdx.y == 0 && t == 0) {
     st[ST_REORTH] = re ? 1 : 0;
-    if (re) P.zs[p] = 1.f;
+    if (re) P.zs[p] = 1.0;
   }
   if (!re) return;
   const int k = P.desc[p].k, n = k + j + 1;
@@ -1302,8 +1349,8 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
     const double sv = (v < k) ? 1.0 : P.hscale[(size_t)p * (P.m + 1) + v - k];
     if (lane == 0) {
       P.coefB[(size_t)p * P.NC + v] = make_double2(sv * e.x, sv * e.y);
-      P.coefS[(size_t)p * DD_SW_MAXN + v] =
-          make_float2((float)(sv * sv * e.x), (float)(sv * sv * e.y));
+      ((c2<T>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] =
+          to_c<T>(make_double2(sv * sv * e.x, sv * sv * e.y));
     }
   }
 }

@@ -23,8 +23,8 @@ struct dd_solver {
   std::vector<void*> allocs;
   size_t bytes = 0;       // device workspace of the solver (owned or the caller's)
   bool owns_workspace = true;
-  // one-sweep Arnoldi steps: 0 off, 1 k_fused_sweep (complex128), 2 k_sweep
-  // (complex64; with two passes also k_pass2), both for kmax + m + 1 <= 128
+  // one-sweep Arnoldi steps: 0 off, 2 k_sweep (with two passes also k_pass2),
+  // 1 k_fused_sweep (complex128 with 65 to 128 vectors, on request, one pass)
   int fused = 0;
   int sw_grid = 0;        // workgroups of k_sweep
   int sw_most = 0;        // tiles of a cycle, at most
@@ -33,7 +33,7 @@ struct dd_solver {
   int* pinned = nullptr;     // 2 status snapshots + 1 final
   double* pinnedD = nullptr;
   unsigned long long* pinnedK = nullptr;
-  int* hostact = nullptr;    // progress of complex64 one-sweep steps, written by the device
+  int* hostact = nullptr;    // progress of one-sweep steps, written by the device
   hipEvent_t ev[2] = {nullptr, nullptr};
   bool has_subspace = false;
   // the basis slots and small matrices hold the last cycle of a solve (for

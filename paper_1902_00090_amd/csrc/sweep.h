@@ -1,4 +1,4 @@
-// One-sweep Arnoldi step in complex64: the update of step j, the stencil and
+// One-sweep Arnoldi step: the update of step j, the stencil and
 // the dot products of step j + 1 in one pass over the basis.
 //
 // The Krylov vectors are normalised one step late, q_i = s_i q~_i with FP64
@@ -38,6 +38,7 @@
 #define DD_SW_OUT 0x80000000u         // an offset past every descriptor's range
 
 typedef unsigned int sw_u2 __attribute__((ext_vector_type(2)));
+typedef unsigned int sw_u4 __attribute__((ext_vector_type(4)));
 
 // A value that no kernel writes while this one runs, at a uniform address:
 // a scalar load, which does not queue behind the vector loads in flight.
@@ -48,16 +49,46 @@ __device__ __forceinline__ float2 ld_uni(const float2* p) {
   const auto q = (const __attribute__((address_space(4))) float*)p;
   return make_float2(q[0], q[1]);
 }
+__device__ __forceinline__ double2 ld_uni(const double2* p) {
+  const auto q = (const __attribute__((address_space(4))) double*)p;
+  return make_double2(q[0], q[1]);
+}
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t sw_rsrc(const void* p, size_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float2 sw_ld2(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  const sw_u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
-  return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+__device__ __forceinline__ double sw_f64(unsigned lo, unsigned hi) {
+  return __hiloint2double((int)hi, (int)lo);
 }
-__device__ __forceinline__ float sw_ld1(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+// A complex and a real value of type T through a descriptor.
+template <typename T> __device__ __forceinline__ c2<T> sw_ldc(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  if constexpr (sizeof(T) == 4) {
+    const sw_u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    return make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
+  } else {
+    const sw_u4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+    return make_double2(sw_f64(v.x, v.y), sw_f64(v.z, v.w));
+  }
 }
+template <typename T> __device__ __forceinline__ T sw_ldr(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  if constexpr (sizeof(T) == 4) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+  } else {
+    const sw_u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+    return sw_f64(v.x, v.y);
+  }
+}
+__device__ __forceinline__ float sw_fma(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double sw_fma(double a, double b, double c) { return fma(a, b, c); }
+
+template <typename T> struct OpP;
+template <> struct OpP<float> {
+  template <typename D> static __device__ __forceinline__ const float2* cf(const D& d) { return d.cf32; }
+  template <typename D> static __device__ __forceinline__ const float* eps(const D& d) { return d.eps32; }
+};
+template <> struct OpP<double> {
+  template <typename D> static __device__ __forceinline__ const double2* cf(const D& d) { return d.cf64; }
+  template <typename D> static __device__ __forceinline__ const double* eps(const D& d) { return d.eps64; }
+};
 
 // Strips of a grid of nx columns, and their common width.
 __host__ __device__ inline int sw_strips(int nx) { return (nx + DD_SW_COLS - 1) / DD_SW_COLS; }
@@ -162,40 +193,46 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int
 
 // Adds the lanes' dots to the wave's sums: lanes 2 i and 2 i + 1 hold value i
 // (real and imaginary parts alternate).
-template <int PER>
-__device__ __forceinline__ void sw_fold(float2 (&acc)[PER], double& dsum, int lane) {
-  float v[32];
+template <typename T, int PER>
+__device__ __forceinline__ void sw_fold(c2<T> (&acc)[PER], double& dsum, int lane) {
+  T v[32];
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
-    v[2 * i] = (i < PER) ? acc[i < PER ? i : 0].x : 0.f;
-    v[2 * i + 1] = (i < PER) ? acc[i < PER ? i : 0].y : 0.f;
+    v[2 * i] = (i < PER) ? acc[i < PER ? i : 0].x : T(0);
+    v[2 * i + 1] = (i < PER) ? acc[i < PER ? i : 0].y : T(0);
   }
-  butterfly_step<float, 32>(v, lane);
+  butterfly_step<T, 32>(v, lane);
   dsum += (double)(v[0] + __shfl_xor(v[0], 1, 64));
 #pragma unroll
-  for (int i = 0; i < PER; ++i) acc[i] = make_float2(0.f, 0.f);
+  for (int i = 0; i < PER; ++i) acc[i] = cmk<c2<T>>(T(0), T(0));
 }
 
-template <int PER> struct SweepRow {
-  float2 b[PER];          // the wave's basis values at its lane's column
-  float2 z;               // z_j (last wave; zero in the others)
-  float eps;
-  float2 pr, pl;          // diagonal preconditioner
+template <typename T, int PER> struct SweepRow {
+  c2<T> b[PER];           // the wave's basis values at its lane's column
+  c2<T> z;                // z_j (last wave; zero in the others)
+  T eps;
+  c2<T> pr, pl;           // diagonal preconditioner
 };
 
-// The lane's neighbours in the wave (0 past its ends).
-__device__ __forceinline__ float2 from_west(float2 v) {
-  return make_float2(__uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.x), 0x138, 0xf, 0xf, false)),
-                     __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.y), 0x138, 0xf, 0xf, false)));
+// The lane's neighbours in the wave (0 past its ends): DPP shifts by one lane.
+template <int CTRL> __device__ __forceinline__ float sw_dpp(float x) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), CTRL, 0xf, 0xf, false));
 }
-__device__ __forceinline__ float2 from_east(float2 v) {
-  return make_float2(__uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.x), 0x130, 0xf, 0xf, false)),
-                     __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v.y), 0x130, 0xf, 0xf, false)));
+template <int CTRL> __device__ __forceinline__ double sw_dpp(double x) {
+  return __hiloint2double(
+      __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, false),
+      __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, false));
+}
+template <typename V> __device__ __forceinline__ V from_west(V v) {
+  return cmk<V>(sw_dpp<0x138>(v.x), sw_dpp<0x138>(v.y));
+}
+template <typename V> __device__ __forceinline__ V from_east(V v) {
+  return cmk<V>(sw_dpp<0x130>(v.x), sw_dpp<0x130>(v.y));
 }
 
 // NW waves of PER vectors each.  PC: the problems carry a diagonal
 // preconditioner, z = P_L A P_R q~.
-template <int NW, int PER, bool PC>
+template <typename T, int NW, int PER, bool PC>
 __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
   const int count = ld_uni(P.sw.count), G = ld_uni(P.sw.count + 1);
   if ((int)blockIdx.x >= G) return;
@@ -203,8 +240,10 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
   const int g = (G % 8 == 0) ? (int)(blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  __shared__ float2 part[2][NW][64];
-  const float2 zero = make_float2(0.f, 0.f);
+  using V = c2<T>;
+  constexpr unsigned CB = sizeof(V);                // bytes of a cell's value
+  __shared__ V part[2][NW][64];
+  const V zero = cmk<V>(T(0), T(0));
 
   for (int tile = g; tile < count; tile += G) {
     const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw.tiles + tile);
@@ -214,32 +253,32 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
     const int nx = d->nx, ny = d->ny, k = d->k;
     const size_t Dp = d->Dp;
     const int n = k + j + 1;
-    const float2* B = (const float2*)d->basis + (size_t)(P.kmax - k) * Dp;
-    float2* qn = (float2*)d->basis + (size_t)(P.kmax + j + 1) * Dp;
-    const float2* zin = (const float2*)d->Z + (size_t)(j & 1) * Dp;
-    float2* zout = (float2*)d->Z + (size_t)((j + 1) & 1) * Dp;
-    const float2* cf = d->cf32;
-    const float om2 = (float)d->omega2;
-    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * 8);
-    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(zin, (size_t)Dp * 8);
-    const __amdgpu_buffer_rsrc_t rE = sw_rsrc(d->eps32, (size_t)nx * ny * 4);
+    const V* B = (const V*)d->basis + (size_t)(P.kmax - k) * Dp;
+    V* qn = (V*)d->basis + (size_t)(P.kmax + j + 1) * Dp;
+    const V* zin = (const V*)d->Z + (size_t)(j & 1) * Dp;
+    V* zout = (V*)d->Z + (size_t)((j + 1) & 1) * Dp;
+    const V* cf = OpP<T>::cf(*d);
+    const T om2 = (T)d->omega2;
+    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * CB);
+    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(zin, (size_t)Dp * CB);
+    const __amdgpu_buffer_rsrc_t rE = sw_rsrc(OpP<T>::eps(*d), (size_t)nx * ny * (CB / 2));
     const bool has_pl = PC && d->pl != nullptr, has_pr = PC && d->pr != nullptr;
-    const __amdgpu_buffer_rsrc_t rL = sw_rsrc(has_pl ? d->pl : B, has_pl ? (size_t)Dp * 8 : 0);
-    const __amdgpu_buffer_rsrc_t rR = sw_rsrc(has_pr ? d->pr : B, has_pr ? (size_t)Dp * 8 : 0);
-    const unsigned vec = (unsigned)Dp * 8u;         // bytes of one vector
-    const float2* cS = P.coefS + (size_t)p * DD_SW_MAXN + wave;
-    float2 gc[PER];
+    const __amdgpu_buffer_rsrc_t rL = sw_rsrc(has_pl ? d->pl : B, has_pl ? (size_t)Dp * CB : 0);
+    const __amdgpu_buffer_rsrc_t rR = sw_rsrc(has_pr ? d->pr : B, has_pr ? (size_t)Dp * CB : 0);
+    const unsigned vec = (unsigned)Dp * CB;         // bytes of one vector
+    const V* cS = (const V*)P.coefS + (size_t)p * DD_SW_MAXN + wave;
+    V gc[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) gc[i] = ld_uni(cS + NW * i);
-    const float zs = ld_uni(P.zs + p);
-    float2 acc[PER];
+    const T zs = (T)ld_uni(P.zs + p);
+    V acc[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) acc[i] = zero;
-    float2 accn = zero;                              // conj(q~_{j+1}) z_{j+1}
-    float un2 = 0.f, zz2 = 0.f;                      // ||q~_{j+1}||^2, ||z_{j+1}||^2
+    V accn = zero;                              // conj(q~_{j+1}) z_{j+1}
+    T un2 = T(0), zz2 = T(0);                      // ||q~_{j+1}||^2, ||z_{j+1}||^2
     double dsum = 0.0, dn0 = 0.0, dn1 = 0.0, dn2 = 0.0, dn3 = 0.0;
     auto fold = [&]() {
-      sw_fold<PER>(acc, dsum, lane);
+      sw_fold<T, PER>(acc, dsum, lane);
       if (wave == 0) {
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) {
@@ -253,7 +292,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
         dn2 += (double)un2;
         dn3 += (double)zz2;
         accn = zero;
-        un2 = zz2 = 0.f;
+        un2 = zz2 = T(0);
       }
     };
 
@@ -264,68 +303,71 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
     int c = x0 - 1 + lane;
     c = (c < 0) ? c + nx : ((c >= nx) ? c - nx : c);
     c = lane_ok ? c : 0;
-    float2 cxm = zero, cxp = zero;
+    V cxm = zero, cxp = zero;
     if (owned) {
       cxm = cf[c];
       cxp = cf[nx + c];
     }
     const int N = nrows + 2;
-    SweepRow<PER> S0, S1, S2, S3;
+    // rows in flight before they are needed: two, in complex128 (whose sets are
+    // twice as large) none
+    constexpr int AHEAD = sizeof(T) == 4 ? 2 : 0;
+    SweepRow<T, PER> S0, S1, S2, S3;
     // byte offsets of the lane's cell in row 0 of the wave's first vector, of z
     // and of eps; a row adds the same to every lane
-    const unsigned ob = lane_ok ? (unsigned)c * 8u + (unsigned)wave * vec : DD_SW_OUT;
-    const unsigned oz = (lane_ok && wave == NW - 1) ? (unsigned)c * 8u : DD_SW_OUT;
-    const unsigned oe = lane_ok ? (unsigned)c * 4u : DD_SW_OUT;
-    auto load = [&](SweepRow<PER>& s, int t) {
+    const unsigned ob = lane_ok ? (unsigned)c * CB + (unsigned)wave * vec : DD_SW_OUT;
+    const unsigned oz = (lane_ok && wave == NW - 1) ? (unsigned)c * CB : DD_SW_OUT;
+    const unsigned oe = lane_ok ? (unsigned)c * (CB / 2) : DD_SW_OUT;
+    auto load = [&](SweepRow<T, PER>& s, int t) {
       int y = ya - 1 + t;
       y = (y < 0) ? y + ny : ((y >= ny) ? y - ny : y);
       // rows past the tile are not fetched (a lane outside the strip may wrap
       // into the range there: it is read and not used)
-      const unsigned row = (t < N) ? (unsigned)(y * nx) * 4u : DD_SW_OUT / 2;
+      const unsigned row = (t < N) ? (unsigned)(y * nx) * (CB / 2) : DD_SW_OUT / 2;
       unsigned o = ob + 2 * row;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        s.b[i] = sw_ld2(rB, o);
+        s.b[i] = sw_ldc<T>(rB, o);
         o += NW * vec;
         asm("" : "+v"(o));      // one running offset: the multiples would fill the scalar registers
       }
-      s.z = sw_ld2(rZ, oz + 2 * row);
-      s.eps = sw_ld1(rE, oe + row);
+      s.z = sw_ldc<T>(rZ, oz + 2 * row);
+      s.eps = sw_ldr<T>(rE, oe + row);
       if (PC) {
-        s.pr = sw_ld2(rR, (lane_ok ? (unsigned)c * 8u : DD_SW_OUT) + 2 * row);
-        s.pl = sw_ld2(rL, (lane_ok ? (unsigned)c * 8u : DD_SW_OUT) + 2 * row);
+        s.pr = sw_ldc<T>(rR, (lane_ok ? (unsigned)c * CB : DD_SW_OUT) + 2 * row);
+        s.pl = sw_ldc<T>(rL, (lane_ok ? (unsigned)c * CB : DD_SW_OUT) + 2 * row);
       }
     };
     // the new row's values one and two rows back: q~, P_R q~ and its
     // neighbours to the west and east
-    float2 u1 = zero, r1 = zero, r2 = zero, rw = zero, re = zero;
-    auto step = [&](SweepRow<PER>& cur, SweepRow<PER>& prev, SweepRow<PER>& ahead, int t) {
-      load(ahead, t + 2);
+    V u1 = zero, r1 = zero, r2 = zero, rw = zero, re = zero;
+    auto step = [&](SweepRow<T, PER>& cur, SweepRow<T, PER>& prev, SweepRow<T, PER>& ahead, int t) {
+      load(ahead, t + AHEAD);
       __builtin_amdgcn_sched_barrier(0);   // rows are fetched, and so waited for, in order
       const int ys = max(ya, ya + t - 2);
-      const float2 cym = ld_uni(cf + 2 * nx + ys), cyp = ld_uni(cf + 2 * nx + ny + ys);
-      float2 pu = cmk<float2>(-zs * cur.z.x, -zs * cur.z.y);
+      const V cym = ld_uni(cf + 2 * nx + ys), cyp = ld_uni(cf + 2 * nx + ny + ys);
+      V pu = cmk<V>(-zs * cur.z.x, -zs * cur.z.y);
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        pu.x = fmaf(-gc[i].y, cur.b[i].y, fmaf(gc[i].x, cur.b[i].x, pu.x));
-        pu.y = fmaf(gc[i].y, cur.b[i].x, fmaf(gc[i].x, cur.b[i].y, pu.y));
+        pu.x = sw_fma(-gc[i].y, cur.b[i].y, sw_fma(gc[i].x, cur.b[i].x, pu.x));
+        pu.y = sw_fma(gc[i].y, cur.b[i].x, sw_fma(gc[i].x, cur.b[i].y, pu.y));
       }
       part[t & 1][wave][lane] = pu;
       __syncthreads();
-      float2 u = zero;
+      V u = zero;
 #pragma unroll
       for (int q = 0; q < NW; ++q) u = csub(u, part[t & 1][q][lane]);
       int y = ya - 1 + t;
       y = (y < 0) ? y + ny : ((y >= ny) ? y - ny : y);
       const bool mine = t >= 1 && t <= nrows;
-      float2 r = u;
+      V r = u;
       if (has_pr) r = cmul(u, cur.pr);
       if (t >= 2) {
-        float2 z = cmul(cxm, csub(r1, rw));
+        V z = cmul(cxm, csub(r1, rw));
         z = csub(z, cmul(cxp, csub(re, r1)));
         z = cadd(z, cmul(cym, csub(r1, r2)));
         z = csub(z, cmul(cyp, csub(r, r1)));
-        const float de = om2 * prev.eps;
+        const T de = om2 * prev.eps;
         z.x -= de * r1.x;
         z.y -= de * r1.y;
         if (!owned) z = zero;
@@ -333,8 +375,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
         if (wave == 1 && owned) zout[ys * nx + c] = z;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-          acc[i].x = fmaf(prev.b[i].y, z.y, fmaf(prev.b[i].x, z.x, acc[i].x));
-          acc[i].y = fmaf(-prev.b[i].y, z.x, fmaf(prev.b[i].x, z.y, acc[i].y));
+          acc[i].x = sw_fma(prev.b[i].y, z.y, sw_fma(prev.b[i].x, z.x, acc[i].x));
+          acc[i].y = sw_fma(-prev.b[i].y, z.x, sw_fma(prev.b[i].x, z.y, acc[i].y));
         }
         if (wave == 0) {
           accn.x += u1.x * z.x + u1.y * z.y;
@@ -353,21 +395,30 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
       u1 = u;
     };
     __syncthreads();          // the parts of the tile before have been read
-    load(S0, 0);
-    __builtin_amdgcn_sched_barrier(0);
-    load(S1, 1);
-    __builtin_amdgcn_sched_barrier(0);
     int t = 0;
-    for (; t + 4 <= N; t += 4) {
-      step(S0, S3, S2, t);
-      step(S1, S0, S3, t + 1);
-      step(S2, S1, S0, t + 2);
-      step(S3, S2, S1, t + 3);
-      if ((t + 4) % DD_SW_FOLD == 0) fold();
+    if constexpr (AHEAD == 2) {
+      load(S0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      load(S1, 1);
+      __builtin_amdgcn_sched_barrier(0);
+      for (; t + 4 <= N; t += 4) {
+        step(S0, S3, S2, t);
+        step(S1, S0, S3, t + 1);
+        step(S2, S1, S0, t + 2);
+        step(S3, S2, S1, t + 3);
+        if ((t + 4) % DD_SW_FOLD == 0) fold();
+      }
+      if (t < N) step(S0, S3, S2, t);
+      if (t + 1 < N) step(S1, S0, S3, t + 1);
+      if (t + 2 < N) step(S2, S1, S0, t + 2);
+    } else {
+      for (; t + 2 <= N; t += 2) {
+        step(S0, S1, S0, t);
+        step(S1, S0, S1, t + 1);
+        if ((t + 2) % DD_SW_FOLD == 0) fold();
+      }
+      if (t < N) step(S0, S1, S0, t);
     }
-    if (t < N) step(S0, S3, S2, t);
-    if (t + 1 < N) step(S1, S0, S3, t + 1);
-    if (t + 2 < N) step(S2, S1, S0, t + 2);
     fold();
     double* out = (double*)P.partial + tile;
     const size_t ld = P.sw_ld;
@@ -399,14 +450,16 @@ __device__ __forceinline__ bool sw_second_pass(const PlanDev& P, int p) {
 // the raw dots of the result with the basis, one read of the basis.  The tiles
 // are runs of 64 cells; otherwise as k_sweep, without halos and stencil: a run
 // is updated and dotted at once, so three register sets rotate.
-template <int NW, int PER>
+template <typename T, int NW, int PER>
 __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
   const int count = ld_uni(P.sw2.count), G = ld_uni(P.sw2.count + 1);
   if ((int)blockIdx.x >= G) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  __shared__ float2 part[2][NW][64];
-  const float2 zero = make_float2(0.f, 0.f);
+  using V = c2<T>;
+  constexpr unsigned CB = sizeof(V);                // bytes of a cell's value
+  __shared__ V part[2][NW][64];
+  const V zero = cmk<V>(T(0), T(0));
 
   for (int tile = blockIdx.x; tile < count; tile += G) {
     const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw2.tiles + tile);
@@ -415,58 +468,57 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
     const auto* d = (const __attribute__((address_space(4))) ProbDesc*)(P.desc + p);
     const int k = d->k, n = k + j + 1;
     const size_t Dp = d->Dp;
-    const float2* B = (const float2*)d->basis + (size_t)(P.kmax - k) * Dp;
-    float2* z = (float2*)d->Z + (size_t)(j & 1) * Dp;
-    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * 8);
-    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(z, (size_t)Dp * 8);
-    const unsigned vec = (unsigned)Dp * 8u;
-    const float2* cS = P.coefS + (size_t)p * DD_SW_MAXN + wave;
-    float2 gc[PER], acc[PER];
+    const V* B = (const V*)d->basis + (size_t)(P.kmax - k) * Dp;
+    V* z = (V*)d->Z + (size_t)(j & 1) * Dp;
+    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * CB);
+    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(z, (size_t)Dp * CB);
+    const unsigned vec = (unsigned)Dp * CB;
+    const V* cS = (const V*)P.coefS + (size_t)p * DD_SW_MAXN + wave;
+    V gc[PER], acc[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       gc[i] = ld_uni(cS + NW * i);
       acc[i] = zero;
     }
-    const float zs = ld_uni(P.zs + p);
+    const T zs = (T)ld_uni(P.zs + p);
     double dsum = 0.0;
     struct Run {
-      float2 b[PER], z;
+      V b[PER], z;
     } S0, S1, S2;
-    const unsigned ob = (unsigned)lane * 8u + (unsigned)wave * vec;
-    const unsigned oz = (wave == NW - 1) ? (unsigned)lane * 8u : DD_SW_OUT;
+    const unsigned ob = (unsigned)lane * CB + (unsigned)wave * vec;
+    const unsigned oz = (wave == NW - 1) ? (unsigned)lane * CB : DD_SW_OUT;
     auto load = [&](Run& s, int t) {
       // a run past the tile is not fetched
-      const unsigned row = (t < N) ? (unsigned)(ya + t) * 512u : DD_SW_OUT;
+      const unsigned row = (t < N) ? (unsigned)(ya + t) * (64 * CB) : DD_SW_OUT;
       unsigned o = ob + row;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        s.b[i] = sw_ld2(rB, o);
+        s.b[i] = sw_ldc<T>(rB, o);
         o += NW * vec;
         asm("" : "+v"(o));
       }
-      s.z = sw_ld2(rZ, (t < N) ? oz + row : DD_SW_OUT);
+      s.z = sw_ldc<T>(rZ, (t < N) ? oz + row : DD_SW_OUT);
     };
     auto step = [&](Run& cur, Run& ahead, int t) {
       load(ahead, t + 2);
       __builtin_amdgcn_sched_barrier(0);
-      float2 pu = cmk<float2>(-zs * cur.z.x, -zs * cur.z.y);
+      V pu = cmk<V>(-zs * cur.z.x, -zs * cur.z.y);
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        pu.x = fmaf(-gc[i].y, cur.b[i].y, fmaf(gc[i].x, cur.b[i].x, pu.x));
-        pu.y = fmaf(gc[i].y, cur.b[i].x, fmaf(gc[i].x, cur.b[i].y, pu.y));
+        pu.x = sw_fma(-gc[i].y, cur.b[i].y, sw_fma(gc[i].x, cur.b[i].x, pu.x));
+        pu.y = sw_fma(gc[i].y, cur.b[i].x, sw_fma(gc[i].x, cur.b[i].y, pu.y));
       }
       part[t & 1][wave][lane] = pu;
       __syncthreads();
-      float2 u = zero;
+      V u = zero;
 #pragma unroll
       for (int q = 0; q < NW; ++q) u = csub(u, part[t & 1][q][lane]);
       if (wave == 1) z[(ya + t) * 64 + lane] = u;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        acc[i].x = fmaf(cur.b[i].y, u.y, fmaf(cur.b[i].x, u.x, acc[i].x));
-        acc[i].y = fmaf(-cur.b[i].y, u.x, fmaf(cur.b[i].x, u.y, acc[i].y));
+        acc[i].x = sw_fma(cur.b[i].y, u.y, sw_fma(cur.b[i].x, u.x, acc[i].x));
+        acc[i].y = sw_fma(-cur.b[i].y, u.x, sw_fma(cur.b[i].x, u.y, acc[i].y));
       }
-      if (t % DD_SW_FOLD == DD_SW_FOLD - 1) sw_fold<PER>(acc, dsum, lane);
     };
     __syncthreads();          // the parts of the tile before have been read
     load(S0, 0);
@@ -478,10 +530,11 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
       step(S0, S2, t);
       step(S1, S0, t + 1);
       step(S2, S1, t + 2);
+      if ((t + 3) % (DD_SW_FOLD / 3 * 3) == 0) sw_fold<T, PER>(acc, dsum, lane);
     }
     if (t < N) step(S0, S2, t);
     if (t + 1 < N) step(S1, S0, t + 1);
-    sw_fold<PER>(acc, dsum, lane);
+    sw_fold<T, PER>(acc, dsum, lane);
     const int idx = lane >> 1, v = wave + NW * (idx >> 1);
     if ((lane & 1) == 0 && idx < 2 * PER && v < n)
       ((double*)P.partial)[(size_t)(2 * v + (idx & 1)) * P.sw_ld + tile] = dsum;

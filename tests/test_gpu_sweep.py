@@ -1,4 +1,4 @@
-"""The complex64 one-sweep Arnoldi step (k_sweep) at the edges of its tiles.
+"""The one-sweep Arnoldi step (k_sweep, k_pass2) at the edges of its tiles.
 
 After one cycle the stored arrays have to satisfy the relations that the step
 computes, recomputed here in complex128 from the stored vectors themselves:
@@ -7,7 +7,8 @@ computes, recomputed here in complex128 from the stored vectors themselves:
     A q_j (the classical Gram-Schmidt coefficient);
   * A q_j = C B_j + Q h_j.
 
-Both hold to FP32 rounding.  The bounds count the roundings: u = 2^-24; the
+Both hold to rounding.  The bounds count the roundings: u = 2^-24 in complex64,
+2^-53 in complex128; the
 stencil makes at most 12 per term; a dot product is summed over at most 32 rows
 and 8 folds before it is added in FP64; an update sums n products and the nine
 parts of the waves; stored vectors and coefficients are rounded once more.
@@ -22,7 +23,8 @@ from oracle import fdfd, precond
 
 pytestmark = pytest.mark.gpu
 
-U32 = 2.0 ** -24
+U = {"c64": 2.0 ** -24, "c128": 2.0 ** -53}
+DT = {"c64": np.complex64, "c128": np.complex128}
 
 
 def _inst(seed, nx, ny):
@@ -32,8 +34,10 @@ def _inst(seed, nx, ny):
 
 
 def _check(s, p, A, steps, passes=1):
+    u = U[s.inner]
     H, B = s.debug(p, "H").T, s.debug(p, "B").T
-    Q = s.debug(p, "Q").T.astype(np.complex128)
+    Q = s.debug(p, "Q").T.astype(np.complex128)[:, :steps + 1]
+    Q[:, steps] /= H[steps, steps - 1].real          # normalised one step late
     C = s.debug(p, "C").T.astype(np.complex128)
     k = C.shape[1]
     absA = abs(A)
@@ -44,14 +48,14 @@ def _check(s, p, A, steps, passes=1):
         size = np.linalg.norm(absA @ abs(Q[:, j]))
         h = np.concatenate([B[:, j], H[:j + 1, j]])
         d = basis[:, :n].conj().T @ z
-        assert np.abs(h - d).max() <= (12 + 40 + 4) * U32 * size, j
+        assert np.abs(h - d).max() <= (12 + 40 + 4) * u * size, j
         r = z - basis[:, :n] @ h - H[j + 1, j] * Q[:, j + 1]
-        assert np.linalg.norm(r) <= (12 + passes * (n / 8 + 9) + 4) * U32 * (size + np.abs(h).sum()), j
-        assert abs(np.linalg.norm(Q[:, j + 1]) - 1) <= 60 * U32, j
+        assert np.linalg.norm(r) <= (12 + passes * (n / 8 + 9) + 4) * u * (size + np.abs(h).sum()), j
+        assert abs(np.linalg.norm(Q[:, j + 1]) - 1) <= 60 * u, j
     if passes == 2:     # orthogonal to the rounding of one dot product and one update
         E = basis[:, :k + steps + 1]
         E = E.conj().T @ E - np.eye(k + steps + 1)
-        assert np.abs(E).max() <= 2 * (44 + (k + steps) / 8 + 13) * U32
+        assert np.abs(E).max() <= 2 * (44 + (k + steps) / 8 + 13) * u
 
 
 # nx: one strip, the widest strip, the narrowest second strip, an even split,
@@ -60,11 +64,20 @@ def _check(s, p, A, steps, passes=1):
     (20, 15, 0, 31), (62, 7, 0, 33), (63, 9, 3, 61), (124, 8, 0, 64), (125, 11, 0, 97),
     (61, 40, 20, 107), (130, 64, 0, 127)])
 def test_one_cycle_relations(nx, ny, k, restart):
+    _one_cycle(nx, ny, k, restart, "c64")
+
+
+@pytest.mark.parametrize("nx,ny,k,restart", [(20, 15, 0, 16), (63, 9, 3, 30), (125, 11, 0, 63)])
+def test_one_cycle_relations_c128(nx, ny, k, restart):
+    _one_cycle(nx, ny, k, restart, "c128")
+
+
+def _one_cycle(nx, ny, k, restart, inner):
     from paper_1902_00090_amd import FdfdOp, Solver
     inst = _inst(nx + ny, nx, ny)
-    s = Solver([FdfdOp.from_instance(inst)], restart=restart, kmax=k, cgs_passes=1)
+    s = Solver([FdfdOp.from_instance(inst)], restart=restart, kmax=k, cgs_passes=1, inner=inner)
     if k:
-        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(np.complex64)
+        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(DT[inner])
         s.set_subspace([torch.tensor(V, device="cuda")])
     b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
     _, (info,), _ = s.solve([b], tol=0.0, maxit=restart)
@@ -74,16 +87,17 @@ def test_one_cycle_relations(nx, ny, k, restart):
 
 
 # runs of 64 cells: a part of one, one, several and a remainder; the same widths
-@pytest.mark.parametrize("nx,ny,k,restart,adaptive", [
-    (9, 7, 0, 20, False), (20, 16, 0, 33, True), (63, 9, 3, 61, False), (125, 11, 0, 97, True),
-    (61, 40, 20, 107, False)])
-def test_two_passes(nx, ny, k, restart, adaptive):
+@pytest.mark.parametrize("nx,ny,k,restart,adaptive,inner", [
+    (9, 7, 0, 20, False, "c64"), (20, 16, 0, 33, True, "c64"), (63, 9, 3, 61, False, "c64"),
+    (125, 11, 0, 97, True, "c64"), (61, 40, 20, 107, False, "c64"), (9, 7, 0, 15, False, "c128"),
+    (63, 9, 3, 60, True, "c128"), (125, 11, 0, 33, False, "c128")])
+def test_two_passes(nx, ny, k, restart, adaptive, inner):
     from paper_1902_00090_amd import FdfdOp, Solver
     inst = _inst(nx + ny, nx, ny)
     s = Solver([FdfdOp.from_instance(inst)], restart=restart, kmax=k, cgs_passes=2,
-               select_reorth=adaptive)
+               select_reorth=adaptive, inner=inner)
     if k:
-        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(np.complex64)
+        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(DT[inner])
         s.set_subspace([torch.tensor(V, device="cuda")])
     b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
     _, (info,), _ = s.solve([b], tol=0.0, maxit=restart)

@@ -18,15 +18,20 @@
 //  3. F[iy, ix] = a_ix phi_ix(iy).
 //
 // The kernels, all in FP64:
-//  * k_eim_modes: one thread per column.  Sturm-count bisection for the
-//    lowest eigenvalue, then inverse iteration from just below it.  The
-//    shifted matrix is then symmetric positive definite with non-positive
-//    off-diagonals, so its LDL^T sweep needs no pivoting and keeps the
-//    iterate positive.
-//  * k_eim_line: one thread per problem.  The cyclic complex tridiagonal
-//    system is solved by Sherman-Morrison over a tridiagonal elimination with
-//    partial pivoting.  The matrix is indefinite, so pivoting is needed.
+//  * k_eim_bound: lower bounds of the lowest eigenvalues, by sections of the
+//    Gershgorin interval; four lanes of a column try four points at a time.
+//  * k_eim_modes: one thread per column, inverse iteration from just below the
+//    eigenvalue.  The shifted matrix is then symmetric positive definite with
+//    non-positive off-diagonals, so its LDL^T sweep needs no pivoting and keeps
+//    the iterate positive.
+//  * k_eim_line: one wave per problem.  The cyclic complex tridiagonal system
+//    is solved by Sherman-Morrison over a tridiagonal elimination with partial
+//    pivoting.  The matrix is indefinite, so pivoting is needed.
 //  * k_eim_assemble: writes F in complex64.
+// Measured for 64 problems of 480 x 240: one bisecting thread per column with a
+// division in each Sturm step took 4.54 ms and one thread per problem, its rows
+// in memory between the steps, 1.04 ms; these kernels take
+// 0.17, 0.37 and 0.23 ms.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -43,7 +48,7 @@ namespace {
 struct EimDesc {
   int nx, ny;
   double omega, dx;
-  const double* eps;   // [ny][nx]
+  const float* eps;    // [ny][nx]
   const double2* cf;   // cxm [0, nx), cxp [nx, 2nx)
   const double2* b;    // [D] right-hand side
   float2* F;           // [D] output
@@ -63,83 +68,198 @@ __device__ __forceinline__ double2 zdiv(double2 a, double2 b) {
 }
 
 // ------------------------------------------------ column modes (step 1) ----
-__global__ __launch_bounds__(64) void k_eim_modes(const EimDesc* __restrict__ desc,
+// Lower bound of the lowest eigenvalue of 16 columns per wave.  T - x I has a
+// negative eigenvalue where the sequence of its leading minors changes sign:
+// divided by h2^i they obey p_i = t_i p_{i-1} - p_{i-2} with t_i = (d_i - x)/h2,
+// one fused multiply-add a step and no division (the pivots are their ratios,
+// each a division that waits for the one before).  p only grows while it is
+// positive, so it is scaled down every four steps; |t| < 2^100 for finite
+// inputs in FP32.  Lane 16 s + c tries point s + 1 of five sections of column
+// c's interval: 18 rounds leave 2 h2 5^-18 < 2^-40 h2 (the shift below it is off
+// by 1e-10 of the diagonal on purpose).  LDS: the columns' permittivities are
+// read 18 times.
+template <bool LDS>
+__global__ __launch_bounds__(64) void k_eim_bound(const EimDesc* __restrict__ desc,
+                                                  double* __restrict__ sig) {
+  extern __shared__ float eps_l[];
+  const EimDesc d = desc[blockIdx.y];
+  const int c = threadIdx.x & 15, sct = threadIdx.x >> 4;
+  if ((int)blockIdx.x * 16 >= d.nx) return;
+  const int ix = min((int)blockIdx.x * 16 + c, d.nx - 1);
+  const int nx = d.nx, ny = d.ny;
+  const double h2 = 1.0 / (d.dx * d.dx), w2 = d.omega * d.omega;
+  const float* eps = d.eps + ix;
+  float emin = eps[0], emax = emin;
+  for (int i = sct; i < ny; i += 4) {
+    const float e = eps[(size_t)i * nx];
+    if (LDS) eps_l[i * 16 + c] = e;
+    emin = fminf(emin, e);
+    emax = fmaxf(emax, e);
+  }
+  for (int o = 16; o <= 32; o <<= 1) {
+    emin = fminf(emin, __shfl_xor(emin, o, 64));
+    emax = fmaxf(emax, __shfl_xor(emax, o, 64));
+  }
+  __syncthreads();
+  // Gershgorin: the lowest eigenvalue lies in [min diag - 2 h2, min diag]
+  const double dmin = 2.0 * h2 - w2 * (double)emax, dmax = 2.0 * h2 - w2 * (double)emin;
+  const double amax = fmax(fabs(dmin), fabs(dmax));
+  double lo = dmin - 2.0 * h2, width = 2.0 * h2;
+  const double a = -w2 / h2;
+  for (int it = 0; it < 18; ++it) {
+    const double x = lo + width * (0.2 * (sct + 1));
+    const double t0 = 2.0 - x / h2;
+    double p1 = 1.0, p2 = 0.0;
+    int neg = 0;                    // sign bits of the minors
+    int i = 0;
+    for (; i + 8 <= ny; i += 8) {
+      float e[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) e[q] = LDS ? eps_l[(i + q) * 16 + c] : eps[(size_t)(i + q) * nx];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const double p = fma(fma(a, (double)e[q], t0), p1, -p2);
+        neg |= __double2hiint(p);
+        p2 = p1;
+        p1 = p;
+        if (q % 4 == 3) {
+          const double f = (fabs(p1) > 0x1p400) ? 0x1p-400 : 1.0;
+          p1 *= f;
+          p2 *= f;
+        }
+      }
+    }
+    for (; i < ny; ++i) {
+      const double e = LDS ? eps_l[i * 16 + c] : eps[(size_t)i * nx];
+      const double p = fma(fma(a, e, t0), p1, -p2);
+      neg |= __double2hiint(p);
+      const double f = (fabs(p) > 0x1p400) ? 0x1p-400 : 1.0;
+      p2 = p1 * f;
+      p1 = p * f;
+    }
+    // the points without a sign change lie below the eigenvalue
+    const unsigned long long below = __ballot(neg >= 0);
+    const int k = __popcll((below >> c) & 0x0001000100010001ull);
+    lo += width * (0.2 * k);
+    width *= 0.2;
+  }
+  if (sct == 0 && (int)blockIdx.x * 16 + c < nx)
+    sig[d.off1 + ix] = lo - 1e-10 * (amax + 2.0 * h2);
+}
+
+// Inverse iteration from the shift, one thread per column.  The pivots' inverses
+// are formed once (the only divisions); a sweep is then one fused multiply-add a
+// row.  Rows are taken eight at a time so that their loads are in flight
+// together.  Bound by the traffic of its two arrays, which exceed the L2.
+#define DD_EIM_COLS 64
+__global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __restrict__ desc,
                                                   double* __restrict__ phi,
                                                   double* __restrict__ piv,
                                                   double* __restrict__ mu,
                                                   double2* __restrict__ jp) {
   const EimDesc d = desc[blockIdx.y];
-  const int ix = blockIdx.x * 64 + threadIdx.x;
+  const int ix = blockIdx.x * DD_EIM_COLS + threadIdx.x;
   if (ix >= d.nx) return;
   const int nx = d.nx, ny = d.ny;
   const double h2 = 1.0 / (d.dx * d.dx), w2 = d.omega * d.omega, e2 = h2 * h2;
-  const double* eps = d.eps + ix;
+  const float* eps = d.eps + ix;
   double* ph = phi + d.off2 + ix;
   double* pv = piv + d.off2 + ix;
-  auto diag = [&](int i) { return 2.0 * h2 - w2 * eps[(size_t)i * nx]; };
-
-  // Gershgorin: the lowest eigenvalue lies in [min diag - 2 h2, min diag]
-  double dmin = diag(0), amax = fabs(dmin);
-  for (int i = 1; i < ny; ++i) {
-    const double t = diag(i);
-    dmin = fmin(dmin, t);
-    amax = fmax(amax, fabs(t));
-  }
-  const double pivmin = 1e-290 * fmax(1.0, e2);
-  double lo = dmin - 2.0 * h2, hi = dmin;
-  for (int it = 0; it < 52; ++it) {
-    const double x = 0.5 * (lo + hi);
-    // Sturm count: eigenvalues of T below x = negative pivots of T - x I
-    int cnt = 0;
-    double q = 1.0;
-    for (int i = 0; i < ny; ++i) {
-      q = diag(i) - x - (i > 0 ? e2 / q : 0.0);
-      if (fabs(q) < pivmin) q = -pivmin;
-      cnt += (q < 0.0);
+  const double sigma = mu[d.off1 + ix];
+  constexpr int U = 8;
+  // rows [i, i + U) up (or down) with valid addresses past the ends
+  auto row = [&](int i) { return (size_t)min(max(i, 0), ny - 1) * nx; };
+  double ss = 0.0, sum = 0.0;
+  // eight rows are computed while the next eight are in flight
+  double v[U], r[U], vn[U], rn[U];
+  auto fetch = [&](int i0, int dir, bool first) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const size_t at = row(i0 + dir * q);
+      vn[q] = first ? (double)eps[at] : ph[at];
+      if (!first) rn[q] = pv[at];
     }
-    if (cnt >= 1) hi = x; else lo = x;
-  }
-
-  // inverse iteration with the shift just below the eigenvalue
-  const double sigma = lo - 1e-10 * (amax + 2.0 * h2);
-  for (int i = 0; i < ny; ++i) ph[(size_t)i * nx] = 1.0;
+  };
+  auto take = [&]() {
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      v[q] = vn[q];
+      r[q] = rn[q];
+    }
+  };
   for (int it = 0; it < 4; ++it) {
-    double p = diag(0) - sigma, z = ph[0];
-    pv[0] = p;
-    for (int i = 1; i < ny; ++i) {
-      const double l = -h2 / p;              // L factor: off-diagonal / previous pivot
-      p = diag(i) - sigma + h2 * l;           // a_i - sigma - e * l
-      z = ph[(size_t)i * nx] - l * z;
-      pv[(size_t)i * nx] = p;
-      ph[(size_t)i * nx] = z;
+    // L z = v: z_i = v_i + h2 z_{i-1} / p_{i-1}; the first time from ones
+    double z = 0.0, rp = 0.0;
+    fetch(0, 1, it == 0);
+    for (int i0 = 0; i0 < ny; i0 += U) {
+      take();
+      fetch(i0 + U, 1, it == 0);
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (i0 + q < ny) {
+          if (it == 0) {
+            r[q] = 1.0 / (2.0 * h2 - w2 * v[q] - sigma - e2 * rp);
+            v[q] = 1.0;
+            pv[(size_t)(i0 + q) * nx] = r[q];
+          }
+          z = fma(h2 * rp, z, v[q]);
+          rp = r[q];
+          ph[(size_t)(i0 + q) * nx] = z;
+        }
+      }
     }
-    double x = ph[(size_t)(ny - 1) * nx] / pv[(size_t)(ny - 1) * nx];
-    ph[(size_t)(ny - 1) * nx] = x;
-    double ss = x * x;
-    for (int i = ny - 2; i >= 0; --i) {
-      x = (ph[(size_t)i * nx] + h2 * x) / pv[(size_t)i * nx];
-      ph[(size_t)i * nx] = x;
-      ss += x * x;
+    // D L^T x = z: x_i = (z_i + h2 x_{i+1}) / p_i
+    double x = 0.0;
+    ss = sum = 0.0;
+    fetch(ny - 1, -1, false);
+    for (int i0 = ny - 1; i0 >= 0; i0 -= U) {
+      take();
+      fetch(i0 - U, -1, false);
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (i0 - q >= 0) {
+          x = fma(h2 * r[q], x, v[q] * r[q]);
+          ph[(size_t)(i0 - q) * nx] = x;
+          ss = fma(x, x, ss);
+          sum += x;
+        }
+      }
     }
-    const double inv = 1.0 / sqrt(ss);
-    for (int i = 0; i < ny; ++i) ph[(size_t)i * nx] *= inv;
+    // an iteration grows the vector by up to 1e10 / h2: scale it if four of
+    // them could leave the range
+    if (it < 3 && !(ss < 1e120)) {
+      const double f = 1.0 / sqrt(ss);
+      for (int i = 0; i < ny; ++i) ph[(size_t)i * nx] *= f;
+    }
   }
-  // sign (positive), Rayleigh quotient and projection of the source column
-  double sum = 0.0;
-  for (int i = 0; i < ny; ++i) sum += ph[(size_t)i * nx];
-  const double sg = (sum < 0.0) ? -1.0 : 1.0;
-  double rq = 0.0, prev = 0.0;
+  // unit norm and sign (positive), Rayleigh quotient and projection of the
+  // source column
+  const double sc = copysign(1.0 / sqrt(ss), sum);
+  double rq = 0.0, prev = 0.0, cur = sc * ph[0];
   double2 jj = make_double2(0.0, 0.0);
   const double2* bc = d.b + ix;
-  for (int i = 0; i < ny; ++i) {
-    const double v = sg * ph[(size_t)i * nx];
-    const double next = (i + 1 < ny) ? sg * ph[(size_t)(i + 1) * nx] : 0.0;
-    rq += v * (diag(i) * v - h2 * (prev + next));
-    const double2 bv = bc[(size_t)i * nx];
-    jj.x += v * bv.x;
-    jj.y += v * bv.y;
-    ph[(size_t)i * nx] = v;
-    prev = v;
+  for (int i0 = 0; i0 < ny; i0 += U) {
+    float e[U];
+    double2 bv[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      v[q] = ph[row(i0 + q + 1)];
+      e[q] = eps[row(i0 + q)];
+      bv[q] = bc[row(i0 + q)];
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const int i = i0 + q;
+      if (i < ny) {
+        const double next = (i + 1 < ny) ? sc * v[q] : 0.0;
+        rq += cur * ((2.0 * h2 - w2 * (double)e[q]) * cur - h2 * (prev + next));
+        jj.x += cur * bv[q].x;
+        jj.y += cur * bv[q].y;
+        ph[(size_t)i * nx] = cur;
+        prev = cur;
+        cur = next;
+      }
+    }
   }
   mu[d.off1 + ix] = rq;
   jp[d.off1 + ix] = jj;
@@ -153,83 +273,119 @@ __global__ __launch_bounds__(64) void k_eim_modes(const EimDesc* __restrict__ de
 // with diag_0 - gamma, diag_{n-1} - alpha beta / gamma, u = (gamma, 0.., alpha)
 // and v = (1, 0.., beta / gamma).  Then a = y - (v.y / (1 + v.z)) z with
 // T y = j and T z = u.
-__global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ desc, int nb,
+// One wave per problem.  The elimination is a chain of n steps with a division
+// each; all lanes do it, the current row in registers, on rows that they have
+// laid out 64 at a time in LDS.  They then divide the finished rows by their
+// pivots, a row each, so that the back substitution's chain is one complex
+// multiply-add a step.
+struct LineRow {           // a finished row: diagonal, two entries above, right-hand sides
+  double2 d, u, w, y, z;
+};
+__global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ desc,
                                                  const double* __restrict__ mu,
                                                  const double2* __restrict__ jp,
-                                                 double2* __restrict__ dg, double2* __restrict__ du,
-                                                 double2* __restrict__ du2,
-                                                 double2* __restrict__ r1,
-                                                 double2* __restrict__ r2,
+                                                 LineRow* __restrict__ rows,
                                                  double2* __restrict__ amp) {
-  const int p = blockIdx.x * 64 + threadIdx.x;
-  if (p >= nb) return;
-  const EimDesc d = desc[p];
-  const int n = d.nx;
+  const EimDesc d = desc[blockIdx.x];
+  const int n = d.nx, lane = threadIdx.x;
   const size_t o = d.off1;
   const double2* cxm = d.cf;
   const double2* cxp = d.cf + n;
+  LineRow* R = rows + o;
+  __shared__ double2 sub_l[64], dg_l[64], up_l[64], j_l[64];
+  __shared__ LineRow r_l[64];
+  const double2 zero = make_double2(0.0, 0.0);
   auto neg = [](double2 a) { return make_double2(-a.x, -a.y); };
   const double2 beta = neg(cxm[0]), alpha = neg(cxp[n - 1]);
   const double2 diag0 = make_double2(cxm[0].x + cxp[0].x + mu[o], cxm[0].y + cxp[0].y);
   const double2 gamma = neg(diag0);
   const double2 bg = zdiv(beta, gamma);
-  for (int i = 0; i < n; ++i) {
-    double2 t = make_double2(cxm[i].x + cxp[i].x + mu[o + i], cxm[i].y + cxp[i].y);
-    if (i == 0) t = zsub(t, gamma);
-    if (i == n - 1) t = zsub(t, zmul(alpha, bg));
-    dg[o + i] = t;
-    du[o + i] = (i < n - 1) ? neg(cxp[i]) : make_double2(0.0, 0.0);
-    du2[o + i] = make_double2(0.0, 0.0);
-    r1[o + i] = jp[o + i];
-    r2[o + i] = make_double2(0.0, 0.0);
-  }
-  r2[o] = gamma;
-  r2[o + n - 1] = alpha;
-  // elimination with partial pivoting (row i+1's sub-diagonal entry is the
-  // untouched -cxm_{i+1})
-  for (int i = 0; i < n - 1; ++i) {
-    const double2 sub = neg(cxm[i + 1]);
-    const double2 di = dg[o + i];
-    if (zabs2(di) >= zabs2(sub)) {
-      const double2 m = zdiv(sub, di);
-      dg[o + i + 1] = zsub(dg[o + i + 1], zmul(m, du[o + i]));
-      r1[o + i + 1] = zsub(r1[o + i + 1], zmul(m, r1[o + i]));
-      r2[o + i + 1] = zsub(r2[o + i + 1], zmul(m, r2[o + i]));
-    } else {
-      const double2 m = zdiv(di, sub);
-      const double2 d1 = dg[o + i + 1], u0 = du[o + i];
-      const double2 u1 = (i + 1 < n - 1) ? du[o + i + 1] : make_double2(0.0, 0.0);
-      dg[o + i] = sub;
-      du[o + i] = d1;
-      du2[o + i] = u1;
-      dg[o + i + 1] = zsub(u0, zmul(m, d1));
-      if (i + 1 < n - 1) du[o + i + 1] = neg(zmul(m, u1));
-      const double2 a1 = r1[o + i], b1 = r1[o + i + 1];
-      r1[o + i] = b1;
-      r1[o + i + 1] = zsub(a1, zmul(m, b1));
-      const double2 a2 = r2[o + i], b2 = r2[o + i + 1];
-      r2[o + i] = b2;
-      r2[o + i + 1] = zsub(a2, zmul(m, b2));
+  // elimination with partial pivoting; the current row's diagonal, upper entry
+  // and right-hand sides
+  double2 cd = zero, cu = zero, c1 = zero, c2 = zero;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int i = i0 + lane;
+    __syncthreads();
+    if (i < n) {
+      double2 t = make_double2(cxm[i].x + cxp[i].x + mu[o + i], cxm[i].y + cxp[i].y);
+      if (i == 0) t = zsub(t, gamma);
+      if (i == n - 1) t = zsub(t, zmul(alpha, bg));
+      sub_l[lane] = neg(cxm[i]);
+      dg_l[lane] = t;
+      up_l[lane] = (i < n - 1) ? neg(cxp[i]) : zero;
+      j_l[lane] = jp[o + i];
+    }
+    __syncthreads();
+    const int m = min(64, n - i0);
+    for (int q = 0; q < m; ++q) {
+      // row i0 + q joins: it is eliminated by, or takes the place of, the current row
+      const double2 sub = sub_l[q], dg = dg_l[q], up = up_l[q], j1 = j_l[q];
+      const int r = i0 + q;
+      double2 j2 = zero;
+      if (r == 0) j2 = zadd(j2, gamma);
+      if (r == n - 1) j2 = zadd(j2, alpha);
+      if (r == 0) {
+        cd = dg;
+        cu = up;
+        c1 = j1;
+        c2 = j2;
+        continue;
+      }
+      const bool keep = zabs2(cd) >= zabs2(sub);
+      const double2 f = zdiv(keep ? sub : cd, keep ? cd : sub);
+      // finished row r - 1, and the row that f times it is taken from
+      const double2 pu = keep ? cu : dg, pw = keep ? zero : up;
+      const double2 p1 = keep ? c1 : j1, p2 = keep ? c2 : j2;
+      const double2 qd = keep ? dg : cu, qu = keep ? up : zero;
+      const double2 q1 = keep ? j1 : c1, q2 = keep ? j2 : c2;
+      if (lane == 0) R[r - 1] = {keep ? cd : sub, pu, pw, p1, p2};
+      cd = zsub(qd, zmul(f, pu));
+      cu = zsub(qu, zmul(f, pw));
+      c1 = zsub(q1, zmul(f, p1));
+      c2 = zsub(q2, zmul(f, p2));
     }
   }
-  // back substitution, both right-hand sides, in place
-  double2 y1 = zdiv(r1[o + n - 1], dg[o + n - 1]), z1 = zdiv(r2[o + n - 1], dg[o + n - 1]);
-  double2 y2 = make_double2(0.0, 0.0), z2 = y2;   // x_{i+2}
-  r1[o + n - 1] = y1;
-  r2[o + n - 1] = z1;
-  for (int i = n - 2; i >= 0; --i) {
-    const double2 u = du[o + i], w = du2[o + i], di = dg[o + i];
-    const double2 yi = zdiv(zsub(zsub(r1[o + i], zmul(u, y1)), zmul(w, y2)), di);
-    const double2 zi = zdiv(zsub(zsub(r2[o + i], zmul(u, z1)), zmul(w, z2)), di);
-    r1[o + i] = yi;
-    r2[o + i] = zi;
-    y2 = y1; z2 = z1;
-    y1 = yi; z1 = zi;
+  if (lane == 0) R[n - 1] = {cd, zero, zero, c1, c2};
+  __threadfence_block();
+  __syncthreads();
+  // back substitution of both right-hand sides, y_i and z_i left in the rows
+  double2 y1 = zero, y2 = zero, z1 = zero, z2 = zero;
+  for (int i0 = (n - 1) / 64 * 64; i0 >= 0; i0 -= 64) {
+    const int m = min(64, n - i0);
+    __syncthreads();
+    if (lane < m) {
+      LineRow a = R[i0 + lane];
+      const double2 inv = zdiv(make_double2(1.0, 0.0), a.d);
+      a.u = zmul(a.u, inv);
+      a.w = zmul(a.w, inv);
+      a.y = zmul(a.y, inv);
+      a.z = zmul(a.z, inv);
+      r_l[lane] = a;
+    }
+    __syncthreads();
+    double2 my = zero, mz = zero;
+    for (int q = m - 1; q >= 0; --q) {
+      const double2 u = r_l[q].u, w = r_l[q].w;
+      const double2 y = zsub(zsub(r_l[q].y, zmul(w, y2)), zmul(u, y1));
+      const double2 z = zsub(zsub(r_l[q].z, zmul(w, z2)), zmul(u, z1));
+      if (lane == q) {
+        my = y;
+        mz = z;
+      }
+      y2 = y1; z2 = z1;
+      y1 = y; z1 = z;
+    }
+    if (lane < m) {
+      R[i0 + lane].y = my;
+      R[i0 + lane].z = mz;
+    }
   }
-  const double2 vy = zadd(r1[o], zmul(bg, r1[o + n - 1]));
-  const double2 vz = zadd(make_double2(1.0 + r2[o].x, r2[o].y), zmul(bg, r2[o + n - 1]));
+  __threadfence_block();
+  __syncthreads();
+  const double2 vy = zadd(R[0].y, zmul(bg, R[n - 1].y));
+  const double2 vz = zadd(make_double2(1.0 + R[0].z.x, R[0].z.y), zmul(bg, R[n - 1].z));
   const double2 f = zdiv(vy, vz);
-  for (int i = 0; i < n; ++i) amp[o + i] = zsub(r1[o + i], zmul(f, r2[o + i]));
+  for (int i = lane; i < n; i += 64) amp[o + i] = zsub(R[i].y, zmul(f, R[i].z));
 }
 
 // ------------------------------------------------------ field (step 3) ----
@@ -247,9 +403,10 @@ __global__ __launch_bounds__(256) void k_eim_assemble(const EimDesc* __restrict_
 
 }  // namespace
 
-// Scratch layout of one call: phi and pivots (D doubles each); mu (nx
-// doubles); j, diagonal, two super-diagonals, two right-hand sides, amplitude
-// (nx complex each); then the descriptor table.  Every word is written by the
+// Scratch layout of one call: phi and inverse pivots (D doubles each); mu (nx
+// doubles; the shifts until the modes are known); j, the finished rows of the
+// line system (five values), amplitude (nx complex each); then the descriptor
+// table.  Every word is written by the
 // kernels before it is read, so nothing needs clearing between calls.
 static size_t eim_scratch_bytes(size_t s2, size_t s1, int nb) {
   const size_t s1p = (s1 + 1) & ~(size_t)1;   // keeps the complex arrays 16-byte aligned
@@ -278,7 +435,7 @@ static size_t eim_prepare(const char* who, const fdfd_op* const* ops, int nb,
     const fdfd_op* op = ops[p];
     EimDesc& d = hd[p];
     d.nx = op->nx; d.ny = op->ny; d.omega = op->omega; d.dx = op->dx;
-    d.eps = op->eps64; d.cf = op->cf64;
+    d.eps = op->eps32; d.cf = op->cf64;
     d.b = (const double2*)b[p]; d.F = (float2*)F[p];
     d.off2 = s2; d.off1 = s1;
     s2 += (size_t)op->D;
@@ -289,7 +446,7 @@ static size_t eim_prepare(const char* who, const fdfd_op* const* ops, int nb,
   return eim_scratch_bytes(s2, s1, nb);
 }
 
-// Enqueues the three kernels on scratch ws (eim_scratch_bytes long) and waits
+// Enqueues the four kernels on scratch ws (eim_scratch_bytes long) and waits
 // for them.
 static hipError_t eim_run(const std::vector<EimDesc>& hd, size_t s1, int maxnx, int maxD,
                           char* ws, hipStream_t stream) {
@@ -301,13 +458,20 @@ static hipError_t eim_run(const std::vector<EimDesc>& hd, size_t s1, int maxnx, 
   double* piv = phi + s2;
   double* mu = piv + s2;
   double2* z = (double2*)(mu + s1p);
-  double2 *jp = z, *dg = z + s1, *du = z + 2 * s1, *du2 = z + 3 * s1, *r1 = z + 4 * s1,
-          *r2 = z + 5 * s1, *amp = z + 6 * s1;
+  double2 *jp = z, *amp = z + 6 * s1;
+  LineRow* rows = (LineRow*)(z + s1);
+  static_assert(sizeof(LineRow) == 5 * sizeof(double2), "five values a row");
+  int maxny = 0;
+  for (const auto& d : hd) maxny = std::max(maxny, d.ny);
   EimDesc* dd = (EimDesc*)(z + 7 * s1);
   hipError_t e = hipMemcpyAsync(dd, hd.data(), sizeof(EimDesc) * nb, hipMemcpyHostToDevice, stream);
   if (e == hipSuccess) {
-    k_eim_modes<<<dim3((maxnx + 63) / 64, nb), 64, 0, stream>>>(dd, phi, piv, mu, jp);
-    k_eim_line<<<(nb + 63) / 64, 64, 0, stream>>>(dd, nb, mu, jp, dg, du, du2, r1, r2, amp);
+    // the permittivities of 16 columns fit the 64 KB of LDS up to 1024 rows
+    const dim3 gb((maxnx + 15) / 16, nb);
+    if (maxny <= 1024) k_eim_bound<true><<<gb, 64, (size_t)maxny * 64, stream>>>(dd, mu);
+    else k_eim_bound<false><<<gb, 64, 0, stream>>>(dd, mu);
+    k_eim_modes<<<dim3((maxnx + DD_EIM_COLS - 1) / DD_EIM_COLS, nb), DD_EIM_COLS, 0, stream>>>(dd, phi, piv, mu, jp);
+    k_eim_line<<<nb, 64, 0, stream>>>(dd, mu, jp, rows, amp);
     k_eim_assemble<<<dim3((maxD + 255) / 256, nb), 256, 0, stream>>>(dd, phi, amp);
     e = hipGetLastError();
   }

@@ -1,0 +1,28 @@
+"""Effective-index fields at the edges of the column kernels' tiles: columns in
+groups of 16 and 64, rows in groups of 8, the permittivities in LDS up to 1024
+rows and from memory beyond, the line solve in groups of 64 rows."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import eim
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("nx,ny", [(9, 8), (16, 9), (17, 15), (63, 16), (64, 257), (65, 1024),
+                                   (33, 1025), (129, 1031), (193, 40)])
+def test_random_permittivity_matches_oracle(nx, ny):
+    """The field is FP64 rounded to complex64: an error of 2^-24 of each value.
+    The line equation amplifies the modes' rounding (2^-53 times the rows) by
+    its condition, which stays below 1e6 here."""
+    import torch
+    from paper_1902_00090_amd import FdfdOp, eim_field
+    rng = np.random.default_rng(nx * 10000 + ny)
+    eps = (2.085 + 10.165 * rng.random((ny, nx))).astype(np.float32)
+    inst = W.Instance(eps, W.random_complex(rng, nx * ny), nx, ny, 0.025, 1.30, 3)
+    op = FdfdOp.from_instance(inst)
+    (F,) = eim_field([op], [torch.tensor(inst.b, device="cuda")])
+    want = eim.eim_instance(inst)
+    tol = 2.0 ** -24 * np.abs(want) + 1e6 * ny * 2.0 ** -53 * np.abs(want).max()
+    assert (np.abs(F.cpu().numpy() - want) <= tol).all()

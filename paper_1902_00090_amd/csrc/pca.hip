@@ -4,10 +4,11 @@
 // The basis is the leading left singular vectors of the snapshot matrix
 // X = [s_1 .. s_M] whose columns are field vectors (uncentred).  With the
 // snapshots stored as M rows of D elements, G = X^H X (G_ab = <s_a, s_b>) is
-// formed on the device with FP64 accumulation; its leading eigenpairs
-// (sigma_i^2, w_i) come from a Lanczos iteration with full
-// reorthogonalisation on the host (FP64); u_i = X w_i / sigma_i is formed on
-// the device and the basis is re-orthonormalised by one Cholesky QR pass.
+// formed on the device in FP64; its leading eigenpairs (sigma_i^2, w_i) come
+// from a Lanczos iteration with full reorthogonalisation (FP64; on the device
+// from 128 snapshots on, the small tridiagonal problem on the host); u_i =
+// X w_i / sigma_i is formed on the device and the basis is re-orthonormalised by
+// one Cholesky QR pass.
 #include <algorithm>
 #include <cmath>
 #include <complex>
@@ -24,131 +25,364 @@
 using cd = std::complex<double>;
 
 // ------------------------------------------------------------ device Gram ----
-// G_ab = sum_e conj(S[a][e]) S[b][e] for a 32 x 32 output tile (only tiles with
-// b-block >= a-block), over one slice of the element range (split over
-// gridDim.z so that small M still fills the chip).  Elements are staged through
-// LDS in steps of 64; each thread owns a 2 x 2 block of the tile, FP64 sums.
-#define PT 32
-#define PE 64
+// G_ab = sum_e conj(S[a][e]) S[b][e] for a square tile of snapshot pairs (only
+// tiles on and above the diagonal) over one slice of the elements, on the FP64
+// matrix cores: the real part is re^T re + im^T im, the imaginary part re^T im -
+// im^T re, four 16x16x4 products for four elements.  Four waves a workgroup, each
+// B x B blocks of 16 x 16; 32 elements a stage, the next stage's loads in
+// flight during the products.  Bound by the matrix cores: each LDS value feeds
+// 16 B products.  Measured for 1000 snapshots of 115,200 elements: 30.2 ms with
+// a 2 x 2 block of FP64 vector sums a thread, 8 here (0.46 TFLOP; a library
+// product of 4096 x 4096 FP64 matrices runs at 64 TFLOP/s).
+typedef double v4d __attribute__((ext_vector_type(4)));
+#define PE 32
+template <int B>
 __global__ __launch_bounds__(256) void k_pca_gram(const float2* __restrict__ S, int M, int D,
-                                                  int nslices, double2* __restrict__ part) {
-  const int ta = blockIdx.x, tb = blockIdx.y;
-  if (tb < ta) return;
-  const int slice = blockIdx.z;
-  const int per = (D + nslices - 1) / nslices;
-  const int e0 = slice * per, e1 = min(D, e0 + per);
-  __shared__ float2 sa[PT][PE + 1], sb[PT][PE + 1];
-  const int t = threadIdx.x;
-  const int ra = (t / 16) * 2, rb = (t % 16) * 2;   // this thread's 2x2 block
-  double2 acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = make_double2(0.0, 0.0);
+                                                  int per, double2* __restrict__ part) {
+  constexpr int TILE = 32 * B, LD = TILE * PE / 256;
+  // tile (ta, tb), tb >= ta, of the triangle's list
+  int ta = 0, rest = blockIdx.x;
+  const int nta = (M + TILE - 1) / TILE;
+  while (rest >= nta - ta) rest -= nta - ta++;
+  const int tb = ta + rest;
+  const bool diag = ta == tb;
+  const int e0 = blockIdx.y * per, e1 = min(D, e0 + per);
+  __shared__ float2 sa[TILE][PE + 1], sb[TILE][PE + 1];
+  const int t = threadIdx.x, lane = t & 63, wr = (t >> 6) >> 1, wc = (t >> 6) & 1;
+  const int li = lane & 15, lk = lane >> 4;
+  v4d ar[B][B], ai[B][B];
+#pragma unroll
+  for (int i = 0; i < B; ++i)
+#pragma unroll
+    for (int j = 0; j < B; ++j) ar[i][j] = ai[i][j] = v4d{0.0, 0.0, 0.0, 0.0};
+  float2 na[LD], nb[LD];
+  const float2 zero = make_float2(0.f, 0.f);
+  auto fetch = [&](int eb) {
+#pragma unroll
+    for (int q = 0; q < LD; ++q) {
+      const int r = (t + 256 * q) / PE, e = eb + (t + 256 * q) % PE;
+      const int a = ta * TILE + r, b = tb * TILE + r;
+      na[q] = (a < M && e < e1) ? S[(size_t)a * D + e] : zero;
+      if (!diag) nb[q] = (b < M && e < e1) ? S[(size_t)b * D + e] : zero;
+    }
+  };
+  fetch(e0);
+  const float2(*pb)[PE + 1] = diag ? sa : sb;
   for (int eb = e0; eb < e1; eb += PE) {
-    for (int idx = t; idx < PT * PE; idx += 256) {
-      const int r = idx / PE, c = idx % PE;
-      const int e = eb + c;
-      const int a = ta * PT + r, b = tb * PT + r;
-      sa[r][c] = (a < M && e < e1) ? S[(size_t)a * D + e] : make_float2(0.f, 0.f);
-      sb[r][c] = (b < M && e < e1) ? S[(size_t)b * D + e] : make_float2(0.f, 0.f);
+#pragma unroll
+    for (int q = 0; q < LD; ++q) {
+      const int r = (t + 256 * q) / PE, c = (t + 256 * q) % PE;
+      sa[r][c] = na[q];
+      if (!diag) sb[r][c] = nb[q];
     }
     __syncthreads();
-#pragma unroll 4
-    for (int c = 0; c < PE; ++c) {
-      float2 xa[2], xb[2];
-      xa[0] = sa[ra][c]; xa[1] = sa[ra + 1][c];
-      xb[0] = sb[rb][c]; xb[1] = sb[rb + 1][c];
+    if (eb + PE < e1) fetch(eb + PE);
+#pragma unroll
+    for (int kk = 0; kk < PE; kk += 4) {
+      double xr[B], xi[B], yr[B], yi[B];
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        const float2 x = sa[(wr * B + i) * 16 + li][kk + lk];
+        const float2 y = pb[(wc * B + i) * 16 + li][kk + lk];
+        xr[i] = x.x; xi[i] = x.y;
+        yr[i] = y.x; yi[i] = y.y;
+      }
+#pragma unroll
+      for (int i = 0; i < B; ++i)
+#pragma unroll
+        for (int j = 0; j < B; ++j) {
+          ar[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[i], yr[j], ar[i][j], 0, 0, 0);
+          ai[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xr[i], yi[j], ai[i][j], 0, 0, 0);
+          ar[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(xi[i], yi[j], ar[i][j], 0, 0, 0);
+          ai[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xi[i], yr[j], ai[i][j], 0, 0, 0);
+        }
+    }
+    __syncthreads();
+  }
+  // the row and column of each result value in a 16 x 16 block, from products
+  // with the row and column numbers
+  const v4d none = {0.0, 0.0, 0.0, 0.0};
+  const double one = lk == 0 ? 1.0 : 0.0, num = lk == 0 ? (double)li : 0.0;
+  const v4d rows = __builtin_amdgcn_mfma_f64_16x16x4f64(num, one, none, 0, 0, 0);
+  const v4d cols = __builtin_amdgcn_mfma_f64_16x16x4f64(one, num, none, 0, 0, 0);
+  double2* out = part + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * TILE * TILE;
+#pragma unroll
+  for (int i = 0; i < B; ++i)
+#pragma unroll
+    for (int j = 0; j < B; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        out[((wr * B + i) * 16 + (int)rows[v]) * TILE + (wc * B + j) * 16 + (int)cols[v]] =
+            make_double2(ar[i][j][v], ai[i][j][v]);
+}
+
+// G (M x M, row-major, full Hermitian) from the slice partials in a fixed
+// order: 64 entries of a tile a workgroup, four threads an entry (a quarter of
+// the slices each, eight loads in flight).  bad: set if a sum is not finite.
+__global__ __launch_bounds__(256) void k_pca_gram_reduce(const double2* __restrict__ part, int M,
+                                                         int tile, int nslices,
+                                                         double2* __restrict__ G,
+                                                         int* __restrict__ bad) {
+  int ta = 0, rest = blockIdx.x;
+  const int nta = (M + tile - 1) / tile, ntiles = nta * (nta + 1) / 2;
+  while (rest >= nta - ta) rest -= nta - ta++;
+  const int tb = ta + rest, i = blockIdx.y * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
+  const double2* src = part + (size_t)blockIdx.x * tile * tile + i;
+  const size_t ld = (size_t)ntiles * tile * tile;
+  double sx = 0.0, sy = 0.0;
+  for (int s = q; s < nslices; s += 32) {
+    double2 v[8];
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      v[r] = (s + 4 * r < nslices) ? src[(size_t)(s + 4 * r) * ld] : make_double2(0.0, 0.0);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      sx += v[r].x;
+      sy += v[r].y;
+    }
+  }
+  __shared__ double2 sum[4][64];
+  sum[q][threadIdx.x & 63] = make_double2(sx, sy);
+  __syncthreads();
+  if (q != 0) return;
+  const int l = threadIdx.x;
+  sx = (sum[0][l].x + sum[1][l].x) + (sum[2][l].x + sum[3][l].x);
+  sy = (sum[0][l].y + sum[1][l].y) + (sum[2][l].y + sum[3][l].y);
+  const int a = ta * tile + i / tile, b = tb * tile + i % tile;
+  if (a >= M || b >= M) return;
+  if (!isfinite(sx) || !isfinite(sy)) atomicOr(bad, 1);
+  // a diagonal tile holds both halves; its own lower one is left to the upper
+  if (a > b) return;
+  G[(size_t)a * M + b] = make_double2(sx, a == b ? 0.0 : sy);
+  if (a < b) G[(size_t)b * M + a] = make_double2(sx, -sy);
+}
+
+// out[r][e] = sum_m coef[m][r] F[m][e] for R rows (coef: FP64, [M][R]) on the FP64
+// matrix cores.  A workgroup takes 32 rows and 128 elements, a wave 32 of them;
+// a step is four vectors m.  The fields are read once per 32 rows, 128 bytes a
+// vector and half wave, the coefficients from the L2; both straight into the
+// operands, two steps at a time.  step, window: rows [s step, (s + 1) step) take
+// only the vectors within `window` of s (their other coefficients are zero); step = 0:
+// all vectors.  Measured at 115,200 elements: 20 rows from 1000 vectors 1.21 ms
+// as FP64 vector sums with 16 rows a thread (2.07 with 24 and scalar loads), 0.64
+// here; 320 rows from 17 of 32 vectors each 2.45 ms, 0.15 ms here, of which 0.06 ms
+// are the result's bytes.
+__global__ __launch_bounds__(256) void k_field_combine(const float2* __restrict__ F, int M, int D,
+                                                       const double2* __restrict__ coef, int R,
+                                                       int step, int window,
+                                                       float2* __restrict__ out) {
+  const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+  const int r0 = blockIdx.y * 32, e0 = blockIdx.x * 128 + (threadIdx.x >> 6) * 32;
+  int lo = 0, hi = M;
+  if (step > 0) {
+    lo = max(0, r0 / step - window);
+    hi = min(M, min(r0 + 31, R - 1) / step + window + 1);
+  }
+  const v4d none = {0.0, 0.0, 0.0, 0.0};
+  v4d ar[2][2], ai[2][2];             // [rows][elements]
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) ar[i][j] = ai[i][j] = none;
+  int col[2], el[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    col[i] = min(r0 + 16 * i + li, R - 1);
+    el[i] = min(e0 + 16 * i + li, D - 1);
+  }
+  auto fetch = [&](int m0, float2 (&f)[2][2], double2 (&c)[2][2]) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int m = m0 + 4 * u + lk, mc = min(m, hi - 1);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        f[u][i] = F[(size_t)mc * D + el[i]];
+        c[u][i] = coef[(size_t)mc * R + col[i]];
+      }
+      if (m >= hi) c[u][0] = c[u][1] = make_double2(0.0, 0.0);
+    }
+  };
+  float2 f[2][2], fn[2][2];
+  double2 c[2][2], cn[2][2];
+  fetch(lo, fn, cn);
+  for (int m0 = lo; m0 < hi; m0 += 8) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        f[u][i] = fn[u][i];
+        c[u][i] = cn[u][i];
+      }
+    fetch(min(m0 + 8, hi - 1), fn, cn);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          const double axr = xa[i].x, axi = xa[i].y, bxr = xb[j].x, bxi = xb[j].y;
-          acc[i][j].x += axr * bxr + axi * bxi;
-          acc[i][j].y += axr * bxi - axi * bxr;
+          const double fx = f[u][j].x, fy = f[u][j].y;
+          ar[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u][i].x, fx, ar[i][j], 0, 0, 0);
+          ai[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u][i].x, fy, ai[i][j], 0, 0, 0);
+          ar[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(-c[u][i].y, fy, ar[i][j], 0, 0, 0);
+          ai[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(c[u][i].y, fx, ai[i][j], 0, 0, 0);
         }
-    }
-    __syncthreads();
   }
-  const int nta = gridDim.x;
-  double2* out = part + ((size_t)slice * nta * nta + (size_t)ta * nta + tb) * PT * PT;
+  // row and column of the result values, as in k_pca_gram
+  const double one = lk == 0 ? 1.0 : 0.0, num = lk == 0 ? (double)li : 0.0;
+  const v4d rows = __builtin_amdgcn_mfma_f64_16x16x4f64(num, one, none, 0, 0, 0);
+  const v4d cols = __builtin_amdgcn_mfma_f64_16x16x4f64(one, num, none, 0, 0, 0);
+#pragma unroll
   for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) out[(ra + i) * PT + rb + j] = acc[i][j];
-}
-
-// G (M x M, row-major, full Hermitian) from the slice partials, fixed order.
-__global__ void k_pca_gram_reduce(const double2* __restrict__ part, int M, int nta, int nslices,
-                                  double2* __restrict__ G) {
-  const int a = blockIdx.y;
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (a >= M || b >= M) return;
-  const int lo = min(a, b), hi = max(a, b);
-  const int ta = lo / PT, tb = hi / PT;
-  // tile (ta, tb) holds G[lo-range][hi-range]; within it row = lo, col = hi
-  double sx = 0.0, sy = 0.0;
-  for (int s = 0; s < nslices; ++s) {
-    const double2 v = part[((size_t)s * nta * nta + (size_t)ta * nta + tb) * PT * PT +
-                           (lo % PT) * PT + (hi % PT)];
-    sx += v.x;
-    sy += v.y;
-  }
-  // stored value is G[lo][hi]; G[a][b] = that or its conjugate
-  G[(size_t)a * M + b] = (a <= b) ? make_double2(sx, sy) : make_double2(sx, -sy);
-}
-
-// U[i][e] = sum_m coef[m][i] * S[m][e] for i < k (coef FP64, M x k row-major),
-// one thread per element, 16 outputs per pass (grid.y = output group).
-__global__ __launch_bounds__(256) void k_pca_combine(const float2* __restrict__ S, int M, int D,
-                                                     const double2* __restrict__ coef, int k,
-                                                     float2* __restrict__ U) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int o0 = blockIdx.y * 16;
-  __shared__ double2 cf[64][16];
-  double2 acc[16];
 #pragma unroll
-  for (int o = 0; o < 16; ++o) acc[o] = make_double2(0.0, 0.0);
-  for (int m0 = 0; m0 < M; m0 += 64) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < 64 * 16; idx += 256) {
-      const int mm = idx / 16, o = idx % 16;
-      cf[mm][o] = (m0 + mm < M && o0 + o < k) ? coef[(size_t)(m0 + mm) * k + o0 + o]
-                                              : make_double2(0.0, 0.0);
-    }
-    __syncthreads();
-    if (e < D) {
-      const int mend = min(64, M - m0);
-      for (int mm = 0; mm < mend; ++mm) {
-        const float2 s = S[(size_t)(m0 + mm) * D + e];
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int o = 0; o < 16; ++o) {
-          const double2 c = cf[mm][o];
-          acc[o].x += c.x * s.x - c.y * s.y;
-          acc[o].y += c.x * s.y + c.y * s.x;
-        }
+      for (int v = 0; v < 4; ++v) {
+        const int r = r0 + 16 * i + (int)rows[v], e = e0 + 16 * j + (int)cols[v];
+        if (r < R && e < D)
+          out[(size_t)r * D + e] = make_float2((float)ar[i][j][v], (float)ai[i][j][v]);
       }
+}
+
+// ------------------------------------------------------- device Lanczos ----
+// Vectors of M FP64 complex values; Q: the Lanczos vectors, one after the other.
+__device__ __forceinline__ double2 lz_sum(double2 s, double2* l) {   // over the workgroup
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    s.x += __shfl_xor(s.x, o, 64);
+    s.y += __shfl_xor(s.y, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) l[threadIdx.x >> 6] = s;
+  __syncthreads();
+  return make_double2((l[0].x + l[1].x) + (l[2].x + l[3].x), (l[0].y + l[1].y) + (l[2].y + l[3].y));
+}
+// w = G q, a row per workgroup
+__global__ __launch_bounds__(256) void k_lz_matvec(const double2* __restrict__ G, int M,
+                                                   const double2* __restrict__ q,
+                                                   double2* __restrict__ w) {
+  __shared__ double2 l[4];
+  const double2* row = G + (size_t)blockIdx.x * M;
+  double2 s = make_double2(0.0, 0.0);
+  for (int b = threadIdx.x; b < M; b += 256) {
+    const double2 g = row[b], x = q[b];
+    s.x += g.x * x.x - g.y * x.y;
+    s.y += g.x * x.y + g.y * x.x;
+  }
+  s = lz_sum(s, l);
+  if (threadIdx.x == 0) w[blockIdx.x] = s;
+}
+// c_j = q_j^H w, a Lanczos vector per workgroup; the last one's is alpha
+__global__ __launch_bounds__(256) void k_lz_dots(const double2* __restrict__ Q, int M,
+                                                 const double2* __restrict__ w,
+                                                 double2* __restrict__ c, double* alpha) {
+  __shared__ double2 l[4];
+  const double2* q = Q + (size_t)blockIdx.x * M;
+  double2 s = make_double2(0.0, 0.0);
+  for (int i = threadIdx.x; i < M; i += 256) {
+    const double2 a = q[i], x = w[i];
+    s.x += a.x * x.x + a.y * x.y;
+    s.y += a.x * x.y - a.y * x.x;
+  }
+  s = lz_sum(s, l);
+  if (threadIdx.x == 0) {
+    c[blockIdx.x] = s;
+    if (alpha && blockIdx.x + 1 == gridDim.x) *alpha = s.x;
+  }
+}
+// w -= sum_j c_j q_j: 64 entries a workgroup, four threads an entry
+__global__ __launch_bounds__(256) void k_lz_update(const double2* __restrict__ Q, int M, int L,
+                                                   const double2* __restrict__ c,
+                                                   double2* __restrict__ w) {
+  __shared__ double2 sum[4][64];
+  const int l = threadIdx.x & 63, g = threadIdx.x >> 6, i = blockIdx.x * 64 + l;
+  double2 s = make_double2(0.0, 0.0);
+  if (i < M) {
+#pragma unroll 8
+    for (int j = g; j < L; j += 4) {
+      const double2 a = c[j], q = Q[(size_t)j * M + i];
+      s.x += a.x * q.x - a.y * q.y;
+      s.y += a.x * q.y + a.y * q.x;
     }
   }
-  if (e < D)
-#pragma unroll
-    for (int o = 0; o < 16; ++o)
-      if (o0 + o < k) U[(size_t)(o0 + o) * D + e] = make_float2((float)acc[o].x, (float)acc[o].y);
+  sum[g][l] = s;
+  __syncthreads();
+  if (g == 0 && i < M) {
+    double2 x = w[i];
+    x.x -= (sum[0][l].x + sum[1][l].x) + (sum[2][l].x + sum[3][l].x);
+    x.y -= (sum[0][l].y + sum[1][l].y) + (sum[2][l].y + sum[3][l].y);
+    w[i] = x;
+  }
+}
+// beta = ||w||, the next Lanczos vector w / beta
+__global__ __launch_bounds__(256) void k_lz_next(const double2* __restrict__ w, int M, double* beta,
+                                                 double2* __restrict__ q) {
+  __shared__ double2 l[4];
+  double2 s = make_double2(0.0, 0.0);
+  for (int i = threadIdx.x; i < M; i += 256) s.x += w[i].x * w[i].x + w[i].y * w[i].y;
+  const double b = sqrt(lz_sum(s, l).x);
+  if (threadIdx.x == 0) *beta = b;
+  for (int i = threadIdx.x; i < M; i += 256)
+    q[i] = b > 0.0 ? make_double2(w[i].x / b, w[i].y / b) : make_double2(0.0, 0.0);
 }
 
 // ------------------------------------------------------------- host math ----
-// Eigen-decomposition of a real symmetric n x n matrix by cyclic Jacobi
-// rotations (FP64).  A is overwritten; eigenvalues in w, eigenvectors in the
-// columns of V (row-major n x n).
-static void jacobi_eigh(std::vector<double>& A, int n, std::vector<double>& w,
-                        std::vector<double>& V) {
-  V.assign((size_t)n * n, 0.0);
-  for (int i = 0; i < n; ++i) V[(size_t)i * n + i] = 1.0;
-  for (int sweep = 0; sweep < 100; ++sweep) {
-    double off = 0.0, tot = 0.0;
-    for (int i = 0; i < n; ++i)
-      for (int j = 0; j < n; ++j) {
-        const double x = A[(size_t)i * n + j] * A[(size_t)i * n + j];
-        tot += x;
-        if (i != j) off += x;
+// Eigen-decomposition of the real symmetric tridiagonal matrix with diagonal d
+// and off-diagonal e (n - 1 values) by the implicit QR algorithm with Wilkinson
+// shifts (Golub and Van Loan, Matrix Computations, Sec. 8.3): eigenvalues in d,
+// eigenvector i in Z[i n .. i n + n).  About 1.5 n^2 rotations of two rows of Z;
+// cyclic Jacobi sweeps over the full matrix take six times as many.
+static void tridiagonal_eigh(std::vector<double>& d, std::vector<double>& e, int n,
+                             std::vector<double>& Z) {
+  Z.assign((size_t)n * n, 0.0);
+  for (int i = 0; i < n; ++i) Z[(size_t)i * n + i] = 1.0;
+  int hi = n - 1, tries = 0;
+  while (hi > 0) {
+    int lo = hi;
+    while (lo > 0 && std::fabs(e[lo - 1]) > 0x1p-53 * (std::fabs(d[lo - 1]) + std::fabs(d[lo]))) --lo;
+    if (lo > 0) e[lo - 1] = 0.0;
+    if (lo == hi || ++tries > 60 * n) {   // one eigenvalue found (the bound is never met)
+      --hi;
+      continue;
+    }
+    const double del = 0.5 * (d[hi - 1] - d[hi]), eh = e[hi - 1];
+    const double mu = d[hi] - eh * eh / (del + std::copysign(std::hypot(del, eh), del));
+    double x = d[lo] - mu, z = e[lo];
+    for (int k = lo; k < hi; ++k) {
+      const double r = std::hypot(x, z);
+      const double c = r > 0.0 ? x / r : 1.0, s = r > 0.0 ? z / r : 0.0;
+      if (k > lo) e[k - 1] = r;
+      const double a = d[k], b = e[k], g = d[k + 1];
+      d[k] = c * c * a + 2.0 * c * s * b + s * s * g;
+      d[k + 1] = s * s * a - 2.0 * c * s * b + c * c * g;
+      e[k] = c * s * (g - a) + (c * c - s * s) * b;
+      x = e[k];
+      if (k + 1 < hi) {
+        z = s * e[k + 1];
+        e[k + 1] *= c;
       }
-    if (off <= 1e-30 * tot) break;
+      double *p = &Z[(size_t)k * n], *q = p + n;
+      for (int i = 0; i < n; ++i) {
+        const double u = p[i], v = q[i];
+        p[i] = c * u + s * v;
+        q[i] = c * v - s * u;
+      }
+    }
+  }
+}
+
+// The signs of the tridiagonal eigenvectors (rows of Z) as cyclic
+// Jacobi rotations from the identity leave them: the signs of a stored basis
+// follow from them, and users compare bases.  The rotation angles shrink
+// quadratically, so three sweeps settle the directions; each vector takes the
+// sign of its product with the nearest Jacobi vector.
+static void jacobi_signs(const std::vector<double>& alpha, const std::vector<double>& beta, int n,
+                         std::vector<double>& Z) {
+  std::vector<double> A((size_t)n * n, 0.0), V((size_t)n * n, 0.0);   // V: vectors in rows
+  for (int i = 0; i < n; ++i) {
+    A[(size_t)i * n + i] = alpha[i];
+    V[(size_t)i * n + i] = 1.0;
+    if (i + 1 < n) A[(size_t)i * n + i + 1] = A[(size_t)(i + 1) * n + i] = beta[i];
+  }
+  for (int sweep = 0; sweep < 3; ++sweep)
     for (int p = 0; p < n - 1; ++p)
       for (int q = p + 1; q < n; ++q) {
         const double apq = A[(size_t)p * n + q];
@@ -157,105 +391,213 @@ static void jacobi_eigh(std::vector<double>& A, int n, std::vector<double>& w,
         const double theta = (aqq - app) / (2.0 * apq);
         const double t = (theta >= 0 ? 1.0 : -1.0) / (std::fabs(theta) + std::sqrt(theta * theta + 1.0));
         const double c = 1.0 / std::sqrt(t * t + 1.0), s = t * c;
-        for (int r = 0; r < n; ++r) {  // A <- A J (columns p, q)
-          const double arp = A[(size_t)r * n + p], arq = A[(size_t)r * n + q];
-          A[(size_t)r * n + p] = c * arp - s * arq;
-          A[(size_t)r * n + q] = s * arp + c * arq;
+        double *ap = &A[(size_t)p * n], *aq = &A[(size_t)q * n];
+        double *vp = &V[(size_t)p * n], *vq = &V[(size_t)q * n];
+        for (int r = 0; r < n; ++r) {
+          const double x = ap[r], y = aq[r], u = vp[r], v = vq[r];
+          ap[r] = c * x - s * y;
+          aq[r] = s * x + c * y;
+          vp[r] = c * u - s * v;
+          vq[r] = s * u + c * v;
         }
-        for (int r = 0; r < n; ++r) {  // A <- J^T A (rows p, q)
-          const double apr = A[(size_t)p * n + r], aqr = A[(size_t)q * n + r];
-          A[(size_t)p * n + r] = c * apr - s * aqr;
-          A[(size_t)q * n + r] = s * apr + c * aqr;
+        for (int r = 0; r < n; ++r) {   // the columns, by symmetry
+          A[(size_t)r * n + p] = ap[r];
+          A[(size_t)r * n + q] = aq[r];
         }
-        for (int r = 0; r < n; ++r) {  // V <- V J
-          const double vrp = V[(size_t)r * n + p], vrq = V[(size_t)r * n + q];
-          V[(size_t)r * n + p] = c * vrp - s * vrq;
-          V[(size_t)r * n + q] = s * vrp + c * vrq;
-        }
+        ap[p] = app - t * apq;
+        aq[q] = aqq + t * apq;
+        ap[q] = aq[p] = 0.0;
       }
+  for (int i = 0; i < n; ++i) {
+    double best = 0.0;
+    for (int j = 0; j < n; ++j) {
+      double x = 0.0;
+      for (int r = 0; r < n; ++r) x += Z[(size_t)i * n + r] * V[(size_t)j * n + r];
+      if (std::fabs(x) > std::fabs(best)) best = x;
+    }
+    if (best < 0.0)
+      for (int r = 0; r < n; ++r) Z[(size_t)i * n + r] = -Z[(size_t)i * n + r];
   }
-  w.resize(n);
-  for (int i = 0; i < n; ++i) w[i] = A[(size_t)i * n + i];
 }
 
-// Leading k eigenpairs of the Hermitian M x M matrix G (row-major) by Lanczos
-// with full reorthogonalisation (twice per step), restarted never: the Krylov
-// dimension grows until the k leading Ritz pairs have residual
-// beta_L |s_L,i| <= 1e-12 theta_max, or L = M.  Returns eigenvalues
-// (descending) and eigenvectors (M x k, row-major).
-static void lanczos_top(const std::vector<cd>& G, int M, int k, std::vector<double>& theta,
-                        std::vector<cd>& W) {
-  auto matvec = [&](const std::vector<cd>& x, std::vector<cd>& y) {
-    for (int a = 0; a < M; ++a) {
-      cd s = 0.0;
-      const cd* row = &G[(size_t)a * M];
-      for (int b = 0; b < M; ++b) s += row[b] * x[b];
-      y[a] = s;
-    }
-  };
+// Whether the Krylov dimension L (alpha, beta: the tridiagonal matrix, beta[L-1]
+// to the next vector) holds the k leading Ritz pairs to a residual
+// beta_L |s_L,i| <= 1e-12 theta_max; `full` accepts as it is.  evecs, order: the
+// tridiagonal eigenvectors (rows) and their order by falling eigenvalue.
+static bool ritz_done(const std::vector<double>& alpha, const std::vector<double>& beta, int L, int k,
+                      bool full, std::vector<double>& evals, std::vector<double>& evecs,
+                      std::vector<int>& order) {
+  evals.assign(alpha.begin(), alpha.begin() + L);
+  std::vector<double> e(beta.begin(), beta.begin() + L - 1);
+  tridiagonal_eigh(evals, e, L, evecs);
+  order.resize(L);
+  for (int i = 0; i < L; ++i) order[i] = i;
+  std::sort(order.begin(), order.end(), [&](int x, int y) { return evals[x] > evals[y]; });
+  const double b = beta[L - 1];
+  if (full || b == 0.0) return true;
+  if (L < k) return false;
+  const double tmax = std::fabs(evals[order[0]]);
+  for (int i = 0; i < k; ++i)
+    if (b * std::fabs(evecs[(size_t)order[i] * L + L - 1]) > 1e-12 * tmax) return false;
+  return true;
+}
+
+// The Lanczos start: normal random values, the same every time.
+static std::vector<cd> lanczos_start(int M) {
   std::mt19937_64 rng(12345);
   std::normal_distribution<double> nd(0.0, 1.0);
-  std::vector<std::vector<cd>> Q;
-  std::vector<double> alpha, beta;
-  std::vector<cd> q(M), w(M);
+  std::vector<cd> q(M);
   double nq = 0.0;
   for (int i = 0; i < M; ++i) { q[i] = cd(nd(rng), nd(rng)); nq += std::norm(q[i]); }
   nq = std::sqrt(nq);
   for (auto& v : q) v /= nq;
-  Q.push_back(q);
+  return q;
+}
+
+// Complex vector operations on the parts (std::complex products test for NaN and
+// are not vectorised): x^H y, x^T y, y += a x.
+static cd dotc(const cd* x, const cd* y, int n) {
+  const double *a = (const double*)x, *b = (const double*)y;
+  double re = 0.0, im = 0.0;
+  for (int i = 0; i < n; ++i) {
+    re += a[2 * i] * b[2 * i] + a[2 * i + 1] * b[2 * i + 1];
+    im += a[2 * i] * b[2 * i + 1] - a[2 * i + 1] * b[2 * i];
+  }
+  return cd(re, im);
+}
+static cd dotu(const cd* x, const cd* y, int n) {
+  const double *a = (const double*)x, *b = (const double*)y;
+  double re = 0.0, im = 0.0;
+  for (int i = 0; i < n; ++i) {
+    re += a[2 * i] * b[2 * i] - a[2 * i + 1] * b[2 * i + 1];
+    im += a[2 * i] * b[2 * i + 1] + a[2 * i + 1] * b[2 * i];
+  }
+  return cd(re, im);
+}
+static void axpy(cd s, const cd* x, cd* y, int n) {
+  const double sr = s.real(), si = s.imag(), *a = (const double*)x;
+  double* b = (double*)y;
+  for (int i = 0; i < n; ++i) {
+    b[2 * i] += sr * a[2 * i] - si * a[2 * i + 1];
+    b[2 * i + 1] += sr * a[2 * i + 1] + si * a[2 * i];
+  }
+}
+
+// The k leading Ritz vectors W (M x k, row-major) and values theta from L
+// Lanczos vectors Q (one after the other).
+static void ritz_vectors(const std::vector<cd>& Q, int M, int L, int k,
+                         const std::vector<double>& evals, const std::vector<double>& evecs,
+                         const std::vector<int>& order, std::vector<double>& theta,
+                         std::vector<cd>& W) {
+  const int kk = std::min(k, L);
+  theta.assign(k, 0.0);
+  W.assign((size_t)M * k, cd(0.0));
+  std::vector<cd> w(M);
+  for (int i = 0; i < kk; ++i) {
+    theta[i] = evals[order[i]];
+    std::fill(w.begin(), w.end(), cd(0.0));
+    for (int j = 0; j < L; ++j) {
+      const double s = evecs[(size_t)order[i] * L + j];
+      const double* q = (const double*)&Q[(size_t)j * M];
+      double* o = (double*)w.data();
+      for (int r = 0; r < 2 * M; ++r) o[r] += s * q[r];
+    }
+    for (int r = 0; r < M; ++r) W[(size_t)r * k + i] = w[r];
+  }
+}
+
+// Leading k eigenpairs of the Hermitian M x M matrix G (row-major) by Lanczos
+// with full reorthogonalisation (twice per step), restarted never: the Krylov
+// dimension grows until ritz_done, or L = M.  Returns eigenvalues (descending)
+// and eigenvectors (M x k, row-major; signs: of a definite sign).
+static void lanczos_top(const std::vector<cd>& G, int M, int k, bool signs,
+                        std::vector<double>& theta, std::vector<cd>& W) {
+  std::vector<double> alpha, beta;
+  std::vector<cd> w(M), Q = lanczos_start(M);
+  Q.reserve((size_t)M * std::min(M + 1, 2 * k + 64));
   std::vector<double> evals, evecs;
-  const int Lmax = M;
-  for (int L = 1; L <= Lmax; ++L) {
-    matvec(Q[L - 1], w);
-    double a = 0.0;
-    for (int i = 0; i < M; ++i) a += (std::conj(Q[L - 1][i]) * w[i]).real();
-    alpha.push_back(a);
+  std::vector<int> order;
+  for (int L = 1; L <= M; ++L) {
+    const cd* q = &Q[(size_t)(L - 1) * M];
+    for (int a = 0; a < M; ++a) w[a] = dotu(&G[(size_t)a * M], q, M);
+    alpha.push_back(dotc(q, w.data(), M).real());
     for (int pass = 0; pass < 2; ++pass)
       for (int j = 0; j < L; ++j) {
-        cd c = 0.0;
-        for (int i = 0; i < M; ++i) c += std::conj(Q[j][i]) * w[i];
-        for (int i = 0; i < M; ++i) w[i] -= c * Q[j][i];
+        const cd* qj = &Q[(size_t)j * M];
+        axpy(-dotc(qj, w.data(), M), qj, w.data(), M);
       }
-    double b = 0.0;
-    for (int i = 0; i < M; ++i) b += std::norm(w[i]);
-    b = std::sqrt(b);
-    const bool full = (L == Lmax);
-    const bool check = full || (L >= 2 * k + 10 && (L % 10 == 0)) || b == 0.0;
-    if (check) {
-      std::vector<double> T((size_t)L * L, 0.0);
-      for (int i = 0; i < L; ++i) {
-        T[(size_t)i * L + i] = alpha[i];
-        if (i + 1 < L) T[(size_t)i * L + i + 1] = T[(size_t)(i + 1) * L + i] = beta[i];
-      }
-      jacobi_eigh(T, L, evals, evecs);
-      std::vector<int> order(L);
-      for (int i = 0; i < L; ++i) order[i] = i;
-      std::sort(order.begin(), order.end(), [&](int x, int y) { return evals[x] > evals[y]; });
-      bool conv = full || b == 0.0;
-      if (!conv && L >= k) {
-        conv = true;
-        const double tmax = std::fabs(evals[order[0]]);
-        for (int i = 0; i < k; ++i)
-          if (b * std::fabs(evecs[(size_t)(L - 1) * L + order[i]]) > 1e-12 * tmax) conv = false;
-      }
-      if (conv) {
-        const int kk = std::min(k, L);
-        theta.assign(k, 0.0);
-        W.assign((size_t)M * k, cd(0.0));
-        for (int i = 0; i < kk; ++i) {
-          theta[i] = evals[order[i]];
-          for (int j = 0; j < L; ++j) {
-            const double s = evecs[(size_t)j * L + order[i]];
-            for (int r = 0; r < M; ++r) W[(size_t)r * k + i] += s * Q[j][r];
-          }
-        }
+    const double b = std::sqrt(dotc(w.data(), w.data(), M).real());
+    beta.push_back(b);
+    const bool full = (L == M);
+    if (full || (L >= 2 * k + 10 && (L % 10 == 0)) || b == 0.0) {
+      if (ritz_done(alpha, beta, L, k, full, evals, evecs, order)) {
+        if (signs) jacobi_signs(alpha, beta, L, evecs);
+        ritz_vectors(Q, M, L, k, evals, evecs, order, theta, W);
         return;
       }
     }
-    beta.push_back(b);
-    for (int i = 0; i < M; ++i) q[i] = w[i] / b;
-    Q.push_back(q);
+    for (int i = 0; i < M; ++i) Q.push_back(w[i] / b);
   }
+}
+
+// The same iteration on a device matrix G, six small kernels a step; the host
+// looks at the tridiagonal matrix every ten steps.  For 1000 snapshots the host
+// iteration took 40 ms (a product with G, 16 MB, in each of 50 steps) after a
+// 4 ms copy of G; 1.2 ms here.
+static dd_status lanczos_device(const double2* G, int M, int k, std::vector<double>& theta,
+                                std::vector<cd>& W, hipStream_t stream) {
+  DevBuf bQ, bw;
+  int cap = std::min(M, 2 * k + 10 + 40);       // Lanczos vectors that there is room for
+  DD_HIP_CHECK(hipMalloc(&bQ.p, sizeof(double2) * (size_t)(cap + 1) * M));
+  // w, the dot products, then alpha and beta
+  DD_HIP_CHECK(hipMalloc(&bw.p, sizeof(double2) * 2 * (size_t)M + sizeof(double) * 2 * (size_t)M));
+  double2 *Q = bQ.as<double2>(), *w = bw.as<double2>(), *c = w + M;
+  double *da = (double*)(c + M), *db = da + M;
+  const std::vector<cd> q0 = lanczos_start(M);
+  DD_HIP_CHECK(hipMemcpyAsync(Q, q0.data(), sizeof(double2) * M, hipMemcpyHostToDevice, stream));
+  DD_HIP_CHECK(hipStreamSynchronize(stream));
+  std::vector<double> alpha, beta, evals, evecs;
+  std::vector<int> order;
+  const int nu = (M + 63) / 64;
+  for (int L = 1; L <= M; ++L) {
+    if (L > cap) {
+      DevBuf more;
+      const int c2 = std::min(M, 2 * cap);
+      DD_HIP_CHECK(hipMalloc(&more.p, sizeof(double2) * (size_t)(c2 + 1) * M));
+      DD_HIP_CHECK(hipMemcpyAsync(more.p, Q, sizeof(double2) * (size_t)(cap + 1) * M,
+                                  hipMemcpyDeviceToDevice, stream));
+      DD_HIP_CHECK(hipStreamSynchronize(stream));
+      std::swap(more.p, bQ.p);
+      Q = bQ.as<double2>();
+      cap = c2;
+    }
+    k_lz_matvec<<<M, 256, 0, stream>>>(G, M, Q + (size_t)(L - 1) * M, w);
+    for (int pass = 0; pass < 2; ++pass) {
+      k_lz_dots<<<L, 256, 0, stream>>>(Q, M, w, c, pass == 0 ? da + L - 1 : nullptr);
+      k_lz_update<<<nu, 256, 0, stream>>>(Q, M, L, c, w);
+    }
+    k_lz_next<<<1, 256, 0, stream>>>(w, M, db + L - 1, Q + (size_t)L * M);
+    const bool full = (L == M);
+    if (!full && !(L >= 2 * k + 10 && L % 10 == 0)) continue;
+    DD_HIP_CHECK(hipGetLastError());
+    alpha.resize(L);
+    beta.resize(L);
+    DD_HIP_CHECK(hipMemcpyAsync(alpha.data(), da, sizeof(double) * L, hipMemcpyDeviceToHost, stream));
+    DD_HIP_CHECK(hipMemcpyAsync(beta.data(), db, sizeof(double) * L, hipMemcpyDeviceToHost, stream));
+    DD_HIP_CHECK(hipStreamSynchronize(stream));
+    // an invariant space was met on the way: the vectors past it are zero
+    int n = L;
+    for (int i = 0; i < L; ++i)
+      if (beta[i] == 0.0) { n = i + 1; break; }
+    if (!ritz_done(alpha, beta, n, k, full && n == L, evals, evecs, order)) continue;
+    std::vector<cd> hQ((size_t)n * M);
+    DD_HIP_CHECK(hipMemcpyAsync(hQ.data(), Q, sizeof(cd) * hQ.size(), hipMemcpyDeviceToHost, stream));
+    DD_HIP_CHECK(hipStreamSynchronize(stream));
+    jacobi_signs(alpha, beta, n, evecs);
+    ritz_vectors(hQ, M, n, k, evals, evecs, order, theta, W);
+    return DD_OK;
+  }
+  return DD_OK;
 }
 
 // ------------------------------------------------------------------ API ----
@@ -331,25 +673,54 @@ dd_status gram_host(const float2* V, int k, int D, const double2* f, std::vector
   return DD_OK;
 }
 
-// G_ab = <F_a, F_b> (S x S, FP64) of S device rows of D complex64 values,
-// through the tiled Gram kernel.
-static dd_status gram_rows(const float2* F, int S, int D, std::vector<cd>& G, hipStream_t stream) {
-  const int nta = (S + PT - 1) / PT;
-  const int ntiles = nta * (nta + 1) / 2;
-  int nslices = std::max(1, std::min(256, 4096 / std::max(1, ntiles)));
-  nslices = std::min(nslices, std::max(1, D / PE));
-  DevBuf bpart, bG;
-  DD_HIP_CHECK(hipMalloc(&bpart.p, sizeof(double2) * nslices * nta * nta * PT * PT));
-  DD_HIP_CHECK(hipMalloc(&bG.p, sizeof(double2) * S * S));
-  double2 *part = bpart.as<double2>(), *dG = bG.as<double2>();
-  k_pca_gram<<<dim3(nta, nta, nslices), 256, 0, stream>>>(F, S, D, nslices, part);
-  k_pca_gram_reduce<<<dim3((S + 255) / 256, S), 256, 0, stream>>>(part, S, nta, nslices, dG);
+// G_ab = <F_a, F_b> (M x M, FP64) of M device rows of D complex64 values, and
+// whether all of it is finite.  Tiles of 64 x 64 from 49 rows on (below, half of
+// one would be padding), the elements in as many slices (of 2048 workgroups at
+// most) as leave the last round of resident workgroups, three a compute unit,
+// fullest.
+static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, bool* finite,
+                             hipStream_t stream) {
+  const int tile = M > 48 ? 64 : 32;
+  const int nta = (M + tile - 1) / tile, ntiles = nta * (nta + 1) / 2;
+  int dev = 0, ncu = 256;
+  DD_HIP_CHECK(hipGetDevice(&dev));
+  DD_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+  const int most = std::min(std::max(1, std::min(256, 2048 / ntiles)), (D + 4 * PE - 1) / (4 * PE));
+  int nslices = 1;
+  for (int n = 2; n <= most; ++n) {
+    const auto rounds = [&](int x) { return (ntiles * (long long)x + 3 * ncu - 1) / (3 * ncu); };
+    if (rounds(n) * nslices < rounds(nslices) * n) nslices = n;   // rounds / slices falls
+  }
+  const int per = ((D + nslices - 1) / nslices + PE - 1) / PE * PE;
+  nslices = (D + per - 1) / per;
+  DevBuf bpart;
+  DD_HIP_CHECK(hipMalloc(&bpart.p, sizeof(double2) * (size_t)nslices * ntiles * tile * tile));
+  DD_HIP_CHECK(hipMalloc(&bG.p, sizeof(double2) * M * M + sizeof(int)));
+  double2 *part = bpart.as<double2>(), *G = bG.as<double2>();
+  int* bad = (int*)(G + (size_t)M * M);
+  DD_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), stream));
+  if (tile == 64) k_pca_gram<2><<<dim3(ntiles, nslices), 256, 0, stream>>>(F, M, D, per, part);
+  else k_pca_gram<1><<<dim3(ntiles, nslices), 256, 0, stream>>>(F, M, D, per, part);
+  k_pca_gram_reduce<<<dim3(ntiles, tile * tile / 64), 256, 0, stream>>>(part, M, tile, nslices, G,
+                                                                        bad);
   DD_HIP_CHECK(hipGetLastError());
-  std::vector<double2> h((size_t)S * S);
-  DD_HIP_CHECK(hipMemcpyAsync(h.data(), dG, sizeof(double2) * S * S, hipMemcpyDeviceToHost, stream));
+  int hbad = 0;
+  DD_HIP_CHECK(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, stream));
   DD_HIP_CHECK(hipStreamSynchronize(stream));
-  G.resize((size_t)S * S);
-  for (size_t i = 0; i < G.size(); ++i) G[i] = cd(h[i].x, h[i].y);
+  *finite = hbad == 0;
+  return DD_OK;
+}
+
+// The same on the host.
+static dd_status gram_rows(const float2* F, int M, int D, std::vector<cd>& G, bool* finite,
+                           hipStream_t stream) {
+  DevBuf bG;
+  dd_status rc = gram_device(F, M, D, bG, finite, stream);
+  if (rc != DD_OK) return rc;
+  G.resize((size_t)M * M);
+  static_assert(sizeof(cd) == sizeof(double2), "complex layout");
+  DD_HIP_CHECK(hipMemcpyAsync(G.data(), bG.p, sizeof(cd) * G.size(), hipMemcpyDeviceToHost, stream));
+  DD_HIP_CHECK(hipStreamSynchronize(stream));
   return DD_OK;
 }
 
@@ -388,30 +759,26 @@ extern "C" dd_status pca_build(const void* Sv, int M, int D, int k, void* Uv, do
   }
   const float2* S = (const float2*)Sv;
   float2* U = (float2*)Uv;
-  const int nta = (M + PT - 1) / PT;
-  const int ntiles = nta * (nta + 1) / 2;
-  int nslices = std::max(1, std::min(256, 4096 / std::max(1, ntiles)));
-  nslices = std::min(nslices, std::max(1, D / PE));
-  DevBuf bpart, bG, bcoef, bT;
-  DD_HIP_CHECK(hipMalloc(&bpart.p, sizeof(double2) * nslices * nta * nta * PT * PT));
-  DD_HIP_CHECK(hipMalloc(&bG.p, sizeof(double2) * M * M));
-  double2 *part = bpart.as<double2>(), *G = bG.as<double2>();
-  k_pca_gram<<<dim3(nta, nta, nslices), 256, 0, stream>>>(S, M, D, nslices, part);
-  k_pca_gram_reduce<<<dim3((M + 255) / 256, M), 256, 0, stream>>>(part, M, nta, nslices, G);
-  DD_HIP_CHECK(hipGetLastError());
-  std::vector<cd> hG((size_t)M * M);
-  DD_HIP_CHECK(hipMemcpyAsync(hG.data(), G, sizeof(double2) * M * M, hipMemcpyDeviceToHost, stream));
-  DD_HIP_CHECK(hipStreamSynchronize(stream));
-  for (const cd& v : hG)
-    if (!std::isfinite(v.real()) || !std::isfinite(v.imag())) {
-      dd_set_error("pca_build: snapshots contain non-finite values");
-      return DD_ENONFINITE;
-    }
   // G_ab = <s_a, s_b>; with X = [s_1 .. s_M] (D x M), G = X^H X and the left
   // singular vectors are u_i = X w_i / sigma_i for X^H X w_i = sigma_i^2 w_i.
+  DevBuf bG, bcoef, bT;
+  bool finite = true;
   std::vector<double> theta;
   std::vector<cd> W;
-  lanczos_top(hG, M, k, theta, W);
+  dd_status rc = DD_OK;
+  if (M >= 128) {
+    rc = gram_device(S, M, D, bG, &finite, stream);
+    if (rc == DD_OK && finite) rc = lanczos_device(bG.as<double2>(), M, k, theta, W, stream);
+  } else {
+    std::vector<cd> hG;
+    rc = gram_rows(S, M, D, hG, &finite, stream);
+    if (rc == DD_OK && finite) lanczos_top(hG, M, k, true, theta, W);
+  }
+  if (rc != DD_OK) return rc;
+  if (!finite) {
+    dd_set_error("pca_build: snapshots contain non-finite values");
+    return DD_ENONFINITE;
+  }
   std::vector<double2> hc((size_t)M * k);
   for (int i = 0; i < k; ++i) {
     const double s = std::sqrt(std::max(theta[i], 0.0));
@@ -428,12 +795,12 @@ extern "C" dd_status pca_build(const void* Sv, int M, int D, int k, void* Uv, do
   DD_HIP_CHECK(hipMalloc(&bcoef.p, sizeof(double2) * M * k));
   double2* coef = bcoef.as<double2>();
   DD_HIP_CHECK(hipMemcpyAsync(coef, hc.data(), sizeof(double2) * M * k, hipMemcpyHostToDevice, stream));
-  k_pca_combine<<<dim3((D + 255) / 256, (k + 15) / 16), 256, 0, stream>>>(S, M, D, coef, k, U);
+  k_field_combine<<<dim3((D + 127) / 128, (k + 31) / 32), 256, 0, stream>>>(S, M, D, coef, k, 0, 0, U);
   DD_HIP_CHECK(hipGetLastError());
   DD_HIP_CHECK(hipStreamSynchronize(stream));
   // one Cholesky QR pass restores orthonormality lost to FP32 storage
   std::vector<cd> Gu, L, T;
-  dd_status rc = gram_host(U, k, D, nullptr, Gu, stream);
+  rc = gram_host(U, k, D, nullptr, Gu, stream);
   if (rc != DD_OK) return rc;
   if (!chol_inv(Gu, k + 1, k, L, T)) {
     dd_set_error("pca_build: basis Gram matrix not positive definite");
@@ -448,33 +815,6 @@ extern "C" dd_status pca_build(const void* Sv, int M, int D, int k, void* Uv, do
   DD_HIP_CHECK(hipGetLastError());
   DD_HIP_CHECK(hipStreamSynchronize(stream));
   return DD_OK;
-}
-
-// T[s][j] = sum_m coef[s][m][j] F[m] for the S steps of one trajectory:
-// coef is [S][S][k] (FP64, zero outside each step's window), one thread per
-// element, grid.y = (step, group of 16 outputs).
-__global__ __launch_bounds__(256) void k_local_combine(const float2* __restrict__ F, int S, int D,
-                                                       const double2* __restrict__ coef, int k,
-                                                       float2* __restrict__ T) {
-  const int e = blockIdx.x * 256 + threadIdx.x;
-  const int s = blockIdx.y / ((k + 15) / 16), o0 = (blockIdx.y % ((k + 15) / 16)) * 16;
-  if (e >= D) return;
-  double2 acc[16];
-#pragma unroll
-  for (int o = 0; o < 16; ++o) acc[o] = make_double2(0.0, 0.0);
-  for (int m = 0; m < S; ++m) {
-    const float2 f = F[(size_t)m * D + e];
-#pragma unroll
-    for (int o = 0; o < 16; ++o) {
-      if (o0 + o < k) {
-        const double2 c = coef[((size_t)s * S + m) * k + o0 + o];
-        acc[o].x += c.x * f.x - c.y * f.y;
-        acc[o].y += c.x * f.y + c.y * f.x;
-      }
-    }
-  }
-  for (int o = 0; o < 16 && o0 + o < k; ++o)
-    T[((size_t)s * k + o0 + o) * D + e] = make_float2((float)acc[o].x, (float)acc[o].y);
 }
 
 // Training targets of the convolutional predictor from one trajectory's
@@ -493,7 +833,8 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
   const float2* F = (const float2*)Fv;
   // trajectory Gram matrix of the normalised fields (normalisation applied here)
   std::vector<cd> G0;
-  dd_status rc = gram_rows(F, S, D, G0, stream);
+  bool finite = true;
+  dd_status rc = gram_rows(F, S, D, G0, &finite, stream);
   if (rc != DD_OK) return rc;
   std::vector<double> nrm(S);
   for (int a = 0; a < S; ++a) nrm[a] = std::sqrt(std::max(G0[(size_t)a * S + a].real(), 1e-300));
@@ -507,7 +848,7 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
     const int kk = std::min(k, M);
     std::vector<double> theta;
     std::vector<cd> W;
-    lanczos_top(G, M, kk, theta, W);
+    lanczos_top(G, M, kk, false, theta, W);   // phase-free
     for (int j = 0; j < kk; ++j) {
       if (!(theta[j] > 1e-24 * std::max(theta[0], 1e-300))) continue;
       const double sg = std::sqrt(theta[j]);
@@ -517,7 +858,7 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
       for (int m = 0; m < M; ++m) {
         // target_j = sum_m (W_mj / sigma_j) c f_m / ||f_m||  (fields normalised)
         const cd v = W[(size_t)m * kk + j] / sg * c / nrm[lo + m];
-        hc[((size_t)s * S + lo + m) * k + j] = make_double2(v.real(), v.imag());
+        hc[((size_t)(lo + m) * S + s) * k + j] = make_double2(v.real(), v.imag());
       }
     }
   }
@@ -525,8 +866,9 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
   DD_HIP_CHECK(hipMalloc(&bcoef.p, sizeof(double2) * hc.size()));
   double2* coef = bcoef.as<double2>();
   DD_HIP_CHECK(hipMemcpyAsync(coef, hc.data(), sizeof(double2) * hc.size(), hipMemcpyHostToDevice, stream));
-  k_local_combine<<<dim3((D + 255) / 256, S * ((k + 15) / 16)), 256, 0, stream>>>(F, S, D, coef, k,
-                                                                                  (float2*)Tv);
+  // a field that is not finite makes every target so, as its zero coefficients do
+  k_field_combine<<<dim3((D + 127) / 128, (S * k + 31) / 32), 256, 0, stream>>>(
+      F, S, D, coef, S * k, finite ? k : 0, std::min(window, S), (float2*)Tv);
   DD_HIP_CHECK(hipGetLastError());
   DD_HIP_CHECK(hipStreamSynchronize(stream));
   return DD_OK;

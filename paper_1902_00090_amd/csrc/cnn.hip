@@ -163,132 +163,171 @@ __device__ __forceinline__ void store_fields(float* outf, int kf, int D, int b, 
 // times.  Wave w owns output row w of the tile (four pixel tiles of 16).  The
 // weights come from the L2-resident packed copy.  Operand layouts are those
 // described at GemmArgs.
+//
+// Addresses cost the vector units next to nothing.  A thread stages one
+// (column, 16-byte quarter) of every patch row: the row's offset is scalar, the
+// column's is fixed, and loads and stores go through buffer descriptors whose
+// range check is the zero padding and the ragged edge.  A staged pixel is 64
+// bytes; quarter q of pixel p sits at q ^ ((p >> 1) & 3), which spreads the 16
+// pixels of an operand read over the banks (80-byte rows took half as long
+// again: 4.2 against 2.8 clocks a read).  Rows of 72 pixels keep that pattern
+// the same for every row and tile, so that taps differ by constants.
 #define CT_TH 4
 #define CT_TW 64
 #define CT_PH (CT_TH + 2)
-#define CT_PW (CT_TW + 2)
-#define CT_PS 40   // bf16 per staged pixel: 32 channels + 8 of padding (80-byte stride)
+#define CT_PW 72                      // staged row: 66 pixels used, a multiple of 8
+#define CT_OUT 0x80000000u            // an offset past every descriptor's range
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t cnn_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0,
+                                           (int)(bytes < 0x7fffffffu ? bytes : 0x7fffffffu),
+                                           0x00020000);
+}
+__device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, v, s, 0);
+}
+
 template <int MT, bool BWD = false, bool WL = false>
 __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 patch[CT_PH * CT_PW * CT_PS];
+  __shared__ __attribute__((aligned(16))) unsigned char patch[CT_PH * CT_PW * 64];
   // WL: the chunk's weights of all nine taps are staged in LDS with the patch
-  // ([tap][row][40], 80-byte rows), so the tap loop waits on no global load
-  __shared__ __attribute__((aligned(16))) bf16 wl[WL ? 9 * 16 * MT * CT_PS : 8];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // ([tap][row] of 64 bytes, quarters placed as the pixels'), so the tap loop
+  // waits on no global load
+  __shared__ __attribute__((aligned(16))) unsigned char wl[WL ? 9 * 16 * MT * 64 : 16];
+  const int t0 = threadIdx.x, lane = t0 & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t0 >> 6);
   const int x0 = blockIdx.x * CT_TW, y0 = blockIdx.y * CT_TH, b = blockIdx.z;
   const int Hq = a.Hq, Wq = a.Wq;
-  const bool up = (a.mode == MAP_UP);
+  const int sh = (a.mode == MAP_UP) ? 1 : 0;             // source pixel = conv-input pixel >> sh
   f32x4 acc[MT][4];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kq = 8 * (lane >> 4);
-  // weight operand of tap t of the chunk at c0 (rows i * 16 + lane % 16)
-  auto wload = [&](int t, int c0, bf16x8 (&av)[MT]) {
-    const bf16* wt = a.W + (size_t)(BWD ? 8 - t : t) * a.M * a.Ksrc + c0 + kq;
+  const int pl = lane & 15, kg = lane >> 4;
+  // patch rows y0 - 1 .. y0 + 4 of the conv-input grid; the descriptor starts at
+  // the first source row among them
+  const unsigned px2 = 2u * a.Ksrc, row2 = px2 * a.Ws;   // bytes of a source pixel, row
+  const int sy0 = max(y0 - 1, 0) >> sh;
+  const __amdgpu_buffer_rsrc_t rS =
+      cnn_rsrc((const char*)a.src + ((size_t)b * a.Hs + sy0) * row2, (size_t)(a.Hs - sy0) * row2);
+  const int ux = x0 + (t0 >> 2) - 1;                      // this thread's column of every row
+  const unsigned vcol = (ux >= 0 && ux < Wq) ? (unsigned)(ux >> sh) * px2 + 16u * (t0 & 3) : CT_OUT;
+  // columns 64 and 65: eight units a row, threads 0 .. 47
+  const int er = t0 >> 3, ex = 64 + ((t0 >> 2) & 1), euy = y0 - 1 + er, eux = x0 + ex - 1;
+  const unsigned vedge =
+      (er < CT_PH && euy >= 0 && euy < Hq && eux < Wq)
+          ? (unsigned)((euy >> sh) - sy0) * row2 + (unsigned)(eux >> sh) * px2 + 16u * (t0 & 3)
+          : CT_OUT;
+  auto place = [](int pix, int q) { return pix * 64 + ((q ^ ((pix >> 1) & 3)) << 4); };
+  const int lcol = place(t0 >> 2, t0 & 3), ledge = place(er * CT_PW + ex, t0 & 3);
+  // operands: 16 pixels at dx = 0, 1, 2 (rows and pixel tiles are constants away), 16 weight rows
+  int lb[3];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) av[i] = load8(wt + (size_t)(i * 16 + (lane & 15)) * a.Ksrc);
+  for (int dx = 0; dx < 3; ++dx) lb[dx] = place(wave * CT_PW + pl + dx, kg);
+  const int lw = place(pl, kg);
+  const __amdgpu_buffer_rsrc_t rW = cnn_rsrc(a.W, (size_t)9 * a.M * px2);
+  const unsigned tap2 = (unsigned)a.M * px2;              // bytes of a tap's weights
+  const unsigned vw = (unsigned)pl * px2 + 16u * kg;
+  // weight operand of tap t of the chunk at byte c2 (rows i * 16 + lane % 16)
+  auto wload = [&](int t, unsigned c2, bf16x8 (&av)[MT]) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+      av[i] = __builtin_bit_cast(
+          bf16x8, buf_load16(rW, vw, (BWD ? 8 - t : t) * tap2 + 16u * i * px2 + c2));
   };
-  constexpr int NSTG = (CT_PH * CT_PW * 4 + 255) / 256;   // staging loads per thread
-  constexpr int NWI = 9 * 16 * MT * 4, NWS = WL ? (NWI + 255) / 256 : 1;   // weight items
-  for (int c0 = 0; c0 < a.Ksrc; c0 += 32) {
-    // all of this thread's patch loads are issued before the first LDS store,
-    // and tap 0's weights are in flight meanwhile
-    bf16x8 wcur[MT], wnext[MT];
+  // WL: thread t0 stages item (tap, row, quarter) t0 + 256 it
+  constexpr int NWI = 9 * 16 * MT * 4, NWS = WL ? (NWI + 255) / 256 : 1;
+  constexpr int UT = 16 * MT * 4;                         // items of a tap: 128, 256 or 512
+  const unsigned vwl = (unsigned)((t0 % UT) >> 2) * px2 + 16u * (t0 & 3);
+  for (unsigned c2 = 0; c2 < px2; c2 += 64) {
+    // all of this thread's loads are issued before the first LDS store; without
+    // WL tap 0's weights are in flight meanwhile
+    bf16x8 wc[2][MT];
     u32x4 wv[NWS];
     if (WL) {
 #pragma unroll
       for (int it = 0; it < NWS; ++it) {
-        const int u = threadIdx.x + 256 * it;   // (tap, row, quarter)
-        const int tq = u / (16 * MT * 4), rem = u - tq * 16 * MT * 4;
-        wv[it] = u32x4{0u, 0u, 0u, 0u};
-        if (u < NWI)
-          wv[it] = *(const u32x4*)(a.W + ((size_t)(BWD ? 8 - tq : tq) * a.M + (rem >> 2)) * a.Ksrc +
-                                   c0 + 8 * (rem & 3));
+        const int tap = (UT >= 256) ? it / (UT / 256) : it * (256 / UT) + t0 / UT;
+        const unsigned rows = (UT > 256) ? (unsigned)(it % (UT / 256)) * 64u * px2 : 0u;
+        const unsigned at = (unsigned)(BWD ? 8 - tap : tap) * tap2 + rows + c2;
+        if constexpr (UT >= 256) wv[it] = buf_load16(rW, vwl, at);
+        else wv[it] = buf_load16(rW, tap < 9 ? vwl + at : CT_OUT, 0);
       }
     } else {
-      wload(0, c0, wcur);
+      wload(0, c2, wc[0]);
     }
-    u32x4 sv[NSTG];
+    u32x4 sv[CT_PH], se;
 #pragma unroll
-    for (int it = 0; it < NSTG; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      const int pix = u >> 2, q = u & 3;
-      const int py = pix / CT_PW, px = pix - py * CT_PW;
-      const int uy = y0 + py - 1, ux = x0 + px - 1;   // conv-input grid (= output grid)
-      sv[it] = u32x4{0u, 0u, 0u, 0u};
-      if (u < CT_PH * CT_PW * 4 && uy >= 0 && uy < Hq && ux >= 0 && ux < Wq) {
-        const int sy = up ? (uy >> 1) : uy, sx = up ? (ux >> 1) : ux;
-        sv[it] = *(const u32x4*)(a.src + ((size_t)(b * a.Hs + sy) * a.Ws + sx) * a.Ksrc + c0 + 8 * q);
-      }
+    for (int r = 0; r < CT_PH; ++r) {
+      const int uy = y0 - 1 + r;
+      const bool in = uy >= 0 && uy < Hq;
+      sv[r] = buf_load16(rS, in ? vcol : CT_OUT, in ? (unsigned)((uy >> sh) - sy0) * row2 + c2 : 0u);
     }
+    se = buf_load16(rS, vedge, c2);
+    if (c2 > 0) __syncthreads();                          // the chunk before has been read
 #pragma unroll
-    for (int it = 0; it < NSTG; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      if (u < CT_PH * CT_PW * 4) *(u32x4*)(patch + (u >> 2) * CT_PS + 8 * (u & 3)) = sv[it];
-    }
+    for (int r = 0; r < CT_PH; ++r) *(u32x4*)(patch + lcol + r * CT_PW * 64) = sv[r];
+    if (er < CT_PH) *(u32x4*)(patch + ledge) = se;
     if (WL) {
 #pragma unroll
-      for (int it = 0; it < NWS; ++it) {
-        const int u = threadIdx.x + 256 * it;
-        if (u < NWI) *(u32x4*)(wl + (u >> 2) * CT_PS + 8 * (u & 3)) = wv[it];
-      }
+      for (int it = 0; it < NWS; ++it)
+        if (t0 + 256 * it < NWI) *(u32x4*)(wl + place(t0 >> 2, t0 & 3) + it * 64 * 64) = wv[it];
     }
     __syncthreads();
     // taps: the next tap's weights are loaded while this tap's MFMAs run
-#pragma unroll 1
+#pragma unroll
     for (int t = 0; t < 9; ++t) {
+      bf16x8(&w)[MT] = wc[WL ? 0 : t & 1];
       if (WL) {
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
-          wcur[i] = *(const bf16x8*)(wl + ((t * 16 * MT) + i * 16 + (lane & 15)) * CT_PS + kq);
+        for (int i = 0; i < MT; ++i) w[i] = *(const bf16x8*)(wl + lw + (t * MT + i) * 16 * 64);
       } else if (t + 1 < 9) {
-        wload(t + 1, c0, wnext);
+        wload(t + 1, c2, wc[(t + 1) & 1]);
       }
-      const int dy = t / 3, dx = t - 3 * (t / 3);
       bf16x8 bv[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
-        bv[j] = *(const bf16x8*)(patch + ((wave + dy) * CT_PW + 16 * j + (lane & 15) + dx) * CT_PS + kq);
+        bv[j] = *(const bf16x8*)(patch + lb[t % 3] + ((t / 3) * CT_PW + 16 * j) * 64);
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wcur[i], bv[j], acc[i][j], 0, 0, 0);
-      if (!WL && t + 1 < 9) {
-#pragma unroll
-        for (int i = 0; i < MT; ++i) wcur[i] = wnext[i];
-      }
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], bv[j], acc[i][j], 0, 0, 0);
     }
-    __syncthreads();
   }
   const int y = y0 + wave;
   if (y >= Hq) return;
   // epilogue operands (bias, or the ReLU mask of the layer input) are all
   // loaded before any result is stored
-  float4 bias4[MT];
-  u32x2 mk[MT][4];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int r0 = i * 16 + 4 * (lane >> 4);
-    if (!BWD) bias4[i] = *(const float4*)(a.bias + r0);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int x = x0 + 16 * j + (lane & 15);
-      mk[i][j] = u32x2{0u, 0u};
-      if (BWD && x < Wq)
-        mk[i][j] = *(const u32x2*)(a.mask + (((size_t)b * Hq + y) * Wq + x) * a.M + r0);
-    }
-  }
+  const size_t rowp = ((size_t)b * Hq + y) * Wq;          // the row's first pixel
+  const unsigned m2 = 2u * a.M, orow = m2 * Wq;
+  unsigned vo[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int x = x0 + 16 * j + (lane & 15);
-    if (x >= Wq) continue;
-    const size_t p = ((size_t)b * Hq + y) * Wq + x;
+    const int x = x0 + 16 * j + pl;
+    vo[j] = x < Wq ? (unsigned)x * m2 + 8u * kg : CT_OUT;
+  }
+  float4 bias4[MT];
+  u32x2 mk[MT][4];
+  const __amdgpu_buffer_rsrc_t rM = cnn_rsrc(BWD ? (const char*)a.mask + rowp * m2 : nullptr, BWD ? orow : 0);
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    if (!BWD) bias4[i] = *(const float4*)(a.bias + i * 16 + 4 * kg);
+    if (BWD)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        mk[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rM, vo[j], 32 * i, 0);
+  }
+  const bool fields = !BWD && a.outf;
+  const __amdgpu_buffer_rsrc_t rO =
+      cnn_rsrc(fields ? nullptr : (const char*)a.out + rowp * m2, fields ? 0 : orow);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int x = x0 + 16 * j + pl;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      const int r0 = i * 16 + 4 * (lane >> 4);
+      const int r0 = i * 16 + 4 * kg;
       float v[4];
       if (BWD) {
         const bf16x4 m4 = __builtin_bit_cast(bf16x4, mk[i][j]);
@@ -302,13 +341,13 @@ __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
           if (a.relu) v[q] = fmaxf(v[q], 0.f);
         }
       }
-      if (!BWD && a.outf) {
-        store_fields(a.outf, a.nreal / 2, Hq * Wq, b, y * Wq + x, r0, v);
+      if (fields) {
+        if (x < Wq) store_fields(a.outf, a.nreal / 2, Hq * Wq, b, y * Wq + x, r0, v);
       } else {
-        bf16 h[4];
+        bf16x4 h;
 #pragma unroll
         for (int q = 0; q < 4; ++q) h[q] = (bf16)v[q];
-        *(u32x2*)(a.out + p * a.M + r0) = __builtin_bit_cast(u32x2, h);
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), rO, vo[j], 32 * i, 0);
       }
     }
   }
@@ -327,6 +366,7 @@ __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
 // and applies the taps from there; wave w owns output row y0 + w (two pixel
 // tiles of 16).  Loads are issued as in k_conv_tile, and WL stages the
 // weights in LDS as there; operand layouts are those described at GemmArgs.
+#define CT_PS 40   // bf16 per staged pixel: 32 channels + 8 of padding (80-byte stride)
 #define CS_TH 4
 #define CS_TW 32
 template <int MT, int KS, bool BWD, bool WL = false>

@@ -155,14 +155,15 @@ __device__ __forceinline__ void store_fields(float* outf, int kf, int D, int b, 
 // upsample (MAP_UP), and (BWD) the backward-data pass of the plain stride-1
 // layers: the gradient at a layer-input pixel gathers dz through the kernel
 // rotated by 180 degrees (tap t reads weight tap 8 - t of the transposed
-// copy), masked by the ReLU of the layer input.  A workgroup computes a 4 x 64 tile of output pixels of
-// one image for all M = 16 MT output channels.  For every 32 input channels
-// the 6 x 66 input patch (halo included; zero padding and the upsampling are
-// resolved while staging) is written once to LDS and read there by all nine
-// taps, so each source value is fetched from memory once instead of nine
-// times.  Wave w owns output row w of the tile (four pixel tiles of 16).  The
-// weights come from the L2-resident packed copy.  Operand layouts are those
-// described at GemmArgs.
+// copy), masked by the ReLU of the layer input.  A workgroup of TH waves computes
+// a TH x 64 tile of output pixels of one image for 16 MT of the M result
+// channels (blockIdx.z: image, then channel group).  For every 32 input channels
+// the (TH + 2) x 66 input patch (halo included; zero padding and the upsampling
+// are resolved while staging) and the weights of all nine taps are written once
+// to LDS and read there by all taps, so each source value is fetched from memory
+// once instead of nine times and the tap loop waits on no global load.  Wave w
+// owns output row w of the tile (four pixel tiles of 16).  Operand layouts are
+// those described at GemmArgs.
 //
 // Addresses cost the vector units next to nothing.  A thread stages one
 // (column, 16-byte quarter) of every patch row: the row's offset is scalar, the
@@ -172,9 +173,7 @@ __device__ __forceinline__ void store_fields(float* outf, int kf, int D, int b, 
 // pixels of an operand read over the banks (80-byte rows took half as long
 // again: 4.2 against 2.8 clocks a read).  Rows of 72 pixels keep that pattern
 // the same for every row and tile, so that taps differ by constants.
-#define CT_TH 4
 #define CT_TW 64
-#define CT_PH (CT_TH + 2)
 #define CT_PW 72                      // staged row: 66 pixels used, a multiple of 8
 #define CT_OUT 0x80000000u            // an offset past every descriptor's range
 
@@ -186,17 +185,21 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t cnn_rsrc(const void* p, size_t
 __device__ __forceinline__ u32x4 buf_load16(__amdgpu_buffer_rsrc_t r, unsigned v, unsigned s) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, v, s, 0);
 }
+// LDS byte of quarter q of 64-byte item p (a pixel, a weight row)
+__device__ __forceinline__ int cnn_place(int p, int q) {
+  return p * 64 + ((q ^ ((p >> 1) & 3)) << 4);
+}
 
-template <int MT, bool BWD = false, bool WL = false>
-__global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char patch[CT_PH * CT_PW * 64];
-  // WL: the chunk's weights of all nine taps are staged in LDS with the patch
-  // ([tap][row] of 64 bytes, quarters placed as the pixels'), so the tap loop
-  // waits on no global load
-  __shared__ __attribute__((aligned(16))) unsigned char wl[WL ? 9 * 16 * MT * 64 : 16];
+template <int MT, int TH, bool BWD>
+__global__ __launch_bounds__(64 * TH) void k_conv_tile(GemmArgs a) {
+  constexpr int NT = 64 * TH, PH = TH + 2, RP = NT / 256;   // RP patch rows staged at a time
+  __shared__ __attribute__((aligned(16))) unsigned char patch[PH * CT_PW * 64];
+  // the chunk's weights, [tap][row], quarters placed as the pixels'
+  __shared__ __attribute__((aligned(16))) unsigned char wl[9 * 16 * MT * 64];
   const int t0 = threadIdx.x, lane = t0 & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t0 >> 6);
-  const int x0 = blockIdx.x * CT_TW, y0 = blockIdx.y * CT_TH, b = blockIdx.z;
+  const int x0 = blockIdx.x * CT_TW, y0 = blockIdx.y * TH;
+  const int nm = a.M / (16 * MT), b = blockIdx.z / nm, m0 = (blockIdx.z - b * nm) * 16 * MT;
   const int Hq = a.Hq, Wq = a.Wq;
   const int sh = (a.mode == MAP_UP) ? 1 : 0;             // source pixel = conv-input pixel >> sh
   f32x4 acc[MT][4];
@@ -205,87 +208,69 @@ __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int pl = lane & 15, kg = lane >> 4;
-  // patch rows y0 - 1 .. y0 + 4 of the conv-input grid; the descriptor starts at
+  // patch rows y0 - 1 .. y0 + TH of the conv-input grid; the descriptor starts at
   // the first source row among them
   const unsigned px2 = 2u * a.Ksrc, row2 = px2 * a.Ws;   // bytes of a source pixel, row
   const int sy0 = max(y0 - 1, 0) >> sh;
   const __amdgpu_buffer_rsrc_t rS =
       cnn_rsrc((const char*)a.src + ((size_t)b * a.Hs + sy0) * row2, (size_t)(a.Hs - sy0) * row2);
-  const int ux = x0 + (t0 >> 2) - 1;                      // this thread's column of every row
+  // this thread's column of the patch rows tr, tr + RP, ..
+  const int tr = (RP > 1) ? __builtin_amdgcn_readfirstlane(t0 >> 8) : 0, tc = (t0 & 255) >> 2;
+  const int ux = x0 + tc - 1;
   const unsigned vcol = (ux >= 0 && ux < Wq) ? (unsigned)(ux >> sh) * px2 + 16u * (t0 & 3) : CT_OUT;
-  // columns 64 and 65: eight units a row, threads 0 .. 47
+  // columns 64 and 65: eight units a row, threads 0 .. 8 PH - 1
   const int er = t0 >> 3, ex = 64 + ((t0 >> 2) & 1), euy = y0 - 1 + er, eux = x0 + ex - 1;
   const unsigned vedge =
-      (er < CT_PH && euy >= 0 && euy < Hq && eux < Wq)
+      (er < PH && euy >= 0 && euy < Hq && eux < Wq)
           ? (unsigned)((euy >> sh) - sy0) * row2 + (unsigned)(eux >> sh) * px2 + 16u * (t0 & 3)
           : CT_OUT;
-  auto place = [](int pix, int q) { return pix * 64 + ((q ^ ((pix >> 1) & 3)) << 4); };
-  const int lcol = place(t0 >> 2, t0 & 3), ledge = place(er * CT_PW + ex, t0 & 3);
+  const int lcol = cnn_place(tc, t0 & 3), ledge = cnn_place(er * CT_PW + ex, t0 & 3);
   // operands: 16 pixels at dx = 0, 1, 2 (rows and pixel tiles are constants away), 16 weight rows
   int lb[3];
 #pragma unroll
-  for (int dx = 0; dx < 3; ++dx) lb[dx] = place(wave * CT_PW + pl + dx, kg);
-  const int lw = place(pl, kg);
-  const __amdgpu_buffer_rsrc_t rW = cnn_rsrc(a.W, (size_t)9 * a.M * px2);
+  for (int dx = 0; dx < 3; ++dx) lb[dx] = cnn_place(wave * CT_PW + pl + dx, kg);
+  const int lw = cnn_place(pl, kg);
+  // thread t0 stages weight item (tap, row, quarter) t0 + NT it
   const unsigned tap2 = (unsigned)a.M * px2;              // bytes of a tap's weights
-  const unsigned vw = (unsigned)pl * px2 + 16u * kg;
-  // weight operand of tap t of the chunk at byte c2 (rows i * 16 + lane % 16)
-  auto wload = [&](int t, unsigned c2, bf16x8 (&av)[MT]) {
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-      av[i] = __builtin_bit_cast(
-          bf16x8, buf_load16(rW, vw, (BWD ? 8 - t : t) * tap2 + 16u * i * px2 + c2));
-  };
-  // WL: thread t0 stages item (tap, row, quarter) t0 + 256 it
-  constexpr int NWI = 9 * 16 * MT * 4, NWS = WL ? (NWI + 255) / 256 : 1;
+  const __amdgpu_buffer_rsrc_t rW = cnn_rsrc((const char*)a.W + (size_t)m0 * px2,
+                                             (size_t)9 * tap2 - (size_t)m0 * px2);
   constexpr int UT = 16 * MT * 4;                         // items of a tap: 128, 256 or 512
+  constexpr int NWI = 9 * UT, NWS = (NWI + NT - 1) / NT;
   const unsigned vwl = (unsigned)((t0 % UT) >> 2) * px2 + 16u * (t0 & 3);
   for (unsigned c2 = 0; c2 < px2; c2 += 64) {
-    // all of this thread's loads are issued before the first LDS store; without
-    // WL tap 0's weights are in flight meanwhile
-    bf16x8 wc[2][MT];
-    u32x4 wv[NWS];
-    if (WL) {
+    // all of this thread's loads are issued before the first LDS store
+    u32x4 wv[NWS], sv[PH / RP], se;
 #pragma unroll
-      for (int it = 0; it < NWS; ++it) {
-        const int tap = (UT >= 256) ? it / (UT / 256) : it * (256 / UT) + t0 / UT;
-        const unsigned rows = (UT > 256) ? (unsigned)(it % (UT / 256)) * 64u * px2 : 0u;
-        const unsigned at = (unsigned)(BWD ? 8 - tap : tap) * tap2 + rows + c2;
-        if constexpr (UT >= 256) wv[it] = buf_load16(rW, vwl, at);
-        else wv[it] = buf_load16(rW, tap < 9 ? vwl + at : CT_OUT, 0);
+    for (int it = 0; it < NWS; ++it) {
+      if constexpr (UT >= NT) {
+        const int tap = it / (UT / NT);
+        wv[it] = buf_load16(rW, vwl, (unsigned)(BWD ? 8 - tap : tap) * tap2 +
+                                         (unsigned)(it % (UT / NT)) * (NT / 4u) * px2 + c2);
+      } else {
+        const int tap = it * (NT / UT) + t0 / UT;
+        wv[it] = buf_load16(rW, tap < 9 ? vwl + (unsigned)(BWD ? 8 - tap : tap) * tap2 : CT_OUT, c2);
       }
-    } else {
-      wload(0, c2, wc[0]);
     }
-    u32x4 sv[CT_PH], se;
 #pragma unroll
-    for (int r = 0; r < CT_PH; ++r) {
-      const int uy = y0 - 1 + r;
+    for (int r = 0; r < PH / RP; ++r) {
+      const int uy = y0 - 1 + r * RP + tr;
       const bool in = uy >= 0 && uy < Hq;
       sv[r] = buf_load16(rS, in ? vcol : CT_OUT, in ? (unsigned)((uy >> sh) - sy0) * row2 + c2 : 0u);
     }
     se = buf_load16(rS, vedge, c2);
     if (c2 > 0) __syncthreads();                          // the chunk before has been read
 #pragma unroll
-    for (int r = 0; r < CT_PH; ++r) *(u32x4*)(patch + lcol + r * CT_PW * 64) = sv[r];
-    if (er < CT_PH) *(u32x4*)(patch + ledge) = se;
-    if (WL) {
+    for (int it = 0; it < NWS; ++it)
+      if (t0 + NT * it < NWI) *(u32x4*)(wl + cnn_place(t0 >> 2, t0 & 3) + it * NT * 16) = wv[it];
 #pragma unroll
-      for (int it = 0; it < NWS; ++it)
-        if (t0 + 256 * it < NWI) *(u32x4*)(wl + place(t0 >> 2, t0 & 3) + it * 64 * 64) = wv[it];
-    }
+    for (int r = 0; r < PH / RP; ++r) *(u32x4*)(patch + lcol + (r * RP + tr) * CT_PW * 64) = sv[r];
+    if (er < PH) *(u32x4*)(patch + ledge) = se;
     __syncthreads();
-    // taps: the next tap's weights are loaded while this tap's MFMAs run
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-      bf16x8(&w)[MT] = wc[WL ? 0 : t & 1];
-      if (WL) {
+      bf16x8 w[MT], bv[4];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) w[i] = *(const bf16x8*)(wl + lw + (t * MT + i) * 16 * 64);
-      } else if (t + 1 < 9) {
-        wload(t + 1, c2, wc[(t + 1) & 1]);
-      }
-      bf16x8 bv[4];
+      for (int i = 0; i < MT; ++i) w[i] = *(const bf16x8*)(wl + lw + (t * MT + i) * 16 * 64);
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         bv[j] = *(const bf16x8*)(patch + lb[t % 3] + ((t / 3) * CT_PW + 16 * j) * 64);
@@ -306,14 +291,14 @@ __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int x = x0 + 16 * j + pl;
-    vo[j] = x < Wq ? (unsigned)x * m2 + 8u * kg : CT_OUT;
+    vo[j] = x < Wq ? (unsigned)x * m2 + 2u * m0 + 8u * kg : CT_OUT;
   }
   float4 bias4[MT];
   u32x2 mk[MT][4];
   const __amdgpu_buffer_rsrc_t rM = cnn_rsrc(BWD ? (const char*)a.mask + rowp * m2 : nullptr, BWD ? orow : 0);
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
-    if (!BWD) bias4[i] = *(const float4*)(a.bias + i * 16 + 4 * kg);
+    if (!BWD) bias4[i] = *(const float4*)(a.bias + m0 + i * 16 + 4 * kg);
     if (BWD)
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -327,7 +312,7 @@ __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
     const int x = x0 + 16 * j + pl;
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      const int r0 = i * 16 + 4 * kg;
+      const int r0 = m0 + i * 16 + 4 * kg;
       float v[4];
       if (BWD) {
         const bf16x4 m4 = __builtin_bit_cast(bf16x4, mk[i][j]);
@@ -361,167 +346,144 @@ __global__ __launch_bounds__(256) void k_conv_tile(GemmArgs a) {
 //  * KS = 4, backward data of the upsampling layers (BWD): source = dz on the
 //    upsampled grid, the 16 effective weights of k_pack_up_weights, ReLU-mask
 //    epilogue.
-// A workgroup stages the (2 CS_TH + KS - 2) x (2 CS_TW + KS - 2) source patch of
-// its tile in LDS per 32 source channels (zero padding resolved while staging)
-// and applies the taps from there; wave w owns output row y0 + w (two pixel
-// tiles of 16).  Loads are issued as in k_conv_tile, and WL stages the
-// weights in LDS as there; operand layouts are those described at GemmArgs.
-#define CT_PS 40   // bf16 per staged pixel: 32 channels + 8 of padding (80-byte stride)
-#define CS_TH 4
+// A workgroup of TH waves computes TH x 32 output pixels for 16 MT of the M
+// channels.  It stages the (2 TH + KS - 2) x (62 + KS) source patch of its tile
+// and the weights (all nine taps, or eight of the sixteen at a time) in LDS per 32
+// source channels and applies the taps from there; wave w owns output row y0 + w
+// (two pixel tiles of 16).  Staging and addresses are those of k_conv_tile; even
+// and odd source columns are staged apart, so that the 16 pixels of an operand,
+// two columns apart in the source, are neighbours in LDS.
 #define CS_TW 32
-template <int MT, int KS, bool BWD, bool WL = false>
-__global__ __launch_bounds__(256) void k_conv_tile_s2(GemmArgs a) {
-  constexpr int PH = 2 * CS_TH + KS - 2, PW = 2 * CS_TW + KS - 2, NTAP = KS * KS;
-  __shared__ __attribute__((aligned(16))) bf16 patch[PH * PW * CT_PS];
-  // WL: the chunk's weights, staged with the patch ([tap][row][40]) in groups
-  // of NTW taps (all nine for KS = 3; two groups of eight for the 16 taps of
-  // KS = 4, whose weights would not fit LDS at once)
-  constexpr int NTW = WL ? (NTAP > 9 ? NTAP / 2 : NTAP) : 1;
-  __shared__ __attribute__((aligned(16))) bf16 wl[WL ? NTW * 16 * MT * CT_PS : 8];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int x0 = blockIdx.x * CS_TW, y0 = blockIdx.y * CS_TH, b = blockIdx.z;
-  const int Hq = a.Hq, Wq = a.Wq;
+#define CS_PH 40                      // staged half row: 33 pixels used, a multiple of 8
+template <int MT, int KS, int TH, bool BWD>
+__global__ __launch_bounds__(64 * TH) void k_conv_tile_s2(GemmArgs a) {
+  constexpr int NT = 64 * TH, PH = 2 * TH + KS - 2, RP = NT / 256, NR = (PH + RP - 1) / RP;
+  constexpr int NTAP = KS * KS, NTW = NTAP > 9 ? NTAP / 2 : NTAP, NE = KS - 2;   // edge columns
+  __shared__ __attribute__((aligned(16))) unsigned char patch[PH * 2 * CS_PH * 64];
+  __shared__ __attribute__((aligned(16))) unsigned char wl[NTW * 16 * MT * 64];
+  const int t0 = threadIdx.x, lane = t0 & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t0 >> 6);
+  const int x0 = blockIdx.x * CS_TW, y0 = blockIdx.y * TH;
+  const int nm = a.M / (16 * MT), b = blockIdx.z / nm, m0 = (blockIdx.z - b * nm) * 16 * MT;
+  const int Hq = a.Hq, Wq = a.Wq, Hs = a.Hs, Ws = a.Ws;
   f32x4 acc[MT][2];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kq = 8 * (lane >> 4);
-  auto wload = [&](int t, int c0, bf16x8 (&av)[MT]) {
-    const bf16* wt = a.W + (size_t)t * a.M * a.Ksrc + c0 + kq;
+  const int pl = lane & 15, kg = lane >> 4;
+  // patch rows 2 y0 - 1 .. of the source; the descriptor starts at the first one in it
+  const unsigned px2 = 2u * a.Ksrc, row2 = px2 * Ws;
+  const int sy0 = max(2 * y0 - 1, 0);
+  const __amdgpu_buffer_rsrc_t rS =
+      cnn_rsrc((const char*)a.src + ((size_t)b * Hs + sy0) * row2, (size_t)(Hs - sy0) * row2);
+  // LDS item of source column px (of the patch) in patch row r
+  auto item = [](int r, int px) { return (2 * r + (px & 1)) * CS_PH + (px >> 1); };
+  const int tr = (RP > 1) ? __builtin_amdgcn_readfirstlane(t0 >> 8) : 0, tc = (t0 & 255) >> 2;
+  const int sx = 2 * x0 + tc - 1;
+  const unsigned vcol = (sx >= 0 && sx < Ws) ? (unsigned)sx * px2 + 16u * (t0 & 3) : CT_OUT;
+  // columns 64 .. 61 + KS: 4 NE units a row
+  const int er = t0 / (4 * NE), ex = 64 + (t0 >> 2) % NE, esy = 2 * y0 - 1 + er, esx = 2 * x0 + ex - 1;
+  const unsigned vedge = (er < PH && esy >= 0 && esy < Hs && esx < Ws)
+                             ? (unsigned)(esy - sy0) * row2 + (unsigned)esx * px2 + 16u * (t0 & 3)
+                             : CT_OUT;
+  const int lcol = cnn_place(item(0, tc), t0 & 3), ledge = cnn_place(item(er, ex), t0 & 3);
+  // operands: 16 pixels from column m or m + 1 of a half row on
+  int lb[2];
 #pragma unroll
-    for (int i = 0; i < MT; ++i) av[i] = load8(wt + (size_t)(i * 16 + (lane & 15)) * a.Ksrc);
-  };
-  constexpr int NSTG = (PH * PW * 4 + 255) / 256;
-  constexpr int NWI = WL ? NTW * 16 * MT * 4 : 0, NWS = (NWI + 255) / 256;
-  u32x4 wv[NWS > 0 ? NWS : 1];
-  // weights of taps g0 .. g0 + NTW - 1 of chunk c0 into registers, then LDS
-  auto wfetch = [&](int g0, int c0) {
+  for (int h = 0; h < 2; ++h) lb[h] = cnn_place(item(2 * wave, 0) + pl + h, kg);
+  const int lw = cnn_place(pl, kg);
+  const unsigned tap2 = (unsigned)a.M * px2;
+  const __amdgpu_buffer_rsrc_t rW = cnn_rsrc((const char*)a.W + (size_t)m0 * px2,
+                                             (size_t)NTAP * tap2 - (size_t)m0 * px2);
+  constexpr int UT = 16 * MT * 4, NWI = NTW * UT, NWS = (NWI + NT - 1) / NT;
+  const unsigned vwl = (unsigned)((t0 % UT) >> 2) * px2 + 16u * (t0 & 3);
+  u32x4 wv[NWS];
+  // weights of taps g0 .. g0 + NTW - 1 of the chunk at byte c2 into registers, then LDS
+  auto wfetch = [&](int g0, unsigned c2) {
 #pragma unroll
     for (int it = 0; it < NWS; ++it) {
-      const int u = threadIdx.x + 256 * it;   // (tap, row, quarter)
-      const int tq = u / (16 * MT * 4), rem = u - tq * 16 * MT * 4;
-      wv[it] = u32x4{0u, 0u, 0u, 0u};
-      if (u < NWI)
-        wv[it] = *(const u32x4*)(a.W + ((size_t)(g0 + tq) * a.M + (rem >> 2)) * a.Ksrc + c0 +
-                                 8 * (rem & 3));
+      if constexpr (UT >= NT) {
+        wv[it] = buf_load16(rW, vwl, (unsigned)(g0 + it / (UT / NT)) * tap2 +
+                                         (unsigned)(it % (UT / NT)) * (NT / 4u) * px2 + c2);
+      } else {
+        const int tap = it * (NT / UT) + t0 / UT;
+        wv[it] = buf_load16(rW, tap < NTW ? vwl + (unsigned)(g0 + tap) * tap2 : CT_OUT, c2);
+      }
     }
   };
   auto wstore = [&]() {
 #pragma unroll
-    for (int it = 0; it < NWS; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      if (u < NWI) *(u32x4*)(wl + (u >> 2) * CT_PS + 8 * (u & 3)) = wv[it];
-    }
+    for (int it = 0; it < NWS; ++it)
+      if (t0 + NT * it < NWI) *(u32x4*)(wl + cnn_place(t0 >> 2, t0 & 3) + it * NT * 16) = wv[it];
   };
-  // without WL the 9-tap kernels keep the weights of the next PD taps in
-  // flight in a register ring (a tap's MFMAs are too few to cover an L2 load
-  // one tap ahead); the 16-tap kernels load one tap ahead (a ring cost them
-  // occupancy)
-  constexpr int PD = (WL || KS == 4) ? 1 : (NTAP < 16 / MT ? NTAP : 16 / MT);
-  for (int c0 = 0; c0 < a.Ksrc; c0 += 32) {
-    bf16x8 wcur[MT], wr[PD][MT];
-    if (WL) {
-      wfetch(0, c0);
-    } else {
+  for (unsigned c2 = 0; c2 < px2; c2 += 64) {
+    wfetch(0, c2);
+    u32x4 sv[NR], se;
 #pragma unroll
-      for (int d = 0; d < PD; ++d) wload(d, c0, wr[d]);
+    for (int r = 0; r < NR; ++r) {
+      const int py = r * RP + tr, sy = 2 * y0 - 1 + py;
+      const bool in = py < PH && sy >= 0 && sy < Hs;
+      sv[r] = buf_load16(rS, in ? vcol : CT_OUT, in ? (unsigned)(sy - sy0) * row2 + c2 : 0u);
     }
-    u32x4 sv[NSTG];
+    se = buf_load16(rS, vedge, c2);
+    if (c2 > 0) __syncthreads();                          // the chunk before has been read
+    wstore();
 #pragma unroll
-    for (int it = 0; it < NSTG; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      const int pix = u >> 2, q = u & 3;
-      const int py = pix / PW, px = pix - py * PW;
-      const int sy = 2 * y0 + py - 1, sx = 2 * x0 + px - 1;   // source grid
-      sv[it] = u32x4{0u, 0u, 0u, 0u};
-      if (u < PH * PW * 4 && sy >= 0 && sy < a.Hs && sx >= 0 && sx < a.Ws)
-        sv[it] = *(const u32x4*)(a.src + ((size_t)(b * a.Hs + sy) * a.Ws + sx) * a.Ksrc + c0 + 8 * q);
-    }
-#pragma unroll
-    for (int it = 0; it < NSTG; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      if (u < PH * PW * 4) *(u32x4*)(patch + (u >> 2) * CT_PS + 8 * (u & 3)) = sv[it];
-    }
-    if (WL) wstore();
+    for (int r = 0; r < NR; ++r)
+      if (r * RP + tr < PH) *(u32x4*)(patch + lcol + (r * RP + tr) * 2 * CS_PH * 64) = sv[r];
+    if (er < PH) *(u32x4*)(patch + ledge) = se;
     __syncthreads();
-    // MFMAs of tap t with weights w
-    auto tap = [&](int t, const bf16x8 (&w)[MT]) {
-      const int ty = t / KS, tx = t - KS * (t / KS);
-      bf16x8 bv[2];
+#pragma unroll
+    for (int t = 0; t < NTAP; ++t) {
+      if (t > 0 && t % NTW == 0) {                        // the second half of sixteen taps
+        wfetch(t, c2);
+        __syncthreads();
+        wstore();
+        __syncthreads();
+      }
+      const int ty = t / KS, tx = t % KS;
+      bf16x8 w[MT], bv[2];
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+        w[i] = *(const bf16x8*)(wl + lw + ((t % NTW) * MT + i) * 16 * 64);
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        bv[j] = *(const bf16x8*)(patch + ((2 * wave + ty) * PW + 2 * (16 * j + (lane & 15)) + tx) *
-                                             CT_PS + kq);
+        bv[j] = *(const bf16x8*)(patch + lb[tx >> 1] + ((2 * ty + (tx & 1)) * CS_PH + 16 * j) * 64);
 #pragma unroll
       for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[i], bv[j], acc[i][j], 0, 0, 0);
-    };
-    if constexpr (WL) {
-#pragma unroll 1
-      for (int t = 0; t < NTAP; ++t) {
-        if (t > 0 && t % NTW == 0) {   // next tap group (only for NTW < NTAP)
-          __syncthreads();
-          wfetch(t, c0);
-          wstore();
-          __syncthreads();
-        }
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-          wcur[i] = *(const bf16x8*)(wl + ((t % NTW) * 16 * MT + i * 16 + (lane & 15)) * CT_PS + kq);
-        tap(t, wcur);
-      }
-    } else if constexpr (PD == 1) {
-#pragma unroll 1
-      for (int t = 0; t < NTAP; ++t) {
-        bf16x8 wnext[MT];
-        if (t + 1 < NTAP) wload(t + 1, c0, wnext);
-        tap(t, wr[0]);
-        if (t + 1 < NTAP) {
-#pragma unroll
-          for (int i = 0; i < MT; ++i) wr[0][i] = wnext[i];
-        }
-      }
-    } else {
-#pragma unroll 1
-      for (int tg = 0; tg < NTAP; tg += PD) {
-#pragma unroll
-        for (int d = 0; d < PD; ++d) {
-          const int t = tg + d;
-          if (t < NTAP) tap(t, wr[d]);
-          if (t + PD < NTAP) wload(t + PD, c0, wr[d]);
-        }
-      }
     }
-    __syncthreads();
   }
   const int y = y0 + wave;
   if (y >= Hq) return;
-  float4 bias4[MT];
-  u32x2 mk[MT][2];
-#pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    const int r0 = i * 16 + 4 * (lane >> 4);
-    if (!BWD) bias4[i] = *(const float4*)(a.bias + r0);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int x = x0 + 16 * j + (lane & 15);
-      mk[i][j] = u32x2{0u, 0u};
-      if (BWD && x < Wq)
-        mk[i][j] = *(const u32x2*)(a.mask + (((size_t)b * Hq + y) * Wq + x) * a.M + r0);
-    }
-  }
+  const size_t rowp = ((size_t)b * Hq + y) * Wq;
+  const unsigned m2 = 2u * a.M, orow = m2 * Wq;
+  unsigned vo[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int x = x0 + 16 * j + (lane & 15);
-    if (x >= Wq) continue;
-    const size_t p = ((size_t)b * Hq + y) * Wq + x;
+    const int x = x0 + 16 * j + pl;
+    vo[j] = x < Wq ? (unsigned)x * m2 + 2u * m0 + 8u * kg : CT_OUT;
+  }
+  float4 bias4[MT];
+  u32x2 mk[MT][2];
+  const __amdgpu_buffer_rsrc_t rM = cnn_rsrc(BWD ? (const char*)a.mask + rowp * m2 : nullptr, BWD ? orow : 0);
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    if (!BWD) bias4[i] = *(const float4*)(a.bias + m0 + i * 16 + 4 * kg);
+    if (BWD)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        mk[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rM, vo[j], 32 * i, 0);
+  }
+  const __amdgpu_buffer_rsrc_t rO = cnn_rsrc((const char*)a.out + rowp * m2, orow);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
 #pragma unroll
     for (int i = 0; i < MT; ++i) {
-      const int r0 = i * 16 + 4 * (lane >> 4);
-      bf16 h[4];
+      bf16x4 h;
       if (BWD) {
         const bf16x4 m4 = __builtin_bit_cast(bf16x4, mk[i][j]);
 #pragma unroll
@@ -535,7 +497,7 @@ __global__ __launch_bounds__(256) void k_conv_tile_s2(GemmArgs a) {
           h[q] = (bf16)v;
         }
       }
-      *(u32x2*)(a.out + p * a.M + r0) = __builtin_bit_cast(u32x2, h);
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), rO, vo[j], 32 * i, 0);
     }
   }
 }
@@ -556,6 +518,7 @@ __global__ __launch_bounds__(256) void k_conv_tile_s2(GemmArgs a) {
 // the odd row.  The next chunk's patch and weights are loaded while the
 // current chunk's MFMAs run.  The epilogue masks by the ReLU of the layer
 // input.
+#define CT_PS 40   // bf16 per staged pixel: 32 channels + 8 of padding (80-byte stride)
 #define BS_TH 8
 #define BS_TW 64
 #define BS_PR 5
@@ -1960,71 +1923,56 @@ extern "C" dd_status dd_cnn_set_params(dd_cnn* n, const float* host, size_t coun
   return DD_OK;
 }
 
-static dd_status gemm_dispatch(const GemmArgs& a, bool bwd, hipStream_t st) {
+// One launch of k_conv_tile: tiles of TH rows, 16 MT channels a workgroup.
+template <int MT, int TH>
+static void launch_conv_tile(const GemmArgs& a, bool bwd, hipStream_t st) {
+  const dim3 grid((a.Wq + CT_TW - 1) / CT_TW, (a.Hq + TH - 1) / TH, a.B * (a.M / (16 * MT)));
+  if (bwd) k_conv_tile<MT, TH, true><<<grid, 64 * TH, 0, st>>>(a);
+  else k_conv_tile<MT, TH, false><<<grid, 64 * TH, 0, st>>>(a);
+}
+
+// The same of k_conv_tile_s2: a 3 x 3 window forward, 4 x 4 backward.
+template <int MT, int KS, int TH>
+static void launch_conv_s2(const GemmArgs& a, hipStream_t st) {
+  const dim3 grid((a.Wq + CS_TW - 1) / CS_TW, (a.Hq + TH - 1) / TH, a.B * (a.M / (16 * MT)));
+  k_conv_tile_s2<MT, KS, TH, KS == 4><<<grid, 64 * TH, 0, st>>>(a);
+}
+
+static dd_status gemm_dispatch(const GemmArgs& a, bool bwd, int ncu, hipStream_t st) {
   const int MT = a.M / 16;
   if ((MT != 2 && MT != 4 && MT != 8) || a.M % 16 || a.Ksrc % 32) {
     dd_set_error("dd_cnn: no convolution kernel for %d result / %d source channels", a.M, a.Ksrc);
     return DD_EINVAL;
   }
-  // several 32-channel chunks: weights staged in LDS (fewer resident
-  // workgroups, no global loads in the tap loop); one chunk: weights from L2
-  const bool wl = a.Ksrc > 32;
-  if (!bwd && (a.mode == MAP_S1 || a.mode == MAP_UP)) {
-    const dim3 grid((a.Wq + CT_TW - 1) / CT_TW, (a.Hq + CT_TH - 1) / CT_TH, a.B);
-    switch (MT) {
-      case 2:
-        if (wl) k_conv_tile<2, false, true><<<grid, 256, 0, st>>>(a);
-        else k_conv_tile<2><<<grid, 256, 0, st>>>(a);
-        break;
-      case 4:
-        if (wl) k_conv_tile<4, false, true><<<grid, 256, 0, st>>>(a);
-        else k_conv_tile<4><<<grid, 256, 0, st>>>(a);
-        break;
-      case 8:
-        if (wl) k_conv_tile<8, false, true><<<grid, 256, 0, st>>>(a);
-        else k_conv_tile<8><<<grid, 256, 0, st>>>(a);
-        break;
-    }
-    return DD_OK;
-  }
-  if (bwd && a.mode == MAP_S1) {
-    const dim3 grid((a.Wq + CT_TW - 1) / CT_TW, (a.Hq + CT_TH - 1) / CT_TH, a.B);
-    switch (MT) {
-      case 2:
-        if (wl) k_conv_tile<2, true, true><<<grid, 256, 0, st>>>(a);
-        else k_conv_tile<2, true><<<grid, 256, 0, st>>>(a);
-        break;
-      case 4:
-        if (wl) k_conv_tile<4, true, true><<<grid, 256, 0, st>>>(a);
-        else k_conv_tile<4, true><<<grid, 256, 0, st>>>(a);
-        break;
-      case 8:
-        if (wl) k_conv_tile<8, true, true><<<grid, 256, 0, st>>>(a);
-        else k_conv_tile<8, true><<<grid, 256, 0, st>>>(a);
-        break;
-    }
+  if (a.mode == MAP_S1 || (!bwd && a.mode == MAP_UP)) {
+    // Tall tiles (the halo a smaller share, the weights staged once for twice the
+    // rows) with all of up to 64 (128 in tall tiles) channels, where they fill
+    // the chip twice; else the most workgroups: 32 channels and 4 rows each.
+    // Measured at 480 x 240, batch 64 (and 1): 32 channels 253, 196, 225 us tall
+    // against 302, 219, 257 (9.1, 7.4, 7.2 against 9.1, 7.0, 7.3); 64 channels 250 us
+    // with all against 256 in halves (14.6 against 10.4); 128 channels 142 us against
+    // 152 in quarters (31 against 10.4).
+    const long long wide = (long long)((a.Wq + CT_TW - 1) / CT_TW) * a.B;
+    const long long tall = wide * ((a.Hq + 7) / 8), flat = wide * ((a.Hq + 3) / 4);
+    if (MT == 8 && tall >= 2 * ncu) launch_conv_tile<8, 8>(a, bwd, st);
+    else if (MT == 4 && flat >= 2 * ncu) launch_conv_tile<4, 4>(a, bwd, st);
+    else if (MT == 2 && tall >= 2 * ncu) launch_conv_tile<2, 8>(a, bwd, st);
+    else launch_conv_tile<2, 4>(a, bwd, st);
     return DD_OK;
   }
   if ((!bwd && a.mode == MAP_S2 && !a.outf) || (bwd && a.mode == MAP_UP)) {
-    const dim3 grid((a.Wq + CS_TW - 1) / CS_TW, (a.Hq + CS_TH - 1) / CS_TH, a.B);
-    if (!bwd) {
-      switch (MT) {
-        case 2: k_conv_tile_s2<2, 3, false><<<grid, 256, 0, st>>>(a); break;
-        case 4: k_conv_tile_s2<4, 3, false><<<grid, 256, 0, st>>>(a); break;
-        case 8:
-          if (a.Ksrc > 32) k_conv_tile_s2<8, 3, false, true><<<grid, 256, 0, st>>>(a);
-          else k_conv_tile_s2<8, 3, false><<<grid, 256, 0, st>>>(a);
-          break;
-      }
+    // As above: 64 channels and 8 rows, or 32 and 4.  Measured at 480 x 240, batch
+    // 64 (and 1): layer 2 229 us against 242 (8.0 against 6.5), layer 3 181 against
+    // 185 (10.9 against 7.2); backward at batch 32, layer 6 159 against 175, layer
+    // 5 128 against 139.  Four rows of 64 channels (one workgroup a compute unit)
+    // are slower than either: 305, 227, 223 and 174 us.
+    const long long tall = (long long)((a.Wq + CS_TW - 1) / CS_TW) * ((a.Hq + 7) / 8) * a.B * (MT / 4);
+    if (tall >= 2 * ncu) {
+      if (bwd) launch_conv_s2<4, 4, 8>(a, st);
+      else launch_conv_s2<4, 3, 8>(a, st);
     } else {
-      switch (MT) {
-        case 2: k_conv_tile_s2<2, 4, true><<<grid, 256, 0, st>>>(a); break;
-        case 4: k_conv_tile_s2<4, 4, true><<<grid, 256, 0, st>>>(a); break;
-        case 8:
-          if (a.Ksrc > 32) k_conv_tile_s2<8, 4, true, true><<<grid, 256, 0, st>>>(a);
-          else k_conv_tile_s2<8, 4, true><<<grid, 256, 0, st>>>(a);
-          break;
-      }
+      if (bwd) launch_conv_s2<2, 4, 4>(a, st);
+      else launch_conv_s2<2, 3, 4>(a, st);
     }
     return DD_OK;
   }
@@ -2077,7 +2025,7 @@ static dd_status forward(dd_cnn* n, const float* eps, const void* eim, int B, hi
       n->last_fields = a.outf;
     }
     else a.out = n->act[l];
-    const dd_status rc = gemm_dispatch(a, false, st);
+    const dd_status rc = gemm_dispatch(a, false, n->ncu, st);
     if (rc != DD_OK) return rc;
   }
   DD_HIP_CHECK(hipGetLastError());
@@ -2260,7 +2208,7 @@ static dd_status backward_from_dz(dd_cnn* n, int B, hipStream_t st) {
     a.B = B; a.Hq = L.Hin; a.Wq = L.Win;
     a.Hs = L.Hout; a.Ws = L.Wout;
     a.Ksrc = L.coutp; a.M = L.cinp; a.mode = L.mode;
-    const dd_status rc = gemm_dispatch(a, true, st);
+    const dd_status rc = gemm_dispatch(a, true, n->ncu, st);
     if (rc != DD_OK) return rc;
   }
   {

@@ -173,7 +173,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
     A.carve(&P.ccpart, (size_t)nb * 33);
     for (SweepPlan* w : {&P.sw, &P.sw2}) {
       if (w == &P.sw2 && P.reorth_mode == 0) break;
-      A.carve(&w->tiles, (size_t)s->sw_most);
+      A.carve(&w->tiles, (size_t)s->sw_most + s->sw_grid);   // the last round has gaps
       A.carve(&w->count, 2);
       A.carve(&w->tile0, (size_t)nb);
       A.carve(&w->ntile, (size_t)nb);
@@ -761,9 +761,9 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     for (int p = 0; p < nb; ++p) active += snap[0][p * ST_NI + ST_ACTIVE];
     if (active == 0) break;
     if (s->fused == 2) {
-      k_sweep_plan<false><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
+      k_sweep_plan<T, false><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
       if (s->P.reorth_mode != 0)
-        k_sweep_plan<true><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
+        k_sweep_plan<T, true><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
     }
     launch_start<T, R>(s, st);
     if (s->fused) {

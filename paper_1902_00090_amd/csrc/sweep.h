@@ -97,11 +97,31 @@ __host__ __device__ inline int sw_width(int nx) {
   return (nx + s - 1) / s;
 }
 
-// One tile: rows [y0, y0 + rows) of a strip of problem p.  The second
-// Gram-Schmidt pass has no stencil: its one strip's rows are runs of 64 cells.
+// One tile: rows [y0, y0 + rows) of a strip of problem p, with what a workgroup
+// needs to know of the problem, so that it addresses the basis after one load.
+// The second Gram-Schmidt pass has no stencil: its one strip's rows are runs of
+// 64 cells.
 struct SweepTile {
   int p, strip, y0, rows;
+  int nx, ny, k, pad;
+  size_t Dp;
+  void *basis, *Z;
+  const void *cf, *eps, *pl, *pr;   // of the inner precision
+  double omega2;
 };
+
+// Workgroup b of the G that walk the tiles takes the tiles sw_first(b) + r G.
+// Workgroup b runs on XCD b % 8: each XCD has neighbouring tiles.
+__device__ __forceinline__ int sw_first(int b, int G) {
+  return (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+}
+// The record of tile t stands where its workgroup finds it without knowing G
+// first: workgroup b's r-th at r G + b.
+template <bool PASS2> __device__ __forceinline__ int sw_position(int t, int G) {
+  if (PASS2 || G % 8 != 0) return t;
+  const int g = t % G;
+  return t - g + g % (G / 8) * 8 + g / (G / 8);
+}
 
 template <bool PASS2> __device__ __forceinline__ int sw_plan_strips(const ProbDesc& d) {
   return PASS2 ? 1 : sw_strips(d.nx);
@@ -123,7 +143,7 @@ template <bool PASS2> __device__ __forceinline__ int sw_plan_rows(const ProbDesc
 // the strips share at their edges: 62 columns are 496 bytes, which touch five
 // lines of 128.  A problem's tiles, and with them its partial sums, are
 // consecutive from tile0[p].
-template <bool PASS2>
+template <typename T, bool PASS2>
 __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int most) {
   const SweepPlan& W = PASS2 ? P.sw2 : P.sw;
   __shared__ int cnt[DD_BLOCK];
@@ -173,17 +193,26 @@ __global__ __launch_bounds__(DD_BLOCK) void k_sweep_plan(PlanDev P, int ncu, int
       __syncthreads();
     }
     if (p < P.nb) {
-      const int t0 = done + cnt[t] - r, ny = sw_plan_rows<PASS2>(P.desc[p]);
-      W.tile0[p] = t0;
+      W.tile0[p] = done + cnt[t] - r;
       W.ntile[p] = r;
       if (!PASS2) P.live[p] = r > 0;
-      for (int i = 0; i < r; ++i) {
-        const int y0 = i / strips * h;
-        W.tiles[t0 + i] = {p, i % strips, y0, min(h, ny - y0)};
-      }
     }
     done += cnt[DD_BLOCK - 1];
     __syncthreads();
+  }
+  for (int i = t; i < done; i += DD_BLOCK) {
+    int p = 0, e = P.nb;           // the last problem whose tiles start at or before i
+    while (e - p > 1) {
+      const int c = (p + e) / 2;
+      if (W.tile0[c] <= i) p = c;
+      else e = c;
+    }
+    const ProbDesc& d = P.desc[p];
+    const int strips = sw_plan_strips<PASS2>(d), ny = sw_plan_rows<PASS2>(d), q = i - W.tile0[p];
+    const int y0 = q / strips * h;
+    W.tiles[sw_position<PASS2>(i, G)] = {
+        p, q % strips, y0, min(h, ny - y0), d.nx, d.ny, d.k, 0, (size_t)d.Dp, d.basis, d.Z,
+        OpP<T>::cf(d), OpP<T>::eps(d), d.pl, d.pr, d.omega2};
   }
   if (t == 0) {
     W.count[0] = done;
@@ -234,10 +263,16 @@ template <typename V> __device__ __forceinline__ V from_east(V v) {
 // preconditioner, z = P_L A P_R q~.
 template <typename T, int NW, int PER, bool PC>
 __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
+  // Each level of these scalar loads is a latency that a short step feels: the
+  // tile's record is loaded beside the counts, whether there is one or not, and
+  // the basis is addressed from it.  Through the count, the tile and the problem's
+  // descriptor in turn a step of one 480 x 240 problem took 24.3 us, so 23.5; one
+  // of 192 x 96 15.7 and 15.0.
+  const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw.tiles) + blockIdx.x;
   const int count = ld_uni(P.sw.count), G = ld_uni(P.sw.count + 1);
+  int nrows = tl->rows;
+  asm volatile("" : "+s"(nrows));
   if ((int)blockIdx.x >= G) return;
-  // workgroup b runs on XCD b % 8: give each XCD neighbouring tiles
-  const int g = (G % 8 == 0) ? (int)(blockIdx.x % 8) * (G / 8) + (int)blockIdx.x / 8 : blockIdx.x;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   using V = c2<T>;
@@ -245,32 +280,30 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
   __shared__ V part[2][NW][64];
   const V zero = cmk<V>(T(0), T(0));
 
-  for (int tile = g; tile < count; tile += G) {
-    const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw.tiles + tile);
-    const int p = tl->p, strip = tl->strip, ya = tl->y0, nrows = tl->rows;
-    if (ld_uni(P.stI + p * ST_NI + ST_ACTIVE) == 0) continue;   // ended within this cycle
-    const auto* d = (const __attribute__((address_space(4))) ProbDesc*)(P.desc + p);
-    const int nx = d->nx, ny = d->ny, k = d->k;
-    const size_t Dp = d->Dp;
-    const int n = k + j + 1;
-    const V* B = (const V*)d->basis + (size_t)(P.kmax - k) * Dp;
-    V* qn = (V*)d->basis + (size_t)(P.kmax + j + 1) * Dp;
-    const V* zin = (const V*)d->Z + (size_t)(j & 1) * Dp;
-    V* zout = (V*)d->Z + (size_t)((j + 1) & 1) * Dp;
-    const V* cf = OpP<T>::cf(*d);
-    const T om2 = (T)d->omega2;
-    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * CB);
-    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(zin, (size_t)Dp * CB);
-    const __amdgpu_buffer_rsrc_t rE = sw_rsrc(OpP<T>::eps(*d), (size_t)nx * ny * (CB / 2));
-    const bool has_pl = PC && d->pl != nullptr, has_pr = PC && d->pr != nullptr;
-    const __amdgpu_buffer_rsrc_t rL = sw_rsrc(has_pl ? d->pl : B, has_pl ? (size_t)Dp * CB : 0);
-    const __amdgpu_buffer_rsrc_t rR = sw_rsrc(has_pr ? d->pr : B, has_pr ? (size_t)Dp * CB : 0);
-    const unsigned vec = (unsigned)Dp * CB;         // bytes of one vector
+  for (int tile = sw_first(blockIdx.x, G); tile < count; tile += G, tl += G) {
+    const int p = tl->p, strip = tl->strip, ya = tl->y0;
+    nrows = tl->rows;
+    const int nx = tl->nx, ny = tl->ny, k = tl->k, n = k + j + 1;
+    const size_t Dp = tl->Dp;
+    int act = ld_uni(P.stI + p * ST_NI + ST_ACTIVE);
     const V* cS = (const V*)P.coefS + (size_t)p * DD_SW_MAXN + wave;
     V gc[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) gc[i] = ld_uni(cS + NW * i);
     const T zs = (T)ld_uni(P.zs + p);
+    const V* B = (const V*)tl->basis + (size_t)(P.kmax - k) * Dp;
+    V* qn = (V*)tl->basis + (size_t)(P.kmax + j + 1) * Dp;
+    const V* zin = (const V*)tl->Z + (size_t)(j & 1) * Dp;
+    V* zout = (V*)tl->Z + (size_t)((j + 1) & 1) * Dp;
+    const V* cf = (const V*)tl->cf;
+    const T om2 = (T)tl->omega2;
+    const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * CB);
+    const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(zin, (size_t)Dp * CB);
+    const __amdgpu_buffer_rsrc_t rE = sw_rsrc(tl->eps, (size_t)nx * ny * (CB / 2));
+    const bool has_pl = PC && tl->pl != nullptr, has_pr = PC && tl->pr != nullptr;
+    const __amdgpu_buffer_rsrc_t rL = sw_rsrc(has_pl ? tl->pl : B, has_pl ? (size_t)Dp * CB : 0);
+    const __amdgpu_buffer_rsrc_t rR = sw_rsrc(has_pr ? tl->pr : B, has_pr ? (size_t)Dp * CB : 0);
+    const unsigned vec = (unsigned)Dp * CB;         // bytes of one vector
     V acc[PER];
 #pragma unroll
     for (int i = 0; i < PER; ++i) acc[i] = zero;
@@ -394,13 +427,17 @@ __global__ __launch_bounds__(64 * NW, 2) void k_sweep(PlanDev P, int j) {
       r1 = r;
       u1 = u;
     };
-    __syncthreads();          // the parts of the tile before have been read
     int t = 0;
     if constexpr (AHEAD == 2) {
       load(S0, 0);
       __builtin_amdgcn_sched_barrier(0);
       load(S1, 1);
       __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("" : "+s"(act) : "s"(gc[0].x), "s"(gc[PER - 1].x), "s"(zs));
+    if (act == 0) continue;   // ended within this cycle (the first rows are on their way by now)
+    __syncthreads();          // the parts of the tile before have been read
+    if constexpr (AHEAD == 2) {
       for (; t + 4 <= N; t += 4) {
         step(S0, S3, S2, t);
         step(S1, S0, S3, t + 1);
@@ -452,7 +489,10 @@ __device__ __forceinline__ bool sw_second_pass(const PlanDev& P, int p) {
 // is updated and dotted at once, so three register sets rotate.
 template <typename T, int NW, int PER>
 __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
+  const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw2.tiles) + blockIdx.x;
   const int count = ld_uni(P.sw2.count), G = ld_uni(P.sw2.count + 1);
+  int N = tl->rows;
+  asm volatile("" : "+s"(N));
   if ((int)blockIdx.x >= G) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -461,15 +501,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
   __shared__ V part[2][NW][64];
   const V zero = cmk<V>(T(0), T(0));
 
-  for (int tile = blockIdx.x; tile < count; tile += G) {
-    const auto* tl = (const __attribute__((address_space(4))) SweepTile*)(P.sw2.tiles + tile);
-    const int p = tl->p, ya = tl->y0, N = tl->rows;
-    if (ld_uni(P.stI + p * ST_NI + ST_ACTIVE) == 0 || !sw_second_pass(P, p)) continue;
-    const auto* d = (const __attribute__((address_space(4))) ProbDesc*)(P.desc + p);
-    const int k = d->k, n = k + j + 1;
-    const size_t Dp = d->Dp;
-    const V* B = (const V*)d->basis + (size_t)(P.kmax - k) * Dp;
-    V* z = (V*)d->Z + (size_t)(j & 1) * Dp;
+  for (int tile = blockIdx.x; tile < count; tile += G, tl += G) {
+    const int p = tl->p, ya = tl->y0, k = tl->k, n = k + j + 1;
+    N = tl->rows;
+    int act = ld_uni(P.stI + p * ST_NI + ST_ACTIVE);
+    const bool second = sw_second_pass(P, p);
+    asm volatile("" : "+s"(act));
+    if (act == 0 || !second) continue;
+    const size_t Dp = tl->Dp;
+    const V* B = (const V*)tl->basis + (size_t)(P.kmax - k) * Dp;
+    V* z = (V*)tl->Z + (size_t)(j & 1) * Dp;
     const __amdgpu_buffer_rsrc_t rB = sw_rsrc(B, (size_t)n * Dp * CB);
     const __amdgpu_buffer_rsrc_t rZ = sw_rsrc(z, (size_t)Dp * CB);
     const unsigned vec = (unsigned)Dp * CB;

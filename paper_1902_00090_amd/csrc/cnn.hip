@@ -67,7 +67,6 @@ struct dd_cnn {
   bf16* wb[NL] = {};
   bf16* wu[NL] = {};         // upsampled layers: effective backward-data weights [16][cinp][coutp]
   float* x0 = nullptr;       // normalised input planes [B][cin0][H][W]
-  double* iscale = nullptr;  // [maxB] effective-index field scale sqrt(D) / ||F||
   double* espart = nullptr;  // [maxB][ES_SLICES] partial sums of |F|^2
   // residual-loss scratch (allocated on first use): V = output fields, W = A V,
   // r = b - W c, s = A^H r
@@ -647,90 +646,144 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
 }
 
 // ------------------------------------------------------------- layer 1 ----
-// Cin = 1 or 3 input planes, 32 output channels, FP32 throughout on the
-// matrix cores: per 16 output pixels the product W[32][9C] . X[9C][16] runs as
-// FP32 16x16x4 MFMAs over K = 9C padded to a multiple of 4 (k = 9 c + tap,
-// padded rows zero).  Lane l supplies weight row l % 16 / k-slot l / 16 and
-// the input of pixel l % 16 at k-slot l / 16; its accumulators hold output
-// channels 4 (l / 16) + q of pixel l % 16.  A wave takes C1_NT tiles of 16
-// consecutive pixels (row-major over [B][H][W]) and issues every input load
-// before its first MFMA; 8-byte bf16 stores of 4 channels.  x0 is planar
-// [B][C][H][W], w is [32][C][9].
-#define C1_NT 8
+// Partial sums of |F_b|^2 of the effective-index fields, grid (ES_SLICES, B);
+// k_conv1_fwd adds them in slice order.
+#define ES_SLICES 64
+__global__ __launch_bounds__(256) void k_eim_scale_part(const float2* __restrict__ eim, int D,
+                                                        double* __restrict__ part) {
+  const float2* f = eim + (size_t)blockIdx.y * D;
+  const int per = (D + ES_SLICES - 1) / ES_SLICES, e0 = blockIdx.x * per, e1 = min(D, e0 + per);
+  double s = 0.0;
+  for (int e = e0 + threadIdx.x; e < e1; e += 256) {
+    const float2 v = f[e];
+    s += (double)v.x * v.x + (double)v.y * v.y;
+  }
+  __shared__ double lds[8];
+  s = block_sum1<double>(s, lds);
+  if (threadIdx.x == 0) part[(size_t)blockIdx.y * ES_SLICES + blockIdx.x] = s;
+}
+
+// The network's input and its first layer.  Input planes [B][C][H][W]: plane 0 =
+// (eps - 2.085) / (12.25 - 2.085); for C = 3, planes 1 and 2 = real and imaginary
+// part of the effective-index field scaled to unit RMS per pixel, by
+// sqrt(D) / ||F_b|| (0 for an all-zero field).
+//
+// C input planes, 32 output channels, FP32 throughout on the matrix cores: per 16
+// output pixels the product W[32][9C] . X[9C][16] runs as FP32 16x16x4 MFMAs over
+// K = 9C padded to a multiple of 4 (k = 9 c + tap, padded rows zero).  Lane l
+// supplies weight row l % 16 / k-slot l / 16 and the input of pixel l % 16 at
+// k-slot l / 16; tile i's row r is channel 8 (r / 4) + 4 i + r % 4, so that the two
+// tiles leave a lane 8 neighbouring channels of its pixel: one 16-byte store, and
+// a wave's stores are contiguous.
+//
+// A workgroup forms the planes of C1_TH rows of 64 pixels and a ring around them
+// in LDS, stores its own pixels' (for the weight gradient) and reads its operands
+// there, at addresses that differ by constants.  At 480 x 240 with three planes,
+// batch 64, 195 us, of which the writes alone (32 bf16 channels of each pixel, the
+// planes) would take 125 and the MFMAs 85; at batch 1, 8.8 us.  With the planes
+// formed by kernels before it, and gathered from memory per pixel and tap with the
+// bounds tested for each, 234 + 38 us, and 14.8 us in three launches.
+#define C1_TH 8
+#define C1_PS 80      // floats of a row in LDS: its banks and the next row's differ
 template <int C>
-__global__ __launch_bounds__(256) void k_conv1_fwd(const float* __restrict__ x0,
+__global__ __launch_bounds__(256) void k_conv1_fwd(const float* __restrict__ eps,
+                                                   const float2* __restrict__ eim,
+                                                   const double* __restrict__ espart,
                                                    const float* __restrict__ w,
-                                                   const float* __restrict__ bias, int B, int H,
-                                                   int W, bf16* __restrict__ out) {
+                                                   const float* __restrict__ bias, int H, int W,
+                                                   float* __restrict__ x0, bf16* __restrict__ out) {
   constexpr int KS = (9 * C + 3) / 4;   // k-steps of 4
+  constexpr int PL = (C1_TH + 2) * C1_PS;
+  __shared__ float pl[C * PL];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int ks = lane >> 4, col = lane & 15;
-  const int total = B * H * W;
+  const int xa = blockIdx.x * 64, ya = blockIdx.y * C1_TH, b = blockIdx.z;
+  const int HW = H * W;
+  const float* eb = eps + (size_t)b * HW;
+  const float2* fb = eim + (size_t)b * HW;
+  float* xb = x0 + (size_t)b * C * HW;
+  constexpr int NP = (C1_TH + 2) * 66, NI = (NP + 255) / 256;
+  float e[NI];
+  float2 f[NI];
+#pragma unroll
+  for (int it = 0; it < NI; ++it) {
+    const int u = threadIdx.x + 256 * it, r = u / 66, y = ya + r - 1, x = xa + u - 66 * r - 1;
+    const bool ok = u < NP && (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+    e[it] = ok ? eb[y * W + x] : 0.f;
+    if (C == 3) f[it] = ok ? fb[y * W + x] : make_float2(0.f, 0.f);
+  }
   float av[2][KS];
+  const int ch = 8 * (col >> 2) + (col & 3);
 #pragma unroll
   for (int s = 0; s < KS; ++s) {
     const int k = 4 * s + ks;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) av[i][s] = (k < 9 * C) ? w[(16 * i + col) * 9 * C + k] : 0.f;
+    for (int i = 0; i < 2; ++i) av[i][s] = (k < 9 * C) ? w[(ch + 4 * i) * 9 * C + k] : 0.f;
   }
-  // per k-slot: plane offset and tap shift, the same for every pixel tile
-  const int HW = H * W;
-  int koff[KS], kdy[KS], kdx[KS];
+  float sc = 0.f;
+  if (C == 3) {
+    // uniform loads of what the kernel before wrote
+    const auto* ep = (const __attribute__((address_space(4))) double*)(espart + (size_t)b * ES_SLICES);
+    double s = 0.0;
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    const int k = 4 * s + ks, c = k / 9, t = k - 9 * c;
-    kdy[s] = (k < 9 * C) ? t / 3 - 1 : -H;   // padded k-slots fall outside every row
-    kdx[s] = t % 3 - 1;
-    koff[s] = c * HW + kdy[s] * W + kdx[s];
+    for (int i = 0; i < ES_SLICES; ++i) s += ep[i];
+    sc = (float)((s > 0.0) ? sqrt((double)HW / s) : 0.0);
   }
-  const int base = (blockIdx.x * 4 + wave) * 16 * C1_NT;
-  float bv[C1_NT][KS];
-  // (b, y, x) of this lane's pixel, advanced by 16 pixels per tile
-  int b = (unsigned)(base + col) / (unsigned)HW, x = base + col - b * HW;
-  int y = (unsigned)x / (unsigned)W;
-  x -= y * W;
 #pragma unroll
-  for (int j = 0; j < C1_NT; ++j) {
-    const int p = base + 16 * j + col;
-    if (j > 0) {
-      x += 16;
-      while (x >= W) {
-        x -= W;
-        if (++y == H) { y = 0; ++b; }
+  for (int it = 0; it < NI; ++it) {
+    const int u = threadIdx.x + 256 * it, r = u / 66, c = u - 66 * r, y = ya + r - 1, x = xa + c - 1;
+    if (u >= NP) break;
+    const bool in = (unsigned)y < (unsigned)H && (unsigned)x < (unsigned)W;
+    float v[3] = {0.f, 0.f, 0.f};
+    if (in) {
+      v[0] = (e[it] - CNN_EPS_LO) / (CNN_EPS_HI - CNN_EPS_LO);
+      if (C == 3) {
+        v[1] = f[it].x * sc;
+        v[2] = f[it].y * sc;
       }
     }
-    const int pb = p + b * (C - 1) * HW;   // element (b, 0, y, x) of the planar input
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      // out-of-range taps read element 0 and are zeroed after the load, so
-      // every load is issued unconditionally
-      const bool ok = (p < total) & ((unsigned)(y + kdy[s]) < (unsigned)H) &
-                      ((unsigned)(x + kdx[s]) < (unsigned)W);
-      const float v = x0[ok ? (unsigned)(pb + koff[s]) : 0u];
-      bv[j][s] = ok ? v : 0.f;
-    }
+    for (int q = 0; q < C; ++q) pl[q * PL + r * C1_PS + c] = v[q];
+    if (in && r >= 1 && r <= C1_TH && c >= 1 && c <= 64)
+#pragma unroll
+      for (int q = 0; q < C; ++q) xb[(size_t)q * HW + y * W + x] = v[q];
   }
-  float bq[2][4];
+  // per k-slot: plane and tap, the same for every pixel tile; a padded slot's
+  // operand is zeroed after the read
+  int koff[KS];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int s = 0; s < KS; ++s) {
+    const int k = min(4 * s + ks, 9 * C - 1), c = k / 9, t = k - 9 * c;
+    koff[s] = c * PL + (t / 3) * C1_PS + t % 3 + col + 2 * wave * C1_PS;
+  }
+  const bool padded = 4 * (KS - 1) + ks >= 9 * C;
+  float bq[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) bq[i][q] = bias[16 * i + 4 * ks + q];
+  for (int q = 0; q < 8; ++q) bq[q] = bias[8 * ks + q];
+  __syncthreads();
 #pragma unroll
-  for (int j = 0; j < C1_NT; ++j) {
-    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  for (int r = 0; r < 2; ++r) {
+    const int y = ya + 2 * wave + r;
+    if (y >= H) break;
 #pragma unroll
-    for (int s = 0; s < KS; ++s)
+    for (int j = 0; j < 4; ++j) {
+      if (xa + 16 * j >= W) break;
+      float bv[KS];
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][s], bv[j][s], acc[i], 0, 0, 0);
-    const int p = base + 16 * j + col;
-    if (p >= total) continue;
+      for (int s = 0; s < KS; ++s) bv[s] = pl[koff[s] + r * C1_PS + 16 * j];
+      if (padded) bv[KS - 1] = 0.f;
+      f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      bf16 h[4];
+      for (int s = 0; s < KS; ++s)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) h[q] = (bf16)fmaxf(acc[i][q] + bq[i][q], 0.f);
-      *(u32x2*)(out + (size_t)p * 32 + 16 * i + 4 * ks) = __builtin_bit_cast(u32x2, h);
+        for (int i = 0; i < 2; ++i)
+          acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i][s], bv[s], acc[i], 0, 0, 0);
+      const int x = xa + 16 * j + col;
+      if (x >= W) continue;
+      bf16 h[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) h[q] = (bf16)fmaxf(acc[q >> 2][q & 3] + bq[q], 0.f);
+      *(u32x4*)(out + ((size_t)b * HW + y * W + x) * 32 + 8 * ks) = __builtin_bit_cast(u32x4, h);
     }
   }
 }
@@ -1601,50 +1654,6 @@ __global__ __launch_bounds__(256) void k_bgrad_reduce(const float* __restrict__ 
 }
 
 // ------------------------------------------------ input, loss, output ----
-// Input planes [B][C][H][W]: plane 0 = (eps - 2.085) / (12.25 - 2.085); for
-// C = 3, planes 1 and 2 = real and imaginary part of the effective-index field
-// scaled to unit RMS per pixel (iscale[b] = sqrt(D) / ||F_b||).
-__global__ void k_inputs(const float* __restrict__ eps, const float2* __restrict__ eim,
-                         const double* __restrict__ iscale, int B, int D, int C,
-                         float* __restrict__ x0) {
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= B * D) return;
-  const int b = i / D, e = i - b * D;
-  x0[(size_t)b * C * D + e] = (eps[i] - CNN_EPS_LO) / (CNN_EPS_HI - CNN_EPS_LO);
-  if (C == 3) {
-    const float s = (float)iscale[b];
-    const float2 f = eim[i];
-    x0[((size_t)b * C + 1) * D + e] = f.x * s;
-    x0[((size_t)b * C + 2) * D + e] = f.y * s;
-  }
-}
-
-// iscale[b] = sqrt(D / sum |F_b|^2) (0 for an all-zero field), in two steps:
-// ES_SLICES partial sums per problem (grid (ES_SLICES, B)), then their sum in
-// slice order.
-#define ES_SLICES 64
-__global__ __launch_bounds__(256) void k_eim_scale_part(const float2* __restrict__ eim, int D,
-                                                        double* __restrict__ part) {
-  const float2* f = eim + (size_t)blockIdx.y * D;
-  const int per = (D + ES_SLICES - 1) / ES_SLICES, e0 = blockIdx.x * per, e1 = min(D, e0 + per);
-  double s = 0.0;
-  for (int e = e0 + threadIdx.x; e < e1; e += 256) {
-    const float2 v = f[e];
-    s += (double)v.x * v.x + (double)v.y * v.y;
-  }
-  __shared__ double lds[8];
-  s = block_sum1<double>(s, lds);
-  if (threadIdx.x == 0) part[(size_t)blockIdx.y * ES_SLICES + blockIdx.x] = s;
-}
-__global__ void k_eim_scale(const double* __restrict__ part, int B, int D,
-                            double* __restrict__ iscale) {
-  const int b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= B) return;
-  double s = 0.0;
-  for (int i = 0; i < ES_SLICES; ++i) s += part[(size_t)b * ES_SLICES + i];
-  iscale[b] = (s > 0.0) ? sqrt((double)D / s) : 0.0;
-}
-
 // loss partials and dz of the last (linear) layer: out and target are complex
 // fields [B][k][D]; dz = 2 (out - t) / count in bf16 with coutp channels.
 // One thread per (pixel, group of 8 channels) (coutp is a multiple of 32), so
@@ -1835,7 +1844,6 @@ extern "C" dd_status dd_cnn_create(int nx, int ny, int max_batch, int k, int in_
   chk(cnn_alloc(n, &n->av, off + 64));
   const size_t D = (size_t)nx * ny;
   chk(cnn_alloc(n, &n->x0, (size_t)max_batch * D * in_channels));
-  chk(cnn_alloc(n, &n->iscale, (size_t)max_batch));
   chk(cnn_alloc(n, &n->espart, (size_t)max_batch * ES_SLICES));
   size_t wp = 0;
   for (int l = 0; l < NL && e == hipSuccess; ++l) {
@@ -1994,21 +2002,17 @@ static dd_status gemm_dispatch(const GemmArgs& a, bool bwd, int ncu, hipStream_t
 static dd_status forward(dd_cnn* n, const float* eps, const void* eim, int B, hipStream_t st,
                          void* fields = nullptr) {
   const int D = n->nx * n->ny;
-  if (n->cin0 == 3) {
-    k_eim_scale_part<<<dim3(ES_SLICES, B), 256, 0, st>>>((const float2*)eim, D, n->espart);
-    k_eim_scale<<<(B + 255) / 256, 256, 0, st>>>(n->espart, B, D, n->iscale);
-  }
-  k_inputs<<<(B * D + 255) / 256, 256, 0, st>>>(eps, (const float2*)eim, n->iscale, B, D, n->cin0,
-                                                 n->x0);
   {
     const CnnLayer& L = n->L[0];
-    const dim3 grid((B * D + 64 * C1_NT - 1) / (64 * C1_NT));
-    if (n->cin0 == 3)
-      k_conv1_fwd<3><<<grid, 256, 0, st>>>(n->x0, n->params + L.woff, n->params + L.boff, B,
-                                           n->ny, n->nx, n->act[0]);
-    else
-      k_conv1_fwd<1><<<grid, 256, 0, st>>>(n->x0, n->params + L.woff, n->params + L.boff, B,
-                                           n->ny, n->nx, n->act[0]);
+    const float *w = n->params + L.woff, *bias = n->params + L.boff;
+    const float2* F = (const float2*)eim;
+    const dim3 grid((n->nx + 63) / 64, (n->ny + C1_TH - 1) / C1_TH, B);
+    if (n->cin0 == 3) {
+      k_eim_scale_part<<<dim3(ES_SLICES, B), 256, 0, st>>>(F, D, n->espart);
+      k_conv1_fwd<3><<<grid, 256, 0, st>>>(eps, F, n->espart, w, bias, n->ny, n->nx, n->x0, n->act[0]);
+    } else {
+      k_conv1_fwd<1><<<grid, 256, 0, st>>>(eps, F, n->espart, w, bias, n->ny, n->nx, n->x0, n->act[0]);
+    }
   }
   for (int l = 1; l < NL; ++l) {
     const CnnLayer& L = n->L[l];

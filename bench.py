@@ -49,7 +49,7 @@ HBM_PEAK_GBS = 8000.0
 # (FETCH_SIZE, then WRITE_SIZE, calibrated on a 1 GiB device copy) over this
 # workload, as recorded in the profile summary beside the commands that took
 # them; valid only for the kernel sources and batch they were taken with.
-TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_matvec_dot_pca_c4_480x240_b25.md")
+TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "k_sweep_pca_c4_480x240_b25.md")
 
 
 def measured_traffic():
@@ -64,27 +64,14 @@ def measured_traffic():
     return None
 
 
-def _function_text(src, head):
-    """The text of the function whose definition starts at `head` (its
-    template line included), up to its closing brace at column 0."""
-    a = src.index(head)
-    a = src.rfind("template <", 0, a) if "template <" in src[max(0, a - 80):a] else a
-    return src[a:src.index("\n}\n", a) + 3]
-
-
 def kernel_sources_hash():
     """First 16 hex digits of the SHA-256 of the dominant sweep's own source:
-    k_matvec_dot and block_dots (csrc/solver_kernels.h) and the headers they
-    build on (csrc/op.h, csrc/common.h)."""
+    k_sweep (csrc/sweep.h) and the headers it builds on (csrc/op.h,
+    csrc/common.h)."""
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_1902_00090_amd", "csrc")
-    with open(os.path.join(csrc, "solver_kernels.h")) as fh:
-        src = fh.read()
-    for head in ("__device__ __forceinline__ void block_dots(",
-                 "__global__ __launch_bounds__(DD_BLOCK) void k_matvec_dot("):
-        h.update(_function_text(src, head).encode())
-    for f in ("op.h", "common.h"):
+    for f in ("sweep.h", "op.h", "common.h"):
         with open(os.path.join(csrc, f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()[:16]
@@ -99,21 +86,17 @@ def first_below(h, thr):
     return int(idx[0]) + 1 if len(idx) else None
 
 
-def arnoldi_bytes(D, iters, m, k, passes=1, fused=False):
+def arnoldi_bytes(D, iters, m, k, passes=1):
     """Algorithmic HBM bytes of `iters` complex64 Arnoldi steps with restart m
-    and k augmenting vectors.  One sweep per step (fused, one Gram-Schmidt
-    pass): step j reads the k+j+1 basis vectors and A q_j, writes q_{j+1} and
-    A q_{j+1}, and reads eps: 8 D (k+j+1) + 28 D.  Two sweeps: the stencil
-    input, eps and w (20 D), the basis and w for the dots and again for the
-    update, and q_{j+1}: 16 D (k+j) + 44 D; each further Gram-Schmidt pass
-    adds 16 D (k+j) + 24 D."""
+    and k augmenting vectors: step j reads the k+j+1 basis vectors and A q_j,
+    writes q_{j+1} and A q_{j+1}, and reads eps, 8 D (k+j+1) + 28 D; a second
+    Gram-Schmidt pass reads the basis again and rewrites A q_j, 8 D (k+j+1) +
+    16 D."""
     full, rem = divmod(int(iters), m)
     def cyc(n):       # sum over j < n of (k + j)
         return n * k + n * (n - 1) // 2
     sj = full * cyc(m) + cyc(rem)
-    if fused and passes == 1:
-        return 8 * D * sj + 36 * D * iters
-    return (16 * D * sj + 44 * D * iters) + (passes - 1) * (16 * D * sj + 24 * D * iters)
+    return 8 * D * sj + 36 * D * iters + (passes - 1) * (8 * D * sj + 24 * D * iters)
 
 
 def cnn_flops_per_instance(net):
@@ -890,14 +873,11 @@ def c2_leg(args, torch, W, U, ref):
     b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
     out = {"instance": "grating seed 1000, 480x240", "err_factor": ref["err_factor"],
            "kappa_1_estimate": ref["kappa_1"], "sparse_lu_seconds": round(ref["lu_seconds"], 2)}
-    # plain and augmented with the two-sweep Arnoldi step, then both with the
-    # one-sweep step (which moves each basis vector once and takes two
-    # launches per step: the faster of the two for one problem alone)
-    for aug, fused in ((False, False), (True, False), (False, True), (True, True)):
+    for aug in (False, True):
         if aug and U is None:
             continue
         s = Solver([op], restart=args.restart, kmax=args.k if aug else 0, cgs_passes=args.cgs,
-                   use_graph=True, fused=fused)
+                   use_graph=True)
         if aug:
             s.set_subspace([U])
         s.solve([b], tol=args.tol, maxit=args.maxit)       # warm-up (graph capture)
@@ -914,7 +894,7 @@ def c2_leg(args, torch, W, U, ref):
                                    "rel_res_true": inf["rel_res_true"],
                                    "error_vs_sparse_lu": rel_err(x.cpu().numpy(), ref["x"])}
         s.close()
-        out[("augmented" if aug else "plain") + ("_one_sweep" if fused else "")] = res
+        out["augmented" if aug else "plain"] = res
     log(f"C2: {out}")
     return out
 
@@ -940,7 +920,7 @@ def main():
     ap.add_argument("--maxit", type=int, default=30000)
     ap.add_argument("--cgs", type=int, default=1, help="Gram-Schmidt passes (1 or 2)")
     ap.add_argument("--fused", action="store_true",
-                    help="one sweep per Arnoldi step (the slower option, for measurement)")
+                    help="one sweep per Arnoldi step also where it is not the default")
     ap.add_argument("--plain-batches", type=int, default=2)
     ap.add_argument("--first-cycle-batches", type=int, default=0,
                     help="batches also solved with the basis for the first cycle only")
@@ -1223,7 +1203,7 @@ def main():
     ms_k, launches_k, bytes_k = ks[name]
     achieved = bytes_k / (ms_k * 1e-3) / 1e9 if ms_k > 0 else 0.0
     kname = {"matvec_dots": "k_matvec_dot", "second_pass": "k_update_dot",
-             "update_norm": "k_update_norm", "fused_sweep": "k_fused_sweep"}[name]
+             "update_norm": "k_update_norm", "fused_sweep": "k_sweep"}[name]
     traffic = None
     trec = measured_traffic()
     if (trec is not None and trec["kernel"] == kname and args.batch == trec["batch"]

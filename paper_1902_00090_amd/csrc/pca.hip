@@ -32,7 +32,7 @@ using cd = std::complex<double>;
 // B x B blocks of 16 x 16; 32 elements a stage, the next stage's loads in
 // flight during the products.  Bound by the matrix cores: each LDS value feeds
 // 16 B products.  Measured for 1000 snapshots of 115,200 elements: 30.2 ms with
-// a 2 x 2 block of FP64 vector sums a thread, 8 here (0.46 TFLOP; a library
+// a 2 x 2 block of FP64 vector sums a thread, 8.9 here (0.46 TFLOP; a library
 // product of 4096 x 4096 FP64 matrices runs at 64 TFLOP/s).
 typedef double v4d __attribute__((ext_vector_type(4)));
 #define PE 32
@@ -170,7 +170,10 @@ __global__ __launch_bounds__(256) void k_pca_gram_reduce(const double2* __restri
 __global__ __launch_bounds__(256) void k_field_combine(const float2* __restrict__ F, int M, int D,
                                                        const double2* __restrict__ coef, int R,
                                                        int step, int window,
+                                                       const int* __restrict__ bad,
                                                        float2* __restrict__ out) {
+  // a field that is not finite makes every target so, as its zero coefficients do
+  if (bad && *bad) step = 0;
   const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
   const int r0 = blockIdx.y * 32, e0 = blockIdx.x * 128 + (threadIdx.x >> 6) * 32;
   int lo = 0, hi = M;
@@ -241,6 +244,160 @@ __global__ __launch_bounds__(256) void k_field_combine(const float2* __restrict_
         if (r < R && e < D)
           out[(size_t)r * D + e] = make_float2((float)ar[i][j][v], (float)ai[i][j][v]);
       }
+}
+
+// Coefficients of local_pca_targets, one workgroup per step s: the eigenvectors of
+// the Gram matrix G_ab = <F_a, F_b> / (||F_a|| ||F_b||) of the M <= 32 fields of the
+// step's window, by Jacobi rotations in LDS, M / 2 disjoint ones at a time (the
+// circle method's rounds).  A round's rotations are formed by one thread each; then
+// every thread transforms the 2 x 2 blocks G[{p,q},{r,t}] on both sides, in place,
+// and the pairs of columns of W.  Sweeps go on until one meets no element above
+// rounding.  With G w_j = theta_j w_j, u_j = sum_m w_mj F_m / (||F_m|| sigma_j) has
+// u_j^H F_s / ||F_s|| = sigma_j conj(w_sj), and target j is the combination of the
+// fields with coefficients w_mj conj(w_sj) / ||F_m||.  A chain of latencies: about
+// 130 rounds of two barriers each for 17 fields, all steps at once; 32 steps 139 us
+// (on the host one after the other 520 us, with two copies and waits).
+#define PJ_MAX 32
+__global__ __launch_bounds__(256) void k_window_coefs(const double2* __restrict__ G0, int S,
+                                                      int window, int k,
+                                                      double2* __restrict__ coef) {
+  __shared__ double2 G[PJ_MAX][PJ_MAX + 1], W[PJ_MAX][PJ_MAX + 1];   // columns over the banks
+  __shared__ double2 ph[PJ_MAX / 2];       // conj of the phase of G_pq
+  __shared__ double cs[PJ_MAX / 2], sn[PJ_MAX / 2], nrm[PJ_MAX];
+  __shared__ int pr[PJ_MAX / 2][2];        // the round's pairs
+  __shared__ int again, broken, order[PJ_MAX];
+  const int t = threadIdx.x, s = blockIdx.x;
+  const int lo = max(0, s - window), hi = min(S, s + window + 1), M = hi - lo, N = (M + 1) & ~1;
+  const int kk = min(k, M);
+  if (t == 0) broken = 0;
+  if (t < M) {
+    const double g = G0[(size_t)(lo + t) * S + lo + t].x;
+    nrm[t] = sqrt(g < 1e-300 ? 1e-300 : g);
+  }
+  __syncthreads();
+  // an odd M gets a row and a column of zeros, which no rotation touches
+  for (int i = t; i < N * N; i += 256) {
+    const int a = i / N, b = i - a * N;
+    double2 g = make_double2(0.0, 0.0);
+    if (a < M && b < M) {
+      g = G0[(size_t)(lo + a) * S + lo + b];
+      if (!isfinite(g.x) || !isfinite(g.y)) broken = 1;
+      const double q = nrm[a] * nrm[b];
+      g = make_double2(g.x / q, g.y / q);
+    }
+    G[a][b] = g;
+    W[a][b] = make_double2(a == b ? 1.0 : 0.0, 0.0);
+  }
+  __syncthreads();
+  const double tiny = 0x1p-54 * M;          // against the trace
+  const int np = N / 2, n = N - 1;
+  // this thread's items of a round: block (u, v) of G, or row u of pair v of W
+  constexpr int NIT = (PJ_MAX / 2) * (PJ_MAX / 2 + PJ_MAX) / 256;
+  int iu[NIT], iv[NIT];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int i = t + 256 * it, l = i - np * np;
+    iu[it] = l < 0 ? i / np : l % N;
+    iv[it] = l < 0 ? i % np : l / N;
+  }
+  for (int sweep = 0; sweep < 30 && !broken; ++sweep) {
+    if (t == 0) again = 0;
+    for (int r = 0; r < n; ++r) {
+      __syncthreads();
+      if (t < np) {
+        // pair t of round r of the circle method on N players
+        int p = r + t, q = r - t;
+        p = t == 0 ? r : (p >= n ? p - n : p);
+        q = t == 0 ? n : (q < 0 ? q + n : q);
+        if (p > q) {
+          const int x = p;
+          p = q;
+          q = x;
+        }
+        const double2 g = G[p][q];
+        const double a = sqrt(g.x * g.x + g.y * g.y);
+        double c = 1.0, sv = 0.0;
+        double2 e = make_double2(1.0, 0.0);
+        if (a > 1e-40) {
+          if (a > tiny) again = 1;
+          const double ia = 1.0 / a, tau = 0.5 * (G[q][q].x - G[p][p].x) * ia;
+          const double tn = copysign(1.0, tau) / (fabs(tau) + sqrt(1.0 + tau * tau));
+          c = 1.0 / sqrt(1.0 + tn * tn);
+          sv = tn * c;
+          e = make_double2(g.x * ia, -g.y * ia);
+        }
+        cs[t] = c;
+        sn[t] = sv;
+        ph[t] = e;
+        pr[t][0] = p;
+        pr[t][1] = q;
+      }
+      __syncthreads();
+      // columns: x' = c x - s e y, y' = s x + c e y, with e = conj(phase)
+#pragma unroll
+      for (int it = 0; it < NIT; ++it) {
+        const int i = t + 256 * it, u = iu[it], v = iv[it];
+        if (i >= np * np + N * np) break;
+        const int a = pr[v][0], b = pr[v][1];
+        if (i < np * np) {
+          const int p = pr[u][0], q = pr[u][1];
+          const double c1 = cs[u], s1 = sn[u], c2 = cs[v], s2 = sn[v];
+          const double2 e1 = ph[u], e2 = ph[v];
+          double2 z[2][2] = {{G[p][a], G[p][b]}, {G[q][a], G[q][b]}};
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const double2 x = z[h][0], y = make_double2(e2.x * z[h][1].x - e2.y * z[h][1].y,
+                                                        e2.x * z[h][1].y + e2.y * z[h][1].x);
+            z[h][0] = make_double2(c2 * x.x - s2 * y.x, c2 * x.y - s2 * y.y);
+            z[h][1] = make_double2(s2 * x.x + c2 * y.x, s2 * x.y + c2 * y.y);
+          }
+#pragma unroll
+          for (int h = 0; h < 2; ++h) {
+            const double2 x = z[0][h], y = make_double2(e1.x * z[1][h].x + e1.y * z[1][h].y,
+                                                        e1.x * z[1][h].y - e1.y * z[1][h].x);
+            z[0][h] = make_double2(c1 * x.x - s1 * y.x, c1 * x.y - s1 * y.y);
+            z[1][h] = make_double2(s1 * x.x + c1 * y.x, s1 * x.y + c1 * y.y);
+          }
+          if (u == v) {
+            z[0][1] = z[1][0] = make_double2(0.0, 0.0);
+            z[0][0].y = z[1][1].y = 0.0;
+          }
+          G[p][a] = z[0][0];
+          G[p][b] = z[0][1];
+          G[q][a] = z[1][0];
+          G[q][b] = z[1][1];
+        } else {
+          const double2 x = W[u][a], z = W[u][b], e = ph[v];
+          const double2 y = make_double2(e.x * z.x - e.y * z.y, e.x * z.y + e.y * z.x);
+          W[u][a] = make_double2(cs[v] * x.x - sn[v] * y.x, cs[v] * x.y - sn[v] * y.y);
+          W[u][b] = make_double2(sn[v] * x.x + cs[v] * y.x, sn[v] * x.y + cs[v] * y.y);
+        }
+      }
+    }
+    __syncthreads();
+    if (again == 0) break;
+    __syncthreads();
+  }
+  __syncthreads();
+  if (t < M) {   // rank of eigenvalue t: those before it in falling order
+    int before = 0;
+    for (int i = 0; i < M; ++i) before += G[i][i].x > G[t][t].x || (G[i][i].x == G[t][t].x && i < t);
+    order[before] = t;
+  }
+  __syncthreads();
+  const double top = broken ? 0.0 : G[order[0]][order[0]].x;
+  for (int i = t; i < S * k; i += 256) {
+    const int m = i / k - lo, j = i - (m + lo) * k;
+    double2 v = make_double2(0.0, 0.0);
+    if (m >= 0 && m < M && j < kk && !broken) {
+      const int o = order[j];
+      if (G[o][o].x > 1e-24 * fmax(top, 1e-300)) {
+        const double2 a = W[m][o], b = W[s - lo][o];
+        v = make_double2((a.x * b.x + a.y * b.y) / nrm[m], (a.y * b.x - a.x * b.y) / nrm[m]);
+      }
+    }
+    coef[((size_t)(m + lo) * S + s) * k + j] = v;
+  }
 }
 
 // ------------------------------------------------------- device Lanczos ----
@@ -677,8 +834,9 @@ dd_status gram_host(const float2* V, int k, int D, const double2* f, std::vector
 // whether all of it is finite.  Tiles of 64 x 64 from 49 rows on (below, half of
 // one would be padding), the elements in as many slices (of 2048 workgroups at
 // most) as leave the last round of resident workgroups, three a compute unit,
-// fullest.
-static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, bool* finite,
+// fullest.  With finite = nullptr the call does not wait: the flag stays on the
+// device, behind G, and the caller keeps bpart until the kernels are done.
+static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, DevBuf& bpart, bool* finite,
                              hipStream_t stream) {
   const int tile = M > 48 ? 64 : 32;
   const int nta = (M + tile - 1) / tile, ntiles = nta * (nta + 1) / 2;
@@ -693,7 +851,6 @@ static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, bool* fi
   }
   const int per = ((D + nslices - 1) / nslices + PE - 1) / PE * PE;
   nslices = (D + per - 1) / per;
-  DevBuf bpart;
   DD_HIP_CHECK(hipMalloc(&bpart.p, sizeof(double2) * (size_t)nslices * ntiles * tile * tile));
   DD_HIP_CHECK(hipMalloc(&bG.p, sizeof(double2) * M * M + sizeof(int)));
   double2 *part = bpart.as<double2>(), *G = bG.as<double2>();
@@ -704,6 +861,7 @@ static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, bool* fi
   k_pca_gram_reduce<<<dim3(ntiles, tile * tile / 64), 256, 0, stream>>>(part, M, tile, nslices, G,
                                                                         bad);
   DD_HIP_CHECK(hipGetLastError());
+  if (!finite) return DD_OK;
   int hbad = 0;
   DD_HIP_CHECK(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, stream));
   DD_HIP_CHECK(hipStreamSynchronize(stream));
@@ -714,8 +872,8 @@ static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, bool* fi
 // The same on the host.
 static dd_status gram_rows(const float2* F, int M, int D, std::vector<cd>& G, bool* finite,
                            hipStream_t stream) {
-  DevBuf bG;
-  dd_status rc = gram_device(F, M, D, bG, finite, stream);
+  DevBuf bG, bpart;
+  dd_status rc = gram_device(F, M, D, bG, bpart, finite, stream);
   if (rc != DD_OK) return rc;
   G.resize((size_t)M * M);
   static_assert(sizeof(cd) == sizeof(double2), "complex layout");
@@ -761,13 +919,13 @@ extern "C" dd_status pca_build(const void* Sv, int M, int D, int k, void* Uv, do
   float2* U = (float2*)Uv;
   // G_ab = <s_a, s_b>; with X = [s_1 .. s_M] (D x M), G = X^H X and the left
   // singular vectors are u_i = X w_i / sigma_i for X^H X w_i = sigma_i^2 w_i.
-  DevBuf bG, bcoef, bT;
+  DevBuf bG, bpart, bcoef, bT;
   bool finite = true;
   std::vector<double> theta;
   std::vector<cd> W;
   dd_status rc = DD_OK;
   if (M >= 128) {
-    rc = gram_device(S, M, D, bG, &finite, stream);
+    rc = gram_device(S, M, D, bG, bpart, &finite, stream);
     if (rc == DD_OK && finite) rc = lanczos_device(bG.as<double2>(), M, k, theta, W, stream);
   } else {
     std::vector<cd> hG;
@@ -795,7 +953,8 @@ extern "C" dd_status pca_build(const void* Sv, int M, int D, int k, void* Uv, do
   DD_HIP_CHECK(hipMalloc(&bcoef.p, sizeof(double2) * M * k));
   double2* coef = bcoef.as<double2>();
   DD_HIP_CHECK(hipMemcpyAsync(coef, hc.data(), sizeof(double2) * M * k, hipMemcpyHostToDevice, stream));
-  k_field_combine<<<dim3((D + 127) / 128, (k + 31) / 32), 256, 0, stream>>>(S, M, D, coef, k, 0, 0, U);
+  k_field_combine<<<dim3((D + 127) / 128, (k + 31) / 32), 256, 0, stream>>>(
+      S, M, D, coef, k, 0, 0, nullptr, U);
   DD_HIP_CHECK(hipGetLastError());
   DD_HIP_CHECK(hipStreamSynchronize(stream));
   // one Cholesky QR pass restores orthonormality lost to FP32 storage
@@ -831,6 +990,23 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
     return DD_EINVAL;
   }
   const float2* F = (const float2*)Fv;
+  const dim3 grid((D + 127) / 128, (S * k + 31) / 32);
+  if (std::min((long long)S, 2ll * window + 1) <= PJ_MAX) {
+    // the windows' problems fit a workgroup's LDS: nothing leaves the device.
+    // 32 fields of 480 x 240, windows of 17: 380 us, on the host's way below 815
+    DevBuf bG, bpart, bcoef;
+    DD_HIP_CHECK(hipMalloc(&bcoef.p, sizeof(double2) * (size_t)S * S * k));
+    dd_status rc = gram_device(F, S, D, bG, bpart, nullptr, stream);
+    if (rc != DD_OK) return rc;
+    const double2* G = bG.as<double2>();
+    double2* coef = bcoef.as<double2>();
+    k_window_coefs<<<S, 256, 0, stream>>>(G, S, std::min(window, S), k, coef);
+    k_field_combine<<<grid, 256, 0, stream>>>(F, S, D, coef, S * k, k, std::min(window, S),
+                                              (const int*)(G + (size_t)S * S), (float2*)Tv);
+    DD_HIP_CHECK(hipGetLastError());
+    DD_HIP_CHECK(hipStreamSynchronize(stream));
+    return DD_OK;
+  }
   // trajectory Gram matrix of the normalised fields (normalisation applied here)
   std::vector<cd> G0;
   bool finite = true;
@@ -866,9 +1042,8 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
   DD_HIP_CHECK(hipMalloc(&bcoef.p, sizeof(double2) * hc.size()));
   double2* coef = bcoef.as<double2>();
   DD_HIP_CHECK(hipMemcpyAsync(coef, hc.data(), sizeof(double2) * hc.size(), hipMemcpyHostToDevice, stream));
-  // a field that is not finite makes every target so, as its zero coefficients do
-  k_field_combine<<<dim3((D + 127) / 128, (S * k + 31) / 32), 256, 0, stream>>>(
-      F, S, D, coef, S * k, finite ? k : 0, std::min(window, S), (float2*)Tv);
+  k_field_combine<<<grid, 256, 0, stream>>>(F, S, D, coef, S * k, finite ? k : 0,
+                                            std::min(window, S), nullptr, (float2*)Tv);
   DD_HIP_CHECK(hipGetLastError());
   DD_HIP_CHECK(hipStreamSynchronize(stream));
   return DD_OK;

@@ -77,6 +77,45 @@ def test_targets_at_tile_edges(S, D, window, k):
     assert np.abs(T - want).max() <= (2.0 ** -24 + 1e-7) * scale
 
 
+@pytest.mark.parametrize("S,window,k", [(2, 1, 2), (3, 1, 4), (31, 15, 5), (32, 31, 32), (32, 40, 20),
+                                        (33, 15, 31), (33, 16, 12), (40, 12, 25)])
+def test_targets_of_windows_up_to_32_fields(S, window, k):
+    """Windows of 1 to 32 fields, odd and even, are solved on the device; of 33,
+    on the host.  Singular values of a window within a factor of 30 or so: the
+    bound of the test above."""
+    import torch
+    from paper_1902_00090_amd import local_pca_targets
+    rng = np.random.default_rng(S * 100 + window)
+    D = 400
+    Q, _ = np.linalg.qr(W.random_complex(rng, (D, S)))
+    R, _ = np.linalg.qr(W.random_complex(rng, (S, S)))
+    F = (Q * np.geomspace(1.0, 0.1, S)) @ R
+    F = (F * rng.uniform(0.1, 10.0, S)).T.astype(np.complex64)
+    T = local_pca_targets(torch.tensor(F.copy(), device="cuda"), window, k).cpu().numpy()
+    F = F.astype(np.complex128)
+    want = ocnn.local_pca_targets(F / np.linalg.norm(F, axis=1, keepdims=True), window, k)
+    assert np.abs(T - want).max() <= (2.0 ** -24 + 1e-7) * np.abs(want).max()
+
+
+def test_targets_of_degenerate_and_broken_windows():
+    """Equal fields (a window of rank one: its one target is the field, the others
+    vanish), zero fields (all targets vanish), and a field that is not finite (no
+    target is finite where it is not)."""
+    import torch
+    from paper_1902_00090_amd import local_pca_targets
+    rng = np.random.default_rng(5)
+    f = W.random_complex(rng, 300).astype(np.complex64)
+    F = np.tile(f, (7, 1))
+    T = local_pca_targets(torch.tensor(F, device="cuda"), 2, 4).cpu().numpy()
+    unit = f.astype(np.complex128) / np.linalg.norm(f)
+    assert np.abs(T[:, 0] - unit).max() <= 1e-6 and np.abs(T[:, 1:]).max() <= 1e-6
+    assert not local_pca_targets(torch.zeros((5, 64), dtype=torch.complex64, device="cuda"), 1,
+                                 2).cpu().numpy().any()
+    F[3, 17] = np.inf
+    T = local_pca_targets(torch.tensor(F, device="cuda"), 2, 4).cpu().numpy()
+    assert not np.isfinite(T[:, :, 17]).any()
+
+
 @pytest.mark.parametrize("M", [90, 200])
 def test_basis_signs_do_not_depend_on_rounding(M):
     """The phase of a basis vector is fixed by the iteration's start, so that

@@ -150,10 +150,13 @@ __global__ __launch_bounds__(64) void k_eim_bound(const EimDesc* __restrict__ de
 // Inverse iteration from the shift, one thread per column.  The pivots' inverses
 // are formed once (the only divisions); a sweep is then one fused multiply-add a
 // row.  Rows are taken eight at a time so that their loads are in flight
-// together.  Bound by the traffic of its two arrays, which exceed the L2.
+// together.  Bound by the traffic of its two arrays, which exceed the L2 (with the
+// vector in LDS one wave fits a compute unit: 548 us against 360 for 64 problems of
+// 480 x 240).  The vector is kept in the output array, whose complex64 is as large,
+// until the field is assembled: it costs no scratch to allocate and free (a call on
+// those 64 problems 1000 us, with scratch for it 1270).
 #define DD_EIM_COLS 64
 __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __restrict__ desc,
-                                                  double* __restrict__ phi,
                                                   double* __restrict__ piv,
                                                   double* __restrict__ mu,
                                                   double2* __restrict__ jp) {
@@ -163,7 +166,7 @@ __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __rest
   const int nx = d.nx, ny = d.ny;
   const double h2 = 1.0 / (d.dx * d.dx), w2 = d.omega * d.omega, e2 = h2 * h2;
   const float* eps = d.eps + ix;
-  double* ph = phi + d.off2 + ix;
+  double* ph = (double*)d.F + ix;
   double* pv = piv + d.off2 + ix;
   const double sigma = mu[d.off1 + ix];
   constexpr int U = 8;
@@ -390,27 +393,31 @@ __global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ des
 
 // ------------------------------------------------------ field (step 3) ----
 __global__ __launch_bounds__(256) void k_eim_assemble(const EimDesc* __restrict__ desc,
-                                                      const double* __restrict__ phi,
                                                       const double2* __restrict__ amp) {
   const EimDesc d = desc[blockIdx.y];
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= d.nx * d.ny) return;
   const int ix = e % d.nx;
   const double2 a = amp[d.off1 + ix];
-  const double v = phi[d.off2 + e];
+  const double v = ((const double*)d.F)[e];
   d.F[e] = make_float2((float)(a.x * v), (float)(a.y * v));
 }
 
 }  // namespace
 
-// Scratch layout of one call: phi and inverse pivots (D doubles each); mu (nx
-// doubles; the shifts until the modes are known); j, the finished rows of the
-// line system (five values), amplitude (nx complex each); then the descriptor
-// table.  Every word is written by the
-// kernels before it is read, so nothing needs clearing between calls.
+// Scratch layout of one call: inverse pivots (D doubles); mu (nx doubles; the
+// shifts until the modes are known); j, the finished rows of the line system (five
+// values), amplitude (nx complex each); then the descriptor table.  Every word is
+// written by the kernels before it is read, so nothing needs clearing between
+// calls.
+static size_t even(size_t n) { return (n + 1) & ~(size_t)1; }   // 16-byte alignment for what follows
+static size_t eim_used_bytes(size_t s2, size_t s1, int nb) {
+  return sizeof(double) * (even(s2) + even(s1)) + sizeof(double2) * 7 * s1 + sizeof(EimDesc) * nb;
+}
+// The size that a call is charged with where the caller or the library provides the
+// scratch: with D doubles more, which the modes took before they moved to F.
 static size_t eim_scratch_bytes(size_t s2, size_t s1, int nb) {
-  const size_t s1p = (s1 + 1) & ~(size_t)1;   // keeps the complex arrays 16-byte aligned
-  return sizeof(double) * (2 * s2 + s1p) + sizeof(double2) * 7 * s1 + sizeof(EimDesc) * nb;
+  return sizeof(double) * (2 * s2 + even(s1)) + sizeof(double2) * 7 * s1 + sizeof(EimDesc) * nb;
 }
 
 // Validates the arguments and fills the descriptor table; returns the
@@ -453,11 +460,9 @@ static hipError_t eim_run(const std::vector<EimDesc>& hd, size_t s1, int maxnx, 
   const int nb = (int)hd.size();
   size_t s2 = 0;
   for (const auto& d : hd) s2 += (size_t)d.nx * d.ny;
-  const size_t s1p = (s1 + 1) & ~(size_t)1;
-  double* phi = (double*)ws;
-  double* piv = phi + s2;
-  double* mu = piv + s2;
-  double2* z = (double2*)(mu + s1p);
+  double* piv = (double*)ws;
+  double* mu = piv + even(s2);
+  double2* z = (double2*)(mu + even(s1));
   double2 *jp = z, *amp = z + 6 * s1;
   LineRow* rows = (LineRow*)(z + s1);
   static_assert(sizeof(LineRow) == 5 * sizeof(double2), "five values a row");
@@ -470,9 +475,9 @@ static hipError_t eim_run(const std::vector<EimDesc>& hd, size_t s1, int maxnx, 
     const dim3 gb((maxnx + 15) / 16, nb);
     if (maxny <= 1024) k_eim_bound<true><<<gb, 64, (size_t)maxny * 64, stream>>>(dd, mu);
     else k_eim_bound<false><<<gb, 64, 0, stream>>>(dd, mu);
-    k_eim_modes<<<dim3((maxnx + DD_EIM_COLS - 1) / DD_EIM_COLS, nb), DD_EIM_COLS, 0, stream>>>(dd, phi, piv, mu, jp);
+    k_eim_modes<<<dim3((maxnx + DD_EIM_COLS - 1) / DD_EIM_COLS, nb), DD_EIM_COLS, 0, stream>>>(dd, piv, mu, jp);
     k_eim_line<<<nb, 64, 0, stream>>>(dd, mu, jp, rows, amp);
-    k_eim_assemble<<<dim3((maxD + 255) / 256, nb), 256, 0, stream>>>(dd, phi, amp);
+    k_eim_assemble<<<dim3((maxD + 255) / 256, nb), 256, 0, stream>>>(dd, amp);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -486,8 +491,10 @@ extern "C" dd_status eim_field(const fdfd_op* const* ops, int nb, const void* co
   int maxnx = 0, maxD = 0;
   const size_t bytes = eim_prepare("eim_field", ops, nb, b, F, hd, s1, maxnx, maxD);
   if (bytes == 0) return DD_EINVAL;
+  size_t s2 = 0;
+  for (const auto& d : hd) s2 += (size_t)d.nx * d.ny;
   char* ws = nullptr;
-  DD_HIP_CHECK(hipMalloc((void**)&ws, bytes));
+  DD_HIP_CHECK(hipMalloc((void**)&ws, eim_used_bytes(s2, s1, nb)));
   hipError_t e = eim_run(hd, s1, maxnx, maxD, ws, stream);
   (void)hipFree(ws);
   if (e != hipSuccess) {

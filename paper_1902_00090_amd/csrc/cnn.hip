@@ -515,20 +515,25 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile_s2(GemmArgs a) {
 // tile pair (dz column c for dx = 1 at even x and dx = 2 at odd x, column c + 1
 // for dx = 0 at odd x); dz row w serves dy = 1 of the even row and dy = 2 of
 // the odd row.  The next chunk's patch and weights are loaded while the
-// current chunk's MFMAs run.  The epilogue masks by the ReLU of the layer
-// input.
-#define CT_PS 40   // bf16 per staged pixel: 32 channels + 8 of padding (80-byte stride)
+// current chunk's MFMAs run.  Staging and addresses are those of k_conv_tile.
+// Tile i's weight row r is channel 32 (i / 2) + 8 (r / 4) + 4 (i % 2) + r % 4, so
+// that two tiles leave a lane 8 neighbouring channels of its pixel, read from the
+// mask and written 16 bytes at a time.  The epilogue masks by the ReLU of the layer
+// input.  Bound by the traffic of mask, result and dz: at 480 x 240, batch 32,
+// layer 2 (590 MB) 135 us, layer 3 97; with 80-byte pixels, tested bounds and
+// 8-byte accesses 181 and 128.
 #define BS_TH 8
 #define BS_TW 64
 #define BS_PR 5
-#define BS_PC 34
+#define BS_PC 40                      // staged row: 33 pixels used, a multiple of 8
 template <int MT>
 __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
-  __shared__ __attribute__((aligned(16))) bf16 patch[BS_PR * BS_PC * CT_PS];
-  __shared__ __attribute__((aligned(16))) bf16 wl[9 * 16 * MT * CT_PS];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ __attribute__((aligned(16))) unsigned char patch[BS_PR * BS_PC * 64];
+  __shared__ __attribute__((aligned(16))) unsigned char wl[9 * 16 * MT * 64];
+  const int t0 = threadIdx.x, lane = t0 & 63, wave = __builtin_amdgcn_readfirstlane(t0 >> 6);
   const int x0 = blockIdx.x * BS_TW, y0 = blockIdx.y * BS_TH, b = blockIdx.z;
   const int Hq = a.Hq, Wq = a.Wq, py0 = y0 / 2, px0 = x0 / 2;
+  const int pl = lane & 15, kg = lane >> 4;
   f32x4 acc[2][4][MT];   // [row: even, odd][tile][row tile]
 #pragma unroll
   for (int h = 0; h < 2; ++h)
@@ -536,43 +541,45 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int i = 0; i < MT; ++i) acc[h][j][i] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int kq = 8 * (lane >> 4);
-  constexpr int NPI = BS_PR * BS_PC * 4, NSTG = (NPI + 255) / 256;   // patch items
+  constexpr int NPI = BS_PR * 33 * 4, NSTG = (NPI + 255) / 256;      // patch items
   constexpr int NWI = 9 * 16 * MT * 4, NWS = (NWI + 255) / 256;      // weight items
+  // the descriptor starts at the tile's first dz row and ends with the image
+  const unsigned px2 = 2u * a.Ksrc, row2 = px2 * a.Ws;
+  const __amdgpu_buffer_rsrc_t rS = cnn_rsrc(
+      (const char*)a.src + ((size_t)b * a.Hs + py0) * row2, (size_t)(a.Hs - py0) * row2);
+  const __amdgpu_buffer_rsrc_t rW = cnn_rsrc(a.W, (size_t)9 * 16 * MT * px2);
+  unsigned vs[NSTG];
+  int ls[NSTG];
+#pragma unroll
+  for (int it = 0; it < NSTG; ++it) {
+    const int u = t0 + 256 * it, pix = u >> 2, q = u & 3;
+    const int pr = pix / 33, pc = pix - pr * 33;
+    vs[it] = (px0 + pc < a.Ws) ? pr * row2 + (px0 + pc) * px2 + 16u * q : CT_OUT;
+    ls[it] = cnn_place(pr * BS_PC + pc, q);
+  }
+  const unsigned vw = (t0 >> 2) * px2 + 16u * (t0 & 3);   // weight item t0; 64 rows on per round
+  const int lw = cnn_place(t0 >> 2, t0 & 3);
   u32x4 sv[NSTG], wv[NWS];
   auto fetch = [&](int c0) {
 #pragma unroll
-    for (int it = 0; it < NWS; ++it) {
-      const int u = threadIdx.x + 256 * it;   // (tap, row, quarter)
-      const int tq = u / (16 * MT * 4), rem = u - tq * 16 * MT * 4;
-      wv[it] = u32x4{0u, 0u, 0u, 0u};
-      if (u < NWI)
-        wv[it] = *(const u32x4*)(a.W + ((size_t)tq * a.M + (rem >> 2)) * a.Ksrc + c0 + 8 * (rem & 3));
-    }
+    for (int it = 0; it < NWS; ++it) wv[it] = buf_load16(rW, vw + it * 64 * px2 + 2 * c0, 0);
 #pragma unroll
-    for (int it = 0; it < NSTG; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      const int pix = u >> 2, q = u & 3;
-      const int pr = pix / BS_PC, pc = pix - pr * BS_PC;
-      const int sy = py0 + pr, sx = px0 + pc;   // dz grid
-      sv[it] = u32x4{0u, 0u, 0u, 0u};
-      if (u < NPI && sy < a.Hs && sx < a.Ws)
-        sv[it] = *(const u32x4*)(a.src + ((size_t)(b * a.Hs + sy) * a.Ws + sx) * a.Ksrc + c0 + 8 * q);
-    }
+    for (int it = 0; it < NSTG; ++it) sv[it] = buf_load16(rS, vs[it] + 2 * c0, 0);
   };
+  // operands: dz pixels of column pl (rows and tile pairs are constants away), and
+  // of the column after; weight rows of the even and the odd tiles
+  const int pc0 = cnn_place(pl, kg), pc1 = cnn_place(pl + 1, kg);
+  const int wr = 8 * (pl >> 2) + (pl & 3);
+  const int w0 = cnn_place(wr, kg), w1 = cnn_place(wr + 4, kg);
   fetch(0);
   for (int c0 = 0; c0 < a.Ksrc; c0 += 32) {
     __syncthreads();   // the previous chunk's readers are done
 #pragma unroll
-    for (int it = 0; it < NSTG; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      if (u < NPI) *(u32x4*)(patch + (u >> 2) * CT_PS + 8 * (u & 3)) = sv[it];
-    }
+    for (int it = 0; it < NSTG; ++it)
+      if (t0 + 256 * it < NPI) *(u32x4*)(patch + ls[it]) = sv[it];
 #pragma unroll
-    for (int it = 0; it < NWS; ++it) {
-      const int u = threadIdx.x + 256 * it;
-      if (u < NWI) *(u32x4*)(wl + (u >> 2) * CT_PS + 8 * (u & 3)) = wv[it];
-    }
+    for (int it = 0; it < NWS; ++it)
+      if (t0 + 256 * it < NWI) *(u32x4*)(wl + lw + it * 64 * 64) = wv[it];
     __syncthreads();
     if (c0 + 32 < a.Ksrc) fetch(c0 + 32);
     // dz rows w (r = 0) and w + 1 (r = 1) of the patch
@@ -581,9 +588,9 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
       bf16x8 bc[2], bn[2];   // dz columns c and c + 1 of the two tile pairs
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
-        const bf16* pp = patch + ((wave + r) * BS_PC + 16 * jj + (lane & 15)) * CT_PS + kq;
-        bc[jj] = *(const bf16x8*)pp;
-        bn[jj] = *(const bf16x8*)(pp + CT_PS);
+        const unsigned char* pp = patch + ((wave + r) * BS_PC + 16 * jj) * 64;
+        bc[jj] = *(const bf16x8*)(pp + pc0);
+        bn[jj] = *(const bf16x8*)(pp + pc1);
       }
       // (input row h, dy): r = 0 serves (even, 1) and (odd, 2); r = 1 serves (odd, 0)
 #pragma unroll
@@ -595,8 +602,8 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
           bf16x8 wcur[MT];
 #pragma unroll
           for (int i = 0; i < MT; ++i)
-            wcur[i] = *(const bf16x8*)(wl + ((3 * dy + dx) * 16 * MT + i * 16 + (lane & 15)) *
-                                                CT_PS + kq);
+            wcur[i] = *(const bf16x8*)(wl + ((3 * dy + dx) * 16 * MT + 32 * (i >> 1)) * 64 +
+                                       ((i & 1) ? w1 : w0));
           // dx = 1: even tiles 0, 1 from column c; dx = 2: odd tiles from
           // column c; dx = 0: odd tiles from column c + 1
           const int j0 = (dx == 1) ? 0 : 2;
@@ -612,36 +619,35 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
       }
     }
   }
+  const unsigned m2 = 2u * a.M;
+  unsigned vo[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int x = x0 + 2 * (16 * (j & 1) + pl) + (j >> 1);
+    vo[j] = x < Wq ? x * m2 + 16u * kg : CT_OUT;
+  }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
     const int y = y0 + 2 * wave + h;
     if (y >= Hq) break;
-    u32x2 mk[4][MT];
+    const size_t rowp = ((size_t)b * Hq + y) * Wq;
+    const __amdgpu_buffer_rsrc_t rM = cnn_rsrc((const char*)a.mask + rowp * m2, (size_t)Wq * m2);
+    const __amdgpu_buffer_rsrc_t rO = cnn_rsrc((const char*)a.out + rowp * m2, (size_t)Wq * m2);
+    bf16x8 mk[4][MT / 2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int x = x0 + 2 * (16 * (j & 1) + (lane & 15)) + (j >> 1);
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        mk[j][i] = u32x2{0u, 0u};
-        if (x < Wq)
-          mk[j][i] = *(const u32x2*)(a.mask + (((size_t)b * Hq + y) * Wq + x) * a.M + i * 16 +
-                                     4 * (lane >> 4));
+      for (int i = 0; i < MT / 2; ++i) mk[j][i] = __builtin_bit_cast(bf16x8, buf_load16(rM, vo[j] + 64 * i, 0));
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < MT / 2; ++i) {
+        bf16x8 hv;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+          hv[q] = (bf16)(((float)mk[j][i][q] > 0.f) ? acc[h][j][2 * i + (q >> 2)][q & 3] : 0.f);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hv), rO, vo[j] + 64 * i, 0, 0);
       }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int x = x0 + 2 * (16 * (j & 1) + (lane & 15)) + (j >> 1);
-      if (x >= Wq) continue;
-      const size_t p = ((size_t)b * Hq + y) * Wq + x;
-#pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        const bf16x4 m4 = __builtin_bit_cast(bf16x4, mk[j][i]);
-        bf16 hv[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) hv[q] = (bf16)(((float)m4[q] > 0.f) ? acc[h][j][i][q] : 0.f);
-        *(u32x2*)(a.out + p * a.M + i * 16 + 4 * (lane >> 4)) = __builtin_bit_cast(u32x2, hv);
-      }
-    }
   }
 }
 

@@ -189,6 +189,15 @@ __device__ __forceinline__ int cnn_place(int p, int q) {
   return p * 64 + ((q ^ ((p >> 1) & 3)) << 4);
 }
 
+// LDS item of weight row p (of a tap's multiple of 32): row r of tile i is result
+// channel 32 (i / 2) + 8 (r / 4) + 4 (i % 2) + r % 4, so that two tiles leave a lane
+// 8 neighbouring channels of its pixel, read from the mask and written 16 bytes
+// at a time (480 x 240: layer 2 at batch 64 213 us, with 8 bytes 238; layer 4 137 and
+// 151; layer 6 backward at batch 32 138 and 162).
+__device__ __forceinline__ int cnn_wrow(int p) {
+  return (p & ~31) | ((p & 4) << 2) | ((p & 24) >> 1) | (p & 3);
+}
+
 template <int MT, int TH, bool BWD>
 __global__ __launch_bounds__(64 * TH) void k_conv_tile(GemmArgs a) {
   constexpr int NT = 64 * TH, PH = TH + 2, RP = NT / 256;   // RP patch rows staged at a time
@@ -228,7 +237,7 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile(GemmArgs a) {
   int lb[3];
 #pragma unroll
   for (int dx = 0; dx < 3; ++dx) lb[dx] = cnn_place(wave * CT_PW + pl + dx, kg);
-  const int lw = cnn_place(pl, kg);
+  const int lw = cnn_place(pl, kg), lws = cnn_place(cnn_wrow(t0 >> 2), t0 & 3);
   // thread t0 stages weight item (tap, row, quarter) t0 + NT it
   const unsigned tap2 = (unsigned)a.M * px2;              // bytes of a tap's weights
   const __amdgpu_buffer_rsrc_t rW = cnn_rsrc((const char*)a.W + (size_t)m0 * px2,
@@ -260,7 +269,7 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile(GemmArgs a) {
     if (c2 > 0) __syncthreads();                          // the chunk before has been read
 #pragma unroll
     for (int it = 0; it < NWS; ++it)
-      if (t0 + NT * it < NWI) *(u32x4*)(wl + cnn_place(t0 >> 2, t0 & 3) + it * NT * 16) = wv[it];
+      if (t0 + NT * it < NWI) *(u32x4*)(wl + lws + it * NT * 16) = wv[it];
 #pragma unroll
     for (int r = 0; r < PH / RP; ++r) *(u32x4*)(patch + lcol + (r * RP + tr) * CT_PW * 64) = sv[r];
     if (er < PH) *(u32x4*)(patch + ledge) = se;
@@ -290,18 +299,22 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile(GemmArgs a) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int x = x0 + 16 * j + pl;
-    vo[j] = x < Wq ? (unsigned)x * m2 + 2u * m0 + 8u * kg : CT_OUT;
+    vo[j] = x < Wq ? (unsigned)x * m2 + 2u * m0 + 16u * kg : CT_OUT;
   }
-  float4 bias4[MT];
-  u32x2 mk[MT][4];
+  float bq[MT / 2][8];
+  bf16x8 mk[MT / 2][4];
   const __amdgpu_buffer_rsrc_t rM = cnn_rsrc(BWD ? (const char*)a.mask + rowp * m2 : nullptr, BWD ? orow : 0);
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    if (!BWD) bias4[i] = *(const float4*)(a.bias + m0 + i * 16 + 4 * kg);
+  for (int i = 0; i < MT / 2; ++i) {
+    if (!BWD) {
+      const float4* bp = (const float4*)(a.bias + m0 + 32 * i + 8 * kg);
+      const float4 lo = bp[0], hi = bp[1];
+      bq[i][0] = lo.x, bq[i][1] = lo.y, bq[i][2] = lo.z, bq[i][3] = lo.w;
+      bq[i][4] = hi.x, bq[i][5] = hi.y, bq[i][6] = hi.z, bq[i][7] = hi.w;
+    }
     if (BWD)
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        mk[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rM, vo[j], 32 * i, 0);
+      for (int j = 0; j < 4; ++j) mk[i][j] = __builtin_bit_cast(bf16x8, buf_load16(rM, vo[j] + 64 * i, 0));
   }
   const bool fields = !BWD && a.outf;
   const __amdgpu_buffer_rsrc_t rO =
@@ -310,28 +323,28 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile(GemmArgs a) {
   for (int j = 0; j < 4; ++j) {
     const int x = x0 + 16 * j + pl;
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      const int r0 = m0 + i * 16 + 4 * kg;
-      float v[4];
-      if (BWD) {
-        const bf16x4 m4 = __builtin_bit_cast(bf16x4, mk[i][j]);
+    for (int i = 0; i < MT / 2; ++i) {
+      float v[8];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = ((float)m4[q] > 0.f) ? acc[i][j][q] : 0.f;
-      } else {
-        const float bq[4] = {bias4[i].x, bias4[i].y, bias4[i].z, bias4[i].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          v[q] = acc[i][j][q] + bq[q];
+      for (int q = 0; q < 8; ++q) {
+        const float r = acc[2 * i + (q >> 2)][j][q & 3];
+        if (BWD) {
+          v[q] = ((float)mk[i][j][q] > 0.f) ? r : 0.f;
+        } else {
+          v[q] = r + bq[i][q];
           if (a.relu) v[q] = fmaxf(v[q], 0.f);
         }
       }
       if (fields) {
-        if (x < Wq) store_fields(a.outf, a.nreal / 2, Hq * Wq, b, y * Wq + x, r0, v);
-      } else {
-        bf16x4 h;
+        if (x < Wq)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) h[q] = (bf16)v[q];
-        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), rO, vo[j], 32 * i, 0);
+          for (int h = 0; h < 2; ++h)
+            store_fields(a.outf, a.nreal / 2, Hq * Wq, b, y * Wq + x, m0 + 32 * i + 8 * kg + 4 * h, v + 4 * h);
+      } else {
+        bf16x8 h;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) h[q] = (bf16)v[q];
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h), rO, vo[j] + 64 * i, 0, 0);
       }
     }
   }
@@ -391,7 +404,7 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile_s2(GemmArgs a) {
   int lb[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) lb[h] = cnn_place(item(2 * wave, 0) + pl + h, kg);
-  const int lw = cnn_place(pl, kg);
+  const int lw = cnn_place(pl, kg), lws = cnn_place(cnn_wrow(t0 >> 2), t0 & 3);
   const unsigned tap2 = (unsigned)a.M * px2;
   const __amdgpu_buffer_rsrc_t rW = cnn_rsrc((const char*)a.W + (size_t)m0 * px2,
                                              (size_t)NTAP * tap2 - (size_t)m0 * px2);
@@ -414,7 +427,7 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile_s2(GemmArgs a) {
   auto wstore = [&]() {
 #pragma unroll
     for (int it = 0; it < NWS; ++it)
-      if (t0 + NT * it < NWI) *(u32x4*)(wl + cnn_place(t0 >> 2, t0 & 3) + it * NT * 16) = wv[it];
+      if (t0 + NT * it < NWI) *(u32x4*)(wl + lws + it * NT * 16) = wv[it];
   };
   for (unsigned c2 = 0; c2 < px2; c2 += 64) {
     wfetch(0, c2);
@@ -464,39 +477,42 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile_s2(GemmArgs a) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int x = x0 + 16 * j + pl;
-    vo[j] = x < Wq ? (unsigned)x * m2 + 2u * m0 + 8u * kg : CT_OUT;
+    vo[j] = x < Wq ? (unsigned)x * m2 + 2u * m0 + 16u * kg : CT_OUT;
   }
-  float4 bias4[MT];
-  u32x2 mk[MT][2];
+  float bq[MT / 2][8];
+  bf16x8 mk[MT / 2][2];
   const __amdgpu_buffer_rsrc_t rM = cnn_rsrc(BWD ? (const char*)a.mask + rowp * m2 : nullptr, BWD ? orow : 0);
 #pragma unroll
-  for (int i = 0; i < MT; ++i) {
-    if (!BWD) bias4[i] = *(const float4*)(a.bias + m0 + i * 16 + 4 * kg);
+  for (int i = 0; i < MT / 2; ++i) {
+    if (!BWD) {
+      const float4* bp = (const float4*)(a.bias + m0 + 32 * i + 8 * kg);
+      const float4 lo = bp[0], hi = bp[1];
+      bq[i][0] = lo.x, bq[i][1] = lo.y, bq[i][2] = lo.z, bq[i][3] = lo.w;
+      bq[i][4] = hi.x, bq[i][5] = hi.y, bq[i][6] = hi.z, bq[i][7] = hi.w;
+    }
     if (BWD)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        mk[i][j] = __builtin_amdgcn_raw_buffer_load_b64(rM, vo[j], 32 * i, 0);
+      for (int j = 0; j < 2; ++j) mk[i][j] = __builtin_bit_cast(bf16x8, buf_load16(rM, vo[j] + 64 * i, 0));
   }
   const __amdgpu_buffer_rsrc_t rO = cnn_rsrc((const char*)a.out + rowp * m2, orow);
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      bf16x4 h;
-      if (BWD) {
-        const bf16x4 m4 = __builtin_bit_cast(bf16x4, mk[i][j]);
+    for (int i = 0; i < MT / 2; ++i) {
+      bf16x8 h;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) h[q] = (bf16)(((float)m4[q] > 0.f) ? acc[i][j][q] : 0.f);
-      } else {
-        const float bq[4] = {bias4[i].x, bias4[i].y, bias4[i].z, bias4[i].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float v = acc[i][j][q] + bq[q];
+      for (int q = 0; q < 8; ++q) {
+        const float r = acc[2 * i + (q >> 2)][j][q & 3];
+        float v;
+        if (BWD) {
+          v = ((float)mk[i][j][q] > 0.f) ? r : 0.f;
+        } else {
+          v = r + bq[i][q];
           if (a.relu) v = fmaxf(v, 0.f);
-          h[q] = (bf16)v;
         }
+        h[q] = (bf16)v;
       }
-      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, h), rO, vo[j], 32 * i, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h), rO, vo[j] + 64 * i, 0, 0);
     }
   }
 }
@@ -515,10 +531,8 @@ __global__ __launch_bounds__(64 * TH) void k_conv_tile_s2(GemmArgs a) {
 // tile pair (dz column c for dx = 1 at even x and dx = 2 at odd x, column c + 1
 // for dx = 0 at odd x); dz row w serves dy = 1 of the even row and dy = 2 of
 // the odd row.  The next chunk's patch and weights are loaded while the
-// current chunk's MFMAs run.  Staging and addresses are those of k_conv_tile.
-// Tile i's weight row r is channel 32 (i / 2) + 8 (r / 4) + 4 (i % 2) + r % 4, so
-// that two tiles leave a lane 8 neighbouring channels of its pixel, read from the
-// mask and written 16 bytes at a time.  The epilogue masks by the ReLU of the layer
+// current chunk's MFMAs run.  Staging and addresses are those of k_conv_tile, and
+// the order of the weight rows (cnn_wrow).  The epilogue masks by the ReLU of the layer
 // input.  Bound by the traffic of mask, result and dz: at 480 x 240, batch 32,
 // layer 2 (590 MB) 135 us, layer 3 97; with 80-byte pixels, tested bounds and
 // 8-byte accesses 181 and 128.
@@ -558,7 +572,7 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
     ls[it] = cnn_place(pr * BS_PC + pc, q);
   }
   const unsigned vw = (t0 >> 2) * px2 + 16u * (t0 & 3);   // weight item t0; 64 rows on per round
-  const int lw = cnn_place(t0 >> 2, t0 & 3);
+  const int lws = cnn_place(cnn_wrow(t0 >> 2), t0 & 3);
   u32x4 sv[NSTG], wv[NWS];
   auto fetch = [&](int c0) {
 #pragma unroll
@@ -567,10 +581,8 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
     for (int it = 0; it < NSTG; ++it) sv[it] = buf_load16(rS, vs[it] + 2 * c0, 0);
   };
   // operands: dz pixels of column pl (rows and tile pairs are constants away), and
-  // of the column after; weight rows of the even and the odd tiles
-  const int pc0 = cnn_place(pl, kg), pc1 = cnn_place(pl + 1, kg);
-  const int wr = 8 * (pl >> 2) + (pl & 3);
-  const int w0 = cnn_place(wr, kg), w1 = cnn_place(wr + 4, kg);
+  // of the column after; 16 weight rows
+  const int pc0 = cnn_place(pl, kg), pc1 = cnn_place(pl + 1, kg), lw = pc0;
   fetch(0);
   for (int c0 = 0; c0 < a.Ksrc; c0 += 32) {
     __syncthreads();   // the previous chunk's readers are done
@@ -579,7 +591,7 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
       if (t0 + 256 * it < NPI) *(u32x4*)(patch + ls[it]) = sv[it];
 #pragma unroll
     for (int it = 0; it < NWS; ++it)
-      if (t0 + 256 * it < NWI) *(u32x4*)(wl + lw + it * 64 * 64) = wv[it];
+      if (t0 + 256 * it < NWI) *(u32x4*)(wl + lws + it * 64 * 64) = wv[it];
     __syncthreads();
     if (c0 + 32 < a.Ksrc) fetch(c0 + 32);
     // dz rows w (r = 0) and w + 1 (r = 1) of the patch
@@ -602,8 +614,7 @@ __global__ __launch_bounds__(256) void k_bwd_s2_tile(GemmArgs a) {
           bf16x8 wcur[MT];
 #pragma unroll
           for (int i = 0; i < MT; ++i)
-            wcur[i] = *(const bf16x8*)(wl + ((3 * dy + dx) * 16 * MT + 32 * (i >> 1)) * 64 +
-                                       ((i & 1) ? w1 : w0));
+            wcur[i] = *(const bf16x8*)(wl + lw + ((3 * dy + dx) * MT + i) * 16 * 64);
           // dx = 1: even tiles 0, 1 from column c; dx = 2: odd tiles from
           // column c; dx = 0: odd tiles from column c + 1
           const int j0 = (dx == 1) ? 0 : 2;
@@ -1962,10 +1973,10 @@ static dd_status gemm_dispatch(const GemmArgs& a, bool bwd, int ncu, hipStream_t
     // Tall tiles (the halo a smaller share, the weights staged once for twice the
     // rows) with all of up to 64 (128 in tall tiles) channels, where they fill
     // the chip twice; else the most workgroups: 32 channels and 4 rows each.
-    // Measured at 480 x 240, batch 64 (and 1): 32 channels 253, 196, 225 us tall
-    // against 302, 219, 257 (9.1, 7.4, 7.2 against 9.1, 7.0, 7.3); 64 channels 250 us
-    // with all against 256 in halves (14.6 against 10.4); 128 channels 142 us against
-    // 152 in quarters (31 against 10.4).
+    // Measured at 480 x 240, batch 64 (and 1): 32 channels 265, 200, 229 us tall
+    // against 325, 219, 261 (8.4, 6.3, 7.4 against 9.1, 6.7, 7.9); 64 channels 263 us
+    // with all against 274 in halves (13.7 against 9.8); 128 channels 137 us against
+    // 157 in quarters (28.2 against 10.0).
     const long long wide = (long long)((a.Wq + CT_TW - 1) / CT_TW) * a.B;
     const long long tall = wide * ((a.Hq + 7) / 8), flat = wide * ((a.Hq + 3) / 4);
     if (MT == 8 && tall >= 2 * ncu) launch_conv_tile<8, 8>(a, bwd, st);
@@ -1976,10 +1987,10 @@ static dd_status gemm_dispatch(const GemmArgs& a, bool bwd, int ncu, hipStream_t
   }
   if ((!bwd && a.mode == MAP_S2 && !a.outf) || (bwd && a.mode == MAP_UP)) {
     // As above: 64 channels and 8 rows, or 32 and 4.  Measured at 480 x 240, batch
-    // 64 (and 1): layer 2 229 us against 242 (8.0 against 6.5), layer 3 181 against
-    // 185 (10.9 against 7.2); backward at batch 32, layer 6 159 against 175, layer
-    // 5 128 against 139.  Four rows of 64 channels (one workgroup a compute unit)
-    // are slower than either: 305, 227, 223 and 174 us.
+    // 64 (and 1): layer 2 213 us against 245 (6.9 against 6.2), layer 3 174 against
+    // 192 (9.8 against 7.1); backward at batch 32, layer 6 138 against 156, layer
+    // 5 115 against 128.  Four rows of 64 channels (one workgroup a compute unit)
+    // are slower than either: with 8-byte stores 305, 227, 223 and 174 us.
     const long long tall = (long long)((a.Wq + CS_TW - 1) / CS_TW) * ((a.Hq + 7) / 8) * a.B * (MT / 4);
     if (tall >= 2 * ncu) {
       if (bwd) launch_conv_s2<4, 4, 8>(a, st);

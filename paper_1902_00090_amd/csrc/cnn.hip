@@ -806,6 +806,49 @@ __global__ __launch_bounds__(256) void k_conv1_fwd(const float* __restrict__ eps
 }
 
 // --------------------------------------------------- weight gradients ----
+// Waves per SIMD that the weight-gradient kernels' registers are held to: the
+// accumulators, 32 for each block of 8 x 8 in flight, 60 others (left to itself
+// the compiler takes more and one workgroup less is resident: 224 us for layer 4).
+constexpr int wg_waves(int units, int taps, int bpt) {
+  return 512 / (4 * units * taps + 32 * bpt + 60) > 1 ? 512 / (4 * units * taps + 32 * bpt + 60) : 1;
+}
+
+// Stores an 8 x 8 block (r[i]: pixel i, 8 channels) transposed, channel c's 8 pixels
+// at row(c).  Neighbouring threads hold neighbouring channel groups g (of N); groups
+// two apart start a multiple of 256 bytes apart whatever the pitch (a multiple of
+// 16), so that all of them storing channel q met in the same banks: conflicts took
+// 55 to 76% of the LDS's busy cycles, and the LDS was busy 65 to 85% of the time.
+// From 8 groups on, group g therefore takes its channels in the order q ^ (g & 6),
+// which spreads 16 lanes over all banks (two to a bank with 16 groups) at the
+// pitches in use, 9, 11 and 17 times 16 bytes.  At 480 x 240, batch 32, layers 6 to
+// 3: 141, 138, 131 and 76 us, before 178, 168, 172 and 103.  Four groups conflict
+// two by two; turning one bit there spilled registers in the ring (185 us against
+// 144).
+template <int N, typename Row>
+__device__ __forceinline__ void put_transposed(const bf16x8 (&r)[8], int g, Row row) {
+  const int x = N >= 8 ? g & 6 : 0;
+  u32x4 w[8];                      // word d of w[i]: channels 2 d and 2 d + 1, d turned by x
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    w[i] = __builtin_bit_cast(u32x4, r[i]);
+    if constexpr (N >= 8) {
+      const u32x4 v = w[i];
+      const bool s = (x & 4) != 0, h = (x & 2) != 0;
+      const u32x4 u = u32x4{s ? v[2] : v[0], s ? v[3] : v[1], s ? v[0] : v[2], s ? v[1] : v[3]};
+      w[i] = u32x4{h ? u[1] : u[0], h ? u[0] : u[1], h ? u[3] : u[2], h ? u[2] : u[3]};
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    u32x4 t;
+#pragma unroll
+    for (int d = 0; d < 4; ++d)    // lower or upper halves of two pixels' words
+      t[d] = __builtin_amdgcn_perm(w[2 * d + 1][q >> 1], w[2 * d][q >> 1],
+                                   (q & 1) ? 0x07060302u : 0x05040100u);
+    *(u32x4*)row(q ^ x) = t;
+  }
+}
+
 // Weight gradients of a 3x3 layer (stride 1, stride 2 or upsampling) as GEMMs
 // dW[tap][r][c] = sum_p dz[p][r] in[src(p, tap)][c] over stages of PX = 32 S
 // pixels of one output row (the last chunk of a row is ragged).  Work items:
@@ -838,8 +881,13 @@ __global__ __launch_bounds__(256) void k_conv1_fwd(const float* __restrict__ eps
 // (The network's upsampling layers use k_conv_wgrad_up and its 32-channel
 // stride-1 layers k_conv_wgrad_ring; the upsampling map here serves other
 // channel counts.)
+constexpr int wg_row_blocks(int MT, int NT, int S, int MK, int ND) {
+  const int xg = MK == MAP_UP ? 2 * S + 1 : (MK == MAP_S2 ? 8 * S : 4 * S + 2);
+  return (4 * S * 2 * MT + ND * xg * 2 * NT + 255) / 256;
+}
 template <int MT, int NT, int S, int MK, int ND = 1>
-__global__ __launch_bounds__(256) void k_conv_wgrad_row(const bf16* __restrict__ dz,
+__global__ __launch_bounds__(256, wg_waves((MT * NT + 3) / 4, 3 * ND, wg_row_blocks(MT, NT, S, MK, ND)))
+void k_conv_wgrad_row(const bf16* __restrict__ dz,
                                                         const bf16* __restrict__ x, int B,
                                                         int Hout, int Wout, int Hin, int Win,
                                                         int Nc, int stages_per, int nwork,
@@ -976,21 +1024,16 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_row(const bf16* __restrict__
       }
       const int blk = threadIdx.x + 256 * bi;
       if (blk < ABLK) {
-        bf16* dst = &As[(blk % (Mr / 8)) * 8][(blk / (Mr / 8)) * 8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          bf16x8 t;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) t[i] = reg[bi][i][q];
-          *(bf16x8*)(dst + q * LD) = t;
-        }
+        const int g = blk % (Mr / 8);
+        bf16* dst = &As[g * 8][(blk / (Mr / 8)) * 8];
+        put_transposed<Mr / 8>(reg[bi], g, [&](int c) { return dst + c * LD; });
       } else if (blk < NBLK) {
         const int rd = (blk - ABLK) / XBLK, r = blk - ABLK - rd * XBLK;
-        const int m = r / (NB / 8), cg = (r % (NB / 8)) * 8;
+        const int m = r / (NB / 8), g = r % (NB / 8), cg = g * 8;
         bf16 (*Xr)[LDX] = Xs[rd];
+        if constexpr (UP) {   // source pixel i fills columns 16 m + 2 i and 16 m + 2 i + 1
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          if (UP) {   // source pixel i fills columns 16 m + 2 i and 16 m + 2 i + 1
+          for (int q = 0; q < 8; ++q) {
             bf16x8 lo, hi;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -999,12 +1042,10 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_row(const bf16* __restrict__
             }
             *(bf16x8*)&Xr[cg + q][16 * m] = lo;
             *(bf16x8*)&Xr[cg + q][16 * m + 8] = hi;
-          } else {   // stride 2: odd and even groups both land at column 8 m + 8
-            bf16x8 t;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) t[i] = reg[bi][i][q];
-            *(bf16x8*)&Xr[cg + q][S2 ? 8 * m + 8 : 8 * m] = t;
           }
+        } else {   // stride 2: odd and even groups both land at column 8 m + 8
+          bf16* dst = &Xr[cg][S2 ? 8 * m + 8 : 8 * m];
+          put_transposed<NB / 8>(reg[bi], g, [&](int c) { return dst + c * LDX; });
         }
       }
     }
@@ -1095,7 +1136,8 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_row(const bf16* __restrict__
 // rows y - 1 and y are loaded as well.  Staging blocks, the column shifts of
 // the three dx taps and the partials are those of k_conv_wgrad_row (dsplit 1).
 template <int MT, int NT, int S>
-__global__ __launch_bounds__(256) void k_conv_wgrad_ring(const bf16* __restrict__ dz,
+__global__ __launch_bounds__(256, wg_waves((MT * NT + 3) / 4, 9, (4 * S * 2 * MT + (4 * S + 2) * 2 * NT + 255) / 256))
+void k_conv_wgrad_ring(const bf16* __restrict__ dz,
                                                          const bf16* __restrict__ x, int B,
                                                          int H, int W, int Nc, int stages_per,
                                                          int nwork, float* __restrict__ part,
@@ -1149,24 +1191,14 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_ring(const bf16* __restrict_
       const int blk = threadIdx.x + 256 * bi;
       if (blk < ABLK) {
         if (dzrow) {
-          bf16* dst = &As[(blk % (Mr / 8)) * 8][(blk / (Mr / 8)) * 8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            bf16x8 t;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) t[i] = reg[bi][i][q];
-            *(bf16x8*)(dst + q * LD) = t;
-          }
+          const int g = blk % (Mr / 8);
+          bf16* dst = &As[g * 8][(blk / (Mr / 8)) * 8];
+          put_transposed<Mr / 8>(reg[bi], g, [&](int c) { return dst + c * LD; });
         }
       } else if (blk < NBLK) {
-        const int r = blk - ABLK, m = r / (NB / 8), cg = (r % (NB / 8)) * 8;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          bf16x8 t;
-#pragma unroll
-          for (int i = 0; i < 8; ++i) t[i] = reg[bi][i][q];
-          *(bf16x8*)&Xs[xslot][cg + q][8 * m] = t;
-        }
+        const int r = blk - ABLK, m = r / (NB / 8), g = r % (NB / 8);
+        bf16* dst = &Xs[xslot][g * 8][8 * m];
+        put_transposed<NB / 8>(reg[bi], g, [&](int c) { return dst + c * LDX; });
       }
     }
   };
@@ -1298,7 +1330,8 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_ring(const bf16* __restrict_
 // Partials: [slice][16][r][c] (index ((a 2 + b) 2 + sy) 2 + sx), bias
 // [slice][a][r] (every channel-block-0 item sums its dz row).
 template <int MT, int NT, int S>
-__global__ __launch_bounds__(256) void k_conv_wgrad_up(const bf16* __restrict__ dz,
+__global__ __launch_bounds__(256, wg_waves((MT * NT + 3) / 4, 8, (8 * S * 2 * MT + (8 * S + 4) * 2 * NT + 255) / 256))
+void k_conv_wgrad_up(const bf16* __restrict__ dz,
                                                        const bf16* __restrict__ x, int B,
                                                        int Hout, int Wout, int Hin, int Win,
                                                        int Nc, int stages_per, int nwork,
@@ -1372,27 +1405,15 @@ __global__ __launch_bounds__(256) void k_conv_wgrad_up(const bf16* __restrict__ 
 #pragma unroll
     for (int bi = 0; bi < BPT; ++bi) {
       const int blk = threadIdx.x + 256 * bi;
-      bf16* dst = nullptr;
       if (blk < ABLK) {
-        const int par = blk / AHALF, r = blk - par * AHALF;
-        dst = &As[par][(r % (Mr / 8)) * 8][(r / (Mr / 8)) * 8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          bf16x8 t;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) t[e] = reg[bi][e][q];
-          *(bf16x8*)(dst + q * LD) = t;
-        }
+        const int par = blk / AHALF, r = blk - par * AHALF, g = r % (Mr / 8);
+        bf16* dst = &As[par][g * 8][(r / (Mr / 8)) * 8];
+        put_transposed<Mr / 8>(reg[bi], g, [&](int c) { return dst + c * LD; });
       } else if (blk < NBLK) {
         const int sy = (blk - ABLK) / XBLK, r = blk - ABLK - sy * XBLK;
-        const int m = r / (NB / 8), cg = (r % (NB / 8)) * 8;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          bf16x8 t;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) t[e] = reg[bi][e][q];
-          *(bf16x8*)&Xs[sy][cg + q][8 * m] = t;
-        }
+        const int m = r / (NB / 8), g = r % (NB / 8);
+        bf16* dst = &Xs[sy][g * 8][8 * m];
+        put_transposed<NB / 8>(reg[bi], g, [&](int c) { return dst + c * LDX; });
       }
     }
     __syncthreads();

@@ -139,13 +139,13 @@ typedef struct {
                         /* size dd_solver_workspace_bytes reports for the same    */
                         /* operators and options; borrowed until destroy          */
   size_t workspace_bytes;
-  int fused;            /* 1 = one sweep per Arnoldi step where it applies        */
-                        /* (cgs_passes = 1, kmax + restart + 1 <= 128): the       */
-                        /* update of step j, the matvec and the dots of step j+1  */
-                        /* read each basis vector from memory once (30-column     */
-                        /* strips walked down bands of rows); faster for one      */
-                        /* problem alone, slower for batches; 0 (default) = two   */
-                        /* sweeps per step                                        */
+  int fused;            /* one sweep per Arnoldi step (the update of step j, the   */
+                        /* matvec and the dots of step j+1 read each basis vector */
+                        /* from memory once) is taken by itself where             */
+                        /* kmax + restart + 1 is at most 128 (complex128: 64); 1   */
+                        /* = also in complex128 with 65 to 128 and cgs_passes = 1, */
+                        /* where it is faster for one problem alone and slower    */
+                        /* for batches; default 0                                 */
 } dd_solver_opts;
 
 /* Per-problem result (host struct). */
@@ -273,12 +273,13 @@ dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, void* host_o
 
 /* Live timing of the streaming sweeps of an Arnoldi step, recorded with HIP
  * events on the solve stream around every launch while enabled:
- * [0] stencil matvec + first Gram-Schmidt dots (with the fused sweep: the
+ * [0] stencil matvec + first Gram-Schmidt dots (with one sweep per step: the
  * first matvec of each cycle), [1] second Gram-Schmidt pass (update + dots),
- * [2] final update + norm, [3] fused sweep.  bytes[] are the algorithmic
+ * [2] final update + norm, [3] the one sweep.  bytes[] are the algorithmic
  * bytes those launches had to move (inner precision ib bytes per complex, eb
  * per permittivity value, n = basis length of the step):
- * [0] (2 ib + eb) D + ib D n, [1] ib D (2n + 2), [2] ib D (n + 2),
+ * [0] (2 ib + eb) D + ib D n, [1] ib D (2n + 2) (beside one sweep per step, which
+ * applies the pass's update: ib D (n + 2)), [2] ib D (n + 2),
  * [3] ib D (n + 3) + eb D (read the n basis vectors and A q~_j, write q~_{j+1}
  * and A q~_{j+1}, read eps). */
 typedef struct {

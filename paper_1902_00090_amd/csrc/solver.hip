@@ -259,7 +259,8 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     // 480 x 240 problems: one problem is fastest with 2 elements per thread
     // (60 us/step against 63-77 for 1, 4 and 8); a batch of 64 takes 1.13-1.15
     // ms/step with 2, 4 or 8 against 1.35 with 1.  Large batches take 8 (the
-    // fewest partial rows per problem), small ones 2.
+    // fewest partial rows per problem), small ones 2.  (With two sweeps a step;
+    // where a step takes one, only a cycle's start and end go by these chunks.)
     long long nch8 = 0;
     for (int p = 0; p < nb; ++p) nch8 += (ops[p]->D + DD_BLOCK * 8 - 1) / (DD_BLOCK * 8);
     R = (nch8 >= 512) ? 8 : 2;
@@ -305,8 +306,13 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     P.GB = GB;
   }
   // One sweep per Arnoldi step where it applies: a basis of at most 128 vectors
-  // (64 in complex128) whose offsets fit a buffer descriptor; in complex128 up
-  // to 128 on request, by an older kernel.
+  // (64 in complex128, whose values take twice the registers) whose offsets fit a
+  // buffer descriptor.  Whole solves with one sweep a step (two with a second
+  // Gram-Schmidt pass) against two (three): one problem of 480 x 240 257 and 497 ms,
+  // 48 of 192 x 96 381 and 574, nine uneven ones with two passes 268 and 531, one of
+  // 64 x 64 in complex128 with two passes 72 and 129.
+  // In complex128 up to 128 on request, by k_fused_sweep: one problem alone gains by
+  // it, batches lose.
   const bool fits = NC <= (o.inner == DD_C64 ? DD_SW_MAXN : DD_SW_MAXN / 2);
   bool small = true;
   for (int p = 0; p < nb; ++p)

@@ -855,8 +855,9 @@ __global__ __launch_bounds__(DD_BLOCK) void k_combine(PlanDev P) {
 }
 
 // ============================ fused Arnoldi sweep ============================
-// One sweep per Arnoldi step (cgs_passes = 1, k + m + 1 <= 128, nx <= 512).
-// The Krylov vectors are normalised one step late, q_i = s_i q~_i with FP64
+// One sweep per Arnoldi step on request in complex128 with 65 to 128 vectors and one
+// pass, more than k_sweep holds in registers.  Bound by its chain of two barriers a
+// row.  The Krylov vectors are normalised one step late, q_i = s_i q~_i with FP64
 // scales s_i = hscale[i] (C columns: s = 1), and z_j = A q~_j is kept
 // unscaled in a separate double buffer.  With d_v = b_v^H z_j the raw dots of
 // z_j against the basis b = [C, q~_0 .. q~_j], the next vector is the

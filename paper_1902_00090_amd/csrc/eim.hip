@@ -149,12 +149,13 @@ __global__ __launch_bounds__(64) void k_eim_bound(const EimDesc* __restrict__ de
 
 // Inverse iteration from the shift, one thread per column.  The pivots' inverses
 // are formed once (the only divisions); a sweep is then one fused multiply-add a
-// row.  Rows are taken eight at a time so that their loads are in flight
-// together.  Bound by the traffic of its two arrays, which exceed the L2 (with the
-// vector in LDS one wave fits a compute unit: 548 us against 360 for 64 problems of
-// 480 x 240).  The vector is kept in the output array, whose complex64 is as large,
-// until the field is assembled: it costs no scratch to allocate and free (a call on
-// those 64 problems 1000 us, with scratch for it 1270).
+// row.  Rows are taken sixteen at a time so that their loads are in flight
+// together.  Bound by a column's chain of rows, nine times up or down it: 64 problems
+// of 480 x 240 take 342 us, 8 of them 295; with eight rows at a time 365, with 24 340,
+// with the vector in LDS (one wave a compute unit) 548, with scalar row offsets and
+// buffer accesses 484.  The vector is kept in the output array, whose complex64 is as
+// large, until the field is assembled: it costs no scratch to allocate and free (a call
+// on those 64 problems 962 us, with scratch for it 270 more).
 #define DD_EIM_COLS 64
 __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __restrict__ desc,
                                                   double* __restrict__ piv,
@@ -169,11 +170,11 @@ __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __rest
   double* ph = (double*)d.F + ix;
   double* pv = piv + d.off2 + ix;
   const double sigma = mu[d.off1 + ix];
-  constexpr int U = 8;
+  constexpr int U = 16;
   // rows [i, i + U) up (or down) with valid addresses past the ends
   auto row = [&](int i) { return (size_t)min(max(i, 0), ny - 1) * nx; };
   double ss = 0.0, sum = 0.0;
-  // eight rows are computed while the next eight are in flight
+  // sixteen rows are computed while the next sixteen are in flight
   double v[U], r[U], vn[U], rn[U];
   auto fetch = [&](int i0, int dir, bool first) {
 #pragma unroll

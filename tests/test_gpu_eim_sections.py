@@ -1,5 +1,5 @@
 """Effective-index fields at the edges of the column kernels' tiles: columns in
-groups of 16 and 64, rows in groups of 8, the permittivities in LDS up to 1024
+groups of 16 and 64, rows in groups of 16, the permittivities in LDS up to 1024
 rows and from memory beyond, the line solve in groups of 64 rows."""
 import numpy as np
 import pytest

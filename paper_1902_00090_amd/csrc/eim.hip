@@ -279,7 +279,10 @@ __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __rest
 // T y = j and T z = u.
 // One wave per problem.  The elimination is a chain of n steps with a division
 // each; all lanes do it, the current row in registers, on rows that they have
-// laid out 64 at a time in LDS.  They then divide the finished rows by their
+// laid out 64 at a time in LDS, the even lanes with the first right-hand side, the odd
+// ones with the second.  Bound by the instructions of a step, all in one wave: 64
+// problems of 480 columns 194 us; with both sides in every lane and the pivoting as
+// selects 225.  They then divide the finished rows by their
 // pivots, a row each, so that the back substitution's chain is one complex
 // multiply-add a step.
 struct LineRow {           // a finished row: diagonal, two entries above, right-hand sides
@@ -305,8 +308,9 @@ __global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ des
   const double2 gamma = neg(diag0);
   const double2 bg = zdiv(beta, gamma);
   // elimination with partial pivoting; the current row's diagonal, upper entry
-  // and right-hand sides
-  double2 cd = zero, cu = zero, c1 = zero, c2 = zero;
+  // and right-hand side: j in the even lanes, u in the odd ones
+  const int odd = lane & 1;
+  double2 cd = zero, cu = zero, c = zero;
   for (int i0 = 0; i0 < n; i0 += 64) {
     const int i = i0 + lane;
     __syncthreads();
@@ -323,37 +327,43 @@ __global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ des
     const int m = min(64, n - i0);
     for (int q = 0; q < m; ++q) {
       // row i0 + q joins: it is eliminated by, or takes the place of, the current row
-      const double2 sub = sub_l[q], dg = dg_l[q], up = up_l[q], j1 = j_l[q];
+      const double2 sub = sub_l[q], dg = dg_l[q], up = up_l[q];
       const int r = i0 + q;
-      double2 j2 = zero;
-      if (r == 0) j2 = zadd(j2, gamma);
-      if (r == n - 1) j2 = zadd(j2, alpha);
+      double2 j = odd ? zero : j_l[q];
+      if (odd && r == 0) j = zadd(j, gamma);
+      if (odd && r == n - 1) j = zadd(j, alpha);
       if (r == 0) {
         cd = dg;
         cu = up;
-        c1 = j1;
-        c2 = j2;
+        c = j;
         continue;
       }
-      const bool keep = zabs2(cd) >= zabs2(sub);
-      const double2 f = zdiv(keep ? sub : cd, keep ? cd : sub);
-      // finished row r - 1, and the row that f times it is taken from
-      const double2 pu = keep ? cu : dg, pw = keep ? zero : up;
-      const double2 p1 = keep ? c1 : j1, p2 = keep ? c2 : j2;
-      const double2 qd = keep ? dg : cu, qu = keep ? up : zero;
-      const double2 q1 = keep ? j1 : c1, q2 = keep ? j2 : c2;
-      if (lane == 0) R[r - 1] = {keep ? cd : sub, pu, pw, p1, p2};
-      cd = zsub(qd, zmul(f, pu));
-      cu = zsub(qu, zmul(f, pw));
-      c1 = zsub(q1, zmul(f, p1));
-      c2 = zsub(q2, zmul(f, p2));
+      // finished row r - 1, and the current row less f times it; the lanes agree on
+      // the pivot, so it is a branch
+      LineRow* fin = R + r - 1;
+      if (__builtin_amdgcn_readfirstlane(zabs2(cd) >= zabs2(sub))) {
+        const double2 f = zdiv(sub, cd);
+        if (lane == 0) fin->d = cd, fin->u = cu, fin->w = zero;
+        if (lane < 2) (&fin->y)[lane] = c;
+        cd = zsub(dg, zmul(f, cu));
+        cu = up;
+        c = zsub(j, zmul(f, c));
+      } else {
+        const double2 f = zdiv(cd, sub);
+        if (lane == 0) fin->d = sub, fin->u = dg, fin->w = up;
+        if (lane < 2) (&fin->y)[lane] = j;
+        cd = zsub(cu, zmul(f, dg));
+        cu = zsub(zero, zmul(f, up));
+        c = zsub(c, zmul(f, j));
+      }
     }
   }
-  if (lane == 0) R[n - 1] = {cd, zero, zero, c1, c2};
+  if (lane == 0) R[n - 1].d = cd, R[n - 1].u = zero, R[n - 1].w = zero;
+  if (lane < 2) (&R[n - 1].y)[lane] = c;
   __threadfence_block();
   __syncthreads();
   // back substitution of both right-hand sides, y_i and z_i left in the rows
-  double2 y1 = zero, y2 = zero, z1 = zero, z2 = zero;
+  double2 y1 = zero, y2 = zero;
   for (int i0 = (n - 1) / 64 * 64; i0 >= 0; i0 -= 64) {
     const int m = min(64, n - i0);
     __syncthreads();
@@ -367,21 +377,11 @@ __global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ des
       r_l[lane] = a;
     }
     __syncthreads();
-    double2 my = zero, mz = zero;
     for (int q = m - 1; q >= 0; --q) {
-      const double2 u = r_l[q].u, w = r_l[q].w;
-      const double2 y = zsub(zsub(r_l[q].y, zmul(w, y2)), zmul(u, y1));
-      const double2 z = zsub(zsub(r_l[q].z, zmul(w, z2)), zmul(u, z1));
-      if (lane == q) {
-        my = y;
-        mz = z;
-      }
-      y2 = y1; z2 = z1;
-      y1 = y; z1 = z;
-    }
-    if (lane < m) {
-      R[i0 + lane].y = my;
-      R[i0 + lane].z = mz;
+      const double2 y = zsub(zsub((&r_l[q].y)[odd], zmul(r_l[q].w, y2)), zmul(r_l[q].u, y1));
+      if (lane < 2) (&R[i0 + q].y)[lane] = y;
+      y2 = y1;
+      y1 = y;
     }
   }
   __threadfence_block();

@@ -142,10 +142,10 @@ typedef struct {
   int fused;            /* one sweep per Arnoldi step (the update of step j, the   */
                         /* matvec and the dots of step j+1 read each basis vector */
                         /* from memory once) is taken by itself where             */
-                        /* kmax + restart + 1 is at most 128 (complex128: 64); 1   */
-                        /* = also in complex128 with 65 to 128 and cgs_passes = 1, */
-                        /* where it is faster for one problem alone and slower    */
-                        /* for batches; default 0                                 */
+                        /* kmax + restart + 1 is at most 128 (complex128: 64) and  */
+                        /* the grids have fewer than 2^21 cells; 1 = also for the  */
+                        /* rest up to 128 with cgs_passes = 1, where it is faster  */
+                        /* for one problem alone and slower for batches; default 0 */
 } dd_solver_opts;
 
 /* Per-problem result (host struct). */
@@ -301,6 +301,11 @@ dd_status dd_solver_autotune(const fdfd_op* const* ops, int nb, const dd_solver_
 dd_status dd_solver_profile(dd_solver* s, int enable);
 /* Host copy of the accumulated statistics. */
 dd_status dd_solver_kernel_stats(const dd_solver* s, dd_kernel_stats* out);
+
+/* Test introspection, host only: the Arnoldi step that a solver of these grids and
+ * options takes: 2 = one sweep (two with a second Gram-Schmidt pass), 1 = the one
+ * sweep of the fused option, 0 = two sweeps (three).  -1 on bad arguments. */
+int dd_solver_step_path(int nb, const int* nx, const int* ny, const dd_solver_opts* opts);
 
 /* Field elements per thread the solver runs with (the tile width chosen by
  * the rule or the autotuner; 0 for a NULL solver). */

@@ -183,9 +183,10 @@ class Solver:
                  elems_per_thread=0, hist_cap=0, check_every=4, select_reorth=True,
                  use_graph=False, precond=None, workspace=None, fused=False):
         """precond: None, "jacobi" or "pml" (diagonal preconditioners, see the C header).
-        fused: one sweep per Arnoldi step also in complex128 with 65 to 128 basis
-        vectors (kmax + restart + 1) and cgs_passes=1; up to 128 vectors in
-        complex64 and 64 in complex128 every step takes one sweep.
+        fused: with cgs_passes=1 and up to 128 basis vectors (kmax + restart + 1), one
+        sweep per Arnoldi step also in complex128 with 65 or more and on grids of
+        2^21 cells or more; the others up to 128 vectors in complex64 and 64 in
+        complex128 take one sweep by themselves.
         workspace: an optional device tensor (at least workspace_bytes(...) bytes,
         256-byte aligned) that holds all of the solver's device arrays; the
         solver then allocates no device memory and keeps a reference to it."""

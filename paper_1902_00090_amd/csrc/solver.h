@@ -66,6 +66,10 @@ enum { SD_BNORM = 0, SD_RHO, SD_BETA, SD_TRUE, SD_EST, SD_NSUM, SD_NSUM2, SD_PRH
 
 enum { MODE_START = 0, MODE_ARNOLDI = 1 };
 
+// The Arnoldi step: two or three sweeps over the basis, k_fused_sweep, or k_sweep
+// (with a second Gram-Schmidt pass also k_pass2)
+enum { STEP_PLAIN = 0, STEP_FUSED = 1, STEP_SWEEP = 2 };
+
 struct SweepTile;
 // The tiles of one cycle's sweeps (k_sweep_plan)
 struct SweepPlan {
@@ -104,9 +108,9 @@ struct PlanDev {
   int reorth_mode;   // 0 one Gram-Schmidt pass, 1 always two, 2 two where needed
   const double* ctl;  // device [tol, maxit] of the current solve (kernel arguments
                       // stay constant, so captured graphs remain valid)
-  int fused;          // one-sweep Arnoldi steps: 1 k_fused_sweep, 2 k_sweep; k_post_fused
+  int fused;          // the Arnoldi step, STEP_...
   const FusedTile* tiles;
-  // one-sweep steps of k_sweep (fused = 2): update coefficients in the inner
+  // one-sweep steps of k_sweep: update coefficients in the inner
   // precision and the factor of z; the cycle's split of the work (k_sweep_plan)
   void* coefS;        // [nb][128]
   double* zs;         // [nb]

@@ -134,7 +134,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   }
   A.carve(&dd, nb);
   A.carve(&db2p, s->nchunks);
-  if (s->fused == 1) A.carve(&s->dtiles, s->htiles.size());
+  if (s->fused == STEP_FUSED) A.carve(&s->dtiles, s->htiles.size());
   A.carve(&s->dU, nb);
   A.carve(&P.stI, (size_t)nb * ST_NI);
   A.carve(&P.stD, (size_t)nb * SD_ND);
@@ -157,14 +157,14 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   A.carve(&P.bad, (size_t)nb);
   double* part = nullptr;
   const size_t rows = std::max<size_t>({(size_t)s->nchunks, s->htiles.size(),
-                                        s->fused == 2 ? (size_t)s->sw_most : 0});
+                                        s->fused == STEP_SWEEP ? (size_t)s->sw_most : 0});
   A.carve(&part, rows * P.NV);
   P.sw_ld = (size_t)s->sw_most;
   P.partial = part;
   A.carve(&P.gpart, (size_t)nb * P.GB * std::max(1, gram_tiles(std::max(K, 1))) * 32);
   A.carve(&P.hist, (size_t)nb * std::max(1, o.hist_cap));
   A.carve(&s->dctl, 2);
-  if (s->fused == 2) {
+  if (s->fused == STEP_SWEEP) {
     double2* cs = nullptr;
     A.carve(&cs, (size_t)nb * DD_SW_MAXN);
     P.coefS = cs;
@@ -210,6 +210,35 @@ static dd_status tuned_elems_per_thread(const fdfd_op* const* ops, int nb, const
   cache[key] = best;
   *R = best;
   return DD_OK;
+}
+
+// The Arnoldi step of a solver with nvec = kmax + restart + 1 basis vectors: one
+// sweep (k_sweep, with a second Gram-Schmidt pass k_pass2) for a basis of at most
+// 128 vectors (64 in complex128, whose values take twice the registers) whose
+// offsets fit a buffer descriptor.  Whole solves with one sweep a step (two with a
+// second pass) against two (three): one problem of 480 x 240 257 and 497 ms, 48 of
+// 192 x 96 381 and 574, nine uneven ones with two passes 268 and 531, one of 64 x 64
+// in complex128 with two passes 72 and 129.
+// On request and with one pass k_fused_sweep takes what is left up to 128 vectors:
+// complex128 with 65 or more, and grids too large for the descriptors.  One problem
+// alone gains by it, batches lose.  Every path has kernels in both precisions.
+static int step_path(int nb, const int* nx, const int* ny, const dd_solver_opts& o, int nvec) {
+  bool fits = nvec <= (o.inner == DD_C64 ? DD_SW_MAXN : DD_SW_MAXN / 2);
+  for (int p = 0; p < nb; ++p) {
+    // vectors are padded to a multiple of at most 8 elements a thread
+    const size_t D = (size_t)nx[p] * ny[p], pad = DD_BLOCK * 8;
+    fits = fits && (D + pad - 1) / pad * pad * 8 * DD_SW_MAXN < (size_t)DD_SW_OUT;
+  }
+  if (fits) return STEP_SWEEP;
+  return (o.fused && o.cgs_passes == 1 && nvec <= DD_FUSED_MAXN) ? STEP_FUSED : STEP_PLAIN;
+}
+
+extern "C" int dd_solver_step_path(int nb, const int* nx, const int* ny, const dd_solver_opts* opts) {
+  dd_solver_opts o;
+  dd_solver_opts_default(&o);
+  if (opts) o = *opts;
+  if (nb < 1 || !nx || !ny) { dd_set_error("dd_solver_step_path: need nb >= 1 grids"); return -1; }
+  return step_path(nb, nx, ny, o, o.kmax + o.restart + 1);
 }
 
 static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
@@ -305,35 +334,26 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     int GB = (int)std::min<size_t>(32, std::max<size_t>(1, (64ull << 20) / per));
     P.GB = GB;
   }
-  // One sweep per Arnoldi step where it applies: a basis of at most 128 vectors
-  // (64 in complex128, whose values take twice the registers) whose offsets fit a
-  // buffer descriptor.  Whole solves with one sweep a step (two with a second
-  // Gram-Schmidt pass) against two (three): one problem of 480 x 240 257 and 497 ms,
-  // 48 of 192 x 96 381 and 574, nine uneven ones with two passes 268 and 531, one of
-  // 64 x 64 in complex128 with two passes 72 and 129.
-  // In complex128 up to 128 on request, by k_fused_sweep: one problem alone gains by
-  // it, batches lose.
-  const bool fits = NC <= (o.inner == DD_C64 ? DD_SW_MAXN : DD_SW_MAXN / 2);
-  bool small = true;
-  for (int p = 0; p < nb; ++p)
-    small = small && (size_t)s->hdesc[p].Dp * 8 * DD_SW_MAXN < (size_t)DD_SW_OUT;
-  if (fits && small) {
-    s->fused = 2;
+  {
+    std::vector<int> gx(nb), gy(nb);
+    for (int p = 0; p < nb; ++p) { gx[p] = ops[p]->nx; gy[p] = ops[p]->ny; }
+    s->fused = step_path(nb, gx.data(), gy.data(), o, NC);
+  }
+  if (s->fused == STEP_SWEEP) {
     s->sw_grid = 2 * s->ncu;               // at most two workgroups per compute unit
     int strips = 0;                        // one tile each at the least
     for (int p = 0; p < nb; ++p) strips += sw_strips(ops[p]->nx);
     s->sw_most = std::max(strips, 4 * s->sw_grid);
-  } else if (o.fused && o.cgs_passes == 1 && NC <= DD_FUSED_MAXN) {
-    s->fused = 1;
   }
   // Fused sweep tiles: strips of DD_FUSED_SW columns walked down bands of rows
-  if (s->fused == 1) {
+  if (s->fused == STEP_FUSED) {
     // two rounds of tiles over the resident workgroups (w per compute unit),
     // bands of 8 to 64 rows (each band recomputes one halo row at either end)
     int w = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &w, (const void*)k_fused_sweep<double, false>, DD_FUSED_THREADS, 0) != hipSuccess ||
-        w < 1)
+            &w, (o.inner == DD_C64) ? (const void*)k_fused_sweep<float, false>
+                                    : (const void*)k_fused_sweep<double, false>,
+            DD_FUSED_THREADS, 0) != hipSuccess || w < 1)
       w = 1;
     long long strip_rows = 0;
     for (int p = 0; p < nb; ++p)
@@ -405,7 +425,7 @@ extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const d
     for (int c = 0; c < s->hdesc[p].nblk; ++c) b2p[s->hdesc[p].blk0 + c] = p;
   auto chk = [&](hipError_t x) { if (x != hipSuccess && e == hipSuccess) e = x; };
   if (e == hipSuccess) {
-    if (s->fused == 1)
+    if (s->fused == STEP_FUSED)
       chk(hipMemcpy(s->dtiles, s->htiles.data(), sizeof(FusedTile) * s->htiles.size(),
                     hipMemcpyHostToDevice));
     chk(hipMemcpy(dd, s->hdesc.data(), sizeof(ProbDesc) * nb, hipMemcpyHostToDevice));
@@ -576,7 +596,7 @@ static void prof_collect(dd_solver* s) {
 // second-pass test needs every coefficient of the first pass at once.
 static int post_slices(const dd_solver* s, bool first_pass) {
   // k_sweep's steps: a wave a dot product, about a thousand workgroups
-  if (s->fused == 2) return std::max(4, std::min(32, 1024 / s->nb));
+  if (s->fused == STEP_SWEEP) return std::max(4, std::min(32, 1024 / s->nb));
   if (first_pass && s->P.reorth_mode == 2) return 1;
   return std::max(1, std::min(32, 256 / std::max(1, s->nb)));
 }
@@ -652,7 +672,7 @@ template <typename T>
 static void launch_fused_step(dd_solver* s, int j, hipStream_t st) {
   const bool pc = s->o.precond != DD_PRECOND_NONE;
   const int slices = post_slices(s, false);
-  if (s->fused == 2) {
+  if (s->fused == STEP_SWEEP) {
     if (s->P.reorth_mode != 0) {
       prof_mark(s, 1, st);
       launch_pass2<T>(s, j, st);
@@ -665,7 +685,7 @@ static void launch_fused_step(dd_solver* s, int j, hipStream_t st) {
     prof_end(s, st);
     const int poll = (j + 1) % s->o.check_every == 0;
     k_post_sweep<T><<<dim3(s->nb, slices + 1), DD_BLOCK, 0, st>>>(s->P, j, poll);
-  } else if constexpr (sizeof(T) == 8) {
+  } else {
     const int nt = (int)s->htiles.size();
     prof_mark(s, 3, st);
     if (pc) k_fused_sweep<T, true><<<nt, DD_FUSED_THREADS, 0, st>>>(s->P, j);
@@ -766,7 +786,7 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     int active = 0;
     for (int p = 0; p < nb; ++p) active += snap[0][p * ST_NI + ST_ACTIVE];
     if (active == 0) break;
-    if (s->fused == 2) {
+    if (s->fused == STEP_SWEEP) {
       k_sweep_plan<T, false><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
       if (s->P.reorth_mode != 0)
         k_sweep_plan<T, true><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
@@ -784,7 +804,7 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     }
     // k_sweep's steps leave their progress in host memory; no kernel
     // of an earlier cycle runs any more
-    if (s->fused == 2) std::memset(s->hostact, 0, sizeof(int) * nb);
+    if (s->fused == STEP_SWEEP) std::memset(s->hostact, 0, sizeof(int) * nb);
     int pending = -1, grp = 0;
     const int ce = s->o.check_every;
     const bool graph = s->o.use_graph && !s->prof;
@@ -799,7 +819,7 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
       } else {
         launch_any_step<T, R>(s, j, st);
       }
-      if (s->fused == 2) {
+      if (s->fused == STEP_SWEEP) {
         if ((j + 1) % ce == 0 && j + 1 < m) {
           // run at most one group ahead of the device
           if (j + 1 > ce) {
@@ -1052,7 +1072,7 @@ extern "C" dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, v
       DD_HIP_CHECK(hipMemcpy(dst + (size_t)v * d.D * ib,
                              (const char*)d.basis + (size_t)(slot0 + v) * d.Dp * ib, d.D * ib,
                              hipMemcpyDeviceToHost));
-    if (what == 1 && s->fused == 2) {
+    if (what == 1 && s->fused == STEP_SWEEP) {
       // stored unnormalised; the last vector of the cycle is given as it is
       std::vector<double> hs(m + 1);
       int last = 0;

@@ -855,9 +855,10 @@ __global__ __launch_bounds__(DD_BLOCK) void k_combine(PlanDev P) {
 }
 
 // ============================ fused Arnoldi sweep ============================
-// One sweep per Arnoldi step on request in complex128 with 65 to 128 vectors and one
-// pass, more than k_sweep holds in registers.  Bound by its chain of two barriers a
-// row.  The Krylov vectors are normalised one step late, q_i = s_i q~_i with FP64
+// One sweep per Arnoldi step on request, with one pass and up to 128 vectors, where
+// k_sweep does not apply: complex128 with 65 or more, which its registers do not
+// hold, and grids past the range of its buffer descriptors.  Bound by its chain of
+// two barriers a row.  The Krylov vectors are normalised one step late, q_i = s_i q~_i with FP64
 // scales s_i = hscale[i] (C columns: s = 1), and z_j = A q~_j is kept
 // unscaled in a separate double buffer.  With d_v = b_v^H z_j the raw dots of
 // z_j against the basis b = [C, q~_0 .. q~_j], the next vector is the
@@ -1176,21 +1177,21 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     const double gs = snew * sv * sv;
     cNew[v] = dv;
     cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
-    if (P.fused == 2)
+    if (P.fused == STEP_SWEEP)
       ((c2<PT>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] =
           to_c<PT>(make_double2(gs * dv.x, gs * dv.y));
     else
       cB[v] = make_double2(gs * dv.x, gs * dv.y);
   }
   // k_sweep: only the cycle's start comes here
-  if (P.fused == 2 && lead) {
+  if (P.fused == STEP_SWEEP && lead) {
     // slots of vectors that this cycle has not reached yet meet values read as
     // zero: they hold finite numbers
     for (int v = nn + t; v < DD_SW_MAXN; v += DD_BLOCK)
       ((c2<PT>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] = to_c<PT>(make_double2(0.0, 0.0));
     if (t == 0) P.zs[p] = snew;
   }
-  if (P.fused == 2 && P.reorth_mode == 2) {
+  if (P.fused == STEP_SWEEP && P.reorth_mode == 2) {
     // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
     __shared__ double cc_l[8];
     cc = block_sum1<double>(cc, cc_l);

@@ -23,9 +23,7 @@ struct dd_solver {
   std::vector<void*> allocs;
   size_t bytes = 0;       // device workspace of the solver (owned or the caller's)
   bool owns_workspace = true;
-  // one-sweep Arnoldi steps: 0 off, 2 k_sweep (with two passes also k_pass2),
-  // 1 k_fused_sweep (complex128 with 65 to 128 vectors, on request, one pass)
-  int fused = 0;
+  int fused = STEP_PLAIN;   // the Arnoldi step
   int sw_grid = 0;        // workgroups of k_sweep
   int sw_most = 0;        // tiles of a cycle, at most
   std::vector<FusedTile> htiles;

@@ -122,3 +122,17 @@ def test_fused_c64_grating_and_graph_replay():
     assert np.linalg.norm(x - xs) / np.linalg.norm(xs) < 1e-4
     assert np.array_equal(res["graph"][0], x) and np.array_equal(res["graph"][2], h)
     assert abs(info["iters"] - res["two-sweep"][1]["iters"]) <= 0.1 * info["iters"]
+
+
+def test_fused_c64_on_a_grid_past_the_descriptors():
+    """2^21 cells: the offsets of 128 vectors leave a buffer descriptor's range, so
+    the fused option takes k_fused_sweep in complex64.  Six steps: every estimate
+    moves by at most the rounding of its steps' dot products, 56 u of |A| |q|
+    (about three times the new norm), each: 6 * 56 * 3 * 2^-24 = 6e-5."""
+    inst = _inst(700, 2048, 1024)
+    (x,), (inf,), (h,) = _solve([inst], [None], 6, 6, inner="c64")
+    assert inf["iters"] == 6
+    A = fdfd.assemble_instance(inst)
+    xo, io = gmres_aug.gmres_aug(A, inst.b, np.zeros((inst.D, 0)), restart=6, tol=1e-30, maxit=6)
+    np.testing.assert_allclose(h, io["history"][:6], rtol=1e-4)
+    assert np.linalg.norm(x - xo) <= 1e-3 * np.linalg.norm(xo)

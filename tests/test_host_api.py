@@ -221,3 +221,36 @@ def test_small_harmonic_ritz_problem_with_repeated_eigenvalues():
     P = np.zeros((6, 6))
     P[[1, 2, 5], [1, 2, 5]] = 1.0
     np.testing.assert_allclose(P @ Z, Z, atol=1e-12)
+
+
+def test_step_path_rule_and_its_kernels():
+    """The Arnoldi step that a solver takes, over precisions, basis lengths around
+    the limits, passes, the fused option and grids on either side of 2^21 cells;
+    every path that the rule can give has its kernel in that precision."""
+    from paper_1902_00090_amd import _lib
+    lib = _lib.lib()
+    kernels = {0: "_Z12k_matvec_dotI{}Li2ELb0EEv7PlanDevi", 1: "_Z13k_fused_sweepI{}Lb0EEv7PlanDevi",
+               2: "_Z7k_sweepI{}Li4ELi4ELb0EEv7PlanDevi"}
+    raw = C.CDLL(_lib.LIB_PATH)
+    for inner in (_lib.DD_C64, _lib.DD_C128):
+        for nvec in (2, 64, 65, 128, 129, 300):
+            for passes in (1, 2):
+                for fused in (0, 1):
+                    for nx, ny in ((480, 240), (1024, 2047), (2048, 1024), (1450, 1450)):
+                        o = _lib.dd_solver_opts()
+                        lib.dd_solver_opts_default(C.byref(o))
+                        o.inner, o.cgs_passes, o.fused = inner, passes, fused
+                        o.kmax = 1 if nvec < 300 else 50
+                        o.restart = nvec - 1 - o.kmax
+                        small = nx * ny < 2 ** 21 - 2048
+                        want = 0
+                        if small and nvec <= (128 if inner == _lib.DD_C64 else 64):
+                            want = 2
+                        elif fused and passes == 1 and nvec <= 128:
+                            want = 1
+                        # a batch goes by its largest grid
+                        X, Y = (C.c_int * 2)(480, nx), (C.c_int * 2)(240, ny)
+                        assert lib.dd_solver_step_path(2, X, Y, C.byref(o)) == want, \
+                            (inner, nvec, passes, fused, nx, ny)
+                        assert hasattr(raw, kernels[want].format("fd"[inner])), kernels[want]
+    assert lib.dd_solver_step_path(0, None, None, None) == -1

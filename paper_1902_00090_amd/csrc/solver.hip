@@ -786,12 +786,13 @@ static dd_status run_cycles(dd_solver* s, hipStream_t st) {
     int active = 0;
     for (int p = 0; p < nb; ++p) active += snap[0][p * ST_NI + ST_ACTIVE];
     if (active == 0) break;
+    launch_start<T, R>(s, st);
     if (s->fused == STEP_SWEEP) {
+      // after the start, which ends the cycle of a problem whose r~ is zero
       k_sweep_plan<T, false><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
       if (s->P.reorth_mode != 0)
         k_sweep_plan<T, true><<<1, DD_BLOCK, 0, st>>>(s->P, s->ncu, s->sw_most);
     }
-    launch_start<T, R>(s, st);
     if (s->fused) {
       // z_0 = A q~_0 (unscaled) and its dots; then the coefficients of step 0
       const int ngrp = (s->o.kmax + 1 + 15) / 16;

@@ -156,3 +156,38 @@ def test_preconditioned_cycle_relations(kind):
     _check(s, 0, precond.preconditioned(A, pl, pr), 50)
     s.close()
 
+
+
+@pytest.mark.parametrize("inner", ["c64", "c128"])
+@pytest.mark.parametrize("passes", [1, 2])
+def test_start_that_ends_the_cycle(inner, passes):
+    """A uniform medium without PML, a constant source and a constant vector in U:
+    A 1 = -32 and C = -1 / 64 exactly (omega^2 eps and sqrt(D) are powers of two), so
+    the projected start is exactly zero, no step follows and x = -1 / 32; alone, and
+    beside a problem that goes on.  That one's sums may be ordered otherwise: each of
+    the 45 steps moves an estimate by 56 u of |A| |q|, three times the new norm."""
+    from paper_1902_00090_amd import FdfdOp, Solver
+    op = FdfdOp(np.full((64, 64), 2.0, np.float32), 4.0, 0.04, 0)
+    one = torch.ones(4096, dtype=torch.complex128, device="cuda")
+    U1 = torch.ones(1, 4096, dtype=torch.complex64 if inner == "c64" else torch.complex128,
+                    device="cuda")
+    kw = dict(inner=inner, cgs_passes=passes, restart=30, kmax=1, hist_cap=60)
+    other = _inst(11, 33, 21)
+    ob = torch.tensor(other.b, dtype=torch.complex128, device="cuda")
+    s = Solver([FdfdOp.from_instance(other)], **kw)
+    s.solve([ob], tol=1e-14, maxit=45)
+    hist = s.history(0)
+    s.close()
+    assert len(hist) == 45
+    for alone in (True, False):
+        ops = [op] if alone else [op, FdfdOp.from_instance(other)]
+        s = Solver(ops, **kw)
+        for again in range(2):       # on a fresh solver, and on sums that a solve has left
+            s.set_subspace([U1] + [None] * (len(ops) - 1))
+            xs, infos, _ = s.solve([one, ob][:len(ops)], tol=1e-14, maxit=45)
+            assert infos[0]["iters"] == 0 and infos[0]["status"] == 0, infos[0]
+            assert (xs[0].cpu().numpy() == -1 / 32).all()
+            if not alone:
+                assert infos[1]["iters"] == 45
+                np.testing.assert_allclose(s.history(1), hist, rtol=45 * 56 * 3 * U[inner])
+        s.close()

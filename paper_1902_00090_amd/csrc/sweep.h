@@ -502,7 +502,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
   const V zero = cmk<V>(T(0), T(0));
 
   for (int tile = blockIdx.x; tile < count; tile += G, tl += G) {
-    const int p = tl->p, ya = tl->y0, k = tl->k, n = k + j + 1;
+    const int p = tl->p, ya = tl->y0, k = tl->k, n = k + j + 1, cells = tl->nx * tl->ny;
     N = tl->rows;
     int act = ld_uni(P.stI + p * ST_NI + ST_ACTIVE);
     const bool second = sw_second_pass(P, p);
@@ -554,7 +554,9 @@ __global__ __launch_bounds__(64 * NW, 2) void k_pass2(PlanDev P, int j) {
       V u = zero;
 #pragma unroll
       for (int q = 0; q < NW; ++q) u = csub(u, part[t & 1][q][lane]);
-      if (wave == 1) z[(ya + t) * 64 + lane] = u;
+      // the padding stays zero whatever the coefficients are: no later cycle clears it
+      const int e = (ya + t) * 64 + lane;
+      if (wave == 1 && e < cells) z[e] = u;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
         acc[i].x = sw_fma(cur.b[i].y, u.y, sw_fma(cur.b[i].x, u.x, acc[i].x));

@@ -191,3 +191,31 @@ def test_start_that_ends_the_cycle(inner, passes):
                 assert infos[1]["iters"] == 45
                 np.testing.assert_allclose(s.history(1), hist, rtol=45 * 56 * 3 * U[inner])
         s.close()
+
+
+def test_solve_after_an_overflow():
+    """A permittivity of 1e37 three cells from a point source overflows complex64 in
+    the fourth step, whose second pass meets coefficients that are not finite; the
+    next operator of the same solver sees nothing of it (399 cells: runs of 64 end
+    in the vectors' padding)."""
+    from paper_1902_00090_amd import DDError, FdfdOp, Solver
+    good = _inst(21, 21, 19)
+    eps = good.eps.copy()
+    eps[9, 13] = 1e37
+    point = torch.zeros(good.D, dtype=torch.complex128, device="cuda")
+    point[9 * 21 + 10] = 1.0
+    b = torch.tensor(good.b, dtype=torch.complex128, device="cuda")
+    kw = dict(restart=40, cgs_passes=2, select_reorth=False, hist_cap=80)
+    fresh = Solver([FdfdOp.from_instance(good)], **kw)
+    (want,), _, _ = fresh.solve([b], tol=1e-14, maxit=80)
+    s = Solver([FdfdOp(eps, good.omega, good.dx, good.npml)], **kw)
+    try:
+        s.solve([point], tol=1e-14, maxit=8)
+    except DDError:
+        pass
+    s.bind([FdfdOp.from_instance(good)])
+    (x,), _, _ = s.solve([b], tol=1e-14, maxit=80)
+    assert np.array_equal(s.history(0), fresh.history(0))
+    assert torch.equal(x, want)
+    s.close()
+    fresh.close()

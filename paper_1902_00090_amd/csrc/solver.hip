@@ -169,6 +169,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
     A.carve(&cs, (size_t)nb * DD_SW_MAXN);
     P.coefS = cs;
     A.carve(&P.zs, (size_t)nb);
+    A.carve(&P.fs, (size_t)2 * nb);
     A.carve(&P.live, (size_t)2 * nb);
     A.carve(&P.ccpart, (size_t)nb * 33);
     for (SweepPlan* w : {&P.sw, &P.sw2}) {
@@ -1074,13 +1075,19 @@ extern "C" dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, v
                              (const char*)d.basis + (size_t)(slot0 + v) * d.Dp * ib, d.D * ib,
                              hipMemcpyDeviceToHost));
     if (what == 1 && s->fused == STEP_SWEEP) {
-      // stored unnormalised; the last vector of the cycle is given as it is
+      // stored unnormalised; the last vector of the cycle is given so, without its
+      // power of two
       std::vector<double> hs(m + 1);
       int last = 0;
       DD_HIP_CHECK(hipMemcpy(&last, s->P.stI + p * ST_NI + ST_J, sizeof(int), hipMemcpyDeviceToHost));
       DD_HIP_CHECK(hipMemcpy(hs.data(), s->P.hscale + (size_t)p * (m + 1), sizeof(double) * (m + 1),
                              hipMemcpyDeviceToHost));
-      for (int v = 0; v < last; ++v) {
+      double f = 1.0;
+      if (last > 0)
+        DD_HIP_CHECK(hipMemcpy(&f, s->P.fs + (last & 1) * s->nb + p, sizeof(double),
+                               hipMemcpyDeviceToHost));
+      hs[last] = 1.0 / f;
+      for (int v = 0; v <= last; ++v) {
         char* q = dst + (size_t)v * d.D * ib;
         if (s->o.inner == DD_C64)
           for (int e = 0; e < 2 * d.D; ++e) ((float*)q)[e] = (float)(((float*)q)[e] * hs[v]);

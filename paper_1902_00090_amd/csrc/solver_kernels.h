@@ -1168,13 +1168,30 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
       __syncthreads();
     }
   }
+  // k_sweep: only the cycle's start comes here.  The power of two of the next vector
+  // goes by ||w||^2 = s^2 ||z||^2, from the value behind k_matvec_dot's dots
+  double f = 1.0, ww = 0.0;
+  if (P.fused == STEP_SWEEP) {
+    __shared__ double zz_l;
+    if (t < 64) {
+      const PT* row = (const PT*)P.partial + (size_t)d.blk0 * P.NV + 2 * ((nn + 15) / 16) * 16;
+      double zz = 0.0;
+      for (int c = t; c < d.nblk; c += 64) zz += (double)row[(size_t)c * P.NV];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) zz += __shfl_xor(zz, o, DD_WAVE);
+      if (t == 0) zz_l = zz;
+    }
+    __syncthreads();
+    ww = snew * snew * zz_l;
+    f = sw_unit(ww);
+  }
   // the new raw dots and update coefficients (s_v for v <= k + j are those
   // of earlier steps; s_{j+1} = snew)
   double cc = 0.0;      // the slice's part of the first pass's ||c||^2
   for (int v = c0 + t; v < c1; v += DD_BLOCK) {
     const double2 dv = make_double2(red[2 * (v - c0)], red[2 * (v - c0) + 1]);
     const double sv = (v < k) ? 1.0 : (v - k == (init ? 0 : j + 1) ? snew : hs[v - k]);
-    const double gs = snew * sv * sv;
+    const double gs = f * snew * sv * sv;
     cNew[v] = dv;
     cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
     if (P.fused == STEP_SWEEP)
@@ -1183,28 +1200,23 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     else
       cB[v] = make_double2(gs * dv.x, gs * dv.y);
   }
-  // k_sweep: only the cycle's start comes here
   if (P.fused == STEP_SWEEP && lead) {
     // slots of vectors that this cycle has not reached yet meet values read as
     // zero: they hold finite numbers
     for (int v = nn + t; v < DD_SW_MAXN; v += DD_BLOCK)
       ((c2<PT>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] = to_c<PT>(make_double2(0.0, 0.0));
-    if (t == 0) P.zs[p] = snew;
+    if (t == 0) {
+      P.zs[p] = f * snew;
+      P.fs[P.nb + p] = f;
+    }
   }
   if (P.fused == STEP_SWEEP && P.reorth_mode == 2) {
-    // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
+    // for the second-pass test: ||w||^2 and this part of ||c||^2
     __shared__ double cc_l[8];
     cc = block_sum1<double>(cc, cc_l);
     double* out = P.ccpart + (size_t)p * 33;
     if (t == 0) out[1 + blockIdx.y] = cc;
-    if (lead && t < 64) {
-      const PT* row = (const PT*)P.partial + (size_t)d.blk0 * P.NV + 2 * ((nn + 15) / 16) * 16;
-      double zz = 0.0;
-      for (int c = t; c < d.nblk; c += 64) zz += (double)row[(size_t)c * P.NV];
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) zz += __shfl_xor(zz, o, DD_WAVE);
-      if (t == 0) out[0] = snew * snew * zz;
-    }
+    if (lead && t == 0) out[0] = ww;
   }
   if (lead && !init) {
     __syncthreads();
@@ -1280,8 +1292,9 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
     double sum[2];
     sum_tiles<2>(P, {2 * nn, 2 * min(v0, nn)}, t0, nt, sum);
     const double nz = sum[0];
-    const double nrm = sqrt(__shfl(nz, 0, DD_WAVE));
+    const double nrm = sqrt(__shfl(nz, 0, DD_WAVE));     // of q~, with its power of two
     const double snew = (nrm > 0.0) ? 1.0 / nrm : 0.0;
+    const double ww = snew * snew * __shfl(nz, 32, DD_WAVE), f = sw_unit(ww);
     double cc = 0.0;
     for (int v = v0; v < nn; v += step) {
       if (v > v0) {
@@ -1293,7 +1306,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
       const double part = sum[1];
       const double2 dv = make_double2(__shfl(part, 0, DD_WAVE), __shfl(part, 32, DD_WAVE));
       const double sv = (v == k + j + 1) ? snew : hv;
-      const double gs = snew * sv * sv;
+      const double gs = f * snew * sv * sv;
       cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
       if (lane == 0) {
         cNew[v] = dv;
@@ -1301,16 +1314,18 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
             to_c<T>(make_double2(gs * dv.x, gs * dv.y));
       }
     }
-    if (blockIdx.y == 0 && t == 0) P.zs[p] = snew;
+    if (blockIdx.y == 0 && t == 0) {
+      P.zs[p] = f * snew;
+      P.fs[(j & 1) * P.nb + p] = f;      // q~_{j+2}'s
+    }
     if (P.reorth_mode == 2) {
       // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
       __shared__ double cw[4];
       if (lane == 0) cw[wave] = cc;
-      const double zz = __shfl(nz, 32, DD_WAVE);
       __syncthreads();
       double* out = P.ccpart + (size_t)p * 33;
       if (t == 0) out[1 + blockIdx.y] = (cw[0] + cw[1]) + (cw[2] + cw[3]);
-      if (t == 0 && blockIdx.y == 0) out[0] = snew * snew * zz;
+      if (t == 0 && blockIdx.y == 0) out[0] = ww;
     }
     return;
   }
@@ -1320,6 +1335,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
   __shared__ double2 norm;
   __shared__ int fin, nfin;
   const int cgs2 = P.reorth_mode != 0 ? st[ST_REORTH] : 0;
+  const double fj = P.fs[(~j & 1) * P.nb + p];  // of q~_{j+1}
   double2 gj = make_double2(0.0, 0.0);
   int it0 = 0, nre0 = 0;
   double nsum0 = 0.0, nsum20 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
@@ -1353,7 +1369,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
   __syncthreads();
   if (wave == 3) {
     const double nrm = sqrt(__shfl(nz[0], 0, DD_WAVE));
-    if (lane == 0) norm = make_double2(nrm, (nrm > 0.0) ? 1.0 / nrm : 0.0);
+    if (lane == 0) norm = make_double2(nrm / fj, (nrm > 0.0) ? 1.0 / nrm : 0.0);
   }
   arnoldi_column(P, p, j, k, col, norm, cgs2, gj, it0, nre0, nsum0, nsum20, bn, ctl_tol, ctl_maxit,
                  cs_t, sn_t, fin, nfin);
@@ -1365,9 +1381,10 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
                        __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// After k_pass2 of step j: the coefficients h2_v = s_v e_v of the raw dots e_v
-// (coefB, added to the column by k_post_sweep) and the update coefficients
-// s_v h2_v for the sweep, whose z is now the once orthogonalised vector.
+// After k_pass2 of step j: the coefficients h2_v = s_v e_v / f of the raw dots e_v
+// (coefB, added to the column by k_post_sweep; f: the power of two that z has got in
+// the pass) and the update coefficients s_v^2 e_v for the sweep, whose z is now the once
+// orthogonalised vector.
 // Without a second pass the sweep takes the first pass's coefficients, which
 // are already in place.
 template <typename T>
@@ -1383,13 +1400,14 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
     if (re) P.zs[p] = 1.0;
   }
   if (!re) return;
+  const double f1 = 1.0 / P.fs[(~j & 1) * P.nb + p];
   for (int v = blockIdx.y * 4 + wave; v < n; v += 4 * gridDim.y) {
     const double sv = (v < k) ? 1.0 : P.hscale[(size_t)p * (P.m + 1) + v - k];
     double part[1];
     sum_tiles<1>(P, {2 * v}, t0, nt, part);
     const double2 e = make_double2(__shfl(part[0], 0, DD_WAVE), __shfl(part[0], 32, DD_WAVE));
     if (lane == 0) {
-      P.coefB[(size_t)p * P.NC + v] = make_double2(sv * e.x, sv * e.y);
+      P.coefB[(size_t)p * P.NC + v] = make_double2(f1 * sv * e.x, f1 * sv * e.y);
       ((c2<T>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] =
           to_c<T>(make_double2(sv * sv * e.x, sv * sv * e.y));
     }

@@ -6,6 +6,9 @@
 // basis.  With the update coefficients g the sweep forms
 //     q~_{j+1} = zs z_j - sum_v g_v b_v,      b = [C, q~_0 .. q~_j],
 // then z_{j+1} = A q~_{j+1} and its raw dots against [C, q~_0 .. q~_{j+1}].
+// zs and g carry a power of two that keeps ||q~_{j+1}|| at or below one (sw_unit):
+// the sums of FP32 products are then of the size of ||A||^2 at most, whatever the unit of
+// length, and no result changes by it.
 //
 // The stencil needs q~_{j+1} on the cells around, so a workgroup walks a strip
 // of up to 62 columns (64 lanes with one halo column on either side) down the
@@ -121,6 +124,14 @@ template <bool PASS2> __device__ __forceinline__ int sw_position(int t, int G) {
   if (PASS2 || G % 8 != 0) return t;
   const int g = t % G;
   return t - g + g % (G / 8) * 8 + g / (G / 8);
+}
+
+// The power of two f with f sqrt(ww) in [1/2, 1), for ww = ||A q_j||^2: the vector that
+// is left of A q_j, times f, is stored.
+__device__ __forceinline__ double sw_unit(double ww) {
+  if (!(ww > 0.0) || !isfinite(ww)) return 1.0;
+  const int e = ((__double2hiint(ww) >> 20) & 0x7ff) - 1023;      // ww < 2^(e + 1)
+  return __hiloint2double((1023 - ((e + 2) >> 1)) << 20, 0);
 }
 
 template <bool PASS2> __device__ __forceinline__ int sw_plan_strips(const ProbDesc& d) {

@@ -219,3 +219,26 @@ def test_solve_after_an_overflow():
     assert torch.equal(x, want)
     s.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("passes", [1, 2])
+@pytest.mark.parametrize("e", [-20, 24])
+def test_unit_of_length(e, passes):
+    """The same problem in a unit of length of 2^e micrometres: every quantity of
+    the solve is scaled by a power of two, so the history is the same and the field
+    scaled exactly.  In metres A is of size 10^15 and ||A||^3 past the range of
+    complex64."""
+    from paper_1902_00090_amd import FdfdOp, Solver
+    inst = _inst(31, 70, 21)
+    b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
+    u = 2.0 ** e
+    res = []
+    for op in (FdfdOp.from_instance(inst),
+               FdfdOp(inst.eps, inst.omega / u, inst.dx * u, inst.npml)):
+        s = Solver([op], restart=50, cgs_passes=passes, hist_cap=120)
+        (x,), (info,), _ = s.solve([b], tol=1e-14, maxit=120)
+        assert info["iters"] == 120
+        res.append((x.cpu().numpy(), s.history(0)))
+        s.close()
+    assert np.array_equal(res[0][1], res[1][1])
+    assert np.array_equal(res[0][0] * u * u, res[1][0])

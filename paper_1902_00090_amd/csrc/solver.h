@@ -113,8 +113,7 @@ struct PlanDev {
   // one-sweep steps of k_sweep: update coefficients in the inner
   // precision and the factor of z; the cycle's split of the work (k_sweep_plan)
   void* coefS;        // [nb][128]
-  double* zs;         // [nb]
-  double* fs;         // [2][nb] power of two that q~_j carries, by the parity of j
+  double* zs;         // [3][nb] factor; 1 / the power of two that q~_j carries, by the parity of j
   double* ccpart;     // [nb][33] ||w||^2 and the parts of the first pass's ||c||^2
   SweepPlan sw, sw2;  // k_sweep, k_pass2
   size_t sw_ld;       // tiles of a cycle at most: stride of a value's partial sums

@@ -168,8 +168,7 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
     double2* cs = nullptr;
     A.carve(&cs, (size_t)nb * DD_SW_MAXN);
     P.coefS = cs;
-    A.carve(&P.zs, (size_t)nb);
-    A.carve(&P.fs, (size_t)2 * nb);
+    A.carve(&P.zs, (size_t)3 * nb);
     A.carve(&P.live, (size_t)2 * nb);
     A.carve(&P.ccpart, (size_t)nb * 33);
     for (SweepPlan* w : {&P.sw, &P.sw2}) {
@@ -1084,9 +1083,9 @@ extern "C" dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, v
                              hipMemcpyDeviceToHost));
       double f = 1.0;
       if (last > 0)
-        DD_HIP_CHECK(hipMemcpy(&f, s->P.fs + (last & 1) * s->nb + p, sizeof(double),
+        DD_HIP_CHECK(hipMemcpy(&f, s->P.zs + (1 + (last & 1)) * s->nb + p, sizeof(double),
                                hipMemcpyDeviceToHost));
-      hs[last] = 1.0 / f;
+      hs[last] = f;
       for (int v = 0; v <= last; ++v) {
         char* q = dst + (size_t)v * d.D * ib;
         if (s->o.inner == DD_C64)

@@ -1170,6 +1170,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
   }
   // k_sweep: only the cycle's start comes here.  The power of two of the next vector
   // goes by ||w||^2 = s^2 ||z||^2, from the value behind k_matvec_dot's dots
+  int h = 0;
   double f = 1.0, ww = 0.0;
   if (P.fused == STEP_SWEEP) {
     __shared__ double zz_l;
@@ -1183,7 +1184,8 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     }
     __syncthreads();
     ww = snew * snew * zz_l;
-    f = sw_unit(ww);
+    h = sw_unit(ww, 1.0);
+    f = sw_pow2(-h);
   }
   // the new raw dots and update coefficients (s_v for v <= k + j are those
   // of earlier steps; s_{j+1} = snew)
@@ -1207,7 +1209,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
       ((c2<PT>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] = to_c<PT>(make_double2(0.0, 0.0));
     if (t == 0) {
       P.zs[p] = f * snew;
-      P.fs[P.nb + p] = f;
+      P.zs[2 * P.nb + p] = sw_pow2(h);
     }
   }
   if (P.fused == STEP_SWEEP && P.reorth_mode == 2) {
@@ -1294,7 +1296,9 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
     const double nz = sum[0];
     const double nrm = sqrt(__shfl(nz, 0, DD_WAVE));     // of q~, with its power of two
     const double snew = (nrm > 0.0) ? 1.0 / nrm : 0.0;
-    const double ww = snew * snew * __shfl(nz, 32, DD_WAVE), f = sw_unit(ww);
+    const double zz = __shfl(nz, 32, DD_WAVE);
+    const int h = sw_unit(zz, __shfl(nz, 0, DD_WAVE));
+    const double f = sw_pow2(-h);
     double cc = 0.0;
     for (int v = v0; v < nn; v += step) {
       if (v > v0) {
@@ -1306,17 +1310,16 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
       const double part = sum[1];
       const double2 dv = make_double2(__shfl(part, 0, DD_WAVE), __shfl(part, 32, DD_WAVE));
       const double sv = (v == k + j + 1) ? snew : hv;
-      const double gs = f * snew * sv * sv;
+      const double gs = snew * sv * sv, fx = f * dv.x, fy = f * dv.y;
       cc += snew * sv * snew * sv * (dv.x * dv.x + dv.y * dv.y);
       if (lane == 0) {
         cNew[v] = dv;
-        ((c2<T>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] =
-            to_c<T>(make_double2(gs * dv.x, gs * dv.y));
+        ((c2<T>*)P.coefS)[(size_t)p * DD_SW_MAXN + v] = to_c<T>(make_double2(gs * fx, gs * fy));
       }
     }
     if (blockIdx.y == 0 && t == 0) {
       P.zs[p] = f * snew;
-      P.fs[(j & 1) * P.nb + p] = f;      // q~_{j+2}'s
+      P.zs[(1 + (j & 1)) * P.nb + p] = sw_pow2(h);      // of q~_{j+2}
     }
     if (P.reorth_mode == 2) {
       // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
@@ -1325,7 +1328,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
       __syncthreads();
       double* out = P.ccpart + (size_t)p * 33;
       if (t == 0) out[1 + blockIdx.y] = (cw[0] + cw[1]) + (cw[2] + cw[3]);
-      if (t == 0 && blockIdx.y == 0) out[0] = ww;
+      if (t == 0 && blockIdx.y == 0) out[0] = snew * snew * zz;
     }
     return;
   }
@@ -1335,7 +1338,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
   __shared__ double2 norm;
   __shared__ int fin, nfin;
   const int cgs2 = P.reorth_mode != 0 ? st[ST_REORTH] : 0;
-  const double fj = P.fs[(~j & 1) * P.nb + p];  // of q~_{j+1}
+  const double fj = P.zs[(2 - (j & 1)) * P.nb + p];
   double2 gj = make_double2(0.0, 0.0);
   int it0 = 0, nre0 = 0;
   double nsum0 = 0.0, nsum20 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
@@ -1369,7 +1372,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
   __syncthreads();
   if (wave == 3) {
     const double nrm = sqrt(__shfl(nz[0], 0, DD_WAVE));
-    if (lane == 0) norm = make_double2(nrm / fj, (nrm > 0.0) ? 1.0 / nrm : 0.0);
+    if (lane == 0) norm = make_double2(nrm * fj, (nrm > 0.0) ? 1.0 / nrm : 0.0);
   }
   arnoldi_column(P, p, j, k, col, norm, cgs2, gj, it0, nre0, nsum0, nsum20, bn, ctl_tol, ctl_maxit,
                  cs_t, sn_t, fin, nfin);
@@ -1394,13 +1397,13 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int t0 = P.sw2.tile0[p], nt = P.sw2.ntile[p], k = P.desc[p].k, n = k + j + 1;
   const bool re = sw_second_pass(P, p);
+  const double f1 = P.zs[(2 - (j & 1)) * P.nb + p];
   if (st[ST_ACTIVE] == 0) return;
   if (blockIdx.y == 0 && t == 0) {
     st[ST_REORTH] = re ? 1 : 0;
     if (re) P.zs[p] = 1.0;
   }
   if (!re) return;
-  const double f1 = 1.0 / P.fs[(~j & 1) * P.nb + p];
   for (int v = blockIdx.y * 4 + wave; v < n; v += 4 * gridDim.y) {
     const double sv = (v < k) ? 1.0 : P.hscale[(size_t)p * (P.m + 1) + v - k];
     double part[1];

@@ -126,13 +126,16 @@ template <bool PASS2> __device__ __forceinline__ int sw_position(int t, int G) {
   return t - g + g % (G / 8) * 8 + g / (G / 8);
 }
 
-// The power of two f with f sqrt(ww) in [1/2, 1), for ww = ||A q_j||^2: the vector that
-// is left of A q_j, times f, is stored.
-__device__ __forceinline__ double sw_unit(double ww) {
-  if (!(ww > 0.0) || !isfinite(ww)) return 1.0;
-  const int e = ((__double2hiint(ww) >> 20) & 0x7ff) - 1023;      // ww < 2^(e + 1)
-  return __hiloint2double((1023 - ((e + 2) >> 1)) << 20, 0);
+// The power of two f = 2^-h with f ||A q_j|| in (1/4, 1], from zz = ||A q~_j||^2 and un
+// = ||q~_j||^2: the vector that is left of A q_j, times f, is stored.  By the exponents
+// alone, so that it does not wait for the square root of un; 1 if a sum is zero or not
+// finite.
+__device__ __forceinline__ int sw_unit(double zz, double un) {
+  const int ez = __double2hiint(zz) >> 20, eu = __double2hiint(un) >> 20;
+  const bool ok = (unsigned)(ez - 1) < 0x7feu && (unsigned)(eu - 1) < 0x7feu;
+  return ok ? min(max((ez - eu + 2) >> 1, -1000), 1000) : 0;   // zz / un < 2^(ez - eu + 1)
 }
+__device__ __forceinline__ double sw_pow2(int e) { return __hiloint2double((1023 + e) << 20, 0); }
 
 template <bool PASS2> __device__ __forceinline__ int sw_plan_strips(const ProbDesc& d) {
   return PASS2 ? 1 : sw_strips(d.nx);

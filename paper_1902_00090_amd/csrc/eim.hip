@@ -35,6 +35,7 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
+#include <utility>
 #include <vector>
 
 #include "common.h"
@@ -155,9 +156,12 @@ __global__ __launch_bounds__(64) void k_eim_bound(const EimDesc* __restrict__ de
 // with the vector in LDS (one wave a compute unit) 548, with scalar row offsets and
 // buffer accesses 484.  The vector is kept in the output array, whose complex64 is as
 // large, until the field is assembled: it costs no scratch to allocate and free (a call
-// on those 64 problems 962 us, with scratch for it 270 more).
+// on those 64 problems 962 us, with scratch for it 270 more).  Outputs that share memory
+// with a right-hand side, which other columns still read then, are left alone until then
+// and phi is scratch.
 #define DD_EIM_COLS 64
 __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __restrict__ desc,
+                                                  double* __restrict__ phi,
                                                   double* __restrict__ piv,
                                                   double* __restrict__ mu,
                                                   double2* __restrict__ jp) {
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __rest
   const int nx = d.nx, ny = d.ny;
   const double h2 = 1.0 / (d.dx * d.dx), w2 = d.omega * d.omega, e2 = h2 * h2;
   const float* eps = d.eps + ix;
-  double* ph = (double*)d.F + ix;
+  double* ph = (phi ? phi + d.off2 : (double*)d.F) + ix;
   double* pv = piv + d.off2 + ix;
   const double sigma = mu[d.off1 + ix];
   constexpr int U = 16;
@@ -394,31 +398,56 @@ __global__ __launch_bounds__(64) void k_eim_line(const EimDesc* __restrict__ des
 
 // ------------------------------------------------------ field (step 3) ----
 __global__ __launch_bounds__(256) void k_eim_assemble(const EimDesc* __restrict__ desc,
+                                                      const double* phi,
                                                       const double2* __restrict__ amp) {
   const EimDesc d = desc[blockIdx.y];
   const int e = blockIdx.x * 256 + threadIdx.x;
   if (e >= d.nx * d.ny) return;
   const int ix = e % d.nx;
   const double2 a = amp[d.off1 + ix];
-  const double v = ((const double*)d.F)[e];
+  const double v = phi ? phi[d.off2 + e] : ((const double*)d.F)[e];
   d.F[e] = make_float2((float)(a.x * v), (float)(a.y * v));
 }
 
 }  // namespace
 
-// Scratch layout of one call: inverse pivots (D doubles); mu (nx doubles; the
-// shifts until the modes are known); j, the finished rows of the line system (five
-// values), amplitude (nx complex each); then the descriptor table.  Every word is
-// written by the kernels before it is read, so nothing needs clearing between
-// calls.
+// Scratch layout of one call: the modes (D doubles; only where they cannot wait in F),
+// inverse pivots (D doubles); mu (nx doubles; the shifts until the modes are known); j,
+// the finished rows of the line system (five values), amplitude (nx complex each); then
+// the descriptor table.  Every word is written by the kernels before it is read, so
+// nothing needs clearing between calls.
 static size_t even(size_t n) { return (n + 1) & ~(size_t)1; }   // 16-byte alignment for what follows
-static size_t eim_used_bytes(size_t s2, size_t s1, int nb) {
-  return sizeof(double) * (even(s2) + even(s1)) + sizeof(double2) * 7 * s1 + sizeof(EimDesc) * nb;
+static size_t eim_used_bytes(size_t s2, size_t s1, int nb, bool apart) {
+  return sizeof(double) * ((apart ? 2 * s2 : even(s2)) + even(s1)) + sizeof(double2) * 7 * s1 +
+         sizeof(EimDesc) * nb;
 }
 // The size that a call is charged with where the caller or the library provides the
-// scratch: with D doubles more, which the modes took before they moved to F.
+// scratch: room for the modes, whether this call needs it or not.
 static size_t eim_scratch_bytes(size_t s2, size_t s1, int nb) {
-  return sizeof(double) * (2 * s2 + even(s1)) + sizeof(double2) * 7 * s1 + sizeof(EimDesc) * nb;
+  return eim_used_bytes(s2, s1, nb, true);
+}
+
+// Whether an output shares memory with a right-hand side or another output: the modes
+// then have to wait in scratch.
+static bool eim_shared(const std::vector<EimDesc>& hd) {
+  std::vector<std::pair<uintptr_t, uintptr_t>> out, in;   // [begin, end)
+  for (const auto& d : hd) {
+    const size_t D = (size_t)d.nx * d.ny;
+    out.push_back({(uintptr_t)d.F, (uintptr_t)(d.F + D)});
+    in.push_back({(uintptr_t)d.b, (uintptr_t)(d.b + D)});
+  }
+  std::sort(out.begin(), out.end());
+  std::sort(in.begin(), in.end());
+  for (size_t i = 1; i < out.size(); ++i)
+    if (out[i].first < out[i - 1].second) return true;
+  // the outputs are apart: one pass over both lists (right-hand sides may repeat)
+  uintptr_t end = 0;          // of the right-hand sides that begin before this output's end
+  size_t q = 0;
+  for (const auto& f : out) {
+    for (; q < in.size() && in[q].first < f.second; ++q) end = std::max(end, in[q].second);
+    if (end > f.first) return true;
+  }
+  return false;
 }
 
 // Validates the arguments and fills the descriptor table; returns the
@@ -461,8 +490,10 @@ static hipError_t eim_run(const std::vector<EimDesc>& hd, size_t s1, int maxnx, 
   const int nb = (int)hd.size();
   size_t s2 = 0;
   for (const auto& d : hd) s2 += (size_t)d.nx * d.ny;
-  double* piv = (double*)ws;
-  double* mu = piv + even(s2);
+  const bool apart = eim_shared(hd);
+  double* phi = apart ? (double*)ws : nullptr;
+  double* piv = (double*)ws + (apart ? s2 : 0);
+  double* mu = (double*)ws + (apart ? 2 * s2 : even(s2));
   double2* z = (double2*)(mu + even(s1));
   double2 *jp = z, *amp = z + 6 * s1;
   LineRow* rows = (LineRow*)(z + s1);
@@ -476,9 +507,10 @@ static hipError_t eim_run(const std::vector<EimDesc>& hd, size_t s1, int maxnx, 
     const dim3 gb((maxnx + 15) / 16, nb);
     if (maxny <= 1024) k_eim_bound<true><<<gb, 64, (size_t)maxny * 64, stream>>>(dd, mu);
     else k_eim_bound<false><<<gb, 64, 0, stream>>>(dd, mu);
-    k_eim_modes<<<dim3((maxnx + DD_EIM_COLS - 1) / DD_EIM_COLS, nb), DD_EIM_COLS, 0, stream>>>(dd, piv, mu, jp);
+    k_eim_modes<<<dim3((maxnx + DD_EIM_COLS - 1) / DD_EIM_COLS, nb), DD_EIM_COLS, 0, stream>>>(dd, phi, piv,
+                                                                                               mu, jp);
     k_eim_line<<<nb, 64, 0, stream>>>(dd, mu, jp, rows, amp);
-    k_eim_assemble<<<dim3((maxD + 255) / 256, nb), 256, 0, stream>>>(dd, amp);
+    k_eim_assemble<<<dim3((maxD + 255) / 256, nb), 256, 0, stream>>>(dd, phi, amp);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(stream);
@@ -495,7 +527,7 @@ extern "C" dd_status eim_field(const fdfd_op* const* ops, int nb, const void* co
   size_t s2 = 0;
   for (const auto& d : hd) s2 += (size_t)d.nx * d.ny;
   char* ws = nullptr;
-  DD_HIP_CHECK(hipMalloc((void**)&ws, eim_used_bytes(s2, s1, nb)));
+  DD_HIP_CHECK(hipMalloc((void**)&ws, eim_used_bytes(s2, s1, nb, eim_shared(hd))));
   hipError_t e = eim_run(hd, s1, maxnx, maxD, ws, stream);
   (void)hipFree(ws);
   if (e != hipSuccess) {

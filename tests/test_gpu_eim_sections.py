@@ -26,3 +26,27 @@ def test_random_permittivity_matches_oracle(nx, ny):
     want = eim.eim_instance(inst)
     tol = 2.0 ** -24 * np.abs(want) + 1e6 * ny * 2.0 ** -53 * np.abs(want).max()
     assert (np.abs(F.cpu().numpy() - want) <= tol).all()
+
+
+@pytest.mark.parametrize("entry", ["eim_field", "eim_field_noalloc"])
+@pytest.mark.parametrize("over", [(0, 1, 2), (1, 0, 2)])
+def test_outputs_in_the_memory_of_right_hand_sides(entry, over):
+    """A field may be written over its own right-hand side, or over another
+    problem's: every right-hand side is read before an output is written."""
+    import torch
+    from paper_1902_00090_amd import FdfdOp, _lib, eim_field
+    insts = [W.grating(1020, nx=97, ny=43, npml=7), W.grating(1021, nx=97, ny=43, npml=7),
+             W.grating(1022, nx=65, ny=30, npml=7)]
+    ops = [FdfdOp.from_instance(i) for i in insts]
+    want = eim_field(ops, [torch.tensor(i.b, device="cuda") for i in insts])
+    # the right-hand sides behind each other in one buffer, field p in the place of
+    # right-hand side over[p]
+    buf = torch.cat([torch.tensor(i.b, device="cuda") for i in insts])
+    at = [0, insts[0].D, insts[0].D + insts[1].D]
+    F = [buf.view(torch.complex64)[2 * at[o]:2 * at[o] + i.D] for o, i in zip(over, insts)]
+    _lib.check(getattr(_lib.lib(), entry)(
+        _lib.ptr_array([op.handle for op in ops]), 3,
+        _lib.ptr_array([buf[a:].data_ptr() for a in at]),
+        _lib.ptr_array([f.data_ptr() for f in F]), torch.cuda.current_stream().cuda_stream), entry)
+    for p in range(3):
+        assert torch.equal(F[p], want[p]), p

@@ -233,9 +233,9 @@ __global__ __launch_bounds__(DD_EIM_COLS) void k_eim_modes(const EimDesc* __rest
         }
       }
     }
-    // an iteration grows the vector by up to 1e10 / h2: scale it if four of
-    // them could leave the range
-    if (it < 3 && !(ss < 1e120)) {
+    // an iteration multiplies the vector by up to 1e10 / h2: scale it if four of
+    // them could leave the range at either end
+    if (it < 3 && !(ss < 1e120 && ss > 1e-60)) {
       const double f = 1.0 / sqrt(ss);
       for (int i = 0; i < ny; ++i) ph[(size_t)i * nx] *= f;
     }

@@ -50,3 +50,19 @@ def test_outputs_in_the_memory_of_right_hand_sides(entry, over):
         _lib.ptr_array([f.data_ptr() for f in F]), torch.cuda.current_stream().cuda_stream), entry)
     for p in range(3):
         assert torch.equal(F[p], want[p]), p
+
+
+@pytest.mark.parametrize("e", [-100, -60, 60, 100])
+def test_unit_of_length(e):
+    """The same problem in a unit of length of 2^e micrometres, its source scaled with
+    the operator: the same field, to the rounding that scaling a mode on the way may
+    change (tolerances as above)."""
+    import torch
+    from paper_1902_00090_amd import FdfdOp, eim_field
+    inst = W.grating(1030, nx=65, ny=40, npml=7)
+    u = 2.0 ** e
+    op = FdfdOp(inst.eps, inst.omega / u, inst.dx * u, inst.npml)
+    (F,) = eim_field([op], [torch.tensor(inst.b / (u * u), device="cuda")])
+    want = eim.eim_instance(inst)
+    tol = 2.0 ** -24 * np.abs(want) + 1e6 * inst.ny * 2.0 ** -53 * np.abs(want).max()
+    assert (np.abs(F.cpu().numpy() - want) <= tol).all()

@@ -143,9 +143,11 @@ typedef struct {
                         /* matvec and the dots of step j+1 read each basis vector */
                         /* from memory once) is taken by itself where             */
                         /* kmax + restart + 1 is at most 128 (complex128: 64) and  */
-                        /* the grids have fewer than 2^21 cells; 1 = also for the  */
-                        /* rest up to 128 with cgs_passes = 1, where it is faster  */
-                        /* for one problem alone and slower for batches; default 0 */
+                        /* the grids have fewer than 2^21 cells and are not long   */
+                        /* and narrow (where it is slower); 1 = also with more     */
+                        /* vectors, up to 128, or cells, with cgs_passes = 1,      */
+                        /* where it is faster for one problem alone and slower     */
+                        /* for batches; default 0                                  */
 } dd_solver_opts;
 
 /* Per-problem result (host struct). */

@@ -219,18 +219,47 @@ static dd_status tuned_elems_per_thread(const fdfd_op* const* ops, int nb, const
 // second pass) against two (three): one problem of 480 x 240 257 and 497 ms, 48 of
 // 192 x 96 381 and 574, nine uneven ones with two passes 268 and 531, one of 64 x 64
 // in complex128 with two passes 72 and 129.
+// A row of a sweep costs a workgroup about the same for few columns as for the 62 of
+// a full strip (0.5 us for a short basis, a chain of latencies), where two sweeps go by
+// cells.  Where each compute unit has many rows to walk it therefore pays only from a mean
+// number of columns on: more of them the more rows there are, and for a short basis,
+// which gives a row little to do.  Cycles of one grid with one sweep a step, times as fast
+// as with two, by columns a strip, one pass, with 16, 64 and 128 strip rows a compute unit:
+// complex64, 100 vectors, 3 columns 1.07, 0.53, 0.36; 16: 1.28, 1.07, 0.81; 24: 1.44, 1.22,
+// 1.13; 20 vectors, 16 columns 1.19, 0.94, 0.76; 24: 1.23, 1.13, 1.06; 8 vectors, 24 columns
+// 1.11, 0.93, 0.79; 48: 1.11, 1.10, 0.99; complex128, 50 vectors, 8 columns 0.84, 0.63,
+// 0.50; 16: 1.00, 0.87, 0.65; 24: 1.13, 1.01, 0.94; 32: 1.29, 1.10, 1.06.  With four rows
+// 1.2 and more everywhere.
 // On request and with one pass k_fused_sweep takes what is left up to 128 vectors:
 // complex128 with 65 or more, and grids too large for the descriptors.  One problem
-// alone gains by it, batches lose.  Every path has kernels in both precisions.
-static int step_path(int nb, const int* nx, const int* ny, const dd_solver_opts& o, int nvec) {
-  bool fits = nvec <= (o.inner == DD_C64 ? DD_SW_MAXN : DD_SW_MAXN / 2);
+// alone gains by it, batches lose, and so do narrow grids, by up to 20 times.  Every path
+// has kernels in both precisions.
+static int step_path(int nb, const int* nx, const int* ny, const dd_solver_opts& o, int nvec,
+                     int ncu) {
+  const bool c64 = o.inner == DD_C64;
+  bool fits = nvec <= (c64 ? DD_SW_MAXN : DD_SW_MAXN / 2);
+  long long cells = 0, rows = 0;
   for (int p = 0; p < nb; ++p) {
     // vectors are padded to a multiple of at most 8 elements a thread
     const size_t D = (size_t)nx[p] * ny[p], pad = DD_BLOCK * 8;
     fits = fits && (D + pad - 1) / pad * pad * 8 * DD_SW_MAXN < (size_t)DD_SW_OUT;
+    cells += (long long)D;
+    rows += (long long)sw_strips(nx[p]) * ny[p];
   }
-  if (fits) return STEP_SWEEP;
-  return (o.fused && o.cgs_passes == 1 && nvec <= DD_FUSED_MAXN) ? STEP_FUSED : STEP_PLAIN;
+  const bool many = rows > 64ll * ncu;
+  const int need = nvec <= 16 ? 48 : c64 ? (nvec <= 48 || many ? 20 : 10) : (many ? 28 : 20);
+  const bool narrow = rows > (c64 ? 16ll : 8ll) * ncu && cells < need * rows;
+  if (fits && !narrow) return STEP_SWEEP;
+  return (!fits && o.fused && o.cgs_passes == 1 && nvec <= DD_FUSED_MAXN) ? STEP_FUSED : STEP_PLAIN;
+}
+
+// Compute units of the current device; of an MI355X where there is none.
+static int device_cus() {
+  int dev = 0, ncu = 0;
+  if (hipGetDevice(&dev) == hipSuccess &&
+      hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && ncu > 0)
+    return ncu;
+  return 256;
 }
 
 extern "C" int dd_solver_step_path(int nb, const int* nx, const int* ny, const dd_solver_opts* opts) {
@@ -238,7 +267,7 @@ extern "C" int dd_solver_step_path(int nb, const int* nx, const int* ny, const d
   dd_solver_opts_default(&o);
   if (opts) o = *opts;
   if (nb < 1 || !nx || !ny) { dd_set_error("dd_solver_step_path: need nb >= 1 grids"); return -1; }
-  return step_path(nb, nx, ny, o, o.kmax + o.restart + 1);
+  return step_path(nb, nx, ny, o, o.kmax + o.restart + 1, device_cus());
 }
 
 static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
@@ -315,13 +344,7 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     blk += d.nblk;
   }
   s->nchunks = blk;
-  {
-    int dev = 0, ncu = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-        ncu > 0)
-      s->ncu = ncu;
-  }
+  s->ncu = device_cus();
   const int NC = K + m + 1;
   const int NV = ((2 * NC + 31) / 32) * 32 + 32;
   PlanDev& P = s->P;
@@ -337,7 +360,7 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
   {
     std::vector<int> gx(nb), gy(nb);
     for (int p = 0; p < nb; ++p) { gx[p] = ops[p]->nx; gy[p] = ops[p]->ny; }
-    s->fused = step_path(nb, gx.data(), gy.data(), o, NC);
+    s->fused = step_path(nb, gx.data(), gy.data(), o, NC, s->ncu);
   }
   if (s->fused == STEP_SWEEP) {
     s->sw_grid = 2 * s->ncu;               // at most two workgroups per compute unit

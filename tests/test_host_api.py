@@ -254,3 +254,30 @@ def test_step_path_rule_and_its_kernels():
                             (inner, nvec, passes, fused, nx, ny)
                         assert hasattr(raw, kernels[want].format("fd"[inner])), kernels[want]
     assert lib.dd_solver_step_path(0, None, None, None) == -1
+
+
+@pytest.mark.parametrize("inner,nvec,nx,ny,want", [
+    # a mean of few columns a strip and many rows a compute unit (256 of them): two sweeps
+    (0, 101, 3, 40000, 0), (0, 101, 9, 20000, 0), (0, 101, 16, 8192, 2), (0, 101, 16, 20000, 0),
+    (0, 101, 24, 40000, 2), (0, 21, 16, 8192, 0), (0, 21, 24, 30000, 2), (0, 9, 32, 8192, 0),
+    (0, 9, 62, 30000, 2), (0, 9, 64, 30000, 0), (1, 51, 16, 8192, 0), (1, 51, 24, 8192, 2),
+    (1, 51, 24, 40000, 0), (1, 51, 32, 40000, 2),
+    # few rows, however narrow, and short wide grids: one
+    (0, 101, 3, 4096, 2), (0, 9, 5, 1000, 2), (1, 51, 3, 2048, 2), (0, 101, 20000, 9, 2),
+    (0, 101, 480, 240, 2), (1, 51, 64, 64, 2)])
+def test_step_path_of_narrow_grids(inner, nvec, nx, ny, want):
+    import torch
+    from paper_1902_00090_amd import _lib
+    if torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the rows are counted for 256 compute units")
+    o = _lib.dd_solver_opts()
+    _lib.lib().dd_solver_opts_default(C.byref(o))
+    o.inner, o.kmax, o.restart = inner, 0, nvec - 1
+    path = _lib.lib().dd_solver_step_path
+    for fused in (0, 1):                   # narrow grids lose by the fused option too
+        o.fused, o.cgs_passes = fused, 1
+        assert path(1, C.byref(C.c_int(nx)), C.byref(C.c_int(ny)), C.byref(o)) == want
+    # a batch goes by its mean: many wide ones beside it
+    n = 40
+    X, Y = (C.c_int * n)(nx, *[480] * (n - 1)), (C.c_int * n)(ny, *[2000] * (n - 1))
+    assert path(n, X, Y, C.byref(o)) == 2

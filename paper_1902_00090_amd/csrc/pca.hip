@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void k_pca_gram(const float2* __restrict__ S, 
 
 // G (M x M, row-major, full Hermitian) from the slice partials in a fixed
 // order: 64 entries of a tile a workgroup, four threads an entry (a quarter of
-// the slices each, eight loads in flight).  bad: set if a sum is not finite.
+// the slices each, eight loads in flight).  bad (if given): set if a sum is not finite.
 __global__ __launch_bounds__(256) void k_pca_gram_reduce(const double2* __restrict__ part, int M,
                                                          int tile, int nslices,
                                                          double2* __restrict__ G,
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void k_pca_gram_reduce(const double2* __restri
   sy = (sum[0][l].y + sum[1][l].y) + (sum[2][l].y + sum[3][l].y);
   const int a = ta * tile + i / tile, b = tb * tile + i % tile;
   if (a >= M || b >= M) return;
-  if (!isfinite(sx) || !isfinite(sy)) atomicOr(bad, 1);
+  if (bad && (!isfinite(sx) || !isfinite(sy))) atomicOr(bad, 1);
   // a diagonal tile holds both halves; its own lower one is left to the upper
   if (a > b) return;
   G[(size_t)a * M + b] = make_double2(sx, a == b ? 0.0 : sy);
@@ -830,13 +830,12 @@ dd_status gram_host(const float2* V, int k, int D, const double2* f, std::vector
   return DD_OK;
 }
 
-// G_ab = <F_a, F_b> (M x M, FP64) of M device rows of D complex64 values, and
-// whether all of it is finite.  Tiles of 64 x 64 from 49 rows on (below, half of
+// G_ab = <F_a, F_b> (M x M, FP64) of M device rows of D complex64 values.  Tiles of 64 x 64 from 49 rows on (below, half of
 // one would be padding), the elements in as many slices (of 2048 workgroups at
 // most) as leave the last round of resident workgroups, three a compute unit,
-// fullest.  With finite = nullptr the call does not wait: the flag stays on the
-// device, behind G, and the caller keeps bpart until the kernels are done.
-static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, DevBuf& bpart, bool* finite,
+// fullest.  flag: an int behind G that is 0 where all of it is finite.  The call does not
+// wait: the caller keeps bpart until the kernels are done.
+static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, DevBuf& bpart, bool flag,
                              hipStream_t stream) {
   const int tile = M > 48 ? 64 : 32;
   const int nta = (M + tile - 1) / tile, ntiles = nta * (nta + 1) / 2;
@@ -854,31 +853,28 @@ static dd_status gram_device(const float2* F, int M, int D, DevBuf& bG, DevBuf& 
   DD_HIP_CHECK(hipMalloc(&bpart.p, sizeof(double2) * (size_t)nslices * ntiles * tile * tile));
   DD_HIP_CHECK(hipMalloc(&bG.p, sizeof(double2) * M * M + sizeof(int)));
   double2 *part = bpart.as<double2>(), *G = bG.as<double2>();
-  int* bad = (int*)(G + (size_t)M * M);
-  DD_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), stream));
+  int* bad = flag ? (int*)(G + (size_t)M * M) : nullptr;
+  if (flag) DD_HIP_CHECK(hipMemsetAsync(bad, 0, sizeof(int), stream));
   if (tile == 64) k_pca_gram<2><<<dim3(ntiles, nslices), 256, 0, stream>>>(F, M, D, per, part);
   else k_pca_gram<1><<<dim3(ntiles, nslices), 256, 0, stream>>>(F, M, D, per, part);
   k_pca_gram_reduce<<<dim3(ntiles, tile * tile / 64), 256, 0, stream>>>(part, M, tile, nslices, G,
                                                                         bad);
   DD_HIP_CHECK(hipGetLastError());
-  if (!finite) return DD_OK;
-  int hbad = 0;
-  DD_HIP_CHECK(hipMemcpyAsync(&hbad, bad, sizeof(int), hipMemcpyDeviceToHost, stream));
-  DD_HIP_CHECK(hipStreamSynchronize(stream));
-  *finite = hbad == 0;
   return DD_OK;
 }
 
-// The same on the host.
+// The same on the host, and whether all of it is finite.
 static dd_status gram_rows(const float2* F, int M, int D, std::vector<cd>& G, bool* finite,
                            hipStream_t stream) {
   DevBuf bG, bpart;
-  dd_status rc = gram_device(F, M, D, bG, bpart, finite, stream);
+  dd_status rc = gram_device(F, M, D, bG, bpart, false, stream);
   if (rc != DD_OK) return rc;
   G.resize((size_t)M * M);
   static_assert(sizeof(cd) == sizeof(double2), "complex layout");
   DD_HIP_CHECK(hipMemcpyAsync(G.data(), bG.p, sizeof(cd) * G.size(), hipMemcpyDeviceToHost, stream));
   DD_HIP_CHECK(hipStreamSynchronize(stream));
+  *finite = true;
+  for (const cd& v : G) *finite = *finite && std::isfinite(v.real()) && std::isfinite(v.imag());
   return DD_OK;
 }
 
@@ -925,8 +921,14 @@ extern "C" dd_status pca_build(const void* Sv, int M, int D, int k, void* Uv, do
   std::vector<cd> W;
   dd_status rc = DD_OK;
   if (M >= 128) {
-    rc = gram_device(S, M, D, bG, bpart, &finite, stream);
-    if (rc == DD_OK && finite) rc = lanczos_device(bG.as<double2>(), M, k, theta, W, stream);
+    rc = gram_device(S, M, D, bG, bpart, true, stream);
+    if (rc != DD_OK) return rc;
+    int bad = 0;
+    DD_HIP_CHECK(hipMemcpyAsync(&bad, bG.as<double2>() + (size_t)M * M, sizeof(int),
+                                hipMemcpyDeviceToHost, stream));
+    DD_HIP_CHECK(hipStreamSynchronize(stream));
+    finite = bad == 0;
+    if (finite) rc = lanczos_device(bG.as<double2>(), M, k, theta, W, stream);
   } else {
     std::vector<cd> hG;
     rc = gram_rows(S, M, D, hG, &finite, stream);
@@ -996,7 +998,7 @@ extern "C" dd_status local_pca_targets(const void* Fv, int S, int D, int window,
     // 32 fields of 480 x 240, windows of 17: 380 us, on the host's way below 815
     DevBuf bG, bpart, bcoef;
     DD_HIP_CHECK(hipMalloc(&bcoef.p, sizeof(double2) * (size_t)S * S * k));
-    dd_status rc = gram_device(F, S, D, bG, bpart, nullptr, stream);
+    dd_status rc = gram_device(F, S, D, bG, bpart, true, stream);
     if (rc != DD_OK) return rc;
     const double2* G = bG.as<double2>();
     double2* coef = bcoef.as<double2>();

@@ -127,3 +127,21 @@ def test_basis_signs_do_not_depend_on_rounding(M):
     U, _ = pca_build(torch.tensor(S, device="cuda"), 12)
     P, _ = pca_build(torch.tensor(S[:, perm].copy(), device="cuda"), 12)
     assert np.abs(U.cpu().numpy()[:, perm] - P.cpu().numpy()).max() <= 1e-5
+
+
+@pytest.mark.parametrize("M", [1, 5, 127, 128])
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_snapshots_that_are_not_finite(M, bad):
+    """Found in the Gram matrix, on the host below 128 snapshots and by the device's
+    flag from there on; a finite call afterwards sees nothing of it."""
+    import torch
+    from paper_1902_00090_amd import DDError, pca_build
+    rng = np.random.default_rng(M)
+    S = W.random_complex(rng, (M, 70)).astype(np.complex64)
+    S[M // 2, 69] = bad
+    with pytest.raises(DDError, match="non-finite"):
+        pca_build(torch.tensor(S, device="cuda"), 1)
+    S[M // 2, 69] = 0.0
+    U, sg = pca_build(torch.tensor(S, device="cuda"), 1)
+    want = np.linalg.norm(S.astype(np.complex128), 2)
+    np.testing.assert_allclose(sg, [want], rtol=1e-10)

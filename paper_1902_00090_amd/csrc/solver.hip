@@ -181,37 +181,6 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   }
 }
 
-// Validates the options and builds the host-side plan of a solver (problem
-// descriptors, chunk map, workspace parameters); no device memory yet.
-extern "C" dd_status dd_solver_autotune(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
-                                        int* best, double* ms_per_step);
-
-// elems_per_thread = -1: the autotuner's choice for this set of grid sizes and
-// options, measured once per process and remembered.
-static dd_status tuned_elems_per_thread(const fdfd_op* const* ops, int nb, const dd_solver_opts& o,
-                                        int* R) {
-  static std::mutex mu;
-  static std::map<std::string, int> cache;
-  std::string key = std::to_string(nb) + "/" + std::to_string(o.restart) + "/" +
-                    std::to_string(o.inner) + "/" + std::to_string(o.cgs_passes) + "/" +
-                    std::to_string(o.precond) + "/" + std::to_string(o.fused) + ":";
-  for (int p = 0; p < nb; ++p) key += std::to_string(ops[p]->nx) + "x" + std::to_string(ops[p]->ny) + ",";
-  {
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(key);
-    if (it != cache.end()) { *R = it->second; return DD_OK; }
-  }
-  dd_solver_opts t = o;
-  t.elems_per_thread = 0;
-  int best = 0;
-  dd_status rc = dd_solver_autotune(ops, nb, &t, &best, nullptr);
-  if (rc != DD_OK) return rc;
-  std::lock_guard<std::mutex> lock(mu);
-  cache[key] = best;
-  *R = best;
-  return DD_OK;
-}
-
 // The Arnoldi step of a solver with nvec = kmax + restart + 1 basis vectors: one
 // sweep (k_sweep, with a second Gram-Schmidt pass k_pass2) for a basis of at most
 // 128 vectors (64 in complex128, whose values take twice the registers) whose
@@ -262,6 +231,42 @@ static int device_cus() {
   return 256;
 }
 
+static int step_path(const fdfd_op* const* ops, int nb, const dd_solver_opts& o, int ncu) {
+  std::vector<int> gx(nb), gy(nb);
+  for (int p = 0; p < nb; ++p) { gx[p] = ops[p]->nx; gy[p] = ops[p]->ny; }
+  return step_path(nb, gx.data(), gy.data(), o, o.kmax + o.restart + 1, ncu);
+}
+
+extern "C" dd_status dd_solver_autotune(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
+                                        int* best, double* ms_per_step);
+
+// elems_per_thread = -1: the autotuner's choice for this set of grid sizes, options and
+// the step that follows from them, measured once per process and remembered.
+static dd_status tuned_elems_per_thread(const fdfd_op* const* ops, int nb, const dd_solver_opts& o,
+                                        int* R) {
+  static std::mutex mu;
+  static std::map<std::string, int> cache;
+  std::string key = std::to_string(nb) + "/" + std::to_string(o.restart) + "/" +
+                    std::to_string(o.inner) + "/" + std::to_string(o.cgs_passes) + "/" +
+                    std::to_string(o.precond) + "/" + std::to_string(o.fused) + "/" +
+                    std::to_string(step_path(ops, nb, o, device_cus())) + ":";
+  for (int p = 0; p < nb; ++p) key += std::to_string(ops[p]->nx) + "x" + std::to_string(ops[p]->ny) + ",";
+  {
+    std::lock_guard<std::mutex> lock(mu);
+    auto it = cache.find(key);
+    if (it != cache.end()) { *R = it->second; return DD_OK; }
+  }
+  dd_solver_opts t = o;
+  t.elems_per_thread = 0;
+  int best = 0;
+  dd_status rc = dd_solver_autotune(ops, nb, &t, &best, nullptr);
+  if (rc != DD_OK) return rc;
+  std::lock_guard<std::mutex> lock(mu);
+  cache[key] = best;
+  *R = best;
+  return DD_OK;
+}
+
 extern "C" int dd_solver_step_path(int nb, const int* nx, const int* ny, const dd_solver_opts* opts) {
   dd_solver_opts o;
   dd_solver_opts_default(&o);
@@ -270,7 +275,10 @@ extern "C" int dd_solver_step_path(int nb, const int* nx, const int* ny, const d
   return step_path(nb, nx, ny, o, o.kmax + o.restart + 1, device_cus());
 }
 
-static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
+// Validates the options and builds the host-side plan of a solver (problem
+// descriptors, chunk map, workspace parameters); no device memory yet.  path: the
+// Arnoldi step, -1 for the rule's.
+static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts, int path,
                              dd_solver** out) {
   if (!out) { dd_set_error("dd_solver_create: out is NULL"); return DD_EINVAL; }
   *out = nullptr;
@@ -357,11 +365,7 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
     int GB = (int)std::min<size_t>(32, std::max<size_t>(1, (64ull << 20) / per));
     P.GB = GB;
   }
-  {
-    std::vector<int> gx(nb), gy(nb);
-    for (int p = 0; p < nb; ++p) { gx[p] = ops[p]->nx; gy[p] = ops[p]->ny; }
-    s->fused = step_path(nb, gx.data(), gy.data(), o, NC, s->ncu);
-  }
+  s->fused = path >= 0 ? path : step_path(ops, nb, o, s->ncu);
   if (s->fused == STEP_SWEEP) {
     s->sw_grid = 2 * s->ncu;               // at most two workgroups per compute unit
     int strips = 0;                        // one tile each at the least
@@ -409,12 +413,12 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
   return DD_OK;
 }
 
-extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
-                                      dd_solver** out) {
+static dd_status solver_create(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
+                               int path, dd_solver** out) {
   if (!out) { dd_set_error("dd_solver_create: out is NULL"); return DD_EINVAL; }
   *out = nullptr;
   dd_solver* s = nullptr;
-  dd_status rc = solver_plan(ops, nb, opts, &s);
+  dd_status rc = solver_plan(ops, nb, opts, path, &s);
   if (rc != DD_OK) return rc;
   const dd_solver_opts& o = s->o;
   PlanDev& P = s->P;
@@ -484,6 +488,11 @@ extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const d
   return DD_OK;
 }
 
+extern "C" dd_status dd_solver_create(const fdfd_op* const* ops, int nb, const dd_solver_opts* opts,
+                                      dd_solver** out) {
+  return solver_create(ops, nb, opts, -1, out);
+}
+
 extern "C" size_t dd_solver_device_bytes(const dd_solver* s) { return s ? s->bytes : 0; }
 
 extern "C" int dd_solver_elems_per_thread(const dd_solver* s) { return s ? s->R : 0; }
@@ -493,7 +502,7 @@ extern "C" dd_status dd_solver_workspace_bytes(const fdfd_op* const* ops, int nb
   if (!bytes) { dd_set_error("dd_solver_workspace_bytes: bytes is NULL"); return DD_EINVAL; }
   *bytes = 0;
   dd_solver* s = nullptr;
-  dd_status rc = solver_plan(ops, nb, opts, &s);
+  dd_status rc = solver_plan(ops, nb, opts, -1, &s);
   if (rc != DD_OK) return rc;
   Arena A;
   ProbDesc* dd = nullptr;
@@ -990,6 +999,10 @@ extern "C" dd_status dd_solver_autotune(const fdfd_op* const* ops, int nb, const
   dd_solver_opts_default(&o);
   if (opts) o = *opts;
   o.hist_cap = 0;
+  for (int p = 0; p < nb; ++p)
+    if (!ops[p]) { dd_set_error("dd_solver_autotune: ops[%d] is NULL", p); return DD_EINVAL; }
+  // without augmenting vectors, by the step that a solver with them takes
+  const int path = step_path(ops, nb, o, device_cus());
   o.kmax = 0;
   o.workspace = nullptr;      // candidates differ in size: each allocates its own
   o.workspace_bytes = 0;
@@ -1016,7 +1029,7 @@ extern "C" dd_status dd_solver_autotune(const fdfd_op* const* ops, int nb, const
   for (int ci = 0; ci < 4 && rc == DD_OK; ++ci) {
     o.elems_per_thread = cands[ci];
     dd_solver* s = nullptr;
-    rc = dd_solver_create(ops, nb, &o, &s);
+    rc = solver_create(ops, nb, &o, path, &s);
     if (rc != DD_OK) break;
     hipEvent_t e0, e1;
     (void)hipEventCreate(&e0);

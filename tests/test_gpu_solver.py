@@ -355,3 +355,21 @@ def test_gram_schmidt_modes_match_oracle(cgs, select):
             assert infos[t]["iters"] == 90
             np.testing.assert_allclose(s.history(t)[:90], refs[g], rtol=1e-7, atol=1e-14)
         s.close()
+
+
+def test_autotune_times_the_step_that_the_solver_takes():
+    """kmax = 40 and restart = 100 take two sweeps a step, restart = 100 alone one,
+    which takes less than half as long on one 480 x 240 problem; the tuner times the
+    step of the options that it is given (kmax is not in its basis)."""
+    import ctypes as C
+    from paper_1902_00090_amd import _lib, _opts
+    op = _op(W.grating(1000))
+    ms = {}
+    for kmax in (0, 40):
+        o = _opts(restart=100, kmax=kmax, cgs_passes=1)
+        best, t = C.c_int(), (C.c_double * 4)()
+        assert _lib.lib().dd_solver_autotune(_lib.ptr_array([op.handle]), 1, C.byref(o),
+                                             C.byref(best), t) == 0
+        ms[kmax] = min(t)
+    print("autotune ms per step:", ms)
+    assert ms[40] > 1.4 * ms[0]

@@ -167,7 +167,10 @@ void dd_solver_opts_default(dd_solver_opts* o);
 
 /* Device bytes of the workspace a solver for these operators and options
  * needs (*bytes, host out): every vector, the FP64 small state and the
- * partial-sum rows, carved from one block.  No device memory is touched. */
+ * partial sums, carved from one block.  Solvers that take one sweep a step hold
+ * two vectors more a problem, and the records and sums of its tiles: the size is
+ * a function of the grids, the options and the library's version, to be asked for
+ * rather than kept.  No device memory is touched. */
 dd_status dd_solver_workspace_bytes(const fdfd_op* const* ops, int nb,
                                     const dd_solver_opts* opts, size_t* bytes);
 

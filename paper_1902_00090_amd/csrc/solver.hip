@@ -156,10 +156,10 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
   A.carve(&P.keep, (size_t)nb);
   A.carve(&P.bad, (size_t)nb);
   double* part = nullptr;
-  const size_t rows = std::max<size_t>({(size_t)s->nchunks, s->htiles.size(),
-                                        s->fused == STEP_SWEEP ? (size_t)s->sw_most : 0});
-  A.carve(&part, rows * P.NV);
-  P.sw_ld = (size_t)s->sw_most;
+  // rows of NV values, or with k_sweep 2 NC + 2 values of whole lines over the tiles
+  P.sw_ld = ((size_t)s->sw_most + 15) & ~(size_t)15;
+  A.carve(&part, std::max(std::max((size_t)s->nchunks, s->htiles.size()) * P.NV,
+                          P.sw_ld * (2 * P.NC + 2)));
   P.partial = part;
   A.carve(&P.gpart, (size_t)nb * P.GB * std::max(1, gram_tiles(std::max(K, 1))) * 32);
   A.carve(&P.hist, (size_t)nb * std::max(1, o.hist_cap));
@@ -173,7 +173,8 @@ static void layout_workspace(dd_solver* s, Arena& A, ProbDesc*& dd, int*& db2p) 
     A.carve(&P.ccpart, (size_t)nb * 33);
     for (SweepPlan* w : {&P.sw, &P.sw2}) {
       if (w == &P.sw2 && P.reorth_mode == 0) break;
-      A.carve(&w->tiles, (size_t)s->sw_most + s->sw_grid);   // the last round has gaps
+      // rounds of as many records as there are workgroups; the last one has gaps
+      A.carve(&w->tiles, (size_t)(s->sw_most + s->sw_grid - 1) / s->sw_grid * s->sw_grid);
       A.carve(&w->count, 2);
       A.carve(&w->tile0, (size_t)nb);
       A.carve(&w->ntile, (size_t)nb);
@@ -368,9 +369,14 @@ static dd_status solver_plan(const fdfd_op* const* ops, int nb, const dd_solver_
   s->fused = path >= 0 ? path : step_path(ops, nb, o, s->ncu);
   if (s->fused == STEP_SWEEP) {
     s->sw_grid = 2 * s->ncu;               // at most two workgroups per compute unit
-    int strips = 0;                        // one tile each at the least
-    for (int p = 0; p < nb; ++p) strips += sw_strips(ops[p]->nx);
-    s->sw_most = std::max(strips, 4 * s->sw_grid);
+    // tiles: one a strip at the least, and no more than rows
+    long long strips = 0, rows = 0, runs = 0;
+    for (int p = 0; p < nb; ++p) {
+      strips += sw_strips(ops[p]->nx);
+      rows += (long long)sw_strips(ops[p]->nx) * ops[p]->ny;
+      runs += (ops[p]->D + 63) / 64;
+    }
+    s->sw_most = (int)std::max(strips, std::min(4ll * s->sw_grid, std::max(rows, runs)));
   }
   // Fused sweep tiles: strips of DD_FUSED_SW columns walked down bands of rows
   if (s->fused == STEP_FUSED) {

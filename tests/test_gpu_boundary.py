@@ -155,3 +155,16 @@ def test_trained_checkpoint_serves_through_predict_subspace():
     assert all(float(torch.linalg.vector_norm(U1[p, j])) > 0 for p in range(2) for j in range(10))
     pr.close()
     net.close()
+
+
+@pytest.mark.parametrize("nx,ny,restart,inner", [(64, 64, 30, "c64"), (64, 64, 50, "c128"),
+                                                 (96, 48, 40, "c128"), (480, 240, 100, "c64")])
+def test_workspace_is_the_vectors_and_little_more(nx, ny, restart, inner):
+    """The basis, the two vectors A q and the FP64 residual take most of a solver's
+    workspace, also of a small one: tile records and partial sums go by the tiles
+    that its rows can be cut into (20% for all the rest)."""
+    from paper_1902_00090_amd import FdfdOp, workspace_bytes
+    op = FdfdOp(np.full((ny, nx), 2.0, np.float32), 4.0, 0.04, 3)
+    vec = nx * ny * (8 if inner == "c64" else 16)
+    need = (restart + 1 + 2) * vec + nx * ny * 16
+    assert need <= workspace_bytes([op], restart=restart, inner=inner) <= 1.2 * need

@@ -136,3 +136,83 @@ def test_fused_c64_on_a_grid_past_the_descriptors():
     xo, io = gmres_aug.gmres_aug(A, inst.b, np.zeros((inst.D, 0)), restart=6, tol=1e-30, maxit=6)
     np.testing.assert_allclose(h, io["history"][:6], rtol=1e-4)
     assert np.linalg.norm(x - xo) <= 1e-3 * np.linalg.norm(xo)
+
+
+def _path(insts, nvec, inner, fused, passes=1):
+    import ctypes as C
+    from paper_1902_00090_amd import _lib, _opts
+    o = _opts(restart=nvec - 1, kmax=0, inner=inner, cgs_passes=passes, fused=fused)
+    n = len(insts)
+    return _lib.lib().dd_solver_step_path(n, (C.c_int * n)(*[i.nx for i in insts]),
+                                          (C.c_int * n)(*[i.ny for i in insts]), C.byref(o))
+
+
+# k_fused_sweep: complex128 with 65 to 128 vectors (the tests above stay below)
+@pytest.mark.parametrize("k", [0, 4])
+@pytest.mark.parametrize("restart", [70, 120])
+@pytest.mark.parametrize("nx,ny", [(20, 16), (70, 24)])
+def test_fused_long_basis_history_matches_oracle(nx, ny, restart, k):
+    inst = _inst(400 + nx + k, nx, ny)
+    assert _path([inst], restart + max(k, 1) + 1, "c128", True) == 1
+    A = fdfd.assemble_instance(inst)
+    V = W.random_complex(np.random.default_rng(41 + k), (inst.D, k)) if k else None
+    steps = 150
+    (x,), (inf,), (h,) = _solve([inst], [V], restart, steps)
+    xo, io = gmres_aug.gmres_aug(A, inst.b, V if k else np.zeros((inst.D, 0)), restart=restart,
+                                 tol=1e-30, maxit=steps)
+    assert inf["iters"] == steps
+    np.testing.assert_allclose(h, io["history"][:steps], rtol=1e-7, atol=1e-14)
+    np.testing.assert_allclose(x, xo, rtol=0, atol=1e-7 * np.abs(xo).max())
+
+
+@pytest.mark.parametrize("kind", [None, "jacobi", "pml"])
+def test_fused_long_basis_uneven_and_preconditioned(kind):
+    insts = [_inst(500, 20, 16), _inst(502, 500, 8, npml=2), _inst(503, 130, 41)]
+    assert _path(insts, 102, "c128", True) == 1
+    steps = 130
+    xs, infos, hs = _solve(insts, [None] * 3, 100, steps, precond=kind)
+    for p, inst in enumerate(insts):
+        A = fdfd.assemble_instance(inst)
+        V = np.zeros((inst.D, 0))
+        if kind is None:
+            xo, io = gmres_aug.gmres_aug(A, inst.b, V, restart=100, tol=1e-30, maxit=steps)
+        else:
+            pl, pr = (precond.jacobi(A) if kind == "jacobi" else
+                      precond.pml_scaling(inst.nx, inst.ny, inst.omega, inst.dx, inst.npml))
+            xo, io = precond.gmres_aug_precond(A, inst.b, V, pl, pr, restart=100, tol=1e-30,
+                                               maxit=steps)
+        np.testing.assert_allclose(hs[p], io["history"][:steps], rtol=1e-7, atol=1e-14,
+                                   err_msg=inst.name)
+        np.testing.assert_allclose(xs[p], xo, rtol=0, atol=1e-6 * np.abs(xo).max(),
+                                   err_msg=inst.name)
+
+
+def test_fused_and_two_sweep_side_by_side():
+    """480 x 240 in complex128 with 100 vectors to 1e-6: k_fused_sweep, its graph replay
+    (identical) and the two-sweep step, each by the launches that were counted.  This
+    problem's history moves by 1e-5 with the order of a sum, so the two are compared
+    by what they reach and about how many steps they take."""
+    import torch
+    from paper_1902_00090_amd import FdfdOp, Solver
+    inst = W.grating(1000)
+    A = fdfd.assemble_instance(inst)
+    assert [_path([inst], 101, "c128", f) for f in (True, False)] == [1, 0]
+    op = FdfdOp.from_instance(inst)
+    b = torch.tensor(inst.b, device="cuda")
+    res = {}
+    for name, kw in (("fused", dict(fused=True)), ("graph", dict(fused=True, use_graph=True)),
+                     ("two", {})):
+        s = Solver([op], restart=100, inner="c128", cgs_passes=1, hist_cap=20000, **kw)
+        if name != "graph":
+            s.profile()
+        (x,), (info,), _ = s.solve([b], tol=1e-6, maxit=20000)
+        if name != "graph":
+            launches = {n: v[1] for n, v in s.kernel_stats().items()}
+            assert (launches["fused_sweep"] > 0) == (name == "fused"), launches
+            assert (launches["update_norm"] > 0) == (name == "two"), launches
+        res[name] = (x.cpu().numpy(), s.history(0), info["iters"])
+        s.close()
+        assert np.linalg.norm(inst.b - A @ res[name][0]) <= 1e-6 * np.linalg.norm(inst.b)
+    assert np.array_equal(res["graph"][0], res["fused"][0])
+    assert np.array_equal(res["graph"][1], res["fused"][1])
+    assert abs(res["fused"][2] - res["two"][2]) <= 0.1 * res["two"][2]

@@ -200,3 +200,16 @@ def test_recycle_edge_cases():
     y = Y[0].cpu().numpy().T
     np.testing.assert_allclose(np.linalg.norm(A @ y, axis=0), 1.0, rtol=1e-9)
     s.close()
+
+
+def test_recycling_on_the_two_other_steps():
+    """64 and more vectors in complex128: k_fused_sweep, whose stored vectors are not
+    normalised, and the two-sweep step pass on the same spaces."""
+    trajs = [W.trajectory(b, s0, 3, nx, ny, 1.30, npml=3) for b, s0, nx, ny in TRAJS]
+    a, b = (_run_sequence(trajs, 4, 66, 1e-14, 66, fused) for fused in (True, False))
+    for s in range(3):
+        for t in range(len(trajs)):
+            np.testing.assert_allclose(a[s][2][t], b[s][2][t], rtol=1e-7, atol=1e-14)
+            if a[s][3] is not None:
+                np.testing.assert_allclose(a[s][3][1][t], b[s][3][1][t], rtol=1e-6)
+                assert _span_gap(a[s][3][0][t], b[s][3][0][t]) <= 1e-6

@@ -373,3 +373,37 @@ def test_autotune_times_the_step_that_the_solver_takes():
         ms[kmax] = min(t)
     print("autotune ms per step:", ms)
     assert ms[40] > 1.4 * ms[0]
+
+
+# The two-sweep step, which the tests above no longer reach in complex128: 70 vectors
+@pytest.mark.parametrize("R", [1, 2, 4, 8])
+@pytest.mark.parametrize("cgs,select", [(1, True), (2, True), (2, False)])
+def test_two_sweep_modes_and_widths_match_oracle(cgs, select, R):
+    """Histories of one problem and of a batch of three grids, two cycles, against
+    the oracle; graph replay gives the same bits."""
+    import torch
+    from gpu_util import to_dev
+    shapes = [(48, 40), (96, 61), (60, 24)]
+    insts = [tiny_instance(70 + i, nx=nx, ny=ny, npml=4) for i, (nx, ny) in enumerate(shapes)]
+    rng = np.random.default_rng(71)
+    Vs = [W.random_complex(rng, (3, i.D)) for i in insts]
+    for group in ([0], [0, 1, 2]):
+        hist = []
+        for graph in (False, True):
+            s = _solver([_op(insts[g]) for g in group], restart=70, kmax=3, inner="c128",
+                        hist_cap=200, cgs_passes=cgs, select_reorth=select, elems_per_thread=R,
+                        use_graph=graph)
+            s.set_subspace([to_dev(Vs[g], torch.complex128) for g in group])
+            s.profile(not graph)
+            _, infos, _ = s.solve([_b(insts[g]) for g in group], tol=1e-30, maxit=110)
+            if not graph:
+                assert s.kernel_stats()["fused_sweep"][1] == 0
+                assert s.kernel_stats()["update_norm"][1] >= 110
+            assert [i["iters"] for i in infos] == [110] * len(group)
+            hist.append([s.history(t)[:110] for t in range(len(group))])
+            s.close()
+        for t, g in enumerate(group):
+            assert np.array_equal(hist[0][t], hist[1][t])
+            _, io = gmres_aug.gmres_aug(fdfd.assemble_instance(insts[g]), insts[g].b, Vs[g].T,
+                                        restart=70, tol=1e-30, maxit=110)
+            np.testing.assert_allclose(hist[0][t], io["history"][:110], rtol=1e-7, atol=1e-14)

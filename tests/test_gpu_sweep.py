@@ -242,3 +242,49 @@ def test_unit_of_length(e, passes):
         s.close()
     assert np.array_equal(res[0][1], res[1][1])
     assert np.array_equal(res[0][0] * u * u, res[1][0])
+
+
+def _long_path(nx, ny, k, restart, inner, passes):
+    import ctypes as C
+    from paper_1902_00090_amd import _lib, _opts
+    o = _opts(restart=restart, kmax=k, inner=inner, cgs_passes=passes)
+    return _lib.lib().dd_solver_step_path(1, C.byref(C.c_int(nx)), C.byref(C.c_int(ny)), C.byref(o))
+
+
+# the two-sweep step (three with a second pass), which takes the longer bases: the same
+# relations
+@pytest.mark.parametrize("nx,ny,k,restart,inner", [
+    (20, 15, 0, 140, "c64"), (61, 40, 20, 140, "c64"), (130, 64, 3, 200, "c64"),
+    (20, 15, 0, 65, "c128"), (125, 11, 3, 90, "c128")])
+@pytest.mark.parametrize("passes,adaptive", [(1, False), (2, True), (2, False)])
+def test_two_sweep_relations(nx, ny, k, restart, inner, passes, adaptive):
+    from paper_1902_00090_amd import FdfdOp, Solver
+    assert _long_path(nx, ny, k, restart, inner, passes) == 0
+    inst = _inst(nx + ny, nx, ny)
+    s = Solver([FdfdOp.from_instance(inst)], restart=restart, kmax=k, cgs_passes=passes,
+               select_reorth=adaptive, inner=inner)
+    if k:
+        V = W.random_complex(np.random.default_rng(1), (k, inst.D)).astype(DT[inner])
+        s.set_subspace([torch.tensor(V, device="cuda")])
+    b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
+    _, (info,), _ = s.solve([b], tol=0.0, maxit=restart)
+    assert info["iters"] == restart
+    if passes == 2 and not adaptive:
+        assert info["reorth_steps"] == restart
+    _check(s, 0, fdfd.assemble_instance(inst), restart, 1 if passes == 1 else 1.999 if adaptive else 2)
+    s.close()
+
+
+@pytest.mark.parametrize("kind", ["jacobi", "pml"])
+def test_two_sweep_preconditioned_relations(kind):
+    from paper_1902_00090_amd import FdfdOp, Solver
+    inst = _inst(3, 70, 21)
+    assert _long_path(70, 21, 0, 130, "c64", 1) == 0
+    s = Solver([FdfdOp.from_instance(inst)], restart=130, cgs_passes=1, precond=kind)
+    b = torch.tensor(inst.b, dtype=torch.complex128, device="cuda")
+    s.solve([b], tol=0.0, maxit=130)
+    A = fdfd.assemble_instance(inst)
+    pl, pr = (precond.jacobi(A) if kind == "jacobi" else
+              precond.pml_scaling(inst.nx, inst.ny, inst.omega, inst.dx, inst.npml))
+    _check(s, 0, precond.preconditioned(A, pl, pr), 130)
+    s.close()

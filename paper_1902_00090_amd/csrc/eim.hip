@@ -31,7 +31,7 @@
 // Measured for 64 problems of 480 x 240: one bisecting thread per column with a
 // division in each Sturm step took 4.54 ms and one thread per problem, its rows
 // in memory between the steps, 1.04 ms; these kernels take
-// 0.17, 0.37 and 0.23 ms.
+// 0.17, 0.34 and 0.19 ms.
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -73,9 +73,12 @@ __device__ __forceinline__ double2 zdiv(double2 a, double2 b) {
 // negative eigenvalue where the sequence of its leading minors changes sign:
 // divided by h2^i they obey p_i = t_i p_{i-1} - p_{i-2} with t_i = (d_i - x)/h2,
 // one fused multiply-add a step and no division (the pivots are their ratios,
-// each a division that waits for the one before).  p only grows while it is
-// positive, so it is scaled down every four steps; |t| < 2^100 for finite
-// inputs in FP32.  Lane 16 s + c tries point s + 1 of five sections of column
+// each a division that waits for the one before).  p is scaled down every four steps
+// where it has grown past 2^400: four steps multiply it by less than 2^600 while
+// (omega dx)^2 is below 2^20, whatever the FP32 permittivity (|t| < 2^150).  It needs no
+// scaling up: where it falls as the mode does, through a cladding, a step's rounding puts
+// 2^-53 of it into the solution that grows, which takes over after about 2^-27.  Lane
+// 16 s + c tries point s + 1 of five sections of column
 // c's interval: 18 rounds leave 2 h2 5^-18 < 2^-40 h2 (the shift below it is off
 // by 1e-10 of the diagonal on purpose).  LDS: the columns' permittivities are
 // read 18 times.

@@ -700,7 +700,10 @@ static void lanczos_top(const std::vector<cd>& G, int M, int k, bool signs,
 // The same iteration on a device matrix G, six small kernels a step; the host
 // looks at the tridiagonal matrix every ten steps.  For 1000 snapshots the host
 // iteration took 40 ms (a product with G, 16 MB, in each of 50 steps) after a
-// 4 ms copy of G; 1.2 ms here.
+// 4 ms copy of G; 1.2 ms here.  pca_build takes it from 128 snapshots on, where 20
+// components cross: whole calls on 20,000 elements, on the host and here, 112 snapshots
+// 1.44 and 1.66 ms, 128 1.60 and 1.66, 160 2.03 and 1.72, 256 3.81 and 2.17; 5 components
+// cross near 170: 128 0.58 and 0.76 ms, 160 0.76 and 0.78, 200 1.27 and 1.14.
 static dd_status lanczos_device(const double2* G, int M, int k, std::vector<double>& theta,
                                 std::vector<cd>& W, hipStream_t stream) {
   DevBuf bQ, bw;

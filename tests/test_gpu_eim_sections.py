@@ -66,3 +66,21 @@ def test_unit_of_length(e):
     want = eim.eim_instance(inst)
     tol = 2.0 ** -24 * np.abs(want) + 1e6 * inst.ny * 2.0 ** -53 * np.abs(want).max()
     assert (np.abs(F.cpu().numpy() - want) <= tol).all()
+
+
+def test_core_at_the_edge_of_a_long_column():
+    """A guiding core in the first rows and 2000 rows of cladding: below the eigenvalue
+    the minors rise to the core and fall with the mode through the cladding, 0.3 in
+    the exponent a row, until rounding brings the growing solution back."""
+    import torch
+    from paper_1902_00090_amd import FdfdOp, eim_field
+    rng = np.random.default_rng(5)
+    nx, ny = 17, 2050
+    eps = (2.085 + 0.05 * rng.random((ny, nx))).astype(np.float32)
+    eps[3:15] = 12.25
+    inst = W.Instance(eps, W.random_complex(rng, nx * ny), nx, ny, 0.025, 1.30, 3)
+    op = FdfdOp.from_instance(inst)
+    (F,) = eim_field([op], [torch.tensor(inst.b, device="cuda")])
+    want = eim.eim_instance(inst)
+    tol = 2.0 ** -24 * np.abs(want) + 1e6 * ny * 2.0 ** -53 * np.abs(want).max()
+    assert (np.abs(F.cpu().numpy() - want) <= tol).all()

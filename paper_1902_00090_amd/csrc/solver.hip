@@ -7,6 +7,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "solver_kernels.h"
@@ -666,41 +667,41 @@ static void launch_step(dd_solver* s, int j, hipStream_t st) {
   k_post_norm<T><<<nb, DD_BLOCK, 0, st>>>(s->P, j, MODE_ARNOLDI, 0);
 }
 
-// Waves and vectors a wave of the one-sweep kernels for n basis vectors: four
-// waves while their registers hold the rows (two workgroups per compute unit),
-// else eight.  complex128 holds half as many: up to 64 vectors.
-#define DD_SW_LAUNCH(KERNEL, ...)                                          \
-  if constexpr (sizeof(T) == 4) {                                          \
-    if (n <= 16) DD_SW_GO(KERNEL, 4, 4, __VA_ARGS__);                      \
-    else if (n <= 32) DD_SW_GO(KERNEL, 4, 8, __VA_ARGS__);                 \
-    else if (n <= 48) DD_SW_GO(KERNEL, 4, 12, __VA_ARGS__);                \
-    else if (n <= 64) DD_SW_GO(KERNEL, 4, 16, __VA_ARGS__);                \
-    else if (n <= 80) DD_SW_GO(KERNEL, 8, 10, __VA_ARGS__);                \
-    else if (n <= 96) DD_SW_GO(KERNEL, 8, 12, __VA_ARGS__);                \
-    else if (n <= 112) DD_SW_GO(KERNEL, 8, 14, __VA_ARGS__);               \
-    else DD_SW_GO(KERNEL, 8, 16, __VA_ARGS__);                             \
-  } else {                                                                 \
-    if (n <= 16) DD_SW_GO(KERNEL, 4, 4, __VA_ARGS__);                      \
-    else if (n <= 32) DD_SW_GO(KERNEL, 4, 8, __VA_ARGS__);                 \
-    else DD_SW_GO(KERNEL, 8, 8, __VA_ARGS__);                              \
+// Calls go with the waves and the vectors a wave of the one-sweep kernels for n basis
+// vectors: four waves while their registers hold the rows (two workgroups per compute
+// unit), else eight.  complex128 holds half as many: up to 64 vectors.
+template <typename T, typename F>
+static void sweep_shape(int n, F go) {
+#define DD_SW_SHAPE(NW, PER) go(std::integral_constant<int, NW>(), std::integral_constant<int, PER>())
+  if constexpr (sizeof(T) == 4) {
+    if (n <= 16) DD_SW_SHAPE(4, 4);
+    else if (n <= 32) DD_SW_SHAPE(4, 8);
+    else if (n <= 48) DD_SW_SHAPE(4, 12);
+    else if (n <= 64) DD_SW_SHAPE(4, 16);
+    else if (n <= 80) DD_SW_SHAPE(8, 10);
+    else if (n <= 96) DD_SW_SHAPE(8, 12);
+    else if (n <= 112) DD_SW_SHAPE(8, 14);
+    else DD_SW_SHAPE(8, 16);
+  } else {
+    if (n <= 16) DD_SW_SHAPE(4, 4);
+    else if (n <= 32) DD_SW_SHAPE(4, 8);
+    else DD_SW_SHAPE(8, 8);
   }
+#undef DD_SW_SHAPE
+}
 
 template <typename T, bool PC>
 static void launch_sweep(dd_solver* s, int j, hipStream_t st) {
-  const int n = s->o.kmax + j + 1;     // basis vectors, at most
-#define DD_SW_GO(KERNEL, NW, PER, ...) \
-  k_sweep<T, NW, PER, PC><<<s->sw_grid, 64 * NW, 0, st>>>(s->P, j)
-  DD_SW_LAUNCH(k_sweep)
-#undef DD_SW_GO
+  sweep_shape<T>(s->o.kmax + j + 1, [&](auto nw, auto per) {   // basis vectors, at most
+    k_sweep<T, nw.value, per.value, PC><<<s->sw_grid, 64 * nw.value, 0, st>>>(s->P, j);
+  });
 }
 
 template <typename T>
 static void launch_pass2(dd_solver* s, int j, hipStream_t st) {
-  const int n = s->o.kmax + j + 1;
-#define DD_SW_GO(KERNEL, NW, PER, ...) \
-  k_pass2<T, NW, PER><<<s->sw_grid, 64 * NW, 0, st>>>(s->P, j)
-  DD_SW_LAUNCH(k_pass2)
-#undef DD_SW_GO
+  sweep_shape<T>(s->o.kmax + j + 1, [&](auto nw, auto per) {
+    k_pass2<T, nw.value, per.value><<<s->sw_grid, 64 * nw.value, 0, st>>>(s->P, j);
+  });
 }
 
 // One fused Arnoldi step: the second Gram-Schmidt pass of step j where two are

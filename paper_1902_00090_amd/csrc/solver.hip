@@ -1125,7 +1125,7 @@ extern "C" dd_status dd_solver_debug_copy(const dd_solver* s, int p, int what, v
       DD_HIP_CHECK(hipMemcpy(hs.data(), s->P.hscale + (size_t)p * (m + 1), sizeof(double) * (m + 1),
                              hipMemcpyDeviceToHost));
       double f = 1.0;
-      if (last > 0)
+      if (last > 0 && s->o.inner == DD_C64)
         DD_HIP_CHECK(hipMemcpy(&f, s->P.zs + (1 + (last & 1)) * s->nb + p, sizeof(double),
                                hipMemcpyDeviceToHost));
       hs[last] = f;

@@ -1184,7 +1184,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_fused(PlanDev P, int j, int i
     }
     __syncthreads();
     ww = snew * snew * zz_l;
-    h = sw_unit(ww, 1.0);
+    if (sw_has_unit<PT>) h = sw_unit(ww, 1.0);
     f = sw_pow2(-h);
   }
   // the new raw dots and update coefficients (s_v for v <= k + j are those
@@ -1297,7 +1297,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
     const double nrm = sqrt(__shfl(nz, 0, DD_WAVE));     // of q~, with its power of two
     const double snew = (nrm > 0.0) ? 1.0 / nrm : 0.0;
     const double zz = __shfl(nz, 32, DD_WAVE);
-    const int h = sw_unit(zz, __shfl(nz, 0, DD_WAVE));
+    const int h = sw_has_unit<T> ? sw_unit(zz, __shfl(nz, 0, DD_WAVE)) : 0;
     const double f = sw_pow2(-h);
     double cc = 0.0;
     for (int v = v0; v < nn; v += step) {
@@ -1319,7 +1319,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
     }
     if (blockIdx.y == 0 && t == 0) {
       P.zs[p] = f * snew;
-      P.zs[(1 + (j & 1)) * P.nb + p] = sw_pow2(h);      // of q~_{j+2}
+      if (sw_has_unit<T>) P.zs[(1 + (j & 1)) * P.nb + p] = sw_pow2(h);      // of q~_{j+2}
     }
     if (P.reorth_mode == 2) {
       // for the second-pass test: ||w||^2 = s^2 ||z||^2 and this part of ||c||^2
@@ -1338,7 +1338,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_sweep(PlanDev P, int j, int p
   __shared__ double2 norm;
   __shared__ int fin, nfin;
   const int cgs2 = P.reorth_mode != 0 ? st[ST_REORTH] : 0;
-  const double fj = P.zs[(2 - (j & 1)) * P.nb + p];
+  const double fj = sw_has_unit<T> ? P.zs[(2 - (j & 1)) * P.nb + p] : 1.0;
   double2 gj = make_double2(0.0, 0.0);
   int it0 = 0, nre0 = 0;
   double nsum0 = 0.0, nsum20 = 0.0, bn = 0.0, ctl_tol = 0.0, ctl_maxit = 0.0;
@@ -1397,7 +1397,7 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_pass2(PlanDev P, int j) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int t0 = P.sw2.tile0[p], nt = P.sw2.ntile[p], k = P.desc[p].k, n = k + j + 1;
   const bool re = sw_second_pass(P, p);
-  const double f1 = P.zs[(2 - (j & 1)) * P.nb + p];
+  const double f1 = sw_has_unit<T> ? P.zs[(2 - (j & 1)) * P.nb + p] : 1.0;
   if (st[ST_ACTIVE] == 0) return;
   if (blockIdx.y == 0 && t == 0) {
     st[ST_REORTH] = re ? 1 : 0;

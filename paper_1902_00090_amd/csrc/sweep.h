@@ -6,9 +6,9 @@
 // basis.  With the update coefficients g the sweep forms
 //     q~_{j+1} = zs z_j - sum_v g_v b_v,      b = [C, q~_0 .. q~_j],
 // then z_{j+1} = A q~_{j+1} and its raw dots against [C, q~_0 .. q~_{j+1}].
-// zs and g carry a power of two that keeps ||q~_{j+1}|| at or below one (sw_unit):
-// the sums of FP32 products are then of the size of ||A||^2 at most, whatever the unit of
-// length, and no result changes by it.
+// In complex64 zs and g carry a power of two that keeps ||q~_{j+1}|| at or below one
+// (sw_unit): the sums of FP32 products are then of the size of ||A||^2 at most, whatever
+// the unit of length, and no result changes by it.
 //
 // The stencil needs q~_{j+1} on the cells around, so a workgroup walks a strip
 // of up to 62 columns (64 lanes with one halo column on either side) down the
@@ -126,6 +126,8 @@ template <bool PASS2> __device__ __forceinline__ int sw_position(int t, int G) {
   return t - g + g % (G / 8) * 8 + g / (G / 8);
 }
 
+// complex128 has the range for ||A||^4
+template <typename T> constexpr bool sw_has_unit = sizeof(T) == 4;
 // The power of two f = 2^-h with f ||A q_j|| in (1/4, 1], from zz = ||A q~_j||^2 and un
 // = ||q~_j||^2: the vector that is left of A q_j, times f, is stored.  By the exponents
 // alone, so that it does not wait for the square root of un; 1 if a sum is zero or not

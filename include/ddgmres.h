@@ -33,7 +33,8 @@ extern "C" {
 
 typedef enum {
   DD_OK = 0,
-  DD_NOT_CONVERGED = 1, /* iteration budget spent; x holds the last iterate  */
+  DD_NOT_CONVERGED = 1, /* iteration budget spent, or a start that leaves no  */
+                        /* step and no smaller residual; x: last iterate      */
   DD_EINVAL = -1,       /* invalid argument (sizes, omega, dx, pml, tol ...)   */
   DD_ENOMEM = -2,       /* device or host allocation failed                    */
   DD_EHIP = -3,         /* a HIP runtime call failed                           */

@@ -287,7 +287,8 @@ __global__ __launch_bounds__(DD_BLOCK) void k_residual(PlanDev P) {
 }
 
 // One workgroup per problem: ||r||, ||b||; decides whether the problem has
-// converged (||r|| <= tol ||b||), spent its budget, or starts a new cycle.
+// converged (||r|| <= tol ||b||), spent its budget, can make no step, or starts a new
+// cycle.
 __global__ __launch_bounds__(DD_BLOCK) void k_post_residual(PlanDev P, int first) {
   const int p = blockIdx.x;
   int* st = P.stI + p * ST_NI;
@@ -298,6 +299,9 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_residual(PlanDev P, int first
   if (threadIdx.x != 0) return;
   double* sd = P.stD + p * SD_ND;
   const double rho = sqrt(red[0]);
+  // a cycle that its start ended has made no step: without a smaller residual the next
+  // one would be the same, and maxit, which counts steps, would never be met
+  const bool stuck = st[ST_CYCLES] > 0 && st[ST_NCOMB] == 0 && !(rho < sd[SD_RHO]);
   if (first) {
     sd[SD_BNORM] = sqrt(red[1]);
     sd[SD_PBNORM] = d.pl64 ? sqrt(red[3]) : sd[SD_BNORM];
@@ -318,7 +322,9 @@ __global__ __launch_bounds__(DD_BLOCK) void k_post_residual(PlanDev P, int first
     sd[SD_TRUE] = rho / bn;
     if (rho <= P.ctl[0] * bn) {
       st[ST_DONE] = DONE_CONVERGED;
-    } else if (st[ST_ITERS] >= (int)P.ctl[1]) {
+    } else if (!isfinite(sd[SD_PRHO])) {
+      st[ST_DONE] = DONE_NONFINITE;
+    } else if (stuck || st[ST_ITERS] >= (int)P.ctl[1]) {
       st[ST_DONE] = DONE_BUDGET;
     } else {
       st[ST_ACTIVE] = 1;

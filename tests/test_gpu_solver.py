@@ -407,3 +407,32 @@ def test_two_sweep_modes_and_widths_match_oracle(cgs, select, R):
             _, io = gmres_aug.gmres_aug(fdfd.assemble_instance(insts[g]), insts[g].b, Vs[g].T,
                                         restart=70, tol=1e-30, maxit=110)
             np.testing.assert_allclose(hist[0][t], io["history"][:110], rtol=1e-7, atol=1e-14)
+
+
+@pytest.mark.parametrize("inner,restart", [("c64", 30), ("c128", 30), ("c64", 140), ("c128", 70)])
+def test_solves_that_can_make_no_step_end(inner, restart):
+    """maxit counts steps, so a start that leaves none must not start over for ever,
+    in the one-sweep step and the two-sweep one.  (a) A uniform medium, the solution in
+    the span of U and tol = 0: omega^2 eps = 12, and no FP64 number times 12 is
+    0.21.  (b) A Jacobi preconditioner of a zero diagonal: 4 / dx^2 = omega^2 eps = 16."""
+    import torch
+    from paper_1902_00090_amd import DDError, FdfdOp, _lib
+    from gpu_util import to_dev
+    x = 0.21 / 12
+    assert all(12 * v != 0.21 for v in (np.nextafter(x, 0), x, np.nextafter(x, 1)))
+    op = FdfdOp(np.full((64, 64), 3.0, np.float32), 2.0, 0.04, 0)
+    dt = torch.complex64 if inner == "c64" else torch.complex128
+    for passes in (1, 2):
+        s = _solver([op], restart=restart, kmax=1, inner=inner, cgs_passes=passes)
+        s.set_subspace([torch.ones(1, 4096, dtype=dt, device="cuda")])
+        (y,), (info,), st = s.solve([to_dev(np.full(4096, 0.21), torch.complex128)], tol=0.0,
+                                    maxit=40)
+        assert st == 1 and info["iters"] <= 40, info
+        assert np.abs(y.cpu().numpy() + x).max() <= 2.0 ** -55
+        s.close()
+    op = FdfdOp(np.ones((24, 20), np.float32), 4.0, 0.5, 0)
+    s = _solver([op], restart=restart, inner=inner, precond="jacobi")
+    with pytest.raises(DDError) as e:
+        s.solve([to_dev(np.arange(480.0), torch.complex128)], tol=1e-6, maxit=40)
+    assert e.value.status == _lib.DD_ENONFINITE
+    s.close()
